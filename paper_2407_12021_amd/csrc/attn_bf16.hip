@@ -134,8 +134,8 @@ template <int QP, int NW, int KS, int RBW>
 __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
     const uint4* __restrict__ qp, const uint4* __restrict__ kc, const uint4* __restrict__ vc,
     float* __restrict__ part_o, float2* __restrict__ part_ml, const uint64_t* __restrict__ mask,
-    const int32_t* __restrict__ seq_p, const int32_t* __restrict__ seq_n, int n_step, int H, int Hkv, int cap,
-    int n_splits, float scale_log2e, bf16_t* __restrict__ o_final, int RB_total) {
+    const int32_t* __restrict__ seq_p, const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0, int n_step,
+    int H, int Hkv, int cap, int n_splits, float scale_log2e, bf16_t* __restrict__ o_final, int RB_total) {
   constexpr int NT = NW * 64;          // threads
   constexpr int RG = NW / KS;          // row groups (of RBW * 16 rows) per workgroup
   constexpr int UPT = 2 * TILE_U4 / NT;  // staged 16-byte units per thread and tile (K and V)
@@ -156,6 +156,9 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
   const int b = bz / Hkv, kvh = bz - b * Hkv;
   const int G = H / Hkv;
   const int P = seq_p[b], N = seq_n[b], T = P + N;
+  const int n_pad = (N + 15) & ~15, r_seq = row0[b];  // this sequence's rows: r_seq .. r_seq + n_pad
+  const int VR = G * n_pad;
+  if (row_tile * (RG * RBW * 16) >= VR) return;  // a tree shorter than the step's largest has fewer row tiles
   const int n_tiles = (T + TILE - 1) / TILE;
   const int n_plain = P / TILE;  // tiles entirely inside the prefix
   // key ranges of equal cost: a tile that holds tree keys (mask work) counts as two prefix tiles
@@ -163,7 +166,6 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
   auto tile_at_cost = [&](int c) { return c <= n_plain ? c : n_plain + (c - n_plain + 1) / 2; };
   const int t_begin = tile_at_cost((int)((int64_t)split * cost_total / n_splits));
   const int t_end = split + 1 == n_splits ? n_tiles : tile_at_cost((int)((int64_t)(split + 1) * cost_total / n_splits));
-  const int VR = G * n_step;
   const int vrb0 = (row_tile * RG + rg) * RBW;              // first row block of this wavefront
   const int nrb = max(0, min(RBW, VR / 16 - vrb0));         // row blocks that hold rows
   const int row_in = lane & 15, quad = lane >> 4;
@@ -203,14 +205,14 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
 #pragma unroll
   for (int rb = 0; rb < RBW; ++rb) {
     const int vrb = rb < nrb ? vrb0 + rb : 0;
-    const uint4* qsrc = qp + (((int64_t)bz * (VR / 16) + vrb) * 8 << 6) + lane;
+    const uint4* qsrc = qp + (((int64_t)bz * (G * n_step / 16) + vrb) * 8 << 6) + lane;
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
       for (int pl = 0; pl < QP; ++pl) q[rb][kk * QP + pl] = __builtin_bit_cast(f16x8_t, qsrc[(kk * 2 + pl) << 6]);
     const int vr = vrb * 16 + row_in;
-    g_of[rb] = vr / n_step;
-    node_of[rb] = vr - g_of[rb] * n_step;
+    g_of[rb] = vr / n_pad;
+    node_of[rb] = vr - g_of[rb] * n_pad;
   }
   // o_l = ones . P^T: the running sum of each row's weights, present in every element
   f32x4_t o[RBW][8], o_l[RBW];
@@ -251,7 +253,7 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
         }
         s[c2] = QP == 2 ? acc + acc_lo : acc;
       }
-      softmax_chunk(s, plain, key0, quad, P, T, mask + ((int64_t)b * n_step + node_of[rb]) * 4, scale_log2e,
+      softmax_chunk(s, plain, key0, quad, P, T, mask + ((int64_t)r_seq + node_of[rb]) * 4, scale_log2e,
                     m_run[rb], alpha[rb], pb[rb]);
       rescale |= alpha[rb] != 1.0f;
     }
@@ -528,7 +530,7 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
       // a single key range: nothing to merge, the row is normalised here and written as the O projection's input
       // (hi / lo f16 in PackX; four consecutive features sit side by side inside a fragment)
       const float inv = 1.0f / l;
-      const int r = b * n_step + node_of[rb];
+      const int r = r_seq + node_of[rb];
 #pragma unroll
       for (int hb = 0; hb < 8; ++hb) {
         uint16_t hi[4], lo[4];
@@ -555,13 +557,15 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
 // all loads of a batch of eight in flight together; the result does not depend on the launch shape.
 __global__ __launch_bounds__(256) void tree_attn_merge_kernel(bf16_t* __restrict__ op, int RB,
                                                               const float* __restrict__ part_o,
-                                                              const float2* __restrict__ part_ml, int n_splits,
+                                                              const float2* __restrict__ part_ml,
+                                                              const int32_t* __restrict__ row0,
+                                                              const int32_t* __restrict__ blk_seq, int n_splits,
                                                               int n_step, int H, int total) {
   const int gid = blockIdx.x * 256 + threadIdx.x;
   if (gid >= total) return;
   const int d4 = gid & 31, rh = gid >> 5;
   const int r = rh / H, h = rh - r * H;
-  const int b = r / n_step, node = r - b * n_step;
+  const int b = blk_seq[r >> 4], node = r - row0[b];
   const int64_t base = (((int64_t)b * H + h) * n_splits) * n_step + node;
   float M = NEG_BIG, L = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -658,7 +662,7 @@ void bf16_tree_attention(bf16_t* o_packed, int rows_pad, const bf16_t* q_packed,
   bf16_t* o_final = n_splits == 1 ? o_packed : nullptr;  // one key range: the kernel finishes the rows itself
 #define DED_ATTN_ARGS                                                                                              \
   reinterpret_cast<const uint4*>(q_packed), reinterpret_cast<const uint4*>(kc), reinterpret_cast<const uint4*>(vc), \
-      part_o, part_ml, m.mask, m.seq_p, m.seq_n, m.n_step, md.H, md.Hkv, md.cap, n_splits, scale_log2e, o_final,   \
+      part_o, part_ml, m.mask, m.seq_p, m.seq_n, m.row0, m.n_step, md.H, md.Hkv, md.cap, n_splits, scale_log2e, o_final,   \
       rows_pad / 16
 #define DED_ATTN_GO(NW, KS, RBW)                                                                                       \
   if (q_planes == 1) hipLaunchKernelGGL((tree_attn_tiled_kernel<1, NW, KS, RBW>), grid, dim3(NW * 64), 0, s, DED_ATTN_ARGS); \
@@ -683,7 +687,7 @@ void bf16_tree_attention(bf16_t* o_packed, int rows_pad, const bf16_t* q_packed,
   if (n_splits > 1) {
     const int total = m.rows * md.H * 32;
     hipLaunchKernelGGL(tree_attn_merge_kernel, dim3((total + 255) / 256), dim3(256), 0, s, o_packed, rows_pad / 16,
-                       part_o, part_ml, n_splits, m.n_step, md.H, total);
+                       part_o, part_ml, m.row0, m.blk_seq, n_splits, m.n_step, md.H, total);
   }
 }
 

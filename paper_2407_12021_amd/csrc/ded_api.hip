@@ -47,6 +47,23 @@ struct Carve {  // bump allocator over the workspace (base may be null when only
 
 }  // namespace
 
+// Where the parts of a step's description sit inside the uploaded block, for `rows` tree rows of `batch` sequences.
+struct MetaOffsets {
+  size_t token = 0, parent = 0, depth = 0, pos = 0, mask = 0, p = 0, n = 0, row0 = 0, blk_seq = 0, bytes = 0;
+  MetaOffsets() = default;
+  MetaOffsets(int rows, int batch) {
+    auto take = [&](size_t count) {
+      const size_t at = bytes;
+      bytes = align_up(bytes + count, 64);
+      return at;
+    };
+    token = take((size_t)rows * 4), parent = take((size_t)rows * 4), depth = take((size_t)rows * 4);
+    pos = take((size_t)rows * 4), mask = take((size_t)rows * 8 * kMaskWords);
+    p = take((size_t)batch * 4), n = take((size_t)batch * 4), row0 = take((size_t)batch * 4);
+    blk_seq = take((size_t)rows / 16 * 4);
+  }
+};
+
 // Scratch of ded_tree_attention_static: device memory that belongs to the library itself, for callers that
 // cannot allocate and bring no workspace region of their own for it.  One copy per GPU, held until the
 // process ends.  In host code the array's name is only a handle: its device address is resolved once per
@@ -115,7 +132,7 @@ struct ded_ctx {
   size_t meta_bytes = 0;
   hipEvent_t meta_ev = nullptr;  // completion of the last upload from h_meta
   bool meta_inflight = false;
-  size_t off_token = 0, off_parent = 0, off_depth = 0, off_pos = 0, off_mask = 0, off_p = 0, off_n = 0;
+  MetaOffsets off;  // of the pending step: the block is packed to the step's own row count
   // results
   int32_t* d_amax = nullptr;
   float* d_margin = nullptr;
@@ -131,9 +148,9 @@ struct ded_ctx {
   bool have_logits = false;    // the workspace holds the fp32 logits of the last step
   bool poisoned = false;       // the last step's tree slots may hold NaN / infinite K/V: cleared before they can be read
   bool sampling_seen = false;  // ded_sample has been used on this context: steps keep their logits from then on
-  int batch = 0, n_step = 0;
+  int batch = 0, n_step = 0, rows = 0;
   int max_p = 0;
-  std::vector<int32_t> s_p, s_n, s_parent;
+  std::vector<int32_t> s_p, s_n, s_parent, s_row0;
   // profiling
   bool prof_on = false;
   std::vector<hipEvent_t> ev_pool;
@@ -147,16 +164,18 @@ struct ded_ctx {
   // the step description inside a device copy of the meta block that starts at `base`
   StepMeta meta_at(const char* base) const {
     StepMeta m;
-    m.token = reinterpret_cast<const int32_t*>(base + off_token);
-    m.parent = reinterpret_cast<const int32_t*>(base + off_parent);
-    m.depth = reinterpret_cast<const int32_t*>(base + off_depth);
-    m.pos = reinterpret_cast<const int32_t*>(base + off_pos);
-    m.mask = reinterpret_cast<const uint64_t*>(base + off_mask);
-    m.seq_p = reinterpret_cast<const int32_t*>(base + off_p);
-    m.seq_n = reinterpret_cast<const int32_t*>(base + off_n);
+    m.token = reinterpret_cast<const int32_t*>(base + off.token);
+    m.parent = reinterpret_cast<const int32_t*>(base + off.parent);
+    m.depth = reinterpret_cast<const int32_t*>(base + off.depth);
+    m.pos = reinterpret_cast<const int32_t*>(base + off.pos);
+    m.mask = reinterpret_cast<const uint64_t*>(base + off.mask);
+    m.seq_p = reinterpret_cast<const int32_t*>(base + off.p);
+    m.seq_n = reinterpret_cast<const int32_t*>(base + off.n);
+    m.row0 = reinterpret_cast<const int32_t*>(base + off.row0);
+    m.blk_seq = reinterpret_cast<const int32_t*>(base + off.blk_seq);
     m.batch = batch;
     m.n_step = n_step;
-    m.rows = batch * n_step;
+    m.rows = rows;
     return m;
   }
 };
@@ -303,18 +322,7 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
     }
   }
   // step meta block
-  size_t m = 0;
-  auto mtake = [&](size_t n) {
-    m = align_up(m, 256);
-    size_t o = m;
-    m += n;
-    return o;
-  };
-  size_t o_token = mtake((size_t)z.max_rows * 4), o_parent = mtake((size_t)z.max_rows * 4),
-         o_depth = mtake((size_t)z.max_rows * 4), o_pos = mtake((size_t)z.max_rows * 4),
-         o_mask = mtake((size_t)z.max_rows * 8 * kMaskWords), o_p = mtake((size_t)c.max_batch * 4),
-         o_n = mtake((size_t)c.max_batch * 4);
-  m = align_up(m, 256);
+  const size_t m = align_up(MetaOffsets(z.max_rows, c.max_batch).bytes, 256);
   char* dmeta = w.take<char>(m);
   int stride = c.max_nodes + 1;
   int32_t* amax = w.take<int32_t>(z.max_rows_pad);
@@ -330,13 +338,6 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
   if (ctx) {
     ctx->d_meta = dmeta;
     ctx->meta_bytes = m;
-    ctx->off_token = o_token;
-    ctx->off_parent = o_parent;
-    ctx->off_depth = o_depth;
-    ctx->off_pos = o_pos;
-    ctx->off_mask = o_mask;
-    ctx->off_p = o_p;
-    ctx->off_n = o_n;
     ctx->d_amax = amax;
     ctx->d_margin = margin;
     ctx->d_uniform = uniform;
@@ -425,37 +426,45 @@ int validate_step(const ded_config& cfg, int32_t batch, const int32_t* prefix_le
 int ingest_and_upload(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const int32_t* n_nodes,
                       const int32_t* parent, const int32_t* token, char* d_meta_dst = nullptr) {
   const ded_config& cfg = c->cfg;
-  int nmax = 0, pmax = 0;
+  int nmax = 0, pmax = 0, rows = 0;
+  c->s_row0.resize(batch);
   for (int b = 0; b < batch; ++b) {
     nmax = std::max(nmax, n_nodes[b]);
     pmax = std::max(pmax, prefix_len[b]);
+    c->s_row0[b] = rows;
+    rows += round_up(n_nodes[b], 16);
   }
-  int n_step = round_up(nmax, 16);
   if (c->meta_inflight) {  // the pinned mirror may still be feeding the previous upload
     HIP_TRY(hipEventSynchronize(c->meta_ev));
     c->meta_inflight = false;
   }
   c->batch = batch;
-  c->n_step = n_step;
+  c->n_step = round_up(nmax, 16);
+  c->rows = rows;
+  c->off = MetaOffsets(rows, batch);
   c->max_p = pmax;
   c->s_p.assign(prefix_len, prefix_len + batch);
   c->s_n.assign(n_nodes, n_nodes + batch);
   c->s_parent.assign((size_t)batch * cfg.max_nodes, -1);
-  int32_t* h_token = reinterpret_cast<int32_t*>(c->h_meta + c->off_token);
-  int32_t* h_parent = reinterpret_cast<int32_t*>(c->h_meta + c->off_parent);
-  int32_t* h_depth = reinterpret_cast<int32_t*>(c->h_meta + c->off_depth);
-  int32_t* h_pos = reinterpret_cast<int32_t*>(c->h_meta + c->off_pos);
-  uint64_t* h_mask = reinterpret_cast<uint64_t*>(c->h_meta + c->off_mask);
-  int32_t* h_p = reinterpret_cast<int32_t*>(c->h_meta + c->off_p);
-  int32_t* h_n = reinterpret_cast<int32_t*>(c->h_meta + c->off_n);
+  int32_t* h_token = reinterpret_cast<int32_t*>(c->h_meta + c->off.token);
+  int32_t* h_parent = reinterpret_cast<int32_t*>(c->h_meta + c->off.parent);
+  int32_t* h_depth = reinterpret_cast<int32_t*>(c->h_meta + c->off.depth);
+  int32_t* h_pos = reinterpret_cast<int32_t*>(c->h_meta + c->off.pos);
+  uint64_t* h_mask = reinterpret_cast<uint64_t*>(c->h_meta + c->off.mask);
+  int32_t* h_p = reinterpret_cast<int32_t*>(c->h_meta + c->off.p);
+  int32_t* h_n = reinterpret_cast<int32_t*>(c->h_meta + c->off.n);
+  int32_t* h_row0 = reinterpret_cast<int32_t*>(c->h_meta + c->off.row0);
+  int32_t* h_blk = reinterpret_cast<int32_t*>(c->h_meta + c->off.blk_seq);
   for (int b = 0; b < batch; ++b) {
     const int32_t* par = parent + (int64_t)b * cfg.max_nodes;
     const int32_t* tok = token ? token + (int64_t)b * cfg.max_nodes : nullptr;
-    int n = n_nodes[b], P = prefix_len[b];
+    const int n = n_nodes[b], P = prefix_len[b], row0 = c->s_row0[b], n_pad = round_up(n, 16);
     h_p[b] = P;
     h_n[b] = n;
-    for (int i = 0; i < n_step; ++i) {
-      int r = b * n_step + i;
+    h_row0[b] = row0;
+    for (int i = 0; i < n_pad; i += 16) h_blk[(row0 + i) / 16] = b;
+    for (int i = 0; i < n_pad; ++i) {
+      const int r = row0 + i;
       uint64_t* mr = h_mask + (size_t)r * kMaskWords;
       if (i < n) {
         c->s_parent[(size_t)b * cfg.max_nodes + i] = par[i];
@@ -465,7 +474,7 @@ int ingest_and_upload(ded_ctx* c, int32_t batch, const int32_t* prefix_len, cons
           h_depth[r] = 0;
           for (int w = 0; w < kMaskWords; ++w) mr[w] = 0;
         } else {
-          int pr = b * n_step + par[i];
+          const int pr = row0 + par[i];
           h_depth[r] = h_depth[pr] + 1;
           const uint64_t* mp = h_mask + (size_t)pr * kMaskWords;
           for (int w = 0; w < kMaskWords; ++w) mr[w] = mp[w];
@@ -483,7 +492,7 @@ int ingest_and_upload(ded_ctx* c, int32_t batch, const int32_t* prefix_len, cons
   }
   {
     ProfScope ps(c, KC_META);
-    HIP_TRY(hipMemcpyAsync(d_meta_dst ? d_meta_dst : c->d_meta, c->h_meta, c->meta_bytes, hipMemcpyHostToDevice,
+    HIP_TRY(hipMemcpyAsync(d_meta_dst ? d_meta_dst : c->d_meta, c->h_meta, c->off.bytes, hipMemcpyHostToDevice,
                            c->stream));
   }
   HIP_TRY(hipEventRecord(c->meta_ev, c->stream));
@@ -535,7 +544,7 @@ int clear_step_slots(ded_ctx* c) {
 // per-node argmax needs (the logits never reach memory).
 bool lm_head_bf16(ded_ctx* c, bool want_logits) {
   const ModelDims& md = c->md;
-  const int rows = c->batch * c->n_step, rows_pad = round_up(rows, 64), d = md.d;
+  const int rows = c->rows, rows_pad = round_up(rows, 64), d = md.d;
   GemmEpilogue e = {};
   e.rows = rows;
   e.rb_total = rows_pad / 16;
@@ -607,6 +616,8 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
       e.rope_tab = c->rope_tab;
       e.seq_p = m.seq_p;
       e.seq_n = m.seq_n;
+      e.row0 = m.row0;
+      e.blk_seq = m.blk_seq;
       e.n_step = m.n_step;
       e.H = md.H;
       e.Hkv = md.Hkv;
@@ -902,13 +913,13 @@ int ded_sample(ded_ctx* c, float temperature, float top_p, const float* uniform)
   if (!c || !uniform) return DED_EINVAL;
   if (!(temperature > 0.f) || !(top_p > 0.f) || !(top_p <= 1.f)) return DED_EINVAL;
   if (!c->pending || !c->have_argmax) return DED_ESTATE;
-  const int mn = c->cfg.max_nodes, rows = c->batch * c->n_step;
+  const int mn = c->cfg.max_nodes, rows = c->rows;
   float* h_u = reinterpret_cast<float*>(c->h_res);  // nothing else is in flight on the pinned result block
   for (int b = 0; b < c->batch; ++b)
-    for (int i = 0; i < c->n_step; ++i) {
+    for (int i = 0; i < round_up(c->s_n[b], 16); ++i) {
       float u = i < c->s_n[b] ? uniform[(size_t)b * mn + i] : 0.f;
       if (!(u >= 0.f) || !(u < 1.f)) return DED_EINVAL;
-      h_u[b * c->n_step + i] = u;
+      h_u[c->s_row0[b] + i] = u;
     }
   HIP_TRY(hipMemcpyAsync(c->d_uniform, h_u, sizeof(float) * rows, hipMemcpyHostToDevice, c->stream));
   // A step keeps its logits only if the caller asked for them or the context has sampled before; the first
@@ -926,7 +937,7 @@ int ded_sample(ded_ctx* c, float temperature, float top_p, const float* uniform)
   HIP_TRY(hipStreamSynchronize(c->stream));  // h_res is free again
   for (int b = 0; b < c->batch; ++b)
     for (int i = 0; i < c->s_n[b]; ++i)
-      if (h_f[b * c->n_step + i]) {
+      if (h_f[c->s_row0[b] + i]) {
         c->poisoned = true;
         return DED_ENONFINITE;
       }
@@ -936,7 +947,7 @@ int ded_sample(ded_ctx* c, float temperature, float top_p, const float* uniform)
 int ded_get_argmax(ded_ctx* c, int32_t* argmax, float* margin) {
   if (!c || !argmax) return DED_EINVAL;
   if (!c->have_argmax) return DED_ESTATE;
-  const int rows = c->batch * c->n_step, mn = c->cfg.max_nodes;
+  const int rows = c->rows, mn = c->cfg.max_nodes;
   int32_t* h_a = reinterpret_cast<int32_t*>(c->h_res);
   float* h_m = reinterpret_cast<float*>(c->h_res) + c->max_rows_pad;
   HIP_TRY(hipMemcpyAsync(h_a, c->d_amax, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, c->stream));
@@ -946,14 +957,14 @@ int ded_get_argmax(ded_ctx* c, int32_t* argmax, float* margin) {
   HIP_TRY(hipStreamSynchronize(c->stream));
   for (int b = 0; b < c->batch; ++b)
     for (int i = 0; i < c->s_n[b]; ++i)
-      if (h_f[b * c->n_step + i]) {
+      if (h_f[c->s_row0[b] + i]) {
         c->poisoned = true;
         return DED_ENONFINITE;
       }
   for (int b = 0; b < c->batch; ++b)
     for (int i = 0; i < c->s_n[b]; ++i) {
-      argmax[(size_t)b * mn + i] = h_a[b * c->n_step + i];
-      if (margin) margin[(size_t)b * mn + i] = h_m[b * c->n_step + i];
+      argmax[(size_t)b * mn + i] = h_a[c->s_row0[b] + i];
+      if (margin) margin[(size_t)b * mn + i] = h_m[c->s_row0[b] + i];
     }
   return DED_OK;
 }
@@ -1008,15 +1019,16 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
   int ns = 1;
   if (c->bf16) {
     // the key-range count is the workspace path's in both variants, so both give the same bits
-    int nmax = 0, pmax = 0;
+    int nmax = 0, pmax = 0, rows = 0;
     for (int b = 0; b < batch; ++b) {
       nmax = std::max(nmax, n_nodes[b]);
       pmax = std::max(pmax, prefix_len[b]);
+      rows += round_up(n_nodes[b], 16);
     }
     StepMeta shape = {};
     shape.batch = batch;
     shape.n_step = round_up(nmax, 16);
-    shape.rows = batch * shape.n_step;
+    shape.rows = rows;
     ns = bf16_attn_pick_splits(shape, md, pmax, c->attn_part_rows);
     if (st) {  // carve the library's own array; a call that does not fit is refused before anything is enqueued
       const int64_t rows_pad = round_up(shape.rows, 64), qd = (int64_t)md.H * md.hd;

@@ -8,7 +8,9 @@
 namespace ded {
 
 // Device-resident description of the current step (one verification forward).
-// Row r = b * n_step + node; n_step = the step's padded tree size (multiple of 16).
+// The trees lie one after the other, each padded to whole blocks of 16 rows: row r = row0[b] + node, and every
+// 16-row block belongs to one sequence.  (Padding all trees to the largest one instead made a ragged batch pay for
+// rows nobody reads: 192 rows for trees of 37, 21 and 50 nodes where 144 do.)  n_step = the largest padded tree.
 struct StepMeta {
   const int32_t* token;   // [R]   token id of the row (padding rows repeat the root token)
   const int32_t* parent;  // [R]   parent node index inside the sequence, -1 for root / padding
@@ -17,7 +19,9 @@ struct StepMeta {
   const uint64_t* mask;   // [R][4] ancestor-or-self bitmask over node indices (bit j = node j)
   const int32_t* seq_p;   // [B]   prefix_len per sequence
   const int32_t* seq_n;   // [B]   real tree rows per sequence
-  int32_t batch, n_step, rows;  // rows = batch * n_step
+  const int32_t* row0;    // [B]   first row of the sequence (multiple of 16)
+  const int32_t* blk_seq; // [rows / 16] sequence of each 16-row block
+  int32_t batch, n_step, rows;  // rows = sum of the padded tree sizes
 };
 
 struct ModelDims {
@@ -75,7 +79,7 @@ void f32_gather_rows(float* dst, const float* src, const StepMeta& m, int max_no
 //  PackW  W[N][K]   : frag (ng = n/64, kt = k/32, t = (n/16)%4) at (ng*(K/32)+kt)*4+t; lane = ((k%32)/8)*16 + n%16;
 //                      elem k%8; N padded to a multiple of 64 with zero features
 //  PackX  X[R][K]   : frag (kt, rb = r/16, plane hi/lo) at (kt*RB+rb)*2+plane; lane = ((k%32)/8)*16 + r%16; elem k%8
-//  PackQ  per (b,kvh): frag (vrb, kk = hd/32, plane) at (vrb*4+kk)*2+plane, virtual row vr = g*n_step + node
+//  PackQ  per (b,kvh): frag (vrb, kk = hd/32, plane) at (vrb*4+kk)*2+plane, virtual row vr = g*(padded tree rows of b) + node
 //  PackK  per (b,kvh): 32-key group kb; frag (kb, c, kk) at (kb*2+c)*4+kk; key%32 = q8*8 + c*4 + i
 //                      -> lane = ((hdim%32)/8)*16 + q8*4 + i; elem hdim%8
 //  PackVt per (b,kvh): frag (kb, hb = hdim/16) at kb*8+hb; lane = ((key%32)/8)*16 + hdim%16; elem key%8
@@ -110,7 +114,7 @@ struct GemmEpilogue {
   // EPI_QKV: rotary embedding at the row's position, queries -> PackQ (hi/lo), keys / values -> cache
   bf16_t *q_packed, *k_cache, *v_cache;
   const float2* rope_tab;
-  const int32_t *seq_p, *seq_n;
+  const int32_t *seq_p, *seq_n, *row0, *blk_seq;
   int n_step, H, Hkv, cap;
   // EPI_SILU: y_packed(hi) = silu(scale*gate) * (scale*up);  EPI_RESIDUAL: x += Y, y_packed = x*gain (hi/lo), ssq_out
   bf16_t* y_packed;

@@ -396,8 +396,9 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     for (int rb = 0; rb < RBN; ++rb) {
       const int r = (rbase + rb) * 16 + row_in;
       if (r >= e.rows) continue;
-      const int b = r / e.n_step, node = r - b * e.n_step;
-      const bool real = node < e.seq_n[b];
+      const int b = e.blk_seq[r >> 4], node = r - e.row0[b];
+      const int n_b = e.seq_n[b];
+      const bool real = node < n_b;
       const int slot = e.seq_p[b] + node;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -420,7 +421,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
         }
         if (hs < e.H) {
           const int kvh = hs / G, g = hs - kvh * G;
-          const int vr = g * e.n_step + node;
+          const int vr = g * ((n_b + 15) & ~15) + node;
           uint16_t* base = e.q_packed + ((int64_t)b * e.Hkv + kvh) * ((int64_t)G * e.n_step * 128 * 2);
           uint2 hi, lo;
           split4_f16(a, hi, lo);

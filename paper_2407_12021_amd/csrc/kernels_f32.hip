@@ -94,10 +94,10 @@ void f32_gemm(float* Y, const float* X, const float* W, int rows, int N, int K, 
 // Rotate q (in place) and k, append k/v of real nodes to cache slot P + node.
 __global__ void f32_rope_kv_kernel(float* __restrict__ qkv, float* __restrict__ kc, float* __restrict__ vc,
                                    const float2* __restrict__ tab, const int32_t* __restrict__ seq_p,
-                                   const int32_t* __restrict__ seq_n, int n_step, int H, int Hkv, int hd,
-                                   int cap) {
+                                   const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
+                                   const int32_t* __restrict__ blk_seq, int H, int Hkv, int hd, int cap) {
   int r = blockIdx.x, hs = blockIdx.y;
-  int b = r / n_step, node = r - b * n_step;
+  int b = blk_seq[r >> 4], node = r - row0[b];
   int half = hd / 2;
   int width = (H + 2 * Hkv) * hd;
   float* v = qkv + (int64_t)r * width + (int64_t)hs * hd;
@@ -127,7 +127,7 @@ __global__ void f32_rope_kv_kernel(float* __restrict__ qkv, float* __restrict__ 
 void f32_rope_kv(float* qkv, float* kc, float* vc, const float2* tab, const StepMeta& m,
                  const ModelDims& md, hipStream_t s) {
   hipLaunchKernelGGL(f32_rope_kv_kernel, dim3(m.rows, md.H + 2 * md.Hkv), dim3(64), 0, s, qkv, kc, vc, tab,
-                     m.seq_p, m.seq_n, m.n_step, md.H, md.Hkv, md.hd, md.cap);
+                     m.seq_p, m.seq_n, m.row0, m.blk_seq, md.H, md.Hkv, md.hd, md.cap);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -138,13 +138,14 @@ void f32_rope_kv(float* qkv, float* kc, float* vc, const float2* tab, const Step
 __global__ __launch_bounds__(256) void f32_tree_attention_kernel(
     float* __restrict__ o, const float* __restrict__ qkv, int q_stride, const float* __restrict__ kc,
     const float* __restrict__ vc, const uint64_t* __restrict__ mask, const int32_t* __restrict__ seq_p,
-    const int32_t* __restrict__ seq_n, int n_step, int H, int Hkv, int hd, int cap) {
+    const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0, const int32_t* __restrict__ blk_seq, int H,
+    int Hkv, int hd, int cap) {
   __shared__ float sq[256];
   __shared__ float sp[F32_ATT_CHUNK];
   __shared__ float sred[4];
   __shared__ float sacc[256];
   int r = blockIdx.x, h = blockIdx.y;
-  int b = r / n_step, node = r - b * n_step;
+  int b = blk_seq[r >> 4], node = r - row0[b];
   float* out = o + ((int64_t)r * H + h) * hd;
   int nb = seq_n[b];
   if (node >= nb) {
@@ -215,7 +216,7 @@ __global__ __launch_bounds__(256) void f32_tree_attention_kernel(
 void f32_tree_attention(float* o, const float* qkv, int q_stride, const float* kc, const float* vc,
                         const StepMeta& m, const ModelDims& md, hipStream_t s) {
   hipLaunchKernelGGL(f32_tree_attention_kernel, dim3(m.rows, md.H), dim3(256), 0, s, o, qkv, q_stride, kc, vc,
-                     m.mask, m.seq_p, m.seq_n, m.n_step, md.H, md.Hkv, md.hd, md.cap);
+                     m.mask, m.seq_p, m.seq_n, m.row0, m.blk_seq, md.H, md.Hkv, md.hd, md.cap);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -315,10 +316,10 @@ void f32_scatter_tree_kv(float* kc, float* vc, const float* k_tree, const float*
 
 // rows of real nodes between the caller's [B][max_nodes][width] and the padded [R][width] buffers
 __global__ void f32_gather_rows_kernel(float* __restrict__ dst, const float* __restrict__ src,
-                                       const int32_t* __restrict__ seq_n, int n_step, int max_nodes, int width,
-                                       int to_padded) {
+                                       const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
+                                       const int32_t* __restrict__ blk_seq, int max_nodes, int width, int to_padded) {
   int r = blockIdx.x;
-  int b = r / n_step, node = r - b * n_step;
+  int b = blk_seq[r >> 4], node = r - row0[b];
   bool real = node < seq_n[b];
   int64_t pad = (int64_t)r * width, ext = ((int64_t)b * max_nodes + node) * width;
   for (int i = threadIdx.x; i < width; i += blockDim.x) {
@@ -328,8 +329,8 @@ __global__ void f32_gather_rows_kernel(float* __restrict__ dst, const float* __r
 }
 void f32_gather_rows(float* dst, const float* src, const StepMeta& m, int max_nodes, int width,
                      bool to_padded, hipStream_t s) {
-  hipLaunchKernelGGL(f32_gather_rows_kernel, dim3(m.rows), dim3(256), 0, s, dst, src, m.seq_n, m.n_step,
-                     max_nodes, width, to_padded ? 1 : 0);
+  hipLaunchKernelGGL(f32_gather_rows_kernel, dim3(m.rows), dim3(256), 0, s, dst, src, m.seq_n, m.row0,
+                     m.blk_seq, max_nodes, width, to_padded ? 1 : 0);
 }
 
 }  // namespace ded

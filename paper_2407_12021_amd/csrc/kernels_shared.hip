@@ -438,10 +438,11 @@ void launch_sample_top_p(const float* logits, int64_t row_stride, int rows, int 
 
 // ------------------------------------------------------------------------------------------
 __global__ void export_logits_kernel(float* __restrict__ dst, const float* __restrict__ src,
-                                     int64_t src_stride, const int32_t* __restrict__ seq_n, int n_step,
+                                     int64_t src_stride, const int32_t* __restrict__ seq_n,
+                                     const int32_t* __restrict__ row0, const int32_t* __restrict__ blk_seq,
                                      int max_nodes, int V) {
   int r = blockIdx.x;
-  int b = r / n_step, node = r - b * n_step;
+  int b = blk_seq[r >> 4], node = r - row0[b];
   if (node >= seq_n[b]) return;
   const float* s = src + (int64_t)r * src_stride;
   float* d = dst + ((int64_t)b * max_nodes + node) * V;
@@ -451,7 +452,7 @@ __global__ void export_logits_kernel(float* __restrict__ dst, const float* __res
 void launch_export_logits(float* dst, const float* src, int64_t src_stride, const StepMeta& m,
                           int max_nodes, int V, hipStream_t s) {
   hipLaunchKernelGGL(export_logits_kernel, dim3(m.rows), dim3(256), 0, s, dst, src, src_stride, m.seq_n,
-                     m.n_step, max_nodes, V);
+                     m.row0, m.blk_seq, max_nodes, V);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -464,22 +465,22 @@ __global__ __launch_bounds__(64) void accept_walk_kernel(const int32_t* __restri
                                                          const int32_t* __restrict__ depth,
                                                          const int32_t* __restrict__ seq_n,
                                                          const int32_t* __restrict__ amax,
-                                                         const int32_t* __restrict__ row_flag, int n_step,
-                                                         int mode, int32_t* __restrict__ out_n,
+                                                         const int32_t* __restrict__ row_flag,
+                                                         const int32_t* __restrict__ row0, int mode, int32_t* __restrict__ out_n,
                                                          int32_t* __restrict__ out_flag,
                                                          int32_t* __restrict__ out_path,
                                                          int32_t* __restrict__ out_tok, int stride) {
   int b = blockIdx.x;
   int n = seq_n[b];
-  const int32_t* tok = token + (int64_t)b * n_step;
-  const int32_t* par = parent + (int64_t)b * n_step;
-  const int32_t* dep = depth + (int64_t)b * n_step;
-  const int32_t* am = amax + (int64_t)b * n_step;
+  const int32_t* tok = token + row0[b];
+  const int32_t* par = parent + row0[b];
+  const int32_t* dep = depth + row0[b];
+  const int32_t* am = amax + row0[b];
   // a step with a non-finite logit at a real node of any sequence has no verdict: every sequence gets path
   // length 0 (nothing is compacted) and its flag raised
   int bad = 0;
   for (int b2 = 0; b2 < gridDim.x; ++b2)
-    for (int i = threadIdx.x; i < seq_n[b2]; i += 64) bad |= row_flag[(int64_t)b2 * n_step + i];
+    for (int i = threadIdx.x; i < seq_n[b2]; i += 64) bad |= row_flag[row0[b2] + i];
   bad = __any(bad != 0);
   if (bad) {
     if (threadIdx.x == 0) {
@@ -531,7 +532,7 @@ __global__ __launch_bounds__(64) void accept_walk_kernel(const int32_t* __restri
 void launch_accept_walk(const StepMeta& m, const int32_t* amax, const int32_t* row_flag, int mode, int32_t* out_n,
                         int32_t* out_flag, int32_t* out_path, int32_t* out_tok, int stride, hipStream_t s) {
   hipLaunchKernelGGL(accept_walk_kernel, dim3(m.batch), dim3(64), 0, s, m.token, m.parent, m.depth,
-                     m.seq_n, amax, row_flag, m.n_step, mode, out_n, out_flag, out_path, out_tok, stride);
+                     m.seq_n, amax, row_flag, m.row0, mode, out_n, out_flag, out_path, out_tok, stride);
 }
 
 }  // namespace ded
