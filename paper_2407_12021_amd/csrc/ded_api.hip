@@ -115,7 +115,7 @@ struct ded_ctx {
   float* logits = nullptr;
   float2* rope_tab = nullptr;
   // fp32 path
-  float *f_y = nullptr, *f_qkv = nullptr, *f_o = nullptr, *f_gu = nullptr, *f_h = nullptr;
+  float *f_qkv = nullptr, *f_o = nullptr, *f_h = nullptr;
   // bf16 path
   bf16_t *y_p = nullptr, *o_p = nullptr, *h_p = nullptr, *q_p = nullptr;
   float* part = nullptr;
@@ -278,16 +278,12 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
     ctx->rope_tab = tab;
   }
   if (c.dtype == DED_F32) {
-    float* y = w.take<float>((int64_t)z.max_rows_pad * d);
     float* qkv = w.take<float>((int64_t)z.max_rows_pad * qkv_n);
     float* o = w.take<float>((int64_t)z.max_rows_pad * qd);
-    float* gu = w.take<float>((int64_t)z.max_rows_pad * 2 * F);
     float* h = w.take<float>((int64_t)z.max_rows_pad * F);
     if (ctx) {
-      ctx->f_y = y;
       ctx->f_qkv = qkv;
       ctx->f_o = o;
-      ctx->f_gu = gu;
       ctx->f_h = h;
     }
   } else {
@@ -510,19 +506,31 @@ int forward_f32(ded_ctx* c) {
   const int d = md.d, qd = md.H * md.hd, kvd = md.Hkv * md.hd, qkv_n = qd + 2 * kvd, F = md.F;
   { ProfScope p(c, KC_ROPE_TABLE); launch_rope_table(c->rope_tab, m.pos, m.rows, md.hd, md.rope_base, s); }
   { ProfScope p(c, KC_EMBED); f32_embed(c->x, (const float*)c->emb, m, d, s); }
+  auto gemm = [&](int cls, int kind, float* y, const float* x, const void* w, const float* gain, int N, int K, int l) {
+    F32Gemm g = {};
+    g.kind = kind;
+    g.Y = y, g.X = x, g.W = (const float*)w, g.gain = gain;
+    g.eps = md.eps;
+    g.rows = m.rows, g.N = N, g.K = K;
+    if (kind == F32_QKV) {
+      g.kc = (float*)c->kc[l], g.vc = (float*)c->vc[l], g.tab = c->rope_tab;
+      g.m = m;
+      g.H = md.H, g.Hkv = md.Hkv, g.cap = md.cap;
+    }
+    g.hd = md.hd;
+    ProfScope p(c, cls);
+    f32_gemm(g, s);
+  };
   for (int l = 0; l < md.n_layers; ++l) {
-    { ProfScope p(c, KC_RMSNORM); f32_rmsnorm(c->f_y, c->x, c->norm_attn[l], m.rows, d, md.eps, s); }
-    { ProfScope p(c, KC_GEMM_QKV); f32_gemm(c->f_qkv, c->f_y, (const float*)c->wqkv[l], m.rows, qkv_n, d, false, s); }
-    { ProfScope p(c, KC_QKV_EPILOGUE); f32_rope_kv(c->f_qkv, (float*)c->kc[l], (float*)c->vc[l], c->rope_tab, m, md, s); }
+    const bool fused = md.hd % 32 == 0;
+    gemm(KC_GEMM_QKV, fused ? F32_QKV : F32_STORE, c->f_qkv, c->x, c->wqkv[l], c->norm_attn[l], qkv_n, d, l);
+    if (!fused) { ProfScope p(c, KC_QKV_EPILOGUE); f32_rope_kv(c->f_qkv, (float*)c->kc[l], (float*)c->vc[l], c->rope_tab, m, md, s); }
     { ProfScope p(c, KC_TREE_ATTN); f32_tree_attention(c->f_o, c->f_qkv, qkv_n, (const float*)c->kc[l], (const float*)c->vc[l], m, md, s); }
-    { ProfScope p(c, KC_GEMM_O); f32_gemm(c->x, c->f_o, (const float*)c->wo[l], m.rows, d, qd, true, s); }
-    { ProfScope p(c, KC_RMSNORM); f32_rmsnorm(c->f_y, c->x, c->norm_ffn[l], m.rows, d, md.eps, s); }
-    { ProfScope p(c, KC_GEMM_GATE_UP); f32_gemm(c->f_gu, c->f_y, (const float*)c->wgu[l], m.rows, 2 * F, d, false, s); }
-    { ProfScope p(c, KC_SILU_MUL); f32_silu_mul(c->f_h, c->f_gu, m.rows, F, s); }
-    { ProfScope p(c, KC_GEMM_DOWN); f32_gemm(c->x, c->f_h, (const float*)c->wdown[l], m.rows, d, F, true, s); }
+    gemm(KC_GEMM_O, F32_RESIDUAL, c->x, c->f_o, c->wo[l], nullptr, d, qd, l);
+    gemm(KC_GEMM_GATE_UP, F32_SILU, c->f_h, c->x, c->wgu[l], c->norm_ffn[l], 2 * F, d, l);
+    gemm(KC_GEMM_DOWN, F32_RESIDUAL, c->x, c->f_h, c->wdown[l], nullptr, d, F, l);
   }
-  { ProfScope p(c, KC_RMSNORM); f32_rmsnorm(c->f_y, c->x, c->final_norm, m.rows, d, md.eps, s); }
-  { ProfScope p(c, KC_GEMM_LM_HEAD); f32_gemm(c->logits, c->f_y, (const float*)c->lm_head, m.rows, md.V, d, false, s); }
+  gemm(KC_GEMM_LM_HEAD, F32_STORE, c->logits, c->x, c->lm_head, c->final_norm, md.V, d, 0);
   return launch_status();
 }
 

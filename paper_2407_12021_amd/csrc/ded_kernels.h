@@ -54,14 +54,31 @@ void launch_accept_walk(const StepMeta& m, const int32_t* amax, const int32_t* r
 
 // ---- fp32 path (plain row-major everywhere; cache [B][Hkv][cap][hd]) ---------------------
 void f32_embed(float* x, const float* emb, const StepMeta& m, int d, hipStream_t s);
-void f32_rmsnorm(float* y, const float* x, const float* gain, int rows, int d, float eps, hipStream_t s);
-// Y[r][n] (+)= sum_k X[r][k] W[n][k]
-void f32_gemm(float* Y, const float* X, const float* W, int rows, int N, int K, bool accumulate, hipStream_t s);
+// Y[r][n] = sum_k X[r][k] W[n][k] with a fused neighbour on either side.  All kinds but F32_RESIDUAL normalise their
+// input rows: X[r] is taken as x * gain / sqrt(mean(x^2) + eps).
+enum {
+  F32_STORE = 0,     // Y = result, row stride N
+  F32_RESIDUAL = 1,  // Y += result
+  F32_SILU = 2,      // W holds gate and up features one after the other: Y = silu(gate) * up, row stride N / 2
+  F32_QKV = 3        // queries rotated into Y (row stride N), keys rotated / values into the cache; hd % 32 == 0
+};
+struct F32Gemm {
+  int kind;
+  float* Y;
+  const float *X, *W, *gain;
+  float eps;
+  int rows, N, K;  // rows % 16 == 0
+  // F32_QKV
+  float *kc, *vc;
+  const float2* tab;
+  StepMeta m;
+  int H, Hkv, hd, cap;
+};
+void f32_gemm(const F32Gemm& g, hipStream_t s);
 void f32_rope_kv(float* qkv, float* kc, float* vc, const float2* tab, const StepMeta& m,
                  const ModelDims& md, hipStream_t s);
 void f32_tree_attention(float* o, const float* qkv, int q_stride, const float* kc, const float* vc,
                         const StepMeta& m, const ModelDims& md, hipStream_t s);
-void f32_silu_mul(float* h, const float* gu, int rows, int F, hipStream_t s);
 void f32_kv_compact(float* const* kc, float* const* vc, const int32_t* path, const int32_t* n_acc,
                     const StepMeta& m, const ModelDims& md, int stride, hipStream_t s);
 // plain [Hkv][n][hd] <-> cache
