@@ -938,7 +938,7 @@ int ded_sample(ded_ctx* c, float temperature, float top_p, const float* uniform)
     c->have_logits = true;
   }
   { ProfScope p(c, KC_SAMPLE);
-    launch_sample_top_p(c->logits, c->md.V, rows, c->md.V, temperature, top_p, c->d_uniform, c->d_amax, c->stream); }
+    launch_sample_top_p(c->logits, c->md.V, c->meta(), c->md.V, temperature, top_p, c->d_uniform, c->d_amax, c->stream); }
   if (launch_status() != DED_OK) return DED_EHIP;
   int32_t* h_f = reinterpret_cast<int32_t*>(c->h_res) + c->max_rows_pad;
   HIP_TRY(hipMemcpyAsync(h_f, c->d_rowflag, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, c->stream));

@@ -41,9 +41,9 @@ void launch_argmax(const float* logits, int64_t row_stride, int rows, int V, int
 // The same from the candidates the LM-head GEMM leaves with EPI_TOP2: part [rows][groups] x 16 bytes.
 void launch_top2_reduce(const void* part, int groups, int rows, int32_t* amax, float* margin, int32_t* flag,
                         hipStream_t s);
-// Per-row temperature / top-p sample (inverse CDF of uniform[r] over the nucleus in id order) -> token_out[r].
-void launch_sample_top_p(const float* logits, int64_t row_stride, int rows, int V, float temperature, float top_p,
-                         const float* uniform, int32_t* token_out, hipStream_t s);
+// Temperature / top-p sample of every real row (inverse CDF of uniform[r] over the nucleus in id order) -> token_out[r].
+void launch_sample_top_p(const float* logits, int64_t row_stride, const StepMeta& m, int V, float temperature,
+                         float top_p, const float* uniform, int32_t* token_out, hipStream_t s);
 // Copy rows of real nodes to the caller's [batch][max_nodes][V] logits buffer.
 void launch_export_logits(float* dst, const float* src, int64_t src_stride, const StepMeta& m,
                           int max_nodes, int V, hipStream_t s);

@@ -186,254 +186,224 @@ void launch_top2_reduce(const void* part, int groups, int rows, int32_t* amax, f
 // ------------------------------------------------------------------------------------------
 // Temperature / top-p sampling of the model's token at every node (stochastic approval, Sec. 2.4: a token
 // is sampled from the model's distribution and compared with the draft; Sec. 4.4 varies temperature and
-// top-p).  One workgroup per row.  p_i = softmax(logits / T); the nucleus is the smallest set of most
+// top-p).  One workgroup per real row.  p_i = softmax(logits / T); the nucleus is the smallest set of most
 // probable tokens reaching top_p, ties with its last member included; the token is the inverse CDF of the
 // caller's uniform number over the nucleus in token-id order.
-// p is monotone in the logit, so the nucleus is {logit >= t*} with t* the largest threshold under which the
-// set still reaches top_p: found by bisection over the order-preserving integer image of fp32 (<= 32
-// passes over the row, which stays in L2).  Sums are formed in a fixed order (per thread, wavefront
-// shuffles, wavefront order), so the result is reproducible.
-constexpr int SAMPLE_THREADS = 1024;
+//
+// Weights w_i = exp((l_i - max) / T) lie in [0, 1], so their bit patterns order like their values, and the nucleus is
+// {bits(w) >= t*} with t* the largest threshold under which the set still reaches top_p.  t* is found digit by digit
+// (11 + 10 + 10 bits): a histogram of WEIGHT per digit value, a suffix sum over its bins, and on into the bin where the
+// sum crosses top_p.  Weights are added as 64-bit fixed point (units of 2^-40): integer sums do not depend on the order
+// of their terms, so the histogram can be built with LDS atomics and is still reproducible, and a sum over the
+// vocabulary is off by less than V 2^-40 (fp32 sums: some 1e-6).  Only the first digit looks at every token's weight; the
+// later passes compare the logit with the bin's range first.
+// Bound by reading the row (from L2 / last-level cache) five times and by the exponentials of the first histogram.
+// Measured, 144 rows x 128256 tokens: 93 us; a bisection over global memory (34 passes), which served vocabularies beyond
+// what LDS can hold before, took 1.2 ms for these rows.
+constexpr int SAMPLE_THREADS = 1024, SAMPLE_WAVES = SAMPLE_THREADS / 64;
+constexpr int SAMPLE_BINS = 1024;   // bits(w) <= bits(1.0f) = 0x3f800000: the first digit is at most 0x3f8
+constexpr int SAMPLE_COPIES = 8;    // of the first histogram: neighbouring lanes often hit the same bin
+constexpr int SAMPLE_SUBS = SAMPLE_THREADS / SAMPLE_WAVES;  // sub-blocks per wavefront in the inverse CDF
 
-__device__ inline uint32_t ordered_key(float v) {
-  const uint32_t b = __float_as_uint(v);
-  return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+__device__ inline unsigned long long weight_fixed(float w) {  // w * 2^40, w in [0, 1]
+  const float a = w * 256.0f;
+  const unsigned hi = (unsigned)a;
+  const unsigned lo = (unsigned)((a - (float)hi) * 4294967296.0f);  // the difference is exact and below 1
+  return ((unsigned long long)hi << 32) + lo;
 }
-__device__ inline float block_sum(float v, float* sh) {
+__device__ inline unsigned long long wave_sum_u64(unsigned long long v) {
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
-  __syncthreads();
-  float r = 0.f;
-  for (int w = 0; w < SAMPLE_THREADS / 64; ++w) r += sh[w];
-  return r;
+  return v;
 }
-
-// exclusive prefix of v over the threads of the block and the block total, in a fixed order (wavefront scan by
-// shuffles, then the wavefront totals one after the other)
-__device__ inline float block_exclusive_scan(float v, float* sh_w, float& total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float inc = v;
+__device__ inline unsigned long long wave_inclusive_u64(unsigned long long v) {
+  const int lane = threadIdx.x & 63;
   for (int off = 1; off < 64; off <<= 1) {
-    const float o = __shfl_up(inc, off);
-    if (lane >= off) inc += o;
+    const unsigned long long o = __shfl_up(v, off);
+    if (lane >= off) v += o;
   }
+  return v;
+}
+// sums of v over the threads before this one, and over all of them (sh: SAMPLE_WAVES entries; starts with a barrier)
+__device__ inline unsigned long long block_exclusive_u64(unsigned long long v, unsigned long long* sh,
+                                                         unsigned long long& total) {
+  const unsigned long long inc = wave_inclusive_u64(v);
   __syncthreads();
-  if (lane == 63) sh_w[wave] = inc;
+  if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = inc;
   __syncthreads();
-  float before = 0.f, all = 0.f;
-  for (int w = 0; w < SAMPLE_THREADS / 64; ++w) {
-    if (w < wave) before += sh_w[w];
-    all += sh_w[w];
+  unsigned long long before = 0, all = 0;
+  for (int w = 0; w < SAMPLE_WAVES; ++w) {
+    if (w < (int)(threadIdx.x >> 6)) before += sh[w];
+    all += sh[w];
   }
   total = all;
-  return before + (inc - v);
+  return before + inc - v;
 }
 
-__global__ __launch_bounds__(SAMPLE_THREADS) void sample_top_p_kernel(const float* __restrict__ logits,
-                                                                      int64_t row_stride, int V, float inv_temp,
-                                                                      float top_p, const float* __restrict__ uniform,
-                                                                      int32_t* __restrict__ token_out) {
-  __shared__ float sh[SAMPLE_THREADS / 64];
-  __shared__ uint32_t sh_k[2 * (SAMPLE_THREADS / 64)];
-  __shared__ int sh_owner;
-  const float* row = logits + (int64_t)blockIdx.x * row_stride;
-  const int tid = threadIdx.x;
-  // pass 1: extreme keys
-  uint32_t kmax = 0u, kmin = 0xffffffffu;
-  for (int i = tid; i < V; i += SAMPLE_THREADS) {
-    const uint32_t k = ordered_key(row[i]);
-    kmax = k > kmax ? k : kmax;
-    kmin = k < kmin ? k : kmin;
-  }
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint32_t a = __shfl_xor(kmax, off), b = __shfl_xor(kmin, off);
-    kmax = a > kmax ? a : kmax;
-    kmin = b < kmin ? b : kmin;
-  }
-  if ((tid & 63) == 0) {
-    sh_k[tid >> 6] = kmax;
-    sh_k[SAMPLE_THREADS / 64 + (tid >> 6)] = kmin;
-  }
-  __syncthreads();
-  for (int w = 0; w < SAMPLE_THREADS / 64; ++w) {
-    kmax = sh_k[w] > kmax ? sh_k[w] : kmax;
-    kmin = sh_k[SAMPLE_THREADS / 64 + w] < kmin ? sh_k[SAMPLE_THREADS / 64 + w] : kmin;
-  }
-  const uint32_t bmax = (kmax & 0x80000000u) ? (kmax & 0x7fffffffu) : ~kmax;
-  const float m = __uint_as_float(bmax);  // row maximum
-  // weight of the tokens whose key is >= t  (t = 0: all)
-  auto mass = [&](uint32_t t) {
-    float s = 0.f;
-    for (int i = tid; i < V; i += SAMPLE_THREADS) {
-      const float l = row[i];
-      if (ordered_key(l) >= t) s += __expf((l - m) * inv_temp);
+__global__ __launch_bounds__(SAMPLE_THREADS) void sample_top_p_kernel(
+    const float* __restrict__ logits, int64_t row_stride, int V, float inv_temp, float top_p,
+    const float* __restrict__ uniform, const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
+    const int32_t* __restrict__ blk_seq, int32_t* __restrict__ token_out) {
+  __shared__ unsigned long long hist[SAMPLE_COPIES * SAMPLE_BINS];
+  __shared__ unsigned long long sh[SAMPLE_WAVES];
+  __shared__ float sh_f[SAMPLE_WAVES];
+  __shared__ int sh_bin, sh_sub;
+  __shared__ unsigned long long sh_u64;
+  const int r = blockIdx.x, seq = blk_seq[r >> 4];
+  if (r - row0[seq] >= seq_n[seq]) return;  // padding row
+  const float* row = logits + (int64_t)r * row_stride;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+  auto load4 = [&](int i, float (&l)[4]) {  // past the end: no weight
+    if (vec && i + 3 < V) {
+      const float4 v = *reinterpret_cast<const float4*>(row + i);
+      l[0] = v.x, l[1] = v.y, l[2] = v.z, l[3] = v.w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) l[j] = i + j < V ? row[i + j] : -INFINITY;
     }
-    return block_sum(s, sh);
   };
-  const float Z = mass(0u);
-  const float need = top_p * Z;
-  // largest t with mass(t) >= need:  mass(lo) >= need holds (lo = smallest key), mass(hi) < need (hi beyond the largest)
-  uint32_t lo = kmin, hi = kmax + 1u;  // logits are finite, so kmax + 1 does not wrap
-  while (hi - lo > 1u) {
-    const uint32_t mid = lo + ((hi - lo) >> 1);
-    if (mass(mid) >= need) lo = mid;
-    else hi = mid;
-  }
-  // inverse CDF over the nucleus in id order: thread t owns the ids [t * chunk, (t + 1) * chunk)
-  const int chunk = (V + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
-  const int i0 = tid * chunk, i1 = min(V, i0 + chunk);
-  float own = 0.f;
-  int last_kept = -1;
-  for (int i = i0; i < i1; ++i) {
-    const float l = row[i];
-    if (ordered_key(l) >= lo) {
-      own += __expf((l - m) * inv_temp);
-      last_kept = i;
-    }
-  }
-  if (tid == 0) sh_owner = -1;
-  float total;
-  const float before = block_exclusive_scan(own, sh, total);  // its barriers also publish sh_owner
-  const float target = uniform[blockIdx.x] * total;
-  // The chunk that holds the target is the last one that starts at or below it (`before` never decreases with
-  // the thread index).  Its thread takes the first id whose running sum passes the target - or, when its own
-  // running sum (rounded in another order than the scan) stops short of it, the chunk's last nucleus id.
-  if (own > 0.f && before <= target) atomicMax(&sh_owner, tid);
-  __syncthreads();
-  if (tid == sh_owner) {
-    float run = before;
-    int pick = last_kept;
-    for (int i = i0; i < i1; ++i) {
-      const float l = row[i];
-      if (ordered_key(l) >= lo) {
-        run += __expf((l - m) * inv_temp);
-        if (run > target) {
-          pick = i;
-          break;
-        }
-      }
-    }
-    token_out[blockIdx.x] = pick;
-  }
-}
-
-// Same sampler for vocabularies that fit LDS: the weights exp((l - max) / T) are computed once and kept in LDS
-// (they are monotone in the logit, so the bisection runs on their bit patterns), which turns the ~34 passes
-// over the row into LDS traffic.
-constexpr int SAMPLE_LDS_V = 36864;  // 144 KiB of weights
-
-__global__ __launch_bounds__(SAMPLE_THREADS) void sample_top_p_lds_kernel(const float* __restrict__ logits,
-                                                                          int64_t row_stride, int V, float inv_temp,
-                                                                          float top_p, const float* __restrict__ uniform,
-                                                                          int32_t* __restrict__ token_out) {
-  __shared__ float e[SAMPLE_LDS_V];
-  __shared__ float sh[SAMPLE_THREADS / 64];
-  __shared__ int sh_owner;
-  const float* row = logits + (int64_t)blockIdx.x * row_stride;
-  const int tid = threadIdx.x;
   float m = -INFINITY;
-  for (int i = tid; i < V; i += SAMPLE_THREADS) m = fmaxf(m, row[i]);
+#pragma unroll 4
+  for (int i = tid * 4; i < V; i += SAMPLE_THREADS * 4) {
+    float l[4];
+    load4(i, l);
+    m = fmaxf(m, fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])));
+  }
   for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
-  if ((tid & 63) == 0) sh[tid >> 6] = m;
+  for (int i = tid; i < SAMPLE_COPIES * SAMPLE_BINS; i += SAMPLE_THREADS) hist[i] = 0;
+  if (tid == 0) sh_bin = 0, sh_sub = 0, sh_u64 = 0;
+  if (lane == 0) sh_f[wave] = m;
   __syncthreads();
-  for (int w = 0; w < SAMPLE_THREADS / 64; ++w) m = fmaxf(m, sh[w]);
-  float z = 0.f;
-  uint32_t kmin = 0xffffffffu;
-  for (int i = tid; i < V; i += SAMPLE_THREADS) {
-    const float w = __expf((row[i] - m) * inv_temp);  // in [0, 1]: its bit pattern orders like its value
-    e[i] = w;
-    z += w;
-    kmin = min(kmin, __float_as_uint(w));
-  }
-  const float Z = block_sum(z, sh);
-  for (int off = 32; off >= 1; off >>= 1) kmin = min(kmin, (uint32_t)__shfl_xor((int)kmin, off));
-  __shared__ uint32_t sh_k[SAMPLE_THREADS / 64];
-  if ((tid & 63) == 0) sh_k[tid >> 6] = kmin;
-  __syncthreads();
-  for (int w = 0; w < SAMPLE_THREADS / 64; ++w) kmin = min(kmin, sh_k[w]);
-  // largest t with mass(t) >= need, mass(t) = weight of {bits(w) >= t}: 8-way search, seven thresholds per pass
-  // over the LDS copy (one block reduction per pass instead of three)
-  __shared__ float sh7[7][SAMPLE_THREADS / 64];
-  const float need = top_p * Z;
-  uint32_t lo = kmin, hi = 0x3f800000u + 1u;  // mass(lo) >= need; the largest weight is exp(0) = 1, so mass(hi) = 0
-  while (hi - lo > 1u) {
-    const uint32_t span = hi - lo;
-    uint32_t t[7];
+  for (int w = 0; w < SAMPLE_WAVES; ++w) m = fmaxf(m, sh_f[w]);
+  auto weight = [&](float l) {  // in [0, 1] whatever the row holds (a row with a NaN or an infinity is reported, not used)
+    const float w = __expf((l - m) * inv_temp);
+    return w >= 0.f ? fminf(w, 1.0f) : 0.f;
+  };
+  // logit below which the weight is certainly under `w` (the margin covers the rounding of exp and log)
+  auto logit_floor = [&](float w) { return w > 0.f ? m + (__logf(w) - 1e-3f) / inv_temp - 1e-5f * fabsf(m) : -INFINITY; };
+
+#pragma unroll 4
+  for (int i = tid * 4; i < V; i += SAMPLE_THREADS * 4) {
+    float l[4];
+    load4(i, l);
 #pragma unroll
-    for (int j = 0; j < 7; ++j) t[j] = lo + (uint32_t)(((uint64_t)span * (j + 1)) >> 3);  // lo <= t[j] < hi, non-decreasing
-    float sj[7] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int i = tid; i < V; i += SAMPLE_THREADS) {
-      const float w = e[i];
-      const uint32_t k = __float_as_uint(w);
-#pragma unroll
-      for (int j = 0; j < 7; ++j) sj[j] += k >= t[j] ? w : 0.f;
+    for (int j = 0; j < 4; ++j) {
+      const float w = weight(l[j]);
+      const unsigned long long q = weight_fixed(w);
+      if (q) atomicAdd(&hist[(lane & (SAMPLE_COPIES - 1)) * SAMPLE_BINS + (__float_as_uint(w) >> 20)], q);
     }
+  }
+  __syncthreads();
+  unsigned long long own = 0;
 #pragma unroll
-    for (int j = 0; j < 7; ++j)
-      for (int off = 32; off >= 1; off >>= 1) sj[j] += __shfl_xor(sj[j], off);
+  for (int c = 0; c < SAMPLE_COPIES; ++c) own += hist[c * SAMPLE_BINS + tid];
+  // Thread t stands for bin t of the digit.  The crossing bin is the highest one whose suffix sum (plus the weight above
+  // the digit's range) reaches `need`: the one with  suffix >= need  and  suffix without it < need.
+  unsigned long long Z = 0, above = 0, need = 0;
+  auto crossing = [&](unsigned long long in_bin, bool first) {
+    unsigned long long total;
+    const unsigned long long before = block_exclusive_u64(in_bin, sh, total);
+    if (first) {
+      Z = total;
+      need = (unsigned long long)ceil((double)top_p * (double)Z);
+      need = need > Z ? Z : need < 1 ? 1 : need;
+    }
+    const unsigned long long beyond = above + (total - before - in_bin), with = beyond + in_bin;
+    if (with >= need && beyond < need) {
+      sh_bin = tid;
+      sh_u64 = beyond;
+    }
     __syncthreads();
-    if ((tid & 63) == 0) {
-#pragma unroll
-      for (int j = 0; j < 7; ++j) sh7[j][tid >> 6] = sj[j];
-    }
+    above = sh_u64;
+    return (uint32_t)sh_bin;
+  };
+  uint32_t lo = crossing(own, true);  // digits found so far
+  for (int shift = 10; shift >= 0; shift -= 10) {
+    hist[tid] = 0;
+    const float l_min = logit_floor(__uint_as_float(lo << (shift + 10)));
     __syncthreads();
-    uint32_t nlo = lo, nhi = hi;
+    for (int i = tid * 4; i < V; i += SAMPLE_THREADS * 4) {
+      float l[4];
+      load4(i, l);
+      if (fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])) >= l_min) {
 #pragma unroll
-    for (int j = 0; j < 7; ++j) {
-      float f = 0.f;
-      for (int w = 0; w < SAMPLE_THREADS / 64; ++w) f += sh7[j][w];
-      if (f >= need) nlo = t[j] > nlo ? t[j] : nlo;         // thresholds that still reach the target move lo up
-      else nhi = t[j] < nhi ? t[j] : nhi;                    // the first that does not becomes hi
-    }
-    if (nlo == lo && nhi == hi) break;  // cannot happen while span > 1 (t[6] > lo or t[0] == lo handled), safety only
-    lo = nlo;
-    hi = nhi;
-  }
-  const int chunk = (V + SAMPLE_THREADS - 1) / SAMPLE_THREADS;
-  const int i0 = tid * chunk, i1 = min(V, i0 + chunk);
-  float own = 0.f;
-  int last_kept = -1;
-  for (int i = i0; i < i1; ++i) {
-    const float w = e[i];
-    if (__float_as_uint(w) >= lo) {
-      own += w;
-      last_kept = i;
-    }
-  }
-  if (tid == 0) sh_owner = -1;
-  float total;
-  const float before = block_exclusive_scan(own, sh, total);  // its barriers also publish sh_owner
-  const float target = uniform[blockIdx.x] * total;
-  // as in sample_top_p_kernel: the last chunk that starts at or below the target holds it
-  if (own > 0.f && before <= target) atomicMax(&sh_owner, tid);
-  __syncthreads();
-  if (tid == sh_owner) {
-    float run = before;
-    int pick = last_kept;
-    for (int i = i0; i < i1; ++i) {
-      const float w = e[i];
-      if (__float_as_uint(w) >= lo) {
-        run += w;
-        if (run > target) {
-          pick = i;
-          break;
+        for (int j = 0; j < 4; ++j) {
+          const float w = weight(l[j]);
+          const uint32_t bits = __float_as_uint(w);
+          if (bits >> (shift + 10) == lo) atomicAdd(&hist[(bits >> shift) & 1023u], weight_fixed(w));
         }
       }
     }
-    token_out[blockIdx.x] = pick;
+    __syncthreads();
+    lo = (lo << 10) | crossing(hist[tid], false);
+  }
+  // Inverse CDF over the nucleus {bits(w) >= lo} in id order.  The ids are cut into 1024 sub-blocks of whole 256-id
+  // groups, dealt to the wavefronts in turn; their sums locate the target's sub-block, which one wavefront walks.
+  const float l_min = logit_floor(__uint_as_float(lo));
+  auto nucleus_mass = [&](const float (&l)[4], unsigned long long (&q)[4]) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = 0;
+    if (fmaxf(fmaxf(l[0], l[1]), fmaxf(l[2], l[3])) >= l_min) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float w = weight(l[j]);
+        if (__float_as_uint(w) >= lo) q[j] = weight_fixed(w);
+      }
+    }
+  };
+  const int groups = (V + 255) / 256, per_sub = (groups + SAMPLE_WAVES * SAMPLE_SUBS - 1) / (SAMPLE_WAVES * SAMPLE_SUBS);
+  __syncthreads();
+  for (int s = 0; s < SAMPLE_SUBS; ++s) {
+    unsigned long long sum = 0;
+    const int sub = s * SAMPLE_WAVES + wave, g0 = sub * per_sub;
+    for (int gi = g0; gi < min(g0 + per_sub, groups); ++gi) {
+      float l[4];
+      unsigned long long q[4];
+      load4(gi * 256 + lane * 4, l);
+      nucleus_mass(l, q);
+      sum += q[0] + q[1] + q[2] + q[3];
+    }
+    if (g0 < groups) sum = wave_sum_u64(sum);
+    if (lane == 0) hist[sub] = sum;
+  }
+  __syncthreads();
+  unsigned long long total;
+  const unsigned long long mine = hist[tid], before = block_exclusive_u64(mine, sh, total);
+  unsigned long long target = (unsigned long long)((double)uniform[r] * (double)total);
+  target = target < total ? target : total - 1;
+  if (before <= target && target < before + mine) {
+    sh_sub = tid;
+    sh_u64 = before;
+  }
+  __syncthreads();
+  if (wave != sh_sub % SAMPLE_WAVES) return;
+  unsigned long long run = sh_u64;
+  const int g0 = sh_sub * per_sub;
+  for (int gi = g0; gi < min(g0 + per_sub, groups); ++gi) {
+    float l[4];
+    unsigned long long q[4];
+    load4(gi * 256 + lane * 4, l);
+    nucleus_mass(l, q);
+    const unsigned long long sum = q[0] + q[1] + q[2] + q[3], inc = run + wave_inclusive_u64(sum);
+    unsigned long long at = inc - sum;
+    if (at <= target && target < inc) {  // exactly one lane of one group
+      int pick = 0;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (at <= target && target < at + q[j]) pick = j;
+        at += q[j];
+      }
+      token_out[r] = gi * 256 + lane * 4 + pick;
+    }
+    run = __shfl(inc, 63);
   }
 }
 
-void launch_sample_top_p(const float* logits, int64_t row_stride, int rows, int V, float temperature, float top_p,
-                         const float* uniform, int32_t* token_out, hipStream_t s) {
-  if (rows <= 0) return;
-  if (V <= SAMPLE_LDS_V)
-    hipLaunchKernelGGL(sample_top_p_lds_kernel, dim3(rows), dim3(SAMPLE_THREADS), 0, s, logits, row_stride, V,
-                       1.0f / temperature, top_p, uniform, token_out);
-  else
-    hipLaunchKernelGGL(sample_top_p_kernel, dim3(rows), dim3(SAMPLE_THREADS), 0, s, logits, row_stride, V,
-                       1.0f / temperature, top_p, uniform, token_out);
+void launch_sample_top_p(const float* logits, int64_t row_stride, const StepMeta& m, int V, float temperature,
+                         float top_p, const float* uniform, int32_t* token_out, hipStream_t s) {
+  if (m.rows <= 0) return;
+  hipLaunchKernelGGL(sample_top_p_kernel, dim3(m.rows), dim3(SAMPLE_THREADS), 0, s, logits, row_stride, V,
+                     1.0f / temperature, top_p, uniform, m.seq_n, m.row0, m.blk_seq, token_out);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -66,3 +66,64 @@ def test_fp32_projections_and_attention_at_tile_edges(case):
     err = _step_error(cfg, w, prefix_len, nodes, seed=50 + case)
     print(f"max |logit error| {err:.2e}")
     assert err <= 1e-4
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_cache_rows_come_back_and_neighbours_stay(dtype):
+    """Ranges that start, end or lie inside a 32-slot group of the cache: rows come back bit for bit (bf16 values widen to
+    half and back exactly from 2^-14 up), and no slot beside the range changes."""
+    import torch
+    hd = 128 if dtype == "bf16" else 64
+    cfg = di.ModelConfig("kv-edge-" + dtype, 1, 128, 4, 2, hd, 128, 64, dtype=dtype)
+    cap = 192
+    ver = _verifier(cfg, di.make_weights(cfg, seed=3), max_batch=2, kv_capacity=cap, max_nodes=16)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def rows(n):
+        x = torch.randn(2, n, hd, device="cuda", generator=g).to(dt)
+        return torch.where(x.abs() < 2.0 ** -14, torch.ones_like(x), x)
+
+    want = [rows(cap), rows(cap)]
+    ver.kv_store(0, 1, 0, *want)
+    for first, n in ((0, 1), (31, 1), (31, 2), (1, 31), (32, 32), (7, 100), (64, 96), (8, 8), (12, 8), (191, 1), (0, 192)):
+        new = [rows(n), rows(n)]
+        ver.kv_store(0, 1, first, new[0], new[1])
+        for w, x in zip(want, new):
+            w[:, first:first + n] = x
+        for got, w in zip(ver.kv_load(0, 1, 0, cap), want):
+            assert torch.equal(got, w), (first, n)
+        for got, w in zip(ver.kv_load(0, 1, first, n), want):
+            assert torch.equal(got, w[:, first:first + n]), (first, n)
+    assert not any(x.any() for x in ver.kv_load(0, 0, 0, cap))  # the other sequence
+    ver.close()
+
+
+@pytest.mark.parametrize("V", [48, 1008, 4096 + 16, 36880, 262144 + 32])
+def test_sampler_vocabularies(V):
+    """Vocabularies below one pass of the workgroup, off its 4-id and 256-id granules, and above the 1024 sub-blocks of the
+    inverse CDF, against the fp64 sampler on the same logits.  A decision counts where u is clear of every CDF step and of
+    the nucleus boundary by 1e-5: the kernel's sums are exact to V 2^-40, its weights to some 1e-6 relative."""
+    cfg = di.ModelConfig(f"samp-v{V}", 1, 128, 1, 1, 128, 128, V, dtype="bf16")
+    w = di.make_weights(cfg, seed=8, std=0.3)
+    ver = _verifier(cfg, w, max_batch=2, kv_capacity=64, max_nodes=24)
+    nodes = [5, 24]
+    parents = [di.random_tree(n, None, seed=n) for n in nodes]
+    tokens = [di.zipf_tokens(V, n, seed=9, stream=b) for b, n in enumerate(nodes)]
+    logits = ver.verify_step([0, 0], parents, tokens, want_logits=True).cpu().numpy().astype(np.float64)
+    r = np.random.default_rng(1)
+    decided = 0
+    for temperature, top_p in ((1.0, 1.0), (0.4, 0.9), (0.7, 0.3), (2.5, 0.8)):
+        us = [r.random(n).astype(np.float32) for n in nodes]
+        ver.sample(temperature, top_p, us)
+        got, _ = ver.get_argmax()
+        for b, n in enumerate(nodes):
+            ref, info = oracle.sample_rows(logits[b, :n], temperature, top_p, us[b].astype(np.float64))
+            for i in range(n):
+                edge = info[i]["edge_mass"] if info[i]["nucleus_slack"] <= 1e-5 else 0.0
+                if info[i]["cdf_slack"] > 1e-5 + edge:
+                    assert int(got[b, i]) == int(ref[i]), (temperature, top_p, b, i)
+                    decided += 1
+    assert decided >= 0.6 * 4 * sum(nodes), decided
+    ver.accept(mode=0)
+    ver.close()
