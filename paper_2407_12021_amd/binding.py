@@ -338,6 +338,9 @@ def ded_profile_read(ctx) -> dict:
 def _to_device(a, device, dtype: str):
     """numpy (fp32, or uint16 bf16 bit patterns) / torch tensor -> device tensor in storage dtype."""
     import torch
+    if isinstance(a, torch.Tensor) and a.device == device and a.is_contiguous() and \
+            a.dtype == (torch.bfloat16 if dtype == "bf16" else torch.float32):
+        return a
     if isinstance(a, np.ndarray):
         if a.dtype == np.uint16:
             t = torch.from_numpy(a.view(np.int16)).to(device).view(torch.bfloat16)
@@ -468,6 +471,12 @@ class Verifier:
             raise DedError(rc, "ded_get_argmax")
         return a, m
 
+    def _settle(self):
+        """After a call on the context's stream whose buffers torch owns: on torch's current stream their use is ordered
+        by the stream itself; on any other one the caller's next use is not, so the device is waited for."""
+        if self.torch.cuda.current_stream(self.device) != self.stream:
+            self.torch.cuda.synchronize(self.device)
+
     def kv_store(self, layer, seq, first_slot, k_plain=None, v_plain=None):
         """k_plain / v_plain: [Hkv][n][hd] numpy (fp32 or bf16 bits) or device tensors."""
         kt = None if k_plain is None else _to_device(k_plain, self.device, self.dtype)
@@ -477,7 +486,7 @@ class Verifier:
                           vt.data_ptr() if vt is not None else None)
         if rc != DED_OK:
             raise DedError(rc, "ded_kv_store")
-        self.torch.cuda.synchronize(self.device)
+        self._settle()
 
     def kv_load(self, layer, seq, first_slot, n):
         t = self.torch
@@ -487,7 +496,7 @@ class Verifier:
         rc = ded_kv_load(self.ctx, layer, seq, first_slot, n, k.data_ptr(), v.data_ptr())
         if rc != DED_OK:
             raise DedError(rc, "ded_kv_load")
-        t.cuda.synchronize(self.device)
+        self._settle()
         return k, v
 
     def tree_attention(self, layer, prefix_len, parents, q, k_tree, v_tree, out=None, static=False):
