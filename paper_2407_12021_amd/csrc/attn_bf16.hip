@@ -43,6 +43,18 @@ __device__ __forceinline__ float quad_max(float v) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Queries and output of the stand-alone entry point: the caller's bf16 [batch][max_nodes][H][hd] arrays instead of
+// PackQ / PackX (null: those).
+struct PlainQO {
+  const bf16_t* q;
+  bf16_t* out;
+  int max_nodes;
+};
+__device__ inline uint2 pack4_bf16(float a, float b, float c, float d) {
+  return make_uint2((uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16),
+                    (uint32_t)f32_to_bf16(c) | ((uint32_t)f32_to_bf16(d) << 16));
+}
+
 // Online soft-max step of ONE row block (16 rows, one per lane & 15) over ONE 32-key chunk.  s[c2][i] is the raw
 // score (q . k, unscaled) of key key0 + quad * 8 + c2 * 4 + i against the lane's row.  Updates the row's running
 // maximum m_run (in units of score * scale * log2 e), returns the factor alpha by which everything accumulated
@@ -135,7 +147,7 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
     const uint4* __restrict__ qp, const uint4* __restrict__ kc, const uint4* __restrict__ vc,
     float* __restrict__ part_o, float2* __restrict__ part_ml, const uint64_t* __restrict__ mask,
     const int32_t* __restrict__ seq_p, const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0, int n_step,
-    int H, int Hkv, int cap, int n_splits, float scale_log2e, bf16_t* __restrict__ o_final, int RB_total) {
+    int H, int Hkv, int cap, int n_splits, float scale_log2e, bf16_t* __restrict__ o_final, int RB_total, PlainQO plain) {
   constexpr int NT = NW * 64;          // threads
   constexpr int RG = NW / KS;          // row groups (of RBW * 16 rows) per workgroup
   constexpr int UPT = 2 * TILE_U4 / NT;  // staged 16-byte units per thread and tile (K and V)
@@ -205,14 +217,28 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
 #pragma unroll
   for (int rb = 0; rb < RBW; ++rb) {
     const int vrb = rb < nrb ? vrb0 + rb : 0;
-    const uint4* qsrc = qp + (((int64_t)bz * (G * n_step / 16) + vrb) * 8 << 6) + lane;
-#pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-      for (int pl = 0; pl < QP; ++pl) q[rb][kk * QP + pl] = __builtin_bit_cast(f16x8_t, qsrc[(kk * 2 + pl) << 6]);
     const int vr = vrb * 16 + row_in;
     g_of[rb] = vr / n_pad;
     node_of[rb] = vr - g_of[rb] * n_pad;
+    if (QP == 1 && plain.q) {
+      // the caller's bf16 rows, widened here (exact): a lane's eight dims are 16 contiguous bytes of its row
+      const int64_t row = ((int64_t)b * plain.max_nodes + min(node_of[rb], N - 1)) * H + kvh * G + g_of[rb];
+      const uint4* src = reinterpret_cast<const uint4*>(plain.q + row * 128) + quad;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const uint4 v = src[kk * 4];
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          q[rb][kk * QP][j] = (_Float16)bf16_to_f32((uint16_t)(w[j >> 1] >> ((j & 1) * 16)));
+      }
+    } else {
+      const uint4* qsrc = qp + (((int64_t)bz * (G * n_step / 16) + vrb) * 8 << 6) + lane;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+        for (int pl = 0; pl < QP; ++pl) q[rb][kk * QP + pl] = __builtin_bit_cast(f16x8_t, qsrc[(kk * 2 + pl) << 6]);
+    }
   }
   // o_l = ones . P^T: the running sum of each row's weights, present in every element
   f32x4_t o[RBW][8], o_l[RBW];
@@ -526,6 +552,16 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
     if (rb >= nrb) continue;
     const float l = o_l[rb][0];  // every element of the ones-row product holds the row's sum
     const int h = kvh * G + g_of[rb];
+    if (QP == 1 && plain.out && n_splits == 1) {
+      if (node_of[rb] >= N) continue;
+      const float inv = 1.0f / l;
+      bf16_t* dst = plain.out + (((int64_t)b * plain.max_nodes + node_of[rb]) * H + h) * 128 + quad * 4;
+#pragma unroll
+      for (int hb = 0; hb < 8; ++hb)
+        *reinterpret_cast<uint2*>(dst + hb * 16) =
+            pack4_bf16(o[rb][hb][0] * inv, o[rb][hb][1] * inv, o[rb][hb][2] * inv, o[rb][hb][3] * inv);
+      continue;
+    }
     if (o_final) {
       // a single key range: nothing to merge, the row is normalised here and written as the O projection's input
       // (hi / lo f16 in PackX; four consecutive features sit side by side inside a fragment)
@@ -559,8 +595,9 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(bf16_t* __restrict
                                                               const float* __restrict__ part_o,
                                                               const float2* __restrict__ part_ml,
                                                               const int32_t* __restrict__ row0,
-                                                              const int32_t* __restrict__ blk_seq, int n_splits,
-                                                              int n_step, int H, int total) {
+                                                              const int32_t* __restrict__ blk_seq,
+                                                              const int32_t* __restrict__ seq_n, int n_splits,
+                                                              int n_step, int H, int total, PlainQO plain) {
   const int gid = blockIdx.x * 256 + threadIdx.x;
   if (gid >= total) return;
   const int d4 = gid & 31, rh = gid >> 5;
@@ -595,6 +632,12 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(bf16_t* __restrict
   }
   const float inv = 1.0f / L;
   const float v[4] = {acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
+  if (plain.out) {
+    if (node < seq_n[b])
+      *reinterpret_cast<uint2*>(plain.out + (((int64_t)b * plain.max_nodes + node) * H + h) * 128 + d4 * 4) =
+          pack4_bf16(v[0], v[1], v[2], v[3]);
+    return;
+  }
   uint16_t hi[4], lo[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) split_f16(v[i], hi[i], lo[i]);
@@ -651,7 +694,7 @@ int bf16_attn_pick_splits(const StepMeta& m, const ModelDims& md, int max_p, int
 
 void bf16_tree_attention(bf16_t* o_packed, int rows_pad, const bf16_t* q_packed, const bf16_t* kc, const bf16_t* vc,
                          float* part_o, float2* part_ml, int n_splits, int q_planes, const StepMeta& m,
-                         const ModelDims& md, hipStream_t s) {
+                         const ModelDims& md, hipStream_t s, const bf16_t* q_plain, bf16_t* out_plain, int max_nodes) {
   if (md.hd != 128 || n_splits < 1 || m.rows <= 0) return;
   const int G = md.H / md.Hkv;
   const int VR = G * m.n_step;
@@ -659,11 +702,12 @@ void bf16_tree_attention(bf16_t* o_packed, int rows_pad, const bf16_t* q_packed,
   const int row_tiles = (VR + attn_tile_rows(kind) - 1) / attn_tile_rows(kind);
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)md.hd);
   const dim3 grid(n_splits, row_tiles, m.batch * md.Hkv);
+  const PlainQO plain = {q_plain, out_plain, max_nodes};
   bf16_t* o_final = n_splits == 1 ? o_packed : nullptr;  // one key range: the kernel finishes the rows itself
 #define DED_ATTN_ARGS                                                                                              \
   reinterpret_cast<const uint4*>(q_packed), reinterpret_cast<const uint4*>(kc), reinterpret_cast<const uint4*>(vc), \
       part_o, part_ml, m.mask, m.seq_p, m.seq_n, m.row0, m.n_step, md.H, md.Hkv, md.cap, n_splits, scale_log2e, o_final,   \
-      rows_pad / 16
+      rows_pad / 16, plain
 #define DED_ATTN_GO(NW, KS, RBW)                                                                                       \
   if (q_planes == 1) hipLaunchKernelGGL((tree_attn_tiled_kernel<1, NW, KS, RBW>), grid, dim3(NW * 64), 0, s, DED_ATTN_ARGS); \
   else hipLaunchKernelGGL((tree_attn_tiled_kernel<2, NW, KS, RBW>), grid, dim3(NW * 64), 0, s, DED_ATTN_ARGS);
@@ -687,7 +731,7 @@ void bf16_tree_attention(bf16_t* o_packed, int rows_pad, const bf16_t* q_packed,
   if (n_splits > 1) {
     const int total = m.rows * md.H * 32;
     hipLaunchKernelGGL(tree_attn_merge_kernel, dim3((total + 255) / 256), dim3(256), 0, s, o_packed, rows_pad / 16,
-                       part_o, part_ml, m.row0, m.blk_seq, n_splits, m.n_step, md.H, total);
+                       part_o, part_ml, m.row0, m.blk_seq, m.seq_n, n_splits, m.n_step, md.H, total, plain);
   }
 }
 

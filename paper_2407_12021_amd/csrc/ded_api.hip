@@ -1004,11 +1004,9 @@ int ded_kv_load(ded_ctx* c, int32_t layer, int32_t seq, int32_t first_slot, int3
   return kv_copy_common(c, layer, seq, first_slot, n, k_plain, v_plain, false);
 }
 
-// Transient device buffers of one stand-alone attention call: the step description, the queries and the output
-// in operand-fragment form, and the split-KV partials.
+// Transient device buffers of one stand-alone attention call: the step description and the split-KV partials.
 struct AttnScratch {
   char* d_meta;
-  bf16_t *q_p, *o_p;
   float* part_o;
   float2* part_ml;
   int64_t part_rows;
@@ -1023,7 +1021,7 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
   if (rc != DED_OK) return rc;
   if (c->poisoned && (rc = clear_step_slots(c)) != DED_OK) return rc;
   const ModelDims& md = c->md;
-  AttnScratch ws = {c->d_meta, c->q_p, c->o_p, c->attn_part_o, c->attn_part_ml, c->attn_part_rows};
+  AttnScratch ws = {c->d_meta, c->attn_part_o, c->attn_part_ml, c->attn_part_rows};
   int ns = 1;
   if (c->bf16) {
     // the key-range count is the workspace path's in both variants, so both give the same bits
@@ -1039,12 +1037,11 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
     shape.rows = rows;
     ns = bf16_attn_pick_splits(shape, md, pmax, c->attn_part_rows);
     if (st) {  // carve the library's own array; a call that does not fit is refused before anything is enqueued
-      const int64_t rows_pad = round_up(shape.rows, 64), qd = (int64_t)md.H * md.hd;
       const int64_t part_rows = (int64_t)batch * md.H * ns * shape.n_step;
       Carve w(reinterpret_cast<char*>(c->static_scratch));
       ws.d_meta = w.take<char>(c->meta_bytes);
-      ws.q_p = w.take<bf16_t>(rows_pad * qd * 2);
-      ws.o_p = w.take<bf16_t>(rows_pad * qd * 2);
+      // part of the documented size of a call: room for the queries and the output in operand-fragment form
+      w.take<bf16_t>((int64_t)round_up(shape.rows, 64) * md.H * md.hd * 4);
       ws.part_o = w.take<float>(part_rows * md.hd);
       ws.part_ml = w.take<float2>(part_rows);
       ws.part_rows = part_rows;
@@ -1063,12 +1060,10 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
   if (c->bf16) {
     const int rows_pad = round_up(m.rows, 64);
     { ProfScope p(c, KC_LAYOUT);
-      bf16_scatter_tree_kv((bf16_t*)c->kc[layer], (bf16_t*)c->vc[layer], (const bf16_t*)k_tree, (const bf16_t*)v_tree, m, md, mn, s);
-      bf16_pack_q(ws.q_p, (const bf16_t*)q, m, md, mn, s); }
+      bf16_scatter_tree_kv((bf16_t*)c->kc[layer], (bf16_t*)c->vc[layer], (const bf16_t*)k_tree, (const bf16_t*)v_tree, m, md, mn, s); }
     { ProfScope p(c, KC_TREE_ATTN);
-      bf16_tree_attention(ws.o_p, rows_pad, ws.q_p, (const bf16_t*)c->kc[layer], (const bf16_t*)c->vc[layer], ws.part_o,
-                          ws.part_ml, ns, 1, m, md, s); }
-    { ProfScope p(c, KC_LAYOUT); bf16_unpack_o((bf16_t*)out, ws.o_p, rows_pad, m, md, mn, s); }
+      bf16_tree_attention(nullptr, rows_pad, nullptr, (const bf16_t*)c->kc[layer], (const bf16_t*)c->vc[layer], ws.part_o,
+                          ws.part_ml, ns, 1, m, md, s, (const bf16_t*)q, (bf16_t*)out, mn); }
   } else {
     { ProfScope p(c, KC_LAYOUT);
       f32_scatter_tree_kv((float*)c->kc[layer], (float*)c->vc[layer], (const float*)k_tree, (const float*)v_tree, m, md, mn, s);

@@ -162,7 +162,8 @@ bool bf16_gemm(float* part, int64_t part_stride, const bf16_t* x_packed, const b
 // there is more than one key range - the merge; the result is written as PackX(o), hi/lo, for the O projection.
 // n_splits from bf16_attn_pick_splits.  part_o: [B][H][n_splits][n_step][hd] fp32, part_ml: [B][H][n_splits][n_step]
 // float2 (max, sum).  q_planes: 2 = the queries are hi + lo pairs, 1 = their lo plane is known to be zero
-// (queries given as bf16).
+// (queries given as bf16).  With q_plain / out_plain (q_planes = 1) the queries are read from, and the result written to,
+// plain bf16 [batch][max_nodes][H][hd] arrays; q_packed and o_packed are then not touched.
 int bf16_attn_pick_splits(const StepMeta& m, const ModelDims& md, int max_p, int64_t part_rows_cap);
 // Query planes the model path hands to the attention: 2, except 1 (hi plane only) when 512 or more rows share each
 // K / V byte (grouped query heads x tree rows per kv head): there the attention is bound by the matrix cores and the lo
@@ -171,7 +172,8 @@ int bf16_attn_pick_splits(const StepMeta& m, const ModelDims& md, int max_p, int
 int bf16_attn_query_planes(const StepMeta& m, const ModelDims& md);
 void bf16_tree_attention(bf16_t* o_packed, int rows_pad, const bf16_t* q_packed, const bf16_t* kc, const bf16_t* vc,
                          float* part_o, float2* part_ml, int n_splits, int q_planes, const StepMeta& m,
-                         const ModelDims& md, hipStream_t s);
+                         const ModelDims& md, hipStream_t s, const bf16_t* q_plain = nullptr,
+                         bf16_t* out_plain = nullptr, int max_nodes = 0);
 void bf16_kv_compact(bf16_t* const* kc, bf16_t* const* vc, const int32_t* path, const int32_t* n_acc,
                      const StepMeta& m, const ModelDims& md, int stride, hipStream_t s);
 void bf16_kv_copy(bf16_t* kcache, bf16_t* vcache, bf16_t* k_plain, bf16_t* v_plain, bool to_cache,
@@ -179,9 +181,5 @@ void bf16_kv_copy(bf16_t* kcache, bf16_t* vcache, bf16_t* k_plain, bf16_t* v_pla
 void bf16_kv_clear(bf16_t* kcache, bf16_t* vcache, int seq, int first, int n, const ModelDims& md, hipStream_t s);
 void bf16_scatter_tree_kv(bf16_t* kc, bf16_t* vc, const bf16_t* k_tree, const bf16_t* v_tree,
                           const StepMeta& m, const ModelDims& md, int max_nodes, hipStream_t s);
-void bf16_pack_q(bf16_t* q_packed, const bf16_t* q_plain, const StepMeta& m, const ModelDims& md,
-                 int max_nodes, hipStream_t s);
-void bf16_unpack_o(bf16_t* out_plain, const bf16_t* o_packed, int rows_pad, const StepMeta& m,
-                   const ModelDims& md, int max_nodes, hipStream_t s);
 
 }  // namespace ded

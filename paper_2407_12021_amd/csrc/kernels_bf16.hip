@@ -330,45 +330,9 @@ __global__ __launch_bounds__(256) void bf16_scatter_tree_kv_kernel(bf16_t* __res
 }
 void bf16_scatter_tree_kv(bf16_t* kc, bf16_t* vc, const bf16_t* k_tree, const bf16_t* v_tree, const StepMeta& m,
                           const ModelDims& md, int max_nodes, hipStream_t s) {
-  hipLaunchKernelGGL(bf16_scatter_tree_kv_kernel, dim3(max_nodes, m.batch * md.Hkv), dim3(128), 0, s, kc, vc,
-                     k_tree, v_tree, m.seq_p, m.seq_n, md.Hkv, md.cap, max_nodes);
-}
-
-// q plain bf16 [B][max_nodes][H][hd] -> PackQ (hi = exact f16, lo = 0; rows of absent nodes become zero)
-__global__ void bf16_pack_q_kernel(bf16_t* __restrict__ qp, const bf16_t* __restrict__ q,
-                                   const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
-                                   const int32_t* __restrict__ blk_seq, int n_step, int H, int Hkv, int max_nodes) {
-  const int hd = 128;
-  int r = blockIdx.x, h = blockIdx.y, i = threadIdx.x;
-  int b = blk_seq[r >> 4], node = r - row0[b], n_pad = (seq_n[b] + 15) & ~15;
-  int G = H / Hkv, kvh = h / G, g = h - kvh * G;
-  uint16_t hi = 0, lo = 0;
-  if (node < seq_n[b]) split_f16(bf16_to_f32(q[(((int64_t)b * max_nodes + node) * H + h) * hd + i]), hi, lo);
-  bf16_t* base = qp + ((int64_t)b * Hkv + kvh) * ((int64_t)G * n_step * hd * 2);
-  base[packq_index(g * n_pad + node, i, 0)] = hi;
-  base[packq_index(g * n_pad + node, i, 1)] = lo;
-}
-void bf16_pack_q(bf16_t* q_packed, const bf16_t* q_plain, const StepMeta& m, const ModelDims& md, int max_nodes,
-                 hipStream_t s) {
-  hipLaunchKernelGGL(bf16_pack_q_kernel, dim3(m.rows, md.H), dim3(128), 0, s, q_packed, q_plain, m.seq_n, m.row0,
-                     m.blk_seq, m.n_step, md.H, md.Hkv, max_nodes);
-}
-
-// PackX(o) hi + lo [rows_pad][H*hd] -> plain bf16 [B][max_nodes][H][hd]
-__global__ void bf16_unpack_o_kernel(bf16_t* __restrict__ out, const bf16_t* __restrict__ op,
-                                     const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
-                                     const int32_t* __restrict__ blk_seq, int H, int RB, int max_nodes) {
-  const int hd = 128;
-  int r = blockIdx.x, h = blockIdx.y, i = threadIdx.x;
-  int b = blk_seq[r >> 4], node = r - row0[b];
-  if (node >= seq_n[b]) return;
-  float v = f16_to_f32(op[packx_index(r, h * hd + i, RB, 0)]) + f16_to_f32(op[packx_index(r, h * hd + i, RB, 1)]);
-  out[(((int64_t)b * max_nodes + node) * H + h) * hd + i] = f32_to_bf16(v);
-}
-void bf16_unpack_o(bf16_t* out_plain, const bf16_t* o_packed, int rows_pad, const StepMeta& m, const ModelDims& md,
-                   int max_nodes, hipStream_t s) {
-  hipLaunchKernelGGL(bf16_unpack_o_kernel, dim3(m.rows, md.H), dim3(128), 0, s, out_plain, o_packed, m.seq_n,
-                     m.row0, m.blk_seq, md.H, rows_pad / 16, max_nodes);
+  // a tree of n nodes touches at most (n + 30) / 32 + 1 groups
+  hipLaunchKernelGGL(bf16_scatter_tree_kv_kernel, dim3((m.n_step + 30) / 32 + 1, m.batch * md.Hkv), dim3(256), 0, s, kc,
+                     vc, k_tree, v_tree, m.seq_p, m.seq_n, md.Hkv, md.cap, max_nodes);
 }
 
 }  // namespace ded
