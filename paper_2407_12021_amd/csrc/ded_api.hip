@@ -575,10 +575,10 @@ bool lm_head_bf16(ded_ctx* c, bool want_logits) {
   // plane matters for what is carried through the layers, not here, where one rounding of the final normalised input
   // (2^-12 relative) moves a logit by ~2e-4.  Below, the weight stream bounds it and the lo product is free.
   const int planes = rows_pad >= 256 ? 1 : 2;
-  GemmPlan plan = bf16_gemm_plan(rows_pad, md.V, d, planes, std::max(cap, 1));
-  if (bf16_gemm_tiles(rows_pad, md.V, plan) > kGemmCounters) plan.splits = 1;
+  GemmPlan plan = bf16_gemm_plan(rows_pad, md.V, d, planes, std::max(cap, 1), c->part_elems, false);
+  if (!plan.tile && bf16_gemm_tiles(rows_pad, md.V, plan) > kGemmCounters) plan.splits = 1;
   ProfScope p(c, KC_GEMM_LM_HEAD);
-  return bf16_gemm(c->part, slice, c->y_p, (const bf16_t*)c->lm_head, rows_pad, md.V, d, planes, plan, c->counters, e,
+  return bf16_gemm(c->part, slice, c->part_elems, c->y_p, (const bf16_t*)c->lm_head, rows_pad, md.V, d, planes, plan, c->counters, e,
                    c->stream);
 }
 
@@ -597,10 +597,10 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
   auto gemm = [&](int cls, const bf16_t* xp, const void* w, int N, int K, int planes, const GemmEpilogue& epi) {
     const int64_t slice = (int64_t)rows_pad * round_up(N, 64);
     int cap = (int)std::min<int64_t>(8, c->part_elems / slice);
-    GemmPlan plan = bf16_gemm_plan(rows_pad, N, K, planes, std::max(cap, 1));
-    if (bf16_gemm_tiles(rows_pad, N, plan) > kGemmCounters) plan.splits = 1;
+    GemmPlan plan = bf16_gemm_plan(rows_pad, N, K, planes, std::max(cap, 1), c->part_elems, epi.kind == EPI_RESIDUAL);
+    if (!plan.tile && bf16_gemm_tiles(rows_pad, N, plan) > kGemmCounters) plan.splits = 1;
     ProfScope p(c, cls);
-    ok = bf16_gemm(c->part, slice, xp, (const bf16_t*)w, rows_pad, N, K, planes, plan, c->counters,
+    ok = bf16_gemm(c->part, slice, c->part_elems, xp, (const bf16_t*)w, rows_pad, N, K, planes, plan, c->counters,
                    epi, s) && ok;
   };
   // RMSNorm is deferred: whoever produces the residual stream also writes x * gain(next norm) as the next

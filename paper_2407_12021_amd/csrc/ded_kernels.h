@@ -144,19 +144,23 @@ struct GemmEpilogue {
 // hi plane.  rows_pad % 64 == 0, N % 16 == 0 (N % 64 for the paired epilogues), K % 128 == 0.  `part` holds
 // plan.splits slices of part_stride >= rows_pad * round_up(N, 64) floats, `counters` one zeroed int per output tile (left zeroed).
 // Returns false (nothing launched) on an unsupported shape.
-struct GemmPlan {
-  int nwn;     // 0: stream kernel (one feature group per workgroup); 2..4: wide kernel, groups per workgroup;
-               // 8, 9: large-row kernel (256 features x 128 / 256 rows per workgroup)
-  int nw;      // stream kernel: wavefronts splitting the k range
-  int splits;  // split-K slices
-  // large-row kernel only: x_main > 0 = two launches, the first x_main feature tiles (whole scheduling rounds)
-  // unsplit, the others with k split rem_splits ways so that they fill one more round
-  int x_main = 0, rem_splits = 0;
+// Workgroup tiles of the tile kernel (features x rows).
+enum {
+  TILE_256x256 = 1, TILE_256x192, TILE_256x128, TILE_128x256, TILE_128x192, TILE_128x128,
+  TILE_64x256, TILE_64x192, TILE_64x128  // single-plane inputs only
 };
-GemmPlan bf16_gemm_plan(int rows_pad, int N, int K, int planes, int max_splits = 8);
+struct GemmPlan {
+  int nwn;       // 0: stream kernel (one feature group per workgroup); 2..4: wide kernel, groups per workgroup
+  int nw;        // stream kernel: wavefronts splitting the k range
+  int splits;    // split-K slices
+  int tile = 0;  // != 0: the tile kernel, with this workgroup tile
+  int whole = 0; // tile kernel: that many tiles whole, the others with k split `splits` ways
+};
+// (narrow: the 64-feature tiles may be used - the residual epilogue's projections)
+GemmPlan bf16_gemm_plan(int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems, bool narrow);
 int bf16_gemm_tiles(int rows_pad, int N, const GemmPlan& plan);
-bool bf16_gemm(float* part, int64_t part_stride, const bf16_t* x_packed, const bf16_t* w_packed, int rows_pad,
-               int N, int K, int planes, const GemmPlan& plan, int* counters, const GemmEpilogue& epi,
+bool bf16_gemm(float* part, int64_t part_stride, int64_t part_elems, const bf16_t* x_packed, const bf16_t* w_packed,
+               int rows_pad, int N, int K, int planes, const GemmPlan& plan, int* counters, const GemmEpilogue& epi,
                hipStream_t s);
 // Tree-masked attention: split-KV partials (running max, sum, unnormalised output per key range), then - when
 // there is more than one key range - the merge; the result is written as PackX(o), hi/lo, for the O projection.

@@ -285,6 +285,7 @@ __device__ inline float ssq_scale(const GemmEpilogue& e, int lane, int nwv, cons
 template <int EPI, int RBN>
 __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb0, int rbase, float row_scale, int lane,
                                     Acc& acc) {
+  // (row blocks from e.rb_total on are surplus ones of a ragged last row tile: nothing is written for them)
   const int row_in = lane & 15, quad = lane >> 4;
   float scale[RBN];
 #pragma unroll
@@ -297,6 +298,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
       if (n >= N) continue;
 #pragma unroll
       for (int rb = 0; rb < RBN; ++rb) {
+        if (rbase + rb >= e.rb_total) continue;
         const int64_t r = (int64_t)(rbase + rb) * 16 + row_in;
         f32x4_t v = acc[t][rb] * scale[rb];
         *reinterpret_cast<float4*>(e.out + r * e.out_stride + n) = make_float4(v[0], v[1], v[2], v[3]);
@@ -308,6 +310,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     uint4* dst = reinterpret_cast<uint4*>(e.top2_part);
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
+      if (rbase + rb >= e.rb_total) continue;
       const int64_t r = (int64_t)(rbase + rb) * 16 + row_in;
       float v1 = -INFINITY, v2 = -INFINITY;
       int i1 = 0x7fffffff, bad = 0;
@@ -349,6 +352,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     // x += Y;  next GEMM input = (x * gain) as hi/lo f16 (its 1/rms is applied by the consumer);  sum(x^2) per group
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
+      if (rbase + rb >= e.rb_total) continue;
       const int r = (rbase + rb) * 16 + row_in;
       float ss = 0.f;
 #pragma unroll
@@ -374,6 +378,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     // group ng = gate features [32 ng, 32 ng + 32) in tiles 0, 1 and the matching up features in tiles 2, 3
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
+      if (rbase + rb >= e.rb_total) continue;
       const int r = (rbase + rb) * 16 + row_in;
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
@@ -394,6 +399,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     const int G = e.H / e.Hkv;
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
+      if (rbase + rb >= e.rb_total) continue;
       const int r = (rbase + rb) * 16 + row_in;
       if (r >= e.rows) continue;
       const int b = e.blk_seq[r >> 4], node = r - e.row0[b];
@@ -860,178 +866,386 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
 }
 
 // ------------------------------------------------------------------------------------------
-// Large-row kernel (rows_pad >= 256: batched trees).  With hundreds of rows per weight the projection is
-// bound by the matrix cores, not by the weight stream, so this is an ordinary tiled GEMM on the same
-// fragment layouts: a workgroup of 8 wavefronts owns FGS feature groups x RGS row groups (FGS * RGS == 8;
-// a wavefront owns GPW = 2 feature groups x 1 row group: 256 features x 256 rows per workgroup), in units of
-// the 64 x 64 tile the other kernels give a wavefront, so the split-K hand-over and the epilogues are shared.
-// A stage holds CH k steps of the workgroup's weights and activations in LDS (double buffered, one barrier
-// per stage; global loads run two stages ahead in registers).  Per k step a wavefront reads 8 weight and
-// 4 x PLANES activation fragments from LDS for 32 x PLANES matrix instructions: LDS read bandwidth, the
-// limit of a smaller wavefront tile (64 x 64: 52 % of the f16 peak), is a third lower per instruction.
+// Tile kernel (more than 128 rows: wide trees, prompt chunks, batches).  With some hundred rows per weight a projection
+// needs the matrix cores and the operand stream at the same time, so operands have to be far ahead of the products
+// without holding registers: every operand lies in memory as whole fragments, and the fragments go from memory straight
+// into LDS (16 bytes per lane, 1 KiB per instruction): a ring of ST slots of KS k steps each, 96 - 144 KB, all but one or
+// two of them in flight.  The slots are separate arrays and the loop is unrolled over them, so that the compiler sees
+// that a slot's reads do not touch the slots still being filled and leaves the waits to the explicit counts; one barrier
+// per slot.
+// 8 wavefronts = FGS x RGS x KS: FGS groups of GPW x 64 features, RGS groups of RBW x 16 rows; KS = 2: two k groups take
+// alternate k steps and are added through LDS.  Where the registers allow it (AHEAD) the next slot's fragments are read
+// while the present one's are multiplied.
+// A workgroup (one per CU) walks a list of items: whole tiles, or one k range of a tile that is split so that a partly
+// empty round fills up.  The partial sums of a split tile travel as slices as in the kernels above, ticketed per
+// wavefront tile: every wavefront position has a last arriver of its own and no barrier is needed.  The first slots of
+// the next item are requested before a tile's epilogue runs.
+// What bounds it: at 512 rows and more the matrix cores at the chip's power limit (LM head of a 7B shape, 512 rows:
+// 225 us = 1.19 PFLOP/s executed, and no more than 1.26 with operands that never leave the caches); at 256 rows the
+// operand stream, ~55 GB/s into each CU (gate/up of a 7B shape 119 -> 101 us, QKV 73 -> 61, O 48 -> 23, down 78 -> 44).
 // ------------------------------------------------------------------------------------------
-__device__ inline float ssq_direct(const GemmEpilogue& e, int rb0, int lane) {
-  if (!e.ssq_in) return 1.f;
-  const float2* p = reinterpret_cast<const float2*>(e.ssq_in + (int64_t)(rb0 * 16 + lane) * e.ssq_groups);
-  float s = 0.f;
-#pragma unroll 8
-  for (int g = 0; g < (e.ssq_groups >> 1); ++g) s += p[g].x + p[g].y;
-  return 1.0f / sqrtf(s * e.inv_k + e.eps);
+typedef __attribute__((address_space(3))) void lds_void_t;
+typedef __attribute__((address_space(1))) const void glb_void_t;
+__device__ __forceinline__ void load_to_lds(const char* src, uint4* dst) {  // lane i: 16 bytes at its src -> dst[i]
+  __builtin_amdgcn_global_load_lds((glb_void_t*)src, (lds_void_t*)dst, 16, 0, 0);
+}
+template <int N>
+__device__ __forceinline__ void wait_loads() {  // all but the last N vector-memory operations, and every LDS read, are done
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ void barrier_only() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
-// Two shapes (plan.nwn 8 and 9): GPW = 1 feature group per wavefront, wavefront grid 4 x 2 (256 features x 128
-// rows per workgroup: more workgroups, for a few hundred rows and for single-plane inputs), and GPW = 2,
-// wavefront grid 2 x 4 (256 features x 256 rows: fewer LDS bytes per matrix instruction).
-constexpr int LARGE_FEAT_GROUPS = 4;  // feature groups per workgroup (x 64 features), both shapes
-constexpr int large_row_groups(int gpw) { return gpw == 1 ? 2 : 4; }  // 64-row groups per workgroup
+// Slices of the tile kernel: the same device-scope accesses (sc1: performed at the device's point of coherence) as
+// slice_store / slice_load, 16 bytes per lane.
+struct SliceRef {
+  __amdgpu_buffer_rsrc_t r;
+};
+constexpr int AUX_DEVICE_SCOPE = 16;  // sc1
+__device__ __forceinline__ SliceRef slice_ref(float* p, int bytes) {
+  return SliceRef{__builtin_amdgcn_make_buffer_rsrc(p, 0, bytes, 0x00020000)};
+}
+__device__ __forceinline__ void slice_store16(const SliceRef& s, int byte, f32x4_t v) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, v), s.r, byte, 0, AUX_DEVICE_SCOPE);
+}
+__device__ __forceinline__ f32x4_t slice_load16(const SliceRef& s, int byte) {
+  return __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(s.r, byte, 0, AUX_DEVICE_SCOPE));
+}
 
-template <int PLANES, int EPI, int GPW>
-__global__ __launch_bounds__(512) void gemm_large_kernel(float* __restrict__ part, int64_t part_stride,
-                                                         const uint4* __restrict__ xp, const uint4* __restrict__ wp,
-                                                         int RB, int N, int KT, int splits,
-                                                         int* __restrict__ counters, GemmEpilogue epi, int x_off,
-                                                         int slice_ng) {
-  // x_off / slice_ng: a launch may cover only the feature tiles from x_off on (the remainder launch of a plan whose
-  // last scheduling round would be mostly empty; it splits k where the main launch does not); its slices are indexed
-  // by the feature group's offset inside that range, slice_ng groups per row group
-  constexpr int FGS = LARGE_FEAT_GROUPS / GPW, RGS = large_row_groups(GPW);
-  constexpr int CH = (PLANES == 2 && GPW == 2) ? 1 : 2;  // k steps per LDS stage
-  static_assert(FGS * RGS == 8, "8 wavefronts");
-  constexpr int W_U4 = FGS * GPW * TN * 64;         // weights of one k step
-  constexpr int X_U4 = RGS * 4 * PLANES * 64;       // activations of one k step
-  constexpr int STEP_U4 = W_U4 + X_U4;
-  constexpr int STAGE_U4 = CH * STEP_U4;
-  constexpr int UPS = STEP_U4 / 512;                // staged units per thread and k step
-  constexpr int WUPS = W_U4 / 512;                  // ... of which weights (the first ones)
-  constexpr int NU = CH * UPS;
-  static_assert(STEP_U4 % 512 == 0 && W_U4 % 512 == 0 && NU <= 8, "units must not straddle operand kinds");
-  static_assert(PD % CH == 0, "a k range holds whole stages");
-  __shared__ uint4 lds[2][STAGE_U4];
-  __shared__ int s_flag;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int fg = wave % FGS, rg = wave / FGS;
+constexpr int TILE_WAVES = 8;
+constexpr int TILE_LDS = 158 * 1024;  // of the CU's 160 KB, for the ring
+template <int PLANES, int FGS, int GPW, int RBW, int KS>
+struct TileShape {
+  static constexpr int RGS = TILE_WAVES / (FGS * KS);
+  static constexpr int FG = FGS * GPW;             // feature groups per workgroup
+  static constexpr int RBT = RGS * RBW;            // row blocks per workgroup
+  static constexpr int WF = FG * TN, XF = RBT * PLANES;  // fragments per k step
+  static constexpr int SLOT_U4 = KS * (WF + XF) * 64;
+  static constexpr int ST_MAX = TILE_LDS / (SLOT_U4 * 16);
+  static constexpr int ST = ST_MAX >= 6 ? 6 : ST_MAX >= 4 ? 4 : ST_MAX;
+  static constexpr int TILE_ELEMS = FG * 64 * RBT * 16;
+  static constexpr int ACC_REGS = GPW * TN * RBW * 4, FRAG_REGS = (GPW * TN + RBW * PLANES) * 4;
+  static constexpr bool AHEAD = ACC_REGS + 2 * FRAG_REGS <= 168;  // room for two slots' fragments in registers
+  static_assert(ST >= 3, "two slots in flight");
+};
+
+template <int PLANES, int EPI, int FGS, int GPW, int RBW, int KS>
+__global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ part, const uint4* __restrict__ xp,
+                                                           const uint4* __restrict__ wp, int RB, int N, int KT, int tiles,
+                                                           int row_tiles, int n_whole, int parts,
+                                                           int* __restrict__ counters, GemmEpilogue epi) {
+  using S = TileShape<PLANES, FGS, GPW, RBW, KS>;
+  constexpr int RGS = S::RGS, FG = S::FG, RBT = S::RBT, WF = S::WF, XF = S::XF, ST = S::ST;
+  constexpr bool AHEAD = S::AHEAD;
+  constexpr int WJ = (KS * WF + TILE_WAVES - 1) / TILE_WAVES, XJ = (KS * XF + TILE_WAVES - 1) / TILE_WAVES;
+  constexpr int IN_FLIGHT = (ST - 2) * (WJ + XJ);  // this wavefront's loads issued after the slot it waits for
+  static_assert((KS * WF) % TILE_WAVES == 0, "every wavefront fetches the same number of weight fragments");
+  static_assert(IN_FLIGHT < 64, "the wait counter has 6 bits");
+  __shared__ uint4 ring0[S::SLOT_U4], ring1[S::SLOT_U4], ring2[S::SLOT_U4];
+  __shared__ uint4 ring3[ST > 3 ? S::SLOT_U4 : 1], ring4[ST > 4 ? S::SLOT_U4 : 1], ring5[ST > 5 ? S::SLOT_U4 : 1];
+  __shared__ float s_scale[2][RBT * 16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fg = wave % FGS, rg = (wave / FGS) % RGS, kg = wave / (FGS * RGS);
   const int NG = (N + 16 * TN - 1) / (16 * TN);
-  const int bx = blockIdx.x + x_off;
-  const int g_off = x_off * (FGS * GPW);
-  const int g_first = (bx * FGS + fg) * GPW;  // first feature group of this wavefront
-  const int split = blockIdx.y;
-  const int rb_tile = blockIdx.z * (RGS * 4);
-  const int rbw = rb_tile + rg * 4;                 // first row block of this wavefront
-  const int groups = KT / PD;
-  const int k_begin = (int)((int64_t)split * groups / splits) * PD;
-  const int k_end = (int)((int64_t)(split + 1) * groups / splits) * PD;
-  const int n_stages = (k_end - k_begin) / CH;      // >= PD / CH >= 2
+  // Work items: the first n_whole tiles whole, then the others in `parts` k ranges each, range by range.  At any time the
+  // workgroups walk the same k range, so that activations (and the weights, between row tiles) meet in the L2s; items
+  // next to each other run on one XCD (workgroup ids go to the 8 XCDs in turn).
+  const int KP = KT / KS;  // slots' worth of k per tile
+  const int rest = tiles - n_whole, items = n_whole + rest * parts;
+  int item = blockIdx.x;
+  if ((gridDim.x & 7) == 0) item = (item & 7) * (gridDim.x >> 3) + (item >> 3);
+  if (item >= items) return;
+  const int64_t xstep = ((int64_t)RB << 11) * KS;  // bytes of activations per slot's worth of k
 
-  // Unit i of a thread (u = tid + 512 i inside a stage): k step i / UPS of the stage; inside the step the
-  // first WUPS units are weights, the others activations (the kind depends on i only).  off[i] = offset of
-  // the unit from the operand's address at the stage's first k step.
-  const int64_t xstride = (int64_t)RB << 7;         // activations of one k step (all row blocks, 2 planes)
-  int64_t off[NU];
-#pragma unroll
-  for (int i = 0; i < NU; ++i) {
-    const int ks = i / UPS, j = i % UPS;
-    if (j < WUPS) {
-      const int v = tid + j * 512;
-      const int g_raw = bx * (FGS * GPW) + (v >> 8);
-      off[i] = ((((int64_t)(g_raw < NG ? g_raw : NG - 1) * KT + ks) * TN) << 6) + (v & 255);
+  // The segment whose slots are being requested: tile, k range in slots, slots left to request; operand addresses as a
+  // wavefront-uniform base that moves with k and a lane offset per load that is fixed inside a tile.
+  int tile, part_id, kp, kp_end, req_left;
+  const char *wbase, *xbase;
+  uint32_t woff[WJ], xoff[XJ];
+  auto open_segment = [&]() {
+    if (item < n_whole) {
+      tile = item, part_id = -1;
+      kp = 0, kp_end = KP;
     } else {
-      const int xu = tid + (j - WUPS) * 512;
-      const int rbl = xu / (PLANES * 64), rem = xu - rbl * (PLANES * 64);
-      const int rb = rb_tile + rbl < RB ? rb_tile + rbl : RB - 1;  // ragged last row tile: re-read a valid block
-      off[i] = ks * xstride + (rb * 2 + rem / 64) * 64 + (rem & 63);
+      part_id = (item - n_whole) / rest;
+      tile = item - part_id * rest;
+      kp = part_id * KP / parts, kp_end = (part_id + 1) * KP / parts;
     }
-  }
-  struct Stage {  // named members keep the staged units in registers
-    uint4 u0, u1, u2, u3, u4, u5, u6, u7;
+    req_left = kp_end - kp;
+    const int tf = tile / row_tiles, rb_tile = (tile - tf * row_tiles) * RBT;
+    wbase = reinterpret_cast<const char*>(wp) + (((int64_t)tf * FG * KT + kp * KS) << 12);
+    xbase = reinterpret_cast<const char*>(xp) + kp * xstep + ((int64_t)rb_tile << 11);
+#pragma unroll
+    for (int j = 0; j < WJ; ++j) {
+      const int f = j * TILE_WAVES + wave, ks = f / WF, fi = f - ks * WF;
+      const int g = min(fi >> 2, NG - 1 - tf * FG);  // surplus feature groups / row blocks re-read a valid one
+      woff[j] = (((uint32_t)g * KT + ks) << 12) + ((fi & 3) << 10) + (lane << 4);
+    }
+#pragma unroll
+    for (int j = 0; j < XJ; ++j) {
+      const int f = min(j * TILE_WAVES + wave, KS * XF - 1), ks = f / XF, fi = f - ks * XF;
+      const int rb = min(fi / PLANES, RB - 1 - rb_tile), p = fi % PLANES;
+      xoff[j] = (((uint32_t)ks * RB + rb) << 11) + (p << 10) + (lane << 4);
+    }
   };
-#define DED_EACH_UNIT(F) F(0, u0) F(1, u1) F(2, u2) F(3, u3) F(4, u4) F(5, u5) F(6, u6) F(7, u7)
-  auto load_stage = [&](int kt) {
-    Stage st;
-    const uint4* wk = wp + ((int64_t)kt * TN << 6);
-    const uint4* xk = xp + kt * xstride;
-#define DED_LOAD(i, m) \
-    if constexpr (i < NU) st.m = ((i % UPS) < WUPS ? wk : xk)[off[i < NU ? i : 0]];
-    DED_EACH_UNIT(DED_LOAD)
-#undef DED_LOAD
-    return st;
+  auto request = [&](uint4* slot) {
+#pragma unroll
+    for (int j = 0; j < WJ; ++j) load_to_lds(wbase + woff[j], slot + (j * TILE_WAVES + wave) * 64);
+#pragma unroll
+    for (int j = 0; j < XJ; ++j)
+      load_to_lds(xbase + xoff[j], slot + (KS * WF + min(j * TILE_WAVES + wave, KS * XF - 1)) * 64);
+    // (past the segment's end its last slot is read again, so that the loads in flight stay countable)
+    --req_left;
+    wbase += req_left > 0 ? KS << 12 : 0;
+    xbase += req_left > 0 ? xstep : 0;
   };
-  auto store_stage = [&](int buf, const Stage& st) {
-    uint4* d = lds[buf] + tid;
-#define DED_STORE(i, m) \
-    if constexpr (i < NU) d[i * 512] = st.m;
-    DED_EACH_UNIT(DED_STORE)
-#undef DED_STORE
+  auto request_first = [&]() {
+    request(ring0);
+    request(ring1);
+    if constexpr (AHEAD || ST > 3) request(ring2);
+    if constexpr (AHEAD ? ST > 3 : ST > 4) request(ring3);
+    if constexpr (AHEAD ? ST > 4 : ST > 5) request(ring4);
+    if constexpr (AHEAD && ST > 5) request(ring5);
   };
-#undef DED_EACH_UNIT
 
   Acc acc[GPW];
+  // a slot's fragments in registers: the next slot's are read while the present one's are multiplied
+  struct Frags {
+    f16x8_t w[GPW * TN], x[RBW * PLANES];
+  };
+  Frags fa, fb;
+  auto read = [&](const uint4* slot, Frags& f) {
+    const uint4* lw = slot + (kg * WF + fg * (GPW * TN)) * 64 + lane;
+    const uint4* lx = slot + (KS * WF + kg * XF + rg * (RBW * PLANES)) * 64 + lane;
 #pragma unroll
-  for (int gw = 0; gw < GPW; ++gw)
+    for (int i = 0; i < RBW * PLANES; ++i) f.x[i] = __builtin_bit_cast(f16x8_t, lx[i << 6]);
 #pragma unroll
-    for (int t = 0; t < TN; ++t)
+    for (int i = 0; i < GPW * TN; ++i) f.w[i] = __builtin_bit_cast(f16x8_t, lw[i << 6]);
+  };
+  auto compute = [&](const Frags& f) {
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb) acc[gw][t][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int buf) {
+    for (int gw = 0; gw < GPW; ++gw)
 #pragma unroll
-    for (int ks = 0; ks < CH; ++ks) {
-      const uint4* lw = lds[buf] + ks * STEP_U4 + fg * (GPW * TN * 64) + lane;
-      const uint4* lx = lds[buf] + ks * STEP_U4 + W_U4 + rg * (4 * PLANES * 64) + lane;
-      f16x8_t b[4 * PLANES];
+      for (int t = 0; t < TN; ++t)
 #pragma unroll
-      for (int i = 0; i < 4 * PLANES; ++i) b[i] = __builtin_bit_cast(f16x8_t, lx[i << 6]);
+        for (int p = 0; p < PLANES; ++p)
 #pragma unroll
-      for (int gw = 0; gw < GPW; ++gw)
-#pragma unroll
-        for (int t = 0; t < TN; ++t) {
-          f16x8_t a = __builtin_bit_cast(f16x8_t, lw[(gw * TN + t) << 6]);
-#pragma unroll
-          for (int p = 0; p < PLANES; ++p)
-#pragma unroll
-            for (int rb = 0; rb < 4; ++rb)
-              acc[gw][t][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b[rb * PLANES + p], acc[gw][t][rb], 0, 0, 0);
-        }
+          for (int rb = 0; rb < RBW; ++rb)
+            acc[gw][t][rb] =
+                __builtin_amdgcn_mfma_f32_16x16x32_f16(f.w[gw * TN + t], f.x[rb * PLANES + p], acc[gw][t][rb], 0, 0, 0);
+  };
+  // One slot.  With the fragments read a step ahead: the slot's own were read in the step before, by every wavefront once
+  // the barrier is passed, so it is free for the request ST slots ahead, and the barrier also says that every wavefront's
+  // loads of the next slot have landed.  (The scheduling fences keep the products in front of the next step's wait.)
+  auto step_ahead = [&](uint4* slot, const uint4* next, const Frags& now, Frags& then, bool live) {
+    wait_loads<IN_FLIGHT>();
+    barrier_only();
+    request(slot);
+    read(next, then);
+    __builtin_amdgcn_sched_barrier(0);
+    if (live) compute(now);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Otherwise (large wavefront tiles): read and multiplied in the same step; the slot of the step before is free.
+  auto step_direct = [&](const uint4* slot, uint4* freed, bool live) {
+    wait_loads<IN_FLIGHT>();
+    barrier_only();
+    request(freed);
+    if (live) {
+      read(slot, fa);
+      compute(fa);
     }
   };
 
-  // Stage c + 2 is fetched while stage c is computed and stage c + 1 is parked in LDS.
-  Stage s0 = load_stage(k_begin);
-  Stage s1 = load_stage(k_begin + CH);
-  store_stage(0, s0);
-  __syncthreads();
-  int buf = 0;
-  for (int c = 0; c + 2 < n_stages; ++c) {
-    Stage s2 = load_stage(k_begin + (c + 2) * CH);
-    compute(buf);
-    store_stage(buf ^ 1, s1);
-    __syncthreads();
-    s1 = s2;
-    buf ^= 1;
-  }
-  compute(buf);  // second-last stage
-  store_stage(buf ^ 1, s1);
-  __syncthreads();
-  compute(buf ^ 1);  // last stage
-
-  // every wavefront finishes its own GPW tiles of 64 features x 64 rows
-  const bool rows_ok = rbw < RB;
-  const float row_scale = ssq_direct(epi, rows_ok ? rbw : 0, lane);
-  bool last = true;
-  if (splits > 1) {
+  open_segment();
+  request_first();
+  for (int par = 0;; par ^= 1) {
+    const int cur_tile = tile, cur_part = part_id, n = kp_end - kp;
+    const int tf = cur_tile / row_tiles, rb_tile = (cur_tile - tf * row_tiles) * RBT;
+    // (lane numbers of their own for what happens once per tile: the addresses derived from them would otherwise be
+    // formed ahead of the loop over tiles and held, or spilled, across the products)
+    int ltid = tid, llane = lane;
+    asm volatile("" : "+v"(ltid), "+v"(llane));
+    // 1 / rms of the tile's input rows, 16 lanes per row, while the first slots are on their way
+    if (epi.ssq_in) {
+      const int n2 = epi.ssq_groups >> 1, l16 = ltid & 15;
 #pragma unroll
-    for (int gw = 1; gw < GPW; ++gw)
-      if (rows_ok && g_first + gw < NG)
-        store_slice(part + (int64_t)split * part_stride, slice_ng, g_first + gw - g_off, rbw, lane, acc[gw]);
-    last = finish_split(part, part_stride, split, splits, counters, slice_ng, (g_first < NG ? g_first : NG - 1) - g_off, rbw,
-                        lane, rows_ok && g_first < NG, acc[0], &s_flag);
-  }
-  if (last && rows_ok) {
-#pragma unroll
-    for (int gw = 0; gw < GPW; ++gw) {
-      const int ng = g_first + gw;
-      if (ng >= NG) continue;
-      if (splits > 1) load_slices<4>(part, part_stride, splits, slice_ng, ng - g_off, rbw, 0, lane, acc[gw]);
-      run_epilogue<EPI, 4>(epi, ng, N, rbw, rbw, row_scale, lane, acc[gw]);
+      for (int i = 0; i < (RBT * 16 + 31) / 32; ++i) {
+        const int rl = i * 32 + (ltid >> 4);
+        const int r = min(rb_tile * 16 + rl, RB * 16 - 1);
+        const float2* src = reinterpret_cast<const float2*>(epi.ssq_in + (int64_t)r * epi.ssq_groups);
+        float s = 0.f;
+        for (int g = l16; g < n2; g += 16) {
+          const float2 v = src[g];
+          s += v.x + v.y;
+        }
+        s += __shfl_xor(s, 1);
+        s += __shfl_xor(s, 2);
+        s += __shfl_xor(s, 4);
+        s += __shfl_xor(s, 8);
+        if (l16 == 0 && rl < RBT * 16) s_scale[par][rl] = 1.0f / sqrtf(s * epi.inv_k + epi.eps);
+      }
     }
+#pragma unroll
+    for (int gw = 0; gw < GPW; ++gw)
+#pragma unroll
+      for (int t = 0; t < TN; ++t)
+#pragma unroll
+        for (int rb = 0; rb < RBW; ++rb) acc[gw][t][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // (one exit, after whole turns of the ring: an exit behind every step would give every step accumulators of its own)
+    if constexpr (AHEAD) {
+      wait_loads<(ST - 1) * (WJ + XJ)>();
+      barrier_only();
+      read(ring0, fa);
+      if constexpr (ST == 3) {
+        for (int c = 0; c < n; c += 6) {
+          step_ahead(ring0, ring1, fa, fb, true);
+          step_ahead(ring1, ring2, fb, fa, c + 1 < n);
+          step_ahead(ring2, ring0, fa, fb, c + 2 < n);
+          step_ahead(ring0, ring1, fb, fa, c + 3 < n);
+          step_ahead(ring1, ring2, fa, fb, c + 4 < n);
+          step_ahead(ring2, ring0, fb, fa, c + 5 < n);
+        }
+      } else {
+        for (int c = 0; c < n; c += ST) {
+          step_ahead(ring0, ring1, fa, fb, true);
+          step_ahead(ring1, ring2, fb, fa, c + 1 < n);
+          step_ahead(ring2, ring3, fa, fb, c + 2 < n);
+          step_ahead(ring3, ST > 4 ? ring4 : ring0, fb, fa, c + 3 < n);
+          if constexpr (ST > 4) {
+            step_ahead(ring4, ring5, fa, fb, c + 4 < n);
+            step_ahead(ring5, ring0, fb, fa, c + 5 < n);
+          }
+        }
+      }
+    } else {
+      for (int c = 0; c < n; c += ST) {
+        step_direct(ring0, ST == 3 ? ring2 : ST == 4 ? ring3 : ring5, true);
+        step_direct(ring1, ring0, c + 1 < n);
+        step_direct(ring2, ring1, c + 2 < n);
+        if constexpr (ST > 3) step_direct(ring3, ring2, c + 3 < n);
+        if constexpr (ST > 4) step_direct(ring4, ring3, c + 4 < n);
+        if constexpr (ST > 4) step_direct(ring5, ring4, c + 5 < n);
+      }
+    }
+    wait_loads<0>();
+    barrier_only();  // every wavefront has read its last slot, nothing is in flight: the ring is free
+    asm volatile("" : "+v"(llane));
+    if constexpr (KS == 2) {
+      // the second k group hands its sums to the first
+      static_assert(KS == 1 || (GPW == 1 && 2 * TN * RBW * 64 <= S::SLOT_U4 && RGS <= 4), "two hand-over areas per slot");
+      float4* area = reinterpret_cast<float4*>(rg < 2 ? ring0 : ring1) + (rg & 1) * (TN * RBW * 64) + llane;
+      if (kg == 1) {
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+          for (int rb = 0; rb < RBW; ++rb) {
+            const f32x4_t v = acc[0][t][rb];
+            area[(t * RBW + rb) * 64] = make_float4(v[0], v[1], v[2], v[3]);
+          }
+      }
+      __syncthreads();
+      if (kg == 0) {
+#pragma unroll
+        for (int t = 0; t < TN; ++t)
+#pragma unroll
+          for (int rb = 0; rb < RBW; ++rb) {
+            const float4 v = area[(t * RBW + rb) * 64];
+            acc[0][t][rb] += f32x4_t{v.x, v.y, v.z, v.w};
+          }
+      }
+      __syncthreads();
+    }
+    item += gridDim.x;
+    const bool more = item < items;
+    if (more) {
+      open_segment();
+      request_first();
+    }
+
+    // finish the tile, or hand this workgroup's part of it over
+    const int rbw = rb_tile + rg * RBW;
+    bool finish = kg == 0 && rbw < RB;
+    if (cur_part >= 0 && finish) {
+      constexpr int WT_ELEMS = GPW * TN * RBW * 256;  // a wavefront tile, in accumulator order
+      constexpr int NF = GPW * TN * RBW, CF = S::ACC_REGS > 64 ? 2 : 4;  // its fragments; fragments summed together
+      const int wt = rg * FGS + fg, rel = cur_tile - n_whole;
+      auto slice = [&](int pt) {
+        return slice_ref(part + ((int64_t)pt * rest + rel) * S::TILE_ELEMS + (int64_t)wt * WT_ELEMS, WT_ELEMS * 4);
+      };
+      {
+        const SliceRef own = slice(cur_part);
+#pragma unroll
+        for (int i = 0; i < NF; ++i) slice_store16(own, (i << 10) + (llane << 4), acc[i / (TN * RBW)][i / RBW % TN][i % RBW]);
+      }
+#ifdef DED_SPLITK_FENCES
+      __atomic_thread_fence(__ATOMIC_RELEASE);
+#else
+      wait_loads<0>();  // the slice has been stored
+#endif
+      int prev = 0;
+      if (llane == 0) {
+        int* ticket = counters + rel * TILE_WAVES + wt;
+        prev = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (prev == parts - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      prev = __builtin_amdgcn_readfirstlane(prev);
+      asm volatile("" ::: "memory");
+      finish = prev == parts - 1;
+#ifdef DED_SPLITK_FENCES
+      if (finish) __atomic_thread_fence(__ATOMIC_ACQUIRE);
+#endif
+      if (finish) {
+        if (parts == 2) {  // the other part is added to the own (the same sum either way round)
+          const SliceRef other = slice(1 - cur_part);
+#pragma unroll
+          for (int i = 0; i < NF; ++i) {
+            acc[i / (TN * RBW)][i / RBW % TN][i % RBW] += slice_load16(other, (i << 10) + (llane << 4));
+            if (S::ACC_REGS > 64 && i % 8 == 7) __builtin_amdgcn_sched_barrier(0);  // (registers for eight in flight)
+          }
+        } else {  // all parts in k order, four at a time (beyond the last part the last one is read again and not added)
+#pragma unroll
+          for (int c = 0; c < NF; c += CF) {
+            f32x4_t sum[CF];
+#pragma unroll
+            for (int i = 0; i < CF; ++i) sum[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int pt = 0; pt < parts; pt += 4) {
+              f32x4_t v[4][CF];
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const SliceRef sl = slice(min(pt + q, parts - 1));
+#pragma unroll
+                for (int i = 0; i < CF; ++i) v[q][i] = slice_load16(sl, ((c + i) << 10) + (llane << 4));
+              }
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                if (pt + q < parts) {
+#pragma unroll
+                  for (int i = 0; i < CF; ++i) sum[i] += v[q][i];
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < CF; ++i) acc[(c + i) / (TN * RBW)][(c + i) / RBW % TN][(c + i) % RBW] = sum[i];
+            if (S::ACC_REGS > 64) __builtin_amdgcn_sched_barrier(0);
+          }
+        }
+      }
+    }
+    if (finish) {
+      const float row_scale = epi.ssq_in ? s_scale[par][rg * (RBW * 16) + min(llane, RBW * 16 - 1)] : 1.f;
+#pragma unroll
+      for (int gw = 0; gw < GPW; ++gw) {
+        const int ng = (tf * FGS + fg) * GPW + gw;
+        if (ng < NG) run_epilogue<EPI, RBW>(epi, ng, N, rbw, rbw, row_scale, llane, acc[gw]);
+      }
+    }
+    if (!more) break;
   }
 }
 
@@ -1043,7 +1257,7 @@ struct Tune {
 #ifdef DED_GEMM_TUNE_ENV
     if (const char* e = getenv("DED_GEMM_TUNE")) {
       int a = -1, b = 0;
-      if (sscanf(e, "%d,%d", &a, &b) == 2 && a >= 0 && a <= 4 && b >= 1) {
+      if (sscanf(e, "%d,%d", &a, &b) == 2 && a >= 0 && b >= 1) {
         nwn = a;
         splits = b;
       }
@@ -1053,6 +1267,7 @@ struct Tune {
 };
 
 constexpr int kCUs = 256;
+constexpr int kTickets = 1 << 16;  // arrival tickets that a launch may use
 
 // relative cost of a shape: weight stream slowed down by activation reloads and uneven CU filling,
 // plus the split-K slices that are written and read back inside the kernel
@@ -1063,35 +1278,100 @@ double shape_cost(int64_t w_bytes, int64_t slice_bytes, int wgs, double x_per_w,
   return stream + 2.0 * (double)slice_bytes * (splits > 1 ? splits : 0);
 }
 
+struct TileDims {
+  int groups, row_blocks, ks;  // 64-feature groups and 16-row blocks of a workgroup tile, k steps per ring slot
+};
+TileDims tile_dims(int tile) {
+  const int gpt[3] = {4, 2, 1}, rbt[3] = {16, 12, 8};
+  const int i = tile - TILE_256x256;
+  return TileDims{gpt[i / 3], rbt[i % 3], i / 3 == 2 ? 2 : 1};
+}
+int64_t tile_count(int tile, int rows_pad, int N) {
+  const TileDims t = tile_dims(tile);
+  const int NG = (N + 16 * TN - 1) / (16 * TN);
+  return (int64_t)((NG + t.groups - 1) / t.groups) * ((rows_pad / 16 + t.row_blocks - 1) / t.row_blocks);
+}
+// whether the slices of a tile plan fit `part_elems` and its k ranges are not empty
+bool tile_plan_ok(const GemmPlan& p, int rows_pad, int N, int K, int64_t part_elems) {
+  if (p.tile < TILE_256x256 || p.tile > TILE_64x128 || p.splits < 1) return false;
+  const TileDims t = tile_dims(p.tile);
+  const int64_t tiles = tile_count(p.tile, rows_pad, N), rest = tiles - p.whole;
+  if (tiles * p.splits > (1 << 20) || p.whole < 0 || rest < 0) return false;
+  if (p.splits == 1) return rest == 0;
+  return rest > 0 && p.splits <= K / 32 / t.ks && rest * 8 <= kTickets &&
+         rest * p.splits * t.groups * 64 * t.row_blocks * 16 <= part_elems;
+}
+
+// Tile and split of a launch of more than 64 rows.  Every tile shape is weighed with the time of one ring slot on a
+// full chip (measured, in us: 7B- and 8B-width projections, 128 - 2048 rows, random operands); with fewer workgroups a
+// slot is faster, because it is the chip's power and memory that bound it more than the CU.  A round that would be
+// partly empty may split its tiles' k range so that they fill it; the hand-over costs about 3 us and 1.5 us per 64 KB
+// slice beyond the first.  Measured against a register-staged kernel with tiles of 256 x 128 / 256 x 256 (7B widths, us per
+// layer of four projections): 192 rows 251 -> 203, 256 rows 317 -> 229, 512 rows 461 -> 360; 8B widths, 2048 rows:
+// 1408 -> 1250 (QKV 238 -> 182, gate/up 794 -> 752, O 104 -> 85, down 272 -> 228), LM head 2.37 -> 1.93 ms.
+GemmPlan plan_tiles(int rows_pad, int N, int K, int planes, int64_t part_elems, bool narrow) {
+  constexpr double slot_us[2][9] = {{0.97, 0.74, 0.52, 0.50, 0.40, 0.31, 0.62, 0.45, 0.36},
+                                    {1.80, 1.25, 0.86, 0.94, 0.70, 0.51, 0, 0, 0}};
+  GemmPlan best{0, 1, 1, TILE_128x128, 0};
+  double best_cost = 1e300;
+  for (int tile = TILE_256x256; tile <= (narrow && planes == 1 ? TILE_64x128 : TILE_128x128); ++tile) {
+    const TileDims t = tile_dims(tile);
+    const int64_t tiles = tile_count(tile, rows_pad, N);
+    const int slots = K / 32 / t.ks;
+    const int64_t full = tiles / kCUs * kCUs;
+    const double slot = slot_us[planes - 1][tile - TILE_256x256], slice_64k = t.groups * t.row_blocks / 16.0;
+    for (int parts = 1; parts <= 8; ++parts) {
+      GemmPlan p{0, 1, parts, tile, (int)(parts == 1 ? tiles : full)};
+      if (parts > 1 && (tiles - full) * parts > kCUs) break;
+      if (!tile_plan_ok(p, rows_pad, N, K, part_elems)) continue;
+      const double fill = (double)((tiles - full) * parts) / kCUs;
+      double cost = (double)(full / kCUs) * slots * slot;
+      if (tiles > full) cost += (double)((slots + parts - 1) / parts) * slot * (0.4 + 0.6 * fill);
+      if (parts > 1) cost += 3.0 + 1.5 * (parts - 1) * slice_64k;
+      if (cost < best_cost) {
+        best_cost = cost;
+        best = p;
+      }
+    }
+  }
+  return best;
+}
+
 template <int PLANES, int EPI>
 bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float* part, int64_t part_stride,
                   const uint4* xp, const uint4* wp, int RB, int N, int KT, int* counters, const GemmEpilogue& epi,
                   int nw, hipStream_t s) {
   const int splits = plan.splits;
 #define DED_ARGS part, part_stride, xp, wp, RB, N, KT, splits, counters, epi
-  if (plan.nwn == 8 || plan.nwn == 9) {
-    const int rgs = large_row_groups(plan.nwn - 7);
-    const int NG = (N + 16 * TN - 1) / (16 * TN);
-    const int X = (NG + LARGE_FEAT_GROUPS - 1) / LARGE_FEAT_GROUPS, Z = (RB + 4 * rgs - 1) / (4 * rgs);
-    auto go = [&](dim3 grid, int64_t stride, int n_splits, int x_off, int slice_ng) {
-      if (plan.nwn == 8)
-        hipLaunchKernelGGL((gemm_large_kernel<PLANES, EPI, 1>), grid, dim3(512), 0, s, part, stride, xp, wp, RB, N, KT,
-                           n_splits, counters, epi, x_off, slice_ng);
-      else
-        hipLaunchKernelGGL((gemm_large_kernel<PLANES, EPI, 2>), grid, dim3(512), 0, s, part, stride, xp, wp, RB, N, KT,
-                           n_splits, counters, epi, x_off, slice_ng);
-    };
-    if (plan.x_main > 0) {
-      // whole rounds unsplit, then the remaining feature tiles with k split so that they fill one more round
-      const int rem_ng = NG - plan.x_main * LARGE_FEAT_GROUPS;
-      go(dim3(plan.x_main, 1, Z), part_stride, 1, 0, NG);
-      go(dim3(X - plan.x_main, plan.rem_splits, Z), (int64_t)RB * 16 * rem_ng * (16 * TN), plan.rem_splits, plan.x_main, rem_ng);
-    } else {
-      go(dim3(X, splits, Z), part_stride, splits, 0, NG);
-    }
+  if (plan.tile) {
+    const TileDims t = tile_dims(plan.tile);
+    const int row_tiles = (RB + t.row_blocks - 1) / t.row_blocks;
+    const int tiles = ((N + 16 * TN - 1) / (16 * TN) + t.groups - 1) / t.groups * row_tiles;
+    const int items = plan.whole + (tiles - plan.whole) * splits;
+#define DED_TILE(ID, FGS, GPW, RBW, KS)                                                                              \
+  case ID:                                                                                                           \
+    hipLaunchKernelGGL((gemm_tile_kernel<PLANES, EPI, FGS, GPW, RBW, KS>), dim3(std::min(kCUs, items)), dim3(512), 0, s,  \
+                       part, xp, wp, RB, N, KT, tiles, row_tiles, plan.whole, splits, counters, epi);                \
     return true;
+    switch (plan.tile) {
+      DED_TILE(TILE_256x256, 2, 2, 4, 1)
+      DED_TILE(TILE_256x192, 2, 2, 3, 1)
+      DED_TILE(TILE_256x128, 2, 2, 2, 1)
+      DED_TILE(TILE_128x256, 2, 1, 4, 1)
+      DED_TILE(TILE_128x192, 2, 1, 3, 1)
+      DED_TILE(TILE_128x128, 2, 1, 2, 1)
+    }
+    if constexpr (EPI == EPI_RESIDUAL) {
+      switch (plan.tile) {
+        DED_TILE(TILE_64x256, 1, 1, 4, 2)
+        DED_TILE(TILE_64x192, 1, 1, 3, 2)
+        DED_TILE(TILE_64x128, 1, 1, 2, 2)
+      }
+    }
+#undef DED_TILE
+    return false;
   }
-  // the logits epilogues read a single plane only where the projection is matrix-bound (the large-row kernel above)
+  // the logits epilogues read a single plane only where the projection is matrix-bound (the tile kernel above)
   if constexpr (PLANES == 1 && (EPI == EPI_LOGITS || EPI == EPI_TOP2)) {
     return false;
   } else {
@@ -1117,53 +1397,12 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
 
 }  // namespace
 
-GemmPlan bf16_gemm_plan(int rows_pad, int N, int K, int planes, int max_splits) {
+GemmPlan bf16_gemm_plan(int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems, bool narrow) {
   static const Tune tune;
   const int NG = (N + 16 * TN - 1) / (16 * TN), groups = K / (32 * PD), rg = rows_pad / 64;
   const int64_t w_bytes = (int64_t)NG * 64 * K * 2, slice = (int64_t)rows_pad * N * 4;
-  if (rows_pad >= 256) {  // matrix-core bound: the large-row kernel
-    // One workgroup per CU is resident, so a launch runs in ceil(workgroups / CUs) rounds.
-    // Two wavefront tiles: one feature group per wavefront (256 features x 128 rows per workgroup: more workgroups)
-    // or two (256 x 256: a quarter to a third fewer LDS bytes per matrix instruction, which is what bounds this
-    // kernel; measured 15-18 % faster at equal CU filling with two-plane inputs, ~30 % with single-plane ones, whose
-    // small tile reads twice the LDS bytes per matrix instruction).  k is split only as far as it takes to fill the
-    // last round (a split costs its slices: ~15 % per extra slice).  From 512 rows both tiles are weighed; the narrow
-    // single-plane projections (N = d) keep the small one - the large tile leaves them so few workgroups that k has
-    // to be split, which measured slower (Llama-3-8B shape, 2048 rows: O 101 -> 130 us) -, the LM head takes the
-    // large one (3.1 -> 2.2 ms per step at that shape).
-    GemmPlan best{8, 1, 1};
-    double best_cost = 1e300;
-    for (int gpw = 1; gpw <= (rows_pad >= 512 ? 2 : 1); ++gpw) {
-      const int tiles = ((NG + LARGE_FEAT_GROUPS - 1) / LARGE_FEAT_GROUPS) *
-                        ((rows_pad + 64 * large_row_groups(gpw) - 1) / (64 * large_row_groups(gpw)));
-      for (int s = 1; s <= 4 && s <= max_splits && s <= groups; ++s) {
-        const int wgs = tiles * s, rounds = (wgs + kCUs - 1) / kCUs;
-        const double c = (double)rounds * kCUs / wgs * (1.0 + 0.15 * (s - 1)) * (gpw == 1 ? 1.15 : 1.0);
-        if (c < best_cost) {
-          best_cost = c;
-          best = GemmPlan{7 + gpw, 1, s};
-        }
-      }
-      // A last round that is at most half full: the whole rounds stay unsplit and only the feature tiles of the
-      // last one split k, 2 - 4 ways, into one more (shorter) round of their own (a second launch).  The cut has to
-      // fall between feature tiles: whole rounds x CUs must be a multiple of the row tiles.
-      const int X = (NG + LARGE_FEAT_GROUPS - 1) / LARGE_FEAT_GROUPS, Z = tiles / X, full = tiles / kCUs;
-      if (max_splits >= 2 && full >= 1 && (full * kCUs) % Z == 0 && full * kCUs < tiles) {
-        const int x_main = full * kCUs / Z, rem = tiles - full * kCUs;
-        const int rs = std::min(std::min(4, groups), kCUs / rem);
-        if (rs >= 2) {
-          const double c = (full + (1.0 + 0.15 * (rs - 1)) / rs + 0.05) * kCUs / tiles * (gpw == 1 ? 1.15 : 1.0);
-          if (c < best_cost) {
-            best_cost = c;
-            best = GemmPlan{7 + gpw, 1, 1};
-            best.x_main = x_main;
-            best.rem_splits = rs;
-          }
-        }
-      }
-    }
-    return best;
-  }
+  // (up to 128 rows the skinny kernels are still the faster ones: 7B width, 97-row step 5.9 ms against 6.4 ms)
+  if (rows_pad > 128) return plan_tiles(rows_pad, N, K, planes, part_elems, narrow);
   GemmPlan best{0, 1, 1};
   double best_cost = 1e300;
   for (int nwn = 0; nwn <= 4; ++nwn) {
@@ -1196,33 +1435,26 @@ GemmPlan bf16_gemm_plan(int rows_pad, int N, int K, int planes, int max_splits) 
 
 int bf16_gemm_tiles(int rows_pad, int N, const GemmPlan& plan) {
   const int NG = (N + 16 * TN - 1) / (16 * TN);
-  if (plan.nwn >= 8) {
-    const int rgs = large_row_groups(plan.nwn - 7);
-    return ((NG + LARGE_FEAT_GROUPS - 1) / LARGE_FEAT_GROUPS) * ((rows_pad + 64 * rgs - 1) / (64 * rgs));
-  }
   const int gx = plan.nwn == 0 ? NG : (NG + plan.nwn - 1) / plan.nwn;
   return gx * (rows_pad / 64);
 }
 
-bool bf16_gemm(float* part, int64_t part_stride, const bf16_t* x_packed, const bf16_t* w_packed, int rows_pad,
+bool bf16_gemm(float* part, int64_t part_stride, int64_t part_elems, const bf16_t* x_packed, const bf16_t* w_packed, int rows_pad,
                int N, int K, int planes, const GemmPlan& plan, int* counters, const GemmEpilogue& epi,
                hipStream_t s) {
   if (rows_pad <= 0 || rows_pad % 64 || N % 16 || K % (32 * PD) || (planes != 1 && planes != 2)) return false;
   const int RB = rows_pad / 16, KT = K / 32, groups = KT / PD;
   const int NG = (N + 16 * TN - 1) / (16 * TN);
   const int splits = plan.splits;
-  if (splits < 1 || splits > groups || !counters) return false;
-  if (plan.nwn != 0 && plan.nwn < 8 && groups / splits < 2) return false;
-  if (plan.nwn > 9) return false;
-  if (plan.x_main > 0) {  // remainder launch: its 2 - 4 compact slices must fit into one slice of the whole matrix
-    const int X = (NG + LARGE_FEAT_GROUPS - 1) / LARGE_FEAT_GROUPS;
-    if (plan.nwn < 8 || splits != 1 || plan.x_main >= X || plan.rem_splits < 2 || plan.rem_splits > 4 ||
-        plan.rem_splits > groups)
-      return false;
-    const int64_t rem_ng = NG - (int64_t)plan.x_main * LARGE_FEAT_GROUPS;
-    if (plan.rem_splits * rows_pad * rem_ng * (16 * TN) > part_stride) return false;
+  if (splits < 1 || !counters) return false;
+  if (plan.tile) {
+    if (!tile_plan_ok(plan, rows_pad, N, K, part_elems)) return false;
+  } else {
+    if (splits > groups) return false;
+    if (plan.nwn != 0 && groups / splits < 2) return false;
+    if (plan.nwn < 0 || plan.nwn > 4) return false;
+    if (splits > 1 && (part_stride < (int64_t)rows_pad * NG * 16 * TN || splits * part_stride > part_elems)) return false;
   }
-  if (splits > 1 && part_stride < (int64_t)rows_pad * NG * 16 * TN) return false;
   if ((epi.kind == EPI_RESIDUAL || epi.kind == EPI_QKV || epi.kind == EPI_SILU) && N % 64) return false;
   int nw = plan.nw >= 4 ? 4 : plan.nw >= 2 ? 2 : 1;
   while (nw > 1 && splits * nw > groups) nw /= 2;  // every wavefront needs at least one k group
@@ -1233,11 +1465,11 @@ bool bf16_gemm(float* part, int64_t part_stride, const bf16_t* x_packed, const b
   switch (epi.kind) {
     case EPI_LOGITS:
       if (planes == 2) DED_GO(2, EPI_LOGITS);
-      if (plan.nwn >= 8) DED_GO(1, EPI_LOGITS);
+      if (plan.tile) DED_GO(1, EPI_LOGITS);
       return false;
     case EPI_TOP2:
       if (planes == 2) DED_GO(2, EPI_TOP2);
-      if (plan.nwn >= 8) DED_GO(1, EPI_TOP2);
+      if (plan.tile) DED_GO(1, EPI_TOP2);
       return false;
     case EPI_QKV:
       if (planes == 2) DED_GO(2, EPI_QKV);

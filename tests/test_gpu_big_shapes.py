@@ -79,7 +79,7 @@ def _teacher_forced_check(name, check_seqs, layers=2, untaught=(), prefix_len=No
             ver.kv_store(l, b, 0, k, v)
             taught[b].append(tuple(t.float().cpu().numpy().astype(np.float64).transpose(1, 0, 2) for t in (k, v)))
     logits = ver.verify_step(P_b, [s[1] for s in seqs], [s[2] for s in seqs], want_logits=True).clone()
-    # the same step once more gives the same bits (large-row kernels with their split remainder launches, the
+    # the same step once more gives the same bits (tile kernel with its split tiles, the
     # pipelined attention loop: every reduction has a fixed order)
     again = ver.verify_step(P_b, [s[1] for s in seqs], [s[2] for s in seqs], want_logits=True)
     assert torch.equal(logits, again)
