@@ -547,6 +547,16 @@ int clear_step_slots(ded_ctx* c) {
   return launch_status();
 }
 
+// Rows that decide into which k ranges a step's projections are summed: those of its trees padded to the largest, so that
+// the sums of a tree do not depend on how much its neighbours in the batch fall short of it.
+int sum_rows(const ded_ctx* c) { return round_up(c->batch * c->n_step, 64); }
+GemmPlan plan_gemm(const ded_ctx* c, int rows_pad, int N, int K, int planes) {
+  const int rows = sum_rows(c);
+  const int cap = (int)std::min<int64_t>(8, c->part_elems / ((int64_t)rows * round_up(N, 64)));
+  GemmPlan plan = bf16_gemm_plan(rows, rows_pad, N, K, planes, std::max(cap, 1), c->part_elems);
+  if (!plan.tile && bf16_gemm_tiles(rows, N, plan) > kGemmCounters) plan.splits = 1;
+  return plan;
+}
 // LM head of the 16-bit path on the final residual stream (c->y_p / c->ssq as the last layer left them).  With
 // want_logits the fp32 logits are written to the workspace; without, only the per-group top-2 candidates that the
 // per-node argmax needs (the logits never reach memory).
@@ -569,17 +579,14 @@ bool lm_head_bf16(ded_ctx* c, bool want_logits) {
     e.top2_part = c->top2_part;
     e.top2_groups = (md.V + 63) / 64;
   }
-  const int64_t slice = (int64_t)rows_pad * round_up(md.V, 64);
-  int cap = (int)std::min<int64_t>(8, c->part_elems / slice);
   // From 256 rows on the projection is bound by the matrix cores and reads the hi plane of its input alone: the lo
   // plane matters for what is carried through the layers, not here, where one rounding of the final normalised input
   // (2^-12 relative) moves a logit by ~2e-4.  Below, the weight stream bounds it and the lo product is free.
-  const int planes = rows_pad >= 256 ? 1 : 2;
-  GemmPlan plan = bf16_gemm_plan(rows_pad, md.V, d, planes, std::max(cap, 1), c->part_elems, false);
-  if (!plan.tile && bf16_gemm_tiles(rows_pad, md.V, plan) > kGemmCounters) plan.splits = 1;
+  const int planes = sum_rows(c) >= 256 ? 1 : 2;
+  const GemmPlan plan = plan_gemm(c, rows_pad, md.V, d, planes);
   ProfScope p(c, KC_GEMM_LM_HEAD);
-  return bf16_gemm(c->part, slice, c->part_elems, c->y_p, (const bf16_t*)c->lm_head, rows_pad, md.V, d, planes, plan, c->counters, e,
-                   c->stream);
+  return bf16_gemm(c->part, (int64_t)rows_pad * round_up(md.V, 64), c->part_elems, c->y_p, (const bf16_t*)c->lm_head,
+                   rows_pad, md.V, d, planes, plan, c->counters, e, c->stream);
 }
 
 int forward_bf16(ded_ctx* c, bool want_logits) {
@@ -595,13 +602,10 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
   base.eps = md.eps;
   // planes: 2 = the input is consumed as hi + lo, 1 = hi only (enough for the O and down projections)
   auto gemm = [&](int cls, const bf16_t* xp, const void* w, int N, int K, int planes, const GemmEpilogue& epi) {
-    const int64_t slice = (int64_t)rows_pad * round_up(N, 64);
-    int cap = (int)std::min<int64_t>(8, c->part_elems / slice);
-    GemmPlan plan = bf16_gemm_plan(rows_pad, N, K, planes, std::max(cap, 1), c->part_elems, epi.kind == EPI_RESIDUAL);
-    if (!plan.tile && bf16_gemm_tiles(rows_pad, N, plan) > kGemmCounters) plan.splits = 1;
+    const GemmPlan plan = plan_gemm(c, rows_pad, N, K, planes);
     ProfScope p(c, cls);
-    ok = bf16_gemm(c->part, slice, c->part_elems, xp, (const bf16_t*)w, rows_pad, N, K, planes, plan, c->counters,
-                   epi, s) && ok;
+    ok = bf16_gemm(c->part, (int64_t)rows_pad * round_up(N, 64), c->part_elems, xp, (const bf16_t*)w, rows_pad, N, K,
+                     planes, plan, c->counters, epi, s) && ok;
   };
   // RMSNorm is deferred: whoever produces the residual stream also writes x * gain(next norm) as the next
   // GEMM input and sum(x^2) per 64 features; the consuming GEMM multiplies its output rows by 1/rms.

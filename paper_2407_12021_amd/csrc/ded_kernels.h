@@ -146,8 +146,7 @@ struct GemmEpilogue {
 // Returns false (nothing launched) on an unsupported shape.
 // Workgroup tiles of the tile kernel (features x rows).
 enum {
-  TILE_256x256 = 1, TILE_256x192, TILE_256x128, TILE_128x256, TILE_128x192, TILE_128x128,
-  TILE_64x256, TILE_64x192, TILE_64x128  // single-plane inputs only
+  TILE_256x256 = 1, TILE_256x192, TILE_256x128, TILE_128x256, TILE_128x192, TILE_128x128
 };
 struct GemmPlan {
   int nwn;       // 0: stream kernel (one feature group per workgroup); 2..4: wide kernel, groups per workgroup
@@ -156,8 +155,8 @@ struct GemmPlan {
   int tile = 0;  // != 0: the tile kernel, with this workgroup tile
   int whole = 0; // tile kernel: that many tiles whole, the others with k split `splits` ways
 };
-// (narrow: the 64-feature tiles may be used - the residual epilogue's projections)
-GemmPlan bf16_gemm_plan(int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems, bool narrow);
+// sum_rows (a multiple of 64, >= rows_pad) decides into which k ranges the sums are split, rows_pad how they are run.
+GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems);
 int bf16_gemm_tiles(int rows_pad, int N, const GemmPlan& plan);
 bool bf16_gemm(float* part, int64_t part_stride, int64_t part_elems, const bf16_t* x_packed, const bf16_t* w_packed,
                int rows_pad, int N, int K, int planes, const GemmPlan& plan, int* counters, const GemmEpilogue& epi,

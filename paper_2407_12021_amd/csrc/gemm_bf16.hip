@@ -282,9 +282,10 @@ __device__ inline float ssq_scale(const GemmEpilogue& e, int lane, int nwv, cons
   return 1.0f / sqrtf(s * e.inv_k + e.eps);
 }
 
-template <int EPI, int RBN>
+// A wavefront may hold only T of the group's four feature tiles, from tile t0 on (paired epilogues: tiles t0 and t0 + 2).
+template <int EPI, int RBN, int T = TN, typename A>
 __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb0, int rbase, float row_scale, int lane,
-                                    Acc& acc) {
+                                    A& acc, int t0 = 0) {
   // (row blocks from e.rb_total on are surplus ones of a ragged last row tile: nothing is written for them)
   const int row_in = lane & 15, quad = lane >> 4;
   float scale[RBN];
@@ -293,8 +294,8 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
 
   if (EPI == EPI_LOGITS) {
 #pragma unroll
-    for (int t = 0; t < TN; ++t) {
-      const int n = (ng * TN + t) * 16 + quad * 4;
+    for (int t = 0; t < T; ++t) {
+      const int n = (ng * TN + t0 + t) * 16 + quad * 4;
       if (n >= N) continue;
 #pragma unroll
       for (int rb = 0; rb < RBN; ++rb) {
@@ -356,20 +357,22 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
       const int r = (rbase + rb) * 16 + row_in;
       float ss = 0.f;
 #pragma unroll
-      for (int t = 0; t < TN; ++t) {
-        const int n = (ng * TN + t) * 16 + quad * 4;
+      for (int t = 0; t < T; ++t) {
+        const int n = (ng * TN + t0 + t) * 16 + quad * 4;
         float* xp = e.x + (int64_t)r * N + n;
         float4 xv = *reinterpret_cast<const float4*>(xp);
         float4 g = *reinterpret_cast<const float4*>(e.gain + n);
         float xn[4] = {xv.x + acc[t][rb][0], xv.y + acc[t][rb][1], xv.z + acc[t][rb][2], xv.w + acc[t][rb][3]};
         *reinterpret_cast<float4*>(xp) = make_float4(xn[0], xn[1], xn[2], xn[3]);
         ss += xn[0] * xn[0] + xn[1] * xn[1] + xn[2] * xn[2] + xn[3] * xn[3];
+        if (T == 1) e.ssq_out[(int64_t)r * (N / 4) + n / 4] = ss;
         float y[4] = {xn[0] * g.x, xn[1] * g.y, xn[2] * g.z, xn[3] * g.w};
         uint2 hi, lo;
         split4_f16(y, hi, lo);
         *reinterpret_cast<uint2*>(e.y_packed + packx_index(r, n, e.rb_total, 0)) = hi;
         *reinterpret_cast<uint2*>(e.y_packed + packx_index(r, n, e.rb_total, 1)) = lo;
       }
+      if (T == 1) continue;
       ss += __shfl_xor(ss, 16);
       ss += __shfl_xor(ss, 32);
       if (quad == 0) e.ssq_out[(int64_t)r * (N / 64) + ng] = ss;
@@ -381,13 +384,13 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
       if (rbase + rb >= e.rb_total) continue;
       const int r = (rbase + rb) * 16 + row_in;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int f = ng * 32 + t * 16 + quad * 4;
+      for (int t = 0; t < T / 2; ++t) {
+        const int f = ng * 32 + (t0 + t) * 16 + quad * 4;
         if (2 * f >= N) continue;
         float h[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          float gv = acc[t][rb][i] * scale[rb], uv = acc[t + 2][rb][i] * scale[rb];
+          float gv = acc[t][rb][i] * scale[rb], uv = acc[t + T / 2][rb][i] * scale[rb];
           h[i] = gv / (1.0f + __expf(-gv)) * uv;
         }
         *reinterpret_cast<uint2*>(e.y_packed + packx_index(r, f, e.rb_total, 0)) = pack4_f16(h[0], h[1], h[2], h[3]);
@@ -407,13 +410,13 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
       const bool real = node < n_b;
       const int slot = e.seq_p[b] + node;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int d0 = 32 * j + 16 * t + quad * 4;
+      for (int t = 0; t < T / 2; ++t) {
+        const int d0 = 32 * j + 16 * (t0 + t) + quad * 4;
         float a[4], c[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           a[i] = acc[t][rb][i] * scale[rb];
-          c[i] = acc[t + 2][rb][i] * scale[rb];
+          c[i] = acc[t + T / 2][rb][i] * scale[rb];
         }
         if (hs < e.H + e.Hkv) {
 #pragma unroll
@@ -869,13 +872,12 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
 // Tile kernel (more than 128 rows: wide trees, prompt chunks, batches).  With some hundred rows per weight a projection
 // needs the matrix cores and the operand stream at the same time, so operands have to be far ahead of the products
 // without holding registers: every operand lies in memory as whole fragments, and the fragments go from memory straight
-// into LDS (16 bytes per lane, 1 KiB per instruction): a ring of ST slots of KS k steps each, 96 - 144 KB, all but one or
+// into LDS (16 bytes per lane, 1 KiB per instruction): a ring of ST slots of one k step each, 96 - 144 KB, all but one or
 // two of them in flight.  The slots are separate arrays and the loop is unrolled over them, so that the compiler sees
 // that a slot's reads do not touch the slots still being filled and leaves the waits to the explicit counts; one barrier
 // per slot.
-// 8 wavefronts = FGS x RGS x KS: FGS groups of GPW x 64 features, RGS groups of RBW x 16 rows; KS = 2: two k groups take
-// alternate k steps and are added through LDS.  Where the registers allow it (AHEAD) the next slot's fragments are read
-// while the present one's are multiplied.
+// 8 wavefronts = 2 x 4: two groups of GPW x 64 features, four of RBW x 16 rows.  Where the registers allow it (AHEAD) the
+// next slot's fragments are read while the present one's are multiplied.
 // A workgroup (one per CU) walks a list of items: whole tiles, or one k range of a tile that is split so that a partly
 // empty round fills up.  The partial sums of a split tile travel as slices as in the kernels above, ticketed per
 // wavefront tile: every wavefront position has a last arriver of its own and no barrier is needed.  The first slots of
@@ -919,13 +921,13 @@ __device__ __forceinline__ f32x4_t slice_load16(const SliceRef& s, int byte) {
 
 constexpr int TILE_WAVES = 8;
 constexpr int TILE_LDS = 158 * 1024;  // of the CU's 160 KB, for the ring
-template <int PLANES, int FGS, int GPW, int RBW, int KS>
+template <int PLANES, int GPW, int RBW>
 struct TileShape {
-  static constexpr int RGS = TILE_WAVES / (FGS * KS);
+  static constexpr int FGS = 2, RGS = TILE_WAVES / FGS;
   static constexpr int FG = FGS * GPW;             // feature groups per workgroup
   static constexpr int RBT = RGS * RBW;            // row blocks per workgroup
   static constexpr int WF = FG * TN, XF = RBT * PLANES;  // fragments per k step
-  static constexpr int SLOT_U4 = KS * (WF + XF) * 64;
+  static constexpr int SLOT_U4 = (WF + XF) * 64;
   static constexpr int ST_MAX = TILE_LDS / (SLOT_U4 * 16);
   static constexpr int ST = ST_MAX >= 6 ? 6 : ST_MAX >= 4 ? 4 : ST_MAX;
   static constexpr int TILE_ELEMS = FG * 64 * RBT * 16;
@@ -934,33 +936,32 @@ struct TileShape {
   static_assert(ST >= 3, "two slots in flight");
 };
 
-template <int PLANES, int EPI, int FGS, int GPW, int RBW, int KS>
+template <int PLANES, int EPI, int GPW, int RBW>
 __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ part, const uint4* __restrict__ xp,
                                                            const uint4* __restrict__ wp, int RB, int N, int KT, int tiles,
                                                            int row_tiles, int n_whole, int parts,
                                                            int* __restrict__ counters, GemmEpilogue epi) {
-  using S = TileShape<PLANES, FGS, GPW, RBW, KS>;
-  constexpr int RGS = S::RGS, FG = S::FG, RBT = S::RBT, WF = S::WF, XF = S::XF, ST = S::ST;
+  using S = TileShape<PLANES, GPW, RBW>;
+  constexpr int FGS = S::FGS, FG = S::FG, RBT = S::RBT, WF = S::WF, XF = S::XF, ST = S::ST;
   constexpr bool AHEAD = S::AHEAD;
-  constexpr int WJ = (KS * WF + TILE_WAVES - 1) / TILE_WAVES, XJ = (KS * XF + TILE_WAVES - 1) / TILE_WAVES;
+  constexpr int WJ = WF / TILE_WAVES, XJ = (XF + TILE_WAVES - 1) / TILE_WAVES;
   constexpr int IN_FLIGHT = (ST - 2) * (WJ + XJ);  // this wavefront's loads issued after the slot it waits for
-  static_assert((KS * WF) % TILE_WAVES == 0, "every wavefront fetches the same number of weight fragments");
+  static_assert(WF % TILE_WAVES == 0, "every wavefront fetches the same number of weight fragments");
   static_assert(IN_FLIGHT < 64, "the wait counter has 6 bits");
   __shared__ uint4 ring0[S::SLOT_U4], ring1[S::SLOT_U4], ring2[S::SLOT_U4];
   __shared__ uint4 ring3[ST > 3 ? S::SLOT_U4 : 1], ring4[ST > 4 ? S::SLOT_U4 : 1], ring5[ST > 5 ? S::SLOT_U4 : 1];
   __shared__ float s_scale[2][RBT * 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int fg = wave % FGS, rg = (wave / FGS) % RGS, kg = wave / (FGS * RGS);
+  const int fg = wave % FGS, rg = wave / FGS;
   const int NG = (N + 16 * TN - 1) / (16 * TN);
   // Work items: the first n_whole tiles whole, then the others in `parts` k ranges each, range by range.  At any time the
   // workgroups walk the same k range, so that activations (and the weights, between row tiles) meet in the L2s; items
   // next to each other run on one XCD (workgroup ids go to the 8 XCDs in turn).
-  const int KP = KT / KS;  // slots' worth of k per tile
   const int rest = tiles - n_whole, items = n_whole + rest * parts;
   int item = blockIdx.x;
   if ((gridDim.x & 7) == 0) item = (item & 7) * (gridDim.x >> 3) + (item >> 3);
   if (item >= items) return;
-  const int64_t xstep = ((int64_t)RB << 11) * KS;  // bytes of activations per slot's worth of k
+  const int64_t xstep = (int64_t)RB << 11;  // bytes of activations per k step
 
   // The segment whose slots are being requested: tile, k range in slots, slots left to request; operand addresses as a
   // wavefront-uniform base that moves with k and a lane offset per load that is fixed inside a tile.
@@ -970,27 +971,27 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
   auto open_segment = [&]() {
     if (item < n_whole) {
       tile = item, part_id = -1;
-      kp = 0, kp_end = KP;
+      kp = 0, kp_end = KT;
     } else {
       part_id = (item - n_whole) / rest;
       tile = item - part_id * rest;
-      kp = part_id * KP / parts, kp_end = (part_id + 1) * KP / parts;
+      kp = part_id * (KT / PD) / parts * PD, kp_end = (part_id + 1) * (KT / PD) / parts * PD;
     }
     req_left = kp_end - kp;
     const int tf = tile / row_tiles, rb_tile = (tile - tf * row_tiles) * RBT;
-    wbase = reinterpret_cast<const char*>(wp) + (((int64_t)tf * FG * KT + kp * KS) << 12);
+    wbase = reinterpret_cast<const char*>(wp) + (((int64_t)tf * FG * KT + kp) << 12);
     xbase = reinterpret_cast<const char*>(xp) + kp * xstep + ((int64_t)rb_tile << 11);
 #pragma unroll
     for (int j = 0; j < WJ; ++j) {
-      const int f = j * TILE_WAVES + wave, ks = f / WF, fi = f - ks * WF;
-      const int g = min(fi >> 2, NG - 1 - tf * FG);  // surplus feature groups / row blocks re-read a valid one
-      woff[j] = (((uint32_t)g * KT + ks) << 12) + ((fi & 3) << 10) + (lane << 4);
+      const int f = j * TILE_WAVES + wave;
+      const int g = min(f >> 2, NG - 1 - tf * FG);  // surplus feature groups / row blocks re-read a valid one
+      woff[j] = (((uint32_t)g * KT) << 12) + ((f & 3) << 10) + (lane << 4);
     }
 #pragma unroll
     for (int j = 0; j < XJ; ++j) {
-      const int f = min(j * TILE_WAVES + wave, KS * XF - 1), ks = f / XF, fi = f - ks * XF;
-      const int rb = min(fi / PLANES, RB - 1 - rb_tile), p = fi % PLANES;
-      xoff[j] = (((uint32_t)ks * RB + rb) << 11) + (p << 10) + (lane << 4);
+      const int f = min(j * TILE_WAVES + wave, XF - 1);
+      const int rb = min(f / PLANES, RB - 1 - rb_tile), p = f % PLANES;
+      xoff[j] = ((uint32_t)rb << 11) + (p << 10) + (lane << 4);
     }
   };
   auto request = [&](uint4* slot) {
@@ -998,10 +999,10 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
     for (int j = 0; j < WJ; ++j) load_to_lds(wbase + woff[j], slot + (j * TILE_WAVES + wave) * 64);
 #pragma unroll
     for (int j = 0; j < XJ; ++j)
-      load_to_lds(xbase + xoff[j], slot + (KS * WF + min(j * TILE_WAVES + wave, KS * XF - 1)) * 64);
+      load_to_lds(xbase + xoff[j], slot + (WF + min(j * TILE_WAVES + wave, XF - 1)) * 64);
     // (past the segment's end its last slot is read again, so that the loads in flight stay countable)
     --req_left;
-    wbase += req_left > 0 ? KS << 12 : 0;
+    wbase += req_left > 0 ? 1 << 12 : 0;
     xbase += req_left > 0 ? xstep : 0;
   };
   auto request_first = [&]() {
@@ -1020,8 +1021,8 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
   };
   Frags fa, fb;
   auto read = [&](const uint4* slot, Frags& f) {
-    const uint4* lw = slot + (kg * WF + fg * (GPW * TN)) * 64 + lane;
-    const uint4* lx = slot + (KS * WF + kg * XF + rg * (RBW * PLANES)) * 64 + lane;
+    const uint4* lw = slot + fg * (GPW * TN) * 64 + lane;
+    const uint4* lx = slot + (WF + rg * (RBW * PLANES)) * 64 + lane;
 #pragma unroll
     for (int i = 0; i < RBW * PLANES; ++i) f.x[i] = __builtin_bit_cast(f16x8_t, lx[i << 6]);
 #pragma unroll
@@ -1071,25 +1072,14 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
     // formed ahead of the loop over tiles and held, or spilled, across the products)
     int ltid = tid, llane = lane;
     asm volatile("" : "+v"(ltid), "+v"(llane));
-    // 1 / rms of the tile's input rows, 16 lanes per row, while the first slots are on their way
-    if (epi.ssq_in) {
-      const int n2 = epi.ssq_groups >> 1, l16 = ltid & 15;
-#pragma unroll
-      for (int i = 0; i < (RBT * 16 + 31) / 32; ++i) {
-        const int rl = i * 32 + (ltid >> 4);
-        const int r = min(rb_tile * 16 + rl, RB * 16 - 1);
-        const float2* src = reinterpret_cast<const float2*>(epi.ssq_in + (int64_t)r * epi.ssq_groups);
-        float s = 0.f;
-        for (int g = l16; g < n2; g += 16) {
-          const float2 v = src[g];
-          s += v.x + v.y;
-        }
-        s += __shfl_xor(s, 1);
-        s += __shfl_xor(s, 2);
-        s += __shfl_xor(s, 4);
-        s += __shfl_xor(s, 8);
-        if (l16 == 0 && rl < RBT * 16) s_scale[par][rl] = 1.0f / sqrtf(s * epi.inv_k + epi.eps);
-      }
+    // 1 / rms of the tile's input rows, one thread per row, while the first slots are on their way
+    if (epi.ssq_in && ltid < RBT * 16) {
+      const int r = min(rb_tile * 16 + ltid, RB * 16 - 1);
+      const float2* src = reinterpret_cast<const float2*>(epi.ssq_in + (int64_t)r * epi.ssq_groups);
+      float s = 0.f;
+#pragma unroll 16
+      for (int g = 0; g < (epi.ssq_groups >> 1); ++g) s += src[g].x + src[g].y;
+      s_scale[par][ltid] = 1.0f / sqrtf(s * epi.inv_k + epi.eps);
     }
 #pragma unroll
     for (int gw = 0; gw < GPW; ++gw)
@@ -1137,31 +1127,6 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
     wait_loads<0>();
     barrier_only();  // every wavefront has read its last slot, nothing is in flight: the ring is free
     asm volatile("" : "+v"(llane));
-    if constexpr (KS == 2) {
-      // the second k group hands its sums to the first
-      static_assert(KS == 1 || (GPW == 1 && 2 * TN * RBW * 64 <= S::SLOT_U4 && RGS <= 4), "two hand-over areas per slot");
-      float4* area = reinterpret_cast<float4*>(rg < 2 ? ring0 : ring1) + (rg & 1) * (TN * RBW * 64) + llane;
-      if (kg == 1) {
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-#pragma unroll
-          for (int rb = 0; rb < RBW; ++rb) {
-            const f32x4_t v = acc[0][t][rb];
-            area[(t * RBW + rb) * 64] = make_float4(v[0], v[1], v[2], v[3]);
-          }
-      }
-      __syncthreads();
-      if (kg == 0) {
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-#pragma unroll
-          for (int rb = 0; rb < RBW; ++rb) {
-            const float4 v = area[(t * RBW + rb) * 64];
-            acc[0][t][rb] += f32x4_t{v.x, v.y, v.z, v.w};
-          }
-      }
-      __syncthreads();
-    }
     item += gridDim.x;
     const bool more = item < items;
     if (more) {
@@ -1171,7 +1136,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
 
     // finish the tile, or hand this workgroup's part of it over
     const int rbw = rb_tile + rg * RBW;
-    bool finish = kg == 0 && rbw < RB;
+    bool finish = rbw < RB;
     if (cur_part >= 0 && finish) {
       constexpr int WT_ELEMS = GPW * TN * RBW * 256;  // a wavefront tile, in accumulator order
       constexpr int NF = GPW * TN * RBW, CF = S::ACC_REGS > 64 ? 2 : 4;  // its fragments; fragments summed together
@@ -1279,62 +1244,97 @@ double shape_cost(int64_t w_bytes, int64_t slice_bytes, int wgs, double x_per_w,
 }
 
 struct TileDims {
-  int groups, row_blocks, ks;  // 64-feature groups and 16-row blocks of a workgroup tile, k steps per ring slot
+  int groups, row_blocks;  // 64-feature groups and 16-row blocks of a workgroup tile
 };
 TileDims tile_dims(int tile) {
-  const int gpt[3] = {4, 2, 1}, rbt[3] = {16, 12, 8};
-  const int i = tile - TILE_256x256;
-  return TileDims{gpt[i / 3], rbt[i % 3], i / 3 == 2 ? 2 : 1};
+  const int rbt[3] = {16, 12, 8};
+  return TileDims{tile < TILE_128x256 ? 4 : 2, rbt[(tile - TILE_256x256) % 3]};
 }
+int row_tile_count(int tile, int rows_pad) { return (rows_pad / 16 + tile_dims(tile).row_blocks - 1) / tile_dims(tile).row_blocks; }
 int64_t tile_count(int tile, int rows_pad, int N) {
-  const TileDims t = tile_dims(tile);
-  const int NG = (N + 16 * TN - 1) / (16 * TN);
-  return (int64_t)((NG + t.groups - 1) / t.groups) * ((rows_pad / 16 + t.row_blocks - 1) / t.row_blocks);
+  const int NG = (N + 16 * TN - 1) / (16 * TN), groups = tile_dims(tile).groups;
+  return (int64_t)((NG + groups - 1) / groups) * row_tile_count(tile, rows_pad);
 }
 // whether the slices of a tile plan fit `part_elems` and its k ranges are not empty
 bool tile_plan_ok(const GemmPlan& p, int rows_pad, int N, int K, int64_t part_elems) {
-  if (p.tile < TILE_256x256 || p.tile > TILE_64x128 || p.splits < 1) return false;
+  if (p.tile < TILE_256x256 || p.tile > TILE_128x128 || p.splits < 1) return false;
   const TileDims t = tile_dims(p.tile);
   const int64_t tiles = tile_count(p.tile, rows_pad, N), rest = tiles - p.whole;
   if (tiles * p.splits > (1 << 20) || p.whole < 0 || rest < 0) return false;
   if (p.splits == 1) return rest == 0;
-  return rest > 0 && p.splits <= K / 32 / t.ks && rest * 8 <= kTickets &&
+  return rest > 0 && p.splits <= K / (32 * PD) && rest * TILE_WAVES <= kTickets &&
          rest * p.splits * t.groups * 64 * t.row_blocks * 16 <= part_elems;
 }
 
-// Tile and split of a launch of more than 64 rows.  Every tile shape is weighed with the time of one ring slot on a
-// full chip (measured, in us: 7B- and 8B-width projections, 128 - 2048 rows, random operands); with fewer workgroups a
-// slot is faster, because it is the chip's power and memory that bound it more than the CU.  A round that would be
-// partly empty may split its tiles' k range so that they fill it; the hand-over costs about 3 us and 1.5 us per 64 KB
-// slice beyond the first.  Measured against a register-staged kernel with tiles of 256 x 128 / 256 x 256 (7B widths, us per
-// layer of four projections): 192 rows 251 -> 203, 256 rows 317 -> 229, 512 rows 461 -> 360; 8B widths, 2048 rows:
-// 1408 -> 1250 (QKV 238 -> 182, gate/up 794 -> 752, O 104 -> 85, down 272 -> 228), LM head 2.37 -> 1.93 ms.
-GemmPlan plan_tiles(int rows_pad, int N, int K, int planes, int64_t part_elems, bool narrow) {
-  constexpr double slot_us[2][9] = {{0.97, 0.74, 0.52, 0.50, 0.40, 0.31, 0.62, 0.45, 0.36},
-                                    {1.80, 1.25, 0.86, 0.94, 0.70, 0.51, 0, 0, 0}};
-  GemmPlan best{0, 1, 1, TILE_128x128, 0};
+// Into how many k ranges a product of 256 and more rows is summed: the first x_main groups of 256 features in `main`, the
+// others in `rem`.  The shape alone decides it, not the workgroup tile, so that a result has the same bits whichever tile
+// runs.  The ranges are counted so that 256 x 128 (from 512 rows on also 256 x 256) tiles fill the chip's last round of
+// one workgroup per CU: as few as it takes, or whole rounds unsplit and only a mostly empty last one split.
+struct KRanges {
+  int x_main, main, rem;
+};
+KRanges k_ranges(int rows, int N, int K, int planes, int max_splits) {
+  const int NG = (N + 16 * TN - 1) / (16 * TN), groups = K / (32 * PD), X = (NG + 3) / 4;
+  KRanges best{X, 1, 1};
   double best_cost = 1e300;
-  for (int tile = TILE_256x256; tile <= (narrow && planes == 1 ? TILE_64x128 : TILE_128x128); ++tile) {
-    const TileDims t = tile_dims(tile);
-    const int64_t tiles = tile_count(tile, rows_pad, N);
-    const int slots = K / 32 / t.ks;
-    const int64_t full = tiles / kCUs * kCUs;
-    const double slot = slot_us[planes - 1][tile - TILE_256x256], slice_64k = t.groups * t.row_blocks / 16.0;
-    for (int parts = 1; parts <= 8; ++parts) {
-      GemmPlan p{0, 1, parts, tile, (int)(parts == 1 ? tiles : full)};
-      if (parts > 1 && (tiles - full) * parts > kCUs) break;
-      if (!tile_plan_ok(p, rows_pad, N, K, part_elems)) continue;
-      const double fill = (double)((tiles - full) * parts) / kCUs;
-      double cost = (double)(full / kCUs) * slots * slot;
-      if (tiles > full) cost += (double)((slots + parts - 1) / parts) * slot * (0.4 + 0.6 * fill);
-      if (parts > 1) cost += 3.0 + 1.5 * (parts - 1) * slice_64k;
-      if (cost < best_cost) {
-        best_cost = cost;
-        best = p;
+  for (int wide = 0; wide <= (rows >= 512 ? 1 : 0); ++wide) {
+    const int Z = (rows + (wide ? 255 : 127)) / (wide ? 256 : 128), tiles = X * Z;
+    const double slow = wide ? 1.0 : 1.15;
+    for (int s = 1; s <= 4 && s <= max_splits && s <= groups; ++s) {
+      const int wgs = tiles * s, rounds = (wgs + kCUs - 1) / kCUs;
+      const double c = (double)rounds * kCUs / wgs * (1.0 + 0.15 * (s - 1)) * slow;
+      if (c < best_cost) {
+        best_cost = c;
+        best = KRanges{X, s, 1};
+      }
+    }
+    const int full = tiles / kCUs;
+    if (max_splits >= 2 && full >= 1 && (full * kCUs) % Z == 0 && full * kCUs < tiles) {
+      const int rem = tiles - full * kCUs, rs = std::min(std::min(4, groups), kCUs / rem);
+      if (rs >= 2) {
+        const double c = (full + (1.0 + 0.15 * (rs - 1)) / rs + 0.05) * kCUs / tiles * slow;
+        if (c < best_cost) {
+          best_cost = c;
+          best = KRanges{full * kCUs / Z, 1, rs};
+        }
       }
     }
   }
   return best;
+}
+
+// Tile of a launch of 256 and more rows.  Every tile shape is weighed with the time of one ring slot on a full chip
+// (measured, in us: 7B- and 8B-width projections, 128 - 2048 rows, random operands); with fewer workgroups a slot is
+// faster, because it is the chip's power and memory that bound it more than the CU.  A hand-over costs about 3 us and
+// 1.5 us per 64 KB slice beyond the first.
+GemmPlan plan_tiles(int sum_rows, int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems) {
+  constexpr double slot_us[2][6] = {{0.97, 0.74, 0.52, 0.50, 0.40, 0.31}, {1.80, 1.25, 0.86, 0.94, 0.70, 0.51}};
+  const KRanges r = k_ranges(sum_rows, N, K, planes, max_splits);
+  const int parts = r.main > 1 ? r.main : r.rem;
+  GemmPlan best{0, 1, 1, 0, 0};
+  double best_cost = 1e300;
+  for (int tile = TILE_256x256; tile <= TILE_128x128; ++tile) {
+    const TileDims t = tile_dims(tile);
+    const int64_t tiles = tile_count(tile, rows_pad, N);
+    const int64_t whole = r.main > 1 ? 0 : std::min<int64_t>(tiles, (int64_t)r.x_main * (4 / t.groups) * row_tile_count(tile, rows_pad));
+    const int slots = K / 32;
+    const double slot = slot_us[planes - 1][tile - TILE_256x256], slice_64k = t.groups * t.row_blocks / 16.0;
+    const GemmPlan p{0, 1, parts, tile, (int)whole};
+    if (!tile_plan_ok(p, rows_pad, N, K, part_elems)) continue;
+    double cost = 0.0;
+    auto rounds = [&](int64_t items, int len) {
+      const double fill = (double)(items % kCUs) / kCUs;
+      cost += (double)(items / kCUs) * len * slot + (fill > 0 ? len * slot * (0.4 + 0.6 * fill) : 0.0);
+    };
+    rounds(whole, slots);
+    rounds((tiles - whole) * parts, (slots + parts - 1) / parts);
+    if (parts > 1) cost += 3.0 + 1.5 * (parts - 1) * slice_64k;
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = p;
+    }
+  }
+  return best.tile || max_splits <= 1 ? best : plan_tiles(sum_rows, rows_pad, N, K, planes, 1, part_elems);  // no room for slices
 }
 
 template <int PLANES, int EPI>
@@ -1348,25 +1348,18 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
     const int row_tiles = (RB + t.row_blocks - 1) / t.row_blocks;
     const int tiles = ((N + 16 * TN - 1) / (16 * TN) + t.groups - 1) / t.groups * row_tiles;
     const int items = plan.whole + (tiles - plan.whole) * splits;
-#define DED_TILE(ID, FGS, GPW, RBW, KS)                                                                              \
+#define DED_TILE(ID, GPW, RBW)                                                                                       \
   case ID:                                                                                                           \
-    hipLaunchKernelGGL((gemm_tile_kernel<PLANES, EPI, FGS, GPW, RBW, KS>), dim3(std::min(kCUs, items)), dim3(512), 0, s,  \
-                       part, xp, wp, RB, N, KT, tiles, row_tiles, plan.whole, splits, counters, epi);                \
+    hipLaunchKernelGGL((gemm_tile_kernel<PLANES, EPI, GPW, RBW>), dim3(std::min(kCUs, items)), dim3(512), 0, s, part, xp, \
+                       wp, RB, N, KT, tiles, row_tiles, plan.whole, splits, counters, epi);                          \
     return true;
     switch (plan.tile) {
-      DED_TILE(TILE_256x256, 2, 2, 4, 1)
-      DED_TILE(TILE_256x192, 2, 2, 3, 1)
-      DED_TILE(TILE_256x128, 2, 2, 2, 1)
-      DED_TILE(TILE_128x256, 2, 1, 4, 1)
-      DED_TILE(TILE_128x192, 2, 1, 3, 1)
-      DED_TILE(TILE_128x128, 2, 1, 2, 1)
-    }
-    if constexpr (EPI == EPI_RESIDUAL) {
-      switch (plan.tile) {
-        DED_TILE(TILE_64x256, 1, 1, 4, 2)
-        DED_TILE(TILE_64x192, 1, 1, 3, 2)
-        DED_TILE(TILE_64x128, 1, 1, 2, 2)
-      }
+      DED_TILE(TILE_256x256, 2, 4)
+      DED_TILE(TILE_256x192, 2, 3)
+      DED_TILE(TILE_256x128, 2, 2)
+      DED_TILE(TILE_128x256, 1, 4)
+      DED_TILE(TILE_128x192, 1, 3)
+      DED_TILE(TILE_128x128, 1, 2)
     }
 #undef DED_TILE
     return false;
@@ -1397,12 +1390,11 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
 
 }  // namespace
 
-GemmPlan bf16_gemm_plan(int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems, bool narrow) {
+GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems) {
   static const Tune tune;
-  const int NG = (N + 16 * TN - 1) / (16 * TN), groups = K / (32 * PD), rg = rows_pad / 64;
-  const int64_t w_bytes = (int64_t)NG * 64 * K * 2, slice = (int64_t)rows_pad * N * 4;
-  // (up to 128 rows the skinny kernels are still the faster ones: 7B width, 97-row step 5.9 ms against 6.4 ms)
-  if (rows_pad > 128) return plan_tiles(rows_pad, N, K, planes, part_elems, narrow);
+  const int NG = (N + 16 * TN - 1) / (16 * TN), groups = K / (32 * PD), rg = sum_rows / 64;
+  const int64_t w_bytes = (int64_t)NG * 64 * K * 2, slice = (int64_t)sum_rows * N * 4;
+  if (sum_rows >= 256) return plan_tiles(sum_rows, rows_pad, N, K, planes, max_splits, part_elems);
   GemmPlan best{0, 1, 1};
   double best_cost = 1e300;
   for (int nwn = 0; nwn <= 4; ++nwn) {

@@ -130,7 +130,7 @@ def test_sampler_vocabularies(V):
 
 
 # (d, H, Hkv, F, V), prefix lengths, tree sizes: k ranges shorter than the ring and not a multiple of it (K = 128, 384, 640),
-# feature groups and rows that fill no whole tile (odd groups, 130 - 600 rows), tiles split over k 2 - 8 ways and whole,
+# feature groups and rows that fill no whole tile (odd groups, 130 - 600 rows), tiles split over k 2 - 4 ways and whole,
 # single-plane and two-plane LM heads (from 256 rows on)
 TILE_EDGES = [
     ((128, 1, 1, 128, 80), [3, 0], [70, 75]),
@@ -152,3 +152,4 @@ def test_projections_at_tile_edges(case):
     err = _step_error(cfg, w, prefix_len, nodes, seed=70 + case)
     print(f"max |logit error| {err:.2e}")
     assert err <= 2e-2
+
