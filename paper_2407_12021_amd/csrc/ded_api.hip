@@ -557,6 +557,17 @@ GemmPlan plan_gemm(const ded_ctx* c, int rows_pad, int N, int K, int planes) {
   if (!plan.tile && bf16_gemm_tiles(rows, N, plan) > kGemmCounters) plan.splits = 1;
   return plan;
 }
+// Steps of few rows run the slim projections, all or none of them: their sums of squares come per 4 features and lie in
+// the split-K buffer (at least 512 rows of d floats), which such a step has no other use for.
+bool slim_step(const ded_ctx* c) {
+  const ModelDims& md = c->md;
+  if (c->rows > BF16_SLIM_ROWS) return false;
+  const int qd = md.H * md.hd, qkv_n = qd + 2 * md.Hkv * md.hd;
+  auto fits = [&](int N, int K, int planes) { return bf16_gemm_slim_ok(plan_gemm(c, 64, N, K, planes), K, planes); };
+  return fits(md.V, md.d, 2) && (md.n_layers == 0 || (fits(qkv_n, md.d, 2) && fits(md.d, qd, 1) && fits(2 * md.F, md.d, 2) &&
+                                                      fits(md.d, md.F, 1)));
+}
+
 // LM head of the 16-bit path on the final residual stream (c->y_p / c->ssq as the last layer left them).  With
 // want_logits the fp32 logits are written to the workspace; without, only the per-group top-2 candidates that the
 // per-node argmax needs (the logits never reach memory).
@@ -567,8 +578,9 @@ bool lm_head_bf16(ded_ctx* c, bool want_logits) {
   e.rows = rows;
   e.rb_total = rows_pad / 16;
   e.eps = md.eps;
-  e.ssq_in = c->ssq;
-  e.ssq_groups = d / 64;
+  const bool slim = slim_step(c), fine = slim && md.n_layers > 0;  // without layers the embedding's sums are the last ones
+  e.ssq_in = fine ? c->part : c->ssq;
+  e.ssq_groups = fine ? d / 4 : d / 64;
   e.inv_k = 1.0f / (float)d;
   if (want_logits) {
     e.kind = EPI_LOGITS;
@@ -585,6 +597,7 @@ bool lm_head_bf16(ded_ctx* c, bool want_logits) {
   const int planes = sum_rows(c) >= 256 ? 1 : 2;
   const GemmPlan plan = plan_gemm(c, rows_pad, md.V, d, planes);
   ProfScope p(c, KC_GEMM_LM_HEAD);
+  if (slim) return bf16_gemm_slim(c->y_p, (const bf16_t*)c->lm_head, rows, rows_pad, md.V, d, planes, plan, e, c->stream);
   return bf16_gemm(c->part, (int64_t)rows_pad * round_up(md.V, 64), c->part_elems, c->y_p, (const bf16_t*)c->lm_head,
                    rows_pad, md.V, d, planes, plan, c->counters, e, c->stream);
 }
@@ -601,17 +614,22 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
   base.rb_total = rows_pad / 16;
   base.eps = md.eps;
   // planes: 2 = the input is consumed as hi + lo, 1 = hi only (enough for the O and down projections)
+  const bool slim = slim_step(c);
   auto gemm = [&](int cls, const bf16_t* xp, const void* w, int N, int K, int planes, const GemmEpilogue& epi) {
     const GemmPlan plan = plan_gemm(c, rows_pad, N, K, planes);
     ProfScope p(c, cls);
-    ok = bf16_gemm(c->part, (int64_t)rows_pad * round_up(N, 64), c->part_elems, xp, (const bf16_t*)w, rows_pad, N, K,
+    if (slim)
+      ok = bf16_gemm_slim(xp, (const bf16_t*)w, m.rows, rows_pad, N, K, planes, plan, epi, s) && ok;
+    else
+      ok = bf16_gemm(c->part, (int64_t)rows_pad * round_up(N, 64), c->part_elems, xp, (const bf16_t*)w, rows_pad, N, K,
                      planes, plan, c->counters, epi, s) && ok;
   };
   // RMSNorm is deferred: whoever produces the residual stream also writes x * gain(next norm) as the next
   // GEMM input and sum(x^2) per 64 features; the consuming GEMM multiplies its output rows by 1/rms.
-  auto normed_input = [&](GemmEpilogue& e) {
-    e.ssq_in = c->ssq;
-    e.ssq_groups = d / 64;
+  auto normed_input = [&](GemmEpilogue& e, bool embedded = false) {
+    const bool fine = slim && !embedded;
+    e.ssq_in = fine ? c->part : c->ssq;
+    e.ssq_groups = fine ? d / 4 : d / 64;
     e.inv_k = 1.0f / (float)d;
   };
   auto next_gain = [&](int l) { return l < L ? c->norm_attn[l] : c->final_norm; };
@@ -621,7 +639,7 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
     {
       GemmEpilogue e = base;
       e.kind = EPI_QKV;
-      normed_input(e);
+      normed_input(e, l == 0);
       e.q_packed = c->q_p;
       e.k_cache = (bf16_t*)c->kc[l];
       e.v_cache = (bf16_t*)c->vc[l];
@@ -646,7 +664,7 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
       e.x = c->x;
       e.gain = c->norm_ffn[l];
       e.y_packed = c->y_p;
-      e.ssq_out = c->ssq;
+      e.ssq_out = slim ? c->part : c->ssq;
       gemm(KC_GEMM_O, c->o_p, c->wo[l], d, qd, 1, e);
     }
     {
@@ -662,7 +680,7 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
       e.x = c->x;
       e.gain = next_gain(l + 1);
       e.y_packed = c->y_p;
-      e.ssq_out = c->ssq;
+      e.ssq_out = slim ? c->part : c->ssq;
       gemm(KC_GEMM_DOWN, c->h_p, c->wdown[l], d, F, 1, e);
     }
   }

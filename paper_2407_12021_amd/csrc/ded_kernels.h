@@ -161,6 +161,14 @@ int bf16_gemm_tiles(int rows_pad, int N, const GemmPlan& plan);
 bool bf16_gemm(float* part, int64_t part_stride, int64_t part_elems, const bf16_t* x_packed, const bf16_t* w_packed,
                int rows_pad, int N, int K, int planes, const GemmPlan& plan, int* counters, const GemmEpilogue& epi,
                hipStream_t s);
+// Few rows (rows <= BF16_SLIM_ROWS, a multiple of 16): a workgroup takes the whole k range of few features; its wavefronts
+// take the k ranges that `plan` (of 64 rows) gives the skinny kernels and their sums are added in the same order, so the
+// result has the same bits.  EPI_RESIDUAL writes its sums of squares per 4 features here (epi.ssq_out[row][N / 4]), and
+// epi.ssq_groups = d / 4 says that ssq_in holds those.  Returns false where the plan has more than 16 ranges.
+constexpr int BF16_SLIM_ROWS = 32;
+bool bf16_gemm_slim_ok(const GemmPlan& plan, int K, int planes);
+bool bf16_gemm_slim(const bf16_t* x_packed, const bf16_t* w_packed, int rows, int rows_pad, int N, int K, int planes,
+                    const GemmPlan& plan, const GemmEpilogue& epi, hipStream_t s);
 // Tree-masked attention: split-KV partials (running max, sum, unnormalised output per key range), then - when
 // there is more than one key range - the merge; the result is written as PackX(o), hi/lo, for the O projection.
 // n_splits from bf16_attn_pick_splits.  part_o: [B][H][n_splits][n_step][hd] fp32, part_ml: [B][H][n_splits][n_step]

@@ -283,10 +283,10 @@ __device__ inline float ssq_scale(const GemmEpilogue& e, int lane, int nwv, cons
 }
 
 // A wavefront may hold only T of the group's four feature tiles, from tile t0 on (paired epilogues: tiles t0 and t0 + 2).
-template <int EPI, int RBN, int T = TN, typename A>
+template <int EPI, int RBN, int T = TN, bool RAGGED = false, typename A>
 __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb0, int rbase, float row_scale, int lane,
                                     A& acc, int t0 = 0) {
-  // (row blocks from e.rb_total on are surplus ones of a ragged last row tile: nothing is written for them)
+  // (RAGGED: row blocks from e.rb_total on are surplus ones of a last row tile, nothing is written for them)
   const int row_in = lane & 15, quad = lane >> 4;
   float scale[RBN];
 #pragma unroll
@@ -299,7 +299,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
       if (n >= N) continue;
 #pragma unroll
       for (int rb = 0; rb < RBN; ++rb) {
-        if (rbase + rb >= e.rb_total) continue;
+        if (RAGGED && rbase + rb >= e.rb_total) continue;
         const int64_t r = (int64_t)(rbase + rb) * 16 + row_in;
         f32x4_t v = acc[t][rb] * scale[rb];
         *reinterpret_cast<float4*>(e.out + r * e.out_stride + n) = make_float4(v[0], v[1], v[2], v[3]);
@@ -311,7 +311,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     uint4* dst = reinterpret_cast<uint4*>(e.top2_part);
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (rbase + rb >= e.rb_total) continue;
+      if (RAGGED && rbase + rb >= e.rb_total) continue;
       const int64_t r = (int64_t)(rbase + rb) * 16 + row_in;
       float v1 = -INFINITY, v2 = -INFINITY;
       int i1 = 0x7fffffff, bad = 0;
@@ -353,7 +353,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     // x += Y;  next GEMM input = (x * gain) as hi/lo f16 (its 1/rms is applied by the consumer);  sum(x^2) per group
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (rbase + rb >= e.rb_total) continue;
+      if (RAGGED && rbase + rb >= e.rb_total) continue;
       const int r = (rbase + rb) * 16 + row_in;
       float ss = 0.f;
 #pragma unroll
@@ -381,7 +381,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     // group ng = gate features [32 ng, 32 ng + 32) in tiles 0, 1 and the matching up features in tiles 2, 3
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (rbase + rb >= e.rb_total) continue;
+      if (RAGGED && rbase + rb >= e.rb_total) continue;
       const int r = (rbase + rb) * 16 + row_in;
 #pragma unroll
       for (int t = 0; t < T / 2; ++t) {
@@ -402,7 +402,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     const int G = e.H / e.Hkv;
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (rbase + rb >= e.rb_total) continue;
+      if (RAGGED && rbase + rb >= e.rb_total) continue;
       const int r = (rbase + rb) * 16 + row_in;
       if (r >= e.rows) continue;
       const int b = e.blk_seq[r >> 4], node = r - e.row0[b];
@@ -869,6 +869,189 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
 }
 
 // ------------------------------------------------------------------------------------------
+// Slim kernel (one or two row blocks: plain decoding, small trees).  With 16 rows the activations of a projection are a
+// fraction of its weights, so nothing is gained by sharing them between wavefronts, and a workgroup can take few
+// features and the whole k range: one wavefront per k range, fragments straight into registers D steps ahead, no barrier
+// in the loop; the wavefronts' sums meet in LDS and one wavefront per row block runs the epilogue.  No slices, no
+// tickets.  The ranges are those of the skinny kernels' plan (`splits` slices of PER ranges each, SUB) and they are added
+// in the order of those kernels, so that a row's result has the same bits in a small tree as in a larger one.
+// T = 4: a whole 64-feature group; T = 2: tiles t0 and t0 + 2, the partners of the paired epilogues; T = 1: one tile, for
+// the narrow residual projections (N = d gives one workgroup per CU); their sums of squares are kept per 4 features.
+// Bound by the weight stream at 16 rows, by the activations out of the L2s (~13 TB/s) beyond.  7B widths, 16 rows, in a
+// step: QKV 24.8 us, O 8.8, gate/up 37.6, down 18.2, LM head 47.8; plain decoding step 4.13 -> 3.43 ms.  The loops alone
+// would allow 21.8 / 36 / 41 (QKV, gate/up, LM head): the rest is the rows' sums of squares, 64 KB per workgroup.
+// 32 rows: 104 us per layer against 120 with the kernels above, 48 rows 124.
+// ------------------------------------------------------------------------------------------
+struct SlimRanges {
+  int splits, per;  // slices, ranges per slice: 2 = halves of a wide kernel's slice, 4 / 1 = a stream kernel's wavefronts
+  int units;        // k range of slice s: [s * units / splits, (s + 1) * units / splits) groups (wide: then halved), or
+  int step;         // of range i: [i * units / (splits * per), ...) in units of `step` k steps (stream)
+  int wide;
+  int ssq_waves;    // wavefronts that share a row's sums of squares in the kernel of that plan
+};
+
+// ((v0 + v1) + v2) + v3 over the four lanes of a quad, in all of them
+__device__ __forceinline__ float quad_sum(float v) {
+  const int i = __float_as_int(v);
+  const float a = __int_as_float(__builtin_amdgcn_mov_dpp(i, 0x00, 0xf, 0xf, true));
+  const float b = __int_as_float(__builtin_amdgcn_mov_dpp(i, 0x55, 0xf, 0xf, true));
+  const float c = __int_as_float(__builtin_amdgcn_mov_dpp(i, 0xaa, 0xf, 0xf, true));
+  const float d = __int_as_float(__builtin_amdgcn_mov_dpp(i, 0xff, 0xf, 0xf, true));
+  return ((a + b) + c) + d;
+}
+
+template <int T, int RBN, int PLANES, int EPI, int NWMAX>
+__global__ __launch_bounds__(NWMAX * 64) void gemm_slim_kernel(const uint4* __restrict__ xp, const uint4* __restrict__ wp,
+                                                               int RB, int N, int KT, SlimRanges rg, GemmEpilogue epi) {
+  constexpr int STEP_REGS = (T + RBN * PLANES) * 4;
+  constexpr int BUDGET = NWMAX > 8 ? 64 : 100;
+  constexpr int D = STEP_REGS * 6 <= BUDGET ? 6 : STEP_REGS * 4 <= BUDGET ? 4 : STEP_REGS * 3 <= BUDGET ? 3 : 2;
+  extern __shared__ float4 slim_lds[];  // [ranges][RBN][T][64], then the row's sums of squares [16 * RBN][d / 64]
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ranges = blockDim.x >> 6;
+  const int ng = blockIdx.x / (TN / T), t0 = blockIdx.x % (TN / T);
+  int k0, k1;
+  if (rg.wide) {
+    const int sl = wave >> 1, b = sl * rg.units / rg.splits, e = (sl + 1) * rg.units / rg.splits, half = (e - b) * (PD / 2);
+    k0 = b * PD + (wave & 1) * half, k1 = k0 + half;
+  } else {
+    k0 = wave * rg.units / ranges * rg.step, k1 = (wave + 1) * rg.units / ranges * rg.step;
+  }
+  // whole turns of the ring, the first `skip` places of them empty
+  const int n = k1 - k0, turns = (n + D - 1) / D, skip = turns * D - n;
+  const uint4* wsrc = wp + ((((int64_t)ng * KT + k0) * TN + t0) << 6) + lane;
+  const uint4* xsrc = xp + (int64_t)k0 * ((int64_t)RB << 7) + lane;
+  const int64_t xstep = (int64_t)RB << 7;
+
+  uint4 wr[D][T], xr[D][RBN * PLANES];
+  auto issue = [&](int j) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) wr[j][t] = load_weights<true>(wsrc + ((T == 2 ? 2 * t : t) << 6));
+#pragma unroll
+    for (int rb = 0; rb < RBN; ++rb)
+#pragma unroll
+      for (int p = 0; p < PLANES; ++p) xr[j][rb * PLANES + p] = xsrc[(rb * 2 + p) << 6];
+    wsrc += TN * 64;
+    xsrc += xstep;
+  };
+  f32x4_t acc[T][RBN];
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int rb = 0; rb < RBN; ++rb) acc[t][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int j) {
+#pragma unroll
+    for (int p = 0; p < PLANES; ++p)
+#pragma unroll
+      for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int rb = 0; rb < RBN; ++rb)
+          acc[t][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, wr[j][t]),
+                                                              __builtin_bit_cast(f16x8_t, xr[j][rb * PLANES + p]),
+                                                              acc[t][rb], 0, 0, 0);
+  };
+
+#pragma unroll
+  for (int j = 0; j < D; ++j)
+    if (j >= skip && turns > 0) issue(j);
+  // the rows' sums of squares per 64 features, behind the first weights on their way; four features each or summed already
+  float* s_ssq = reinterpret_cast<float*>(slim_lds + ranges * RBN * T * 64);
+  const int d64 = KT / 2, row_len = d64 + 1;  // (odd: the rows start in different banks)
+  float* s_part = s_ssq + 16 * RBN * row_len;  // [row][ssq_waves]
+  if (epi.ssq_in) {
+    const int total = 16 * RBN * d64;
+    if (epi.ssq_groups == d64) {
+      for (int i = threadIdx.x; i < total; i += blockDim.x) s_ssq[i + i / d64] = epi.ssq_in[i];
+    } else {
+      // in the order of the residual epilogue: tiles one after the other, then the four lanes of a row.  Coalesced: four
+      // neighbouring lanes hold the four tiles of a group (a lane that reads all four touches four times the lines: gate/up
+      // 42.9 us)
+      const float4* src = reinterpret_cast<const float4*>(epi.ssq_in);
+      const int total4 = total * 4, stride = blockDim.x;
+      for (int i0 = threadIdx.x; i0 < total4; i0 += 8 * stride) {
+        float4 v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = src[min(i0 + q * stride, total4 - 4 + (lane & 3))];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const float x = quad_sum(v[q].x), y = quad_sum(v[q].y), z = quad_sum(v[q].z), w = quad_sum(v[q].w);
+          const int i = i0 + q * stride;
+          if ((lane & 3) == 0 && i < total4) s_ssq[(i >> 2) + (i >> 2) / d64] = (x + y) + (z + w);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (turns > 1) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      if (j >= skip) compute(j);
+      issue(j);
+    }
+    for (int c = 2; c < turns; ++c) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        compute(j);
+        issue(j);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < D; ++j) compute(j);
+  } else if (turns == 1) {
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+      if (j >= skip) compute(j);
+  }
+
+  if (epi.ssq_in) {  // pairs of groups in the shares that the plan's kernel gives its wavefronts
+    const int n2 = d64 >> 1, per = (n2 + rg.ssq_waves - 1) / rg.ssq_waves;
+    for (int i = threadIdx.x; i < 16 * RBN * rg.ssq_waves; i += blockDim.x) {
+      const int r = i / rg.ssq_waves, w = i - r * rg.ssq_waves;
+      const float* row = s_ssq + r * row_len;
+      float p = 0.f;
+#pragma unroll 4
+      for (int g = w * per; g < min(n2, (w + 1) * per); ++g) p += row[2 * g] + row[2 * g + 1];
+      s_part[i] = p;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < T; ++t)
+#pragma unroll
+    for (int rb = 0; rb < RBN; ++rb) {
+      const f32x4_t v = acc[t][rb];
+      slim_lds[((wave * RBN + rb) * T + t) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+    }
+  __syncthreads();
+  // one wavefront per row block; with fewer ranges than row blocks the first takes the rest too
+  for (int rb = wave; rb < RBN; rb += ranges) {
+    auto at = [&](int w, int t) {
+      const float4 v = slim_lds[((w * RBN + rb) * T + t) * 64 + lane];
+      return f32x4_t{v.x, v.y, v.z, v.w};
+    };
+    f32x4_t sum[T][1];
+#pragma unroll
+    for (int t = 0; t < T; ++t) sum[t][0] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int sl = 0; sl < rg.splits; ++sl) {
+#pragma unroll
+      for (int t = 0; t < T; ++t) {
+        const int w = sl * rg.per;
+        f32x4_t v = at(w, t);
+        if (rg.per == 2) v += at(w + 1, t);
+        if (rg.per == 4) v = (v + at(w + 2, t)) + (at(w + 1, t) + at(w + 3, t));
+        sum[t][0] = sl == 0 ? v : sum[t][0] + v;
+      }
+    }
+    float row_scale = 1.f;
+    if (epi.ssq_in) {
+      float s = 0.f;
+      for (int w = 0; w < rg.ssq_waves; ++w) s += s_part[(rb * 16 + (lane & 15)) * rg.ssq_waves + w];
+      row_scale = 1.0f / sqrtf(s * epi.inv_k + epi.eps);
+    }
+    run_epilogue<EPI, 1, T>(epi, ng, N, rb, rb, row_scale, lane, sum, t0);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
 // Tile kernel (more than 128 rows: wide trees, prompt chunks, batches).  With some hundred rows per weight a projection
 // needs the matrix cores and the operand stream at the same time, so operands have to be far ahead of the products
 // without holding registers: every operand lies in memory as whole fragments, and the fragments go from memory straight
@@ -1207,7 +1390,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
 #pragma unroll
       for (int gw = 0; gw < GPW; ++gw) {
         const int ng = (tf * FGS + fg) * GPW + gw;
-        if (ng < NG) run_epilogue<EPI, RBW>(epi, ng, N, rbw, rbw, row_scale, llane, acc[gw]);
+        if (ng < NG) run_epilogue<EPI, RBW, TN, true>(epi, ng, N, rbw, rbw, row_scale, llane, acc[gw]);
       }
     }
     if (!more) break;
@@ -1474,6 +1657,68 @@ bool bf16_gemm(float* part, int64_t part_stride, int64_t part_elems, const bf16_
       return false;
   }
 #undef DED_GO
+  return false;
+}
+
+static SlimRanges slim_ranges(const GemmPlan& p, int K) {
+  const int groups = K / (32 * PD);
+  if (p.nwn) return SlimRanges{p.splits, 2, groups, 0, 1, 2 * p.nwn};
+  int nw = p.nw >= 4 ? 4 : p.nw >= 2 ? 2 : 1;
+  while (nw > 1 && p.splits * nw > groups) nw /= 2;
+  return SlimRanges{p.splits, nw, K / 32 / RING, RING, 0, nw};
+}
+bool bf16_gemm_slim_ok(const GemmPlan& plan, int K, int planes) {
+  const SlimRanges r = slim_ranges(plan, K);
+  // (two planes: up to 16 ranges x 8 KiB and the sums of squares of 32 rows x K / 64 groups in the CU's LDS)
+  return !plan.tile && r.splits * r.per <= 16 && K % (32 * PD) == 0 && (planes == 1 || K <= 12288);
+}
+
+bool bf16_gemm_slim(const bf16_t* x_packed, const bf16_t* w_packed, int rows, int rows_pad, int N, int K, int planes,
+                    const GemmPlan& plan, const GemmEpilogue& epi, hipStream_t s) {
+  if (rows < 16 || rows > BF16_SLIM_ROWS || rows % 16 || rows_pad != 64 || N % 16 || !bf16_gemm_slim_ok(plan, K, planes)) return false;
+  if (epi.ssq_in && epi.ssq_groups != K / 64 && epi.ssq_groups != K / 4) return false;
+  if ((epi.kind == EPI_RESIDUAL || epi.kind == EPI_QKV || epi.kind == EPI_SILU) && N % 64) return false;
+  const uint4* xp = reinterpret_cast<const uint4*>(x_packed);
+  const uint4* wp = reinterpret_cast<const uint4*>(w_packed);
+  const int RB = rows_pad / 16, NG = (N + 16 * TN - 1) / (16 * TN), rbn = rows / 16;
+  const SlimRanges rg = slim_ranges(plan, K);
+  const int ranges = rg.splits * rg.per;
+  const size_t ssq_bytes = epi.ssq_in ? (size_t)rows * (K / 64 + 1 + rg.ssq_waves) * 4 : 0;
+#define DED_SLIM(R, T, P, E, NW)                                                                                       \
+  {                                                                                                                    \
+    hipLaunchKernelGGL((gemm_slim_kernel<T, R, P, E, NW>), dim3(NG * (TN / T)), dim3(ranges * 64),                       \
+                       (size_t)ranges * R * T * 1024 + ssq_bytes, s, xp, wp, RB, N, K / 32, rg, epi);                  \
+    return true;                                                                                                       \
+  }
+#define DED_SLIM_ROWS(T, P, E, NW) { if (rbn == 1) DED_SLIM(1, T, P, E, NW) else DED_SLIM(2, T, P, E, NW) }
+  // Paired epilogues: whole groups halve the activations fetched per weight, half groups make twice the workgroups.
+  // 7B widths, 16 / 32 rows: QKV (192 groups) 21.8 / 27.6 us with whole groups, 25.1 / 32.0 with halves; gate/up (344
+  // groups, more than one workgroup per CU) 37.8 / 45.6 and 35.9 / 49.2.
+  const bool whole = NG >= 160 && (rows > 16 || NG <= kCUs) && ranges <= 8;
+  if (planes == 2 && epi.kind == EPI_QKV) {
+    if (whole) DED_SLIM_ROWS(4, 2, EPI_QKV, 8)
+    if (ranges <= 8) DED_SLIM_ROWS(2, 2, EPI_QKV, 8)
+    DED_SLIM_ROWS(2, 2, EPI_QKV, 16)
+  }
+  if (planes == 2 && epi.kind == EPI_SILU) {
+    if (whole) DED_SLIM_ROWS(4, 2, EPI_SILU, 8)
+    if (ranges <= 8) DED_SLIM_ROWS(2, 2, EPI_SILU, 8)
+    DED_SLIM_ROWS(2, 2, EPI_SILU, 16)
+  }
+  if (planes == 2 && epi.kind == EPI_LOGITS) {
+    if (ranges <= 8) DED_SLIM_ROWS(4, 2, EPI_LOGITS, 8)
+    DED_SLIM_ROWS(4, 2, EPI_LOGITS, 16)
+  }
+  if (planes == 2 && epi.kind == EPI_TOP2) {
+    if (ranges <= 8) DED_SLIM_ROWS(4, 2, EPI_TOP2, 8)
+    DED_SLIM_ROWS(4, 2, EPI_TOP2, 16)
+  }
+  if (planes == 1 && epi.kind == EPI_RESIDUAL) {
+    if (ranges <= 8) DED_SLIM_ROWS(1, 1, EPI_RESIDUAL, 8)
+    DED_SLIM_ROWS(1, 1, EPI_RESIDUAL, 16)
+  }
+#undef DED_SLIM_ROWS
+#undef DED_SLIM
   return false;
 }
 

@@ -153,3 +153,43 @@ def test_projections_at_tile_edges(case):
     print(f"max |logit error| {err:.2e}")
     assert err <= 2e-2
 
+
+# (layers, d, H, Hkv, F, V), prefix lengths, tree sizes: steps of 16 and 32 padded rows; k ranges of one step of 128, ranges that
+# are no multiple of the ring, half groups and whole groups (160 feature groups and more), 2 to 16 ranges per workgroup, a
+# vocabulary that ends inside a group
+SLIM_EDGES = [
+    ((2, 128, 1, 1, 128, 80), [5], [1]),
+    ((2, 384, 3, 1, 640, 208), [0, 33], [16, 9]),
+    ((2, 640, 5, 5, 896, 1040), [70], [32]),
+    ((1, 4096, 32, 32, 11008, 32048), [19], [1]),
+    ((1, 4096, 32, 8, 14336, 32048), [40], [17]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(SLIM_EDGES)))
+def test_projections_of_few_rows(case):
+    """Bound: the 16-bit path's 2e-2 logit tolerance, as above."""
+    (L, d, H, Hkv, F, V), prefix_len, nodes = SLIM_EDGES[case]
+    cfg = di.ModelConfig(f"slim-edge{case}", L, d, H, Hkv, 128, F, V, dtype="bf16")
+    w = di.make_weights(cfg, seed=80 + case, gain_jitter=0.1, threads=16)
+    err = _step_error(cfg, w, prefix_len, nodes, seed=90 + case)
+    print(f"max |logit error| {err:.2e}")
+    assert err <= 2e-2
+
+
+def test_a_row_has_the_same_bits_in_a_small_tree_and_a_larger_one():
+    """The projections of one and two row blocks add the k ranges of the larger steps in their order: the root's logits of a
+    chain of 1, 17 and 40 nodes are equal bit for bit (one key tile each, so attention sums the same keys too)."""
+    import torch
+    cfg = di.ModelConfig("slim-bits", 2, 4096, 32, 32, 128, 11008, 32000, dtype="bf16")
+    w = di.make_weights(cfg, seed=5, gain_jitter=0.1, threads=16)
+    ver = _verifier(cfg, w, max_batch=1, kv_capacity=128, max_nodes=40)
+    tokens = di.zipf_tokens(cfg.vocab, 60, seed=6)
+    ver.verify_step([0], [di.chain_tree(20)], [tokens[:20]])
+    ver.accept(mode=1)
+    rows = []
+    for n in (40, 17, 1):
+        rows.append(ver.verify_step([20], [di.chain_tree(n)], [tokens[20:20 + n]], want_logits=True)[0, 0].clone())
+    ver.close()
+    assert torch.isfinite(rows[0]).all() and rows[0].abs().max() > 0
+    assert torch.equal(rows[0], rows[1]) and torch.equal(rows[0], rows[2])
