@@ -154,6 +154,7 @@ struct GemmPlan {
   int splits;    // split-K slices
   int tile = 0;  // != 0: the tile kernel, with this workgroup tile
   int whole = 0; // tile kernel: that many tiles whole, the others with k split `splits` ways
+  int ssq_waves = 1;  // tile kernel: shares in which a row's sums of squares are added
 };
 // sum_rows (a multiple of 64, >= rows_pad) decides into which k ranges the sums are split, rows_pad how they are run.
 GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems);

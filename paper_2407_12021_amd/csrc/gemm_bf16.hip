@@ -1052,7 +1052,7 @@ __global__ __launch_bounds__(NWMAX * 64) void gemm_slim_kernel(const uint4* __re
 }
 
 // ------------------------------------------------------------------------------------------
-// Tile kernel (more than 128 rows: wide trees, prompt chunks, batches).  With some hundred rows per weight a projection
+// Tile kernel (a few hundred rows and more: wide trees, prompt chunks, batches).  With that many rows per weight a projection
 // needs the matrix cores and the operand stream at the same time, so operands have to be far ahead of the products
 // without holding registers: every operand lies in memory as whole fragments, and the fragments go from memory straight
 // into LDS (16 bytes per lane, 1 KiB per instruction): a ring of ST slots of one k step each, 96 - 144 KB, all but one or
@@ -1067,7 +1067,7 @@ __global__ __launch_bounds__(NWMAX * 64) void gemm_slim_kernel(const uint4* __re
 // the next item are requested before a tile's epilogue runs.
 // What bounds it: at 512 rows and more the matrix cores at the chip's power limit (LM head of a 7B shape, 512 rows:
 // 225 us = 1.19 PFLOP/s executed, and no more than 1.26 with operands that never leave the caches); at 256 rows the
-// operand stream, ~55 GB/s into each CU (gate/up of a 7B shape 119 -> 101 us, QKV 73 -> 61, O 48 -> 23, down 78 -> 44).
+// operand stream, ~55 GB/s into each CU (gate/up of a 7B shape 119 -> 101 us, QKV 73 -> 61, O 48 -> 27, down 78 -> 44).
 // ------------------------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void glb_void_t;
@@ -1122,7 +1122,7 @@ struct TileShape {
 template <int PLANES, int EPI, int GPW, int RBW>
 __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ part, const uint4* __restrict__ xp,
                                                            const uint4* __restrict__ wp, int RB, int N, int KT, int tiles,
-                                                           int row_tiles, int n_whole, int parts,
+                                                           int row_tiles, int n_whole, int parts, int ssq_waves,
                                                            int* __restrict__ counters, GemmEpilogue epi) {
   using S = TileShape<PLANES, GPW, RBW>;
   constexpr int FGS = S::FGS, FG = S::FG, RBT = S::RBT, WF = S::WF, XF = S::XF, ST = S::ST;
@@ -1260,8 +1260,13 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
       const int r = min(rb_tile * 16 + ltid, RB * 16 - 1);
       const float2* src = reinterpret_cast<const float2*>(epi.ssq_in + (int64_t)r * epi.ssq_groups);
       float s = 0.f;
+      const int n2 = epi.ssq_groups >> 1, per = (n2 + ssq_waves - 1) / ssq_waves;
+      for (int w = 0; w < ssq_waves; ++w) {
+        float p = 0.f;
 #pragma unroll 16
-      for (int g = 0; g < (epi.ssq_groups >> 1); ++g) s += src[g].x + src[g].y;
+        for (int g = w * per; g < min(n2, (w + 1) * per); ++g) p += src[g].x + src[g].y;
+        s += p;
+      }
       s_scale[par][ltid] = 1.0f / sqrtf(s * epi.inv_k + epi.eps);
     }
 #pragma unroll
@@ -1486,13 +1491,12 @@ KRanges k_ranges(int rows, int N, int K, int planes, int max_splits) {
   return best;
 }
 
-// Tile of a launch of 256 and more rows.  Every tile shape is weighed with the time of one ring slot on a full chip
+// Tile of a launch whose sums have k ranges `r`.  Every tile shape is weighed with the time of one ring slot on a full chip
 // (measured, in us: 7B- and 8B-width projections, 128 - 2048 rows, random operands); with fewer workgroups a slot is
 // faster, because it is the chip's power and memory that bound it more than the CU.  A hand-over costs about 3 us and
 // 1.5 us per 64 KB slice beyond the first.
-GemmPlan plan_tiles(int sum_rows, int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems) {
+GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, int64_t part_elems) {
   constexpr double slot_us[2][6] = {{0.97, 0.74, 0.52, 0.50, 0.40, 0.31}, {1.80, 1.25, 0.86, 0.94, 0.70, 0.51}};
-  const KRanges r = k_ranges(sum_rows, N, K, planes, max_splits);
   const int parts = r.main > 1 ? r.main : r.rem;
   GemmPlan best{0, 1, 1, 0, 0};
   double best_cost = 1e300;
@@ -1517,7 +1521,7 @@ GemmPlan plan_tiles(int sum_rows, int rows_pad, int N, int K, int planes, int ma
       best = p;
     }
   }
-  return best.tile || max_splits <= 1 ? best : plan_tiles(sum_rows, rows_pad, N, K, planes, 1, part_elems);  // no room for slices
+  return best;
 }
 
 template <int PLANES, int EPI>
@@ -1534,7 +1538,7 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
 #define DED_TILE(ID, GPW, RBW)                                                                                       \
   case ID:                                                                                                           \
     hipLaunchKernelGGL((gemm_tile_kernel<PLANES, EPI, GPW, RBW>), dim3(std::min(kCUs, items)), dim3(512), 0, s, part, xp, \
-                       wp, RB, N, KT, tiles, row_tiles, plan.whole, splits, counters, epi);                          \
+                       wp, RB, N, KT, tiles, row_tiles, plan.whole, splits, plan.ssq_waves, counters, epi);                          \
     return true;
     switch (plan.tile) {
       DED_TILE(TILE_256x256, 2, 4)
@@ -1577,7 +1581,10 @@ GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, in
   static const Tune tune;
   const int NG = (N + 16 * TN - 1) / (16 * TN), groups = K / (32 * PD), rg = sum_rows / 64;
   const int64_t w_bytes = (int64_t)NG * 64 * K * 2, slice = (int64_t)sum_rows * N * 4;
-  if (sum_rows >= 256) return plan_tiles(sum_rows, rows_pad, N, K, planes, max_splits, part_elems);
+  if (sum_rows >= 256) {
+    const GemmPlan p = plan_tiles(k_ranges(sum_rows, N, K, planes, max_splits), rows_pad, N, K, planes, part_elems);
+    return p.tile ? p : plan_tiles(k_ranges(sum_rows, N, K, planes, 1), rows_pad, N, K, planes, part_elems);  // no room for slices
+  }
   GemmPlan best{0, 1, 1};
   double best_cost = 1e300;
   for (int nwn = 0; nwn <= 4; ++nwn) {
@@ -1604,6 +1611,14 @@ GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, in
         best = p;
       }
     }
+  }
+  // 65 - 255 rows, an unsplit wide kernel: the halves of its k range as the two ranges of the tile kernel, added in the same
+  // order.  Three trees of 144 rows on the 8B shape 10.4 -> 9.36 ms; the 97-row step of the 7B shape (gate/up, LM head)
+  // unchanged.
+  if (rows_pad > 64 && best.nwn && best.splits == 1 && groups % 2 == 0) {
+    GemmPlan p = plan_tiles(KRanges{0, 2, 1}, rows_pad, N, K, planes, part_elems);
+    p.ssq_waves = 2 * best.nwn;
+    if (p.tile) return p;
   }
   return best;
 }
