@@ -444,7 +444,6 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
     const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0, const int32_t* __restrict__ blk_seq, int H,
     int Hkv, int cap) {
   constexpr int NW = HD == 256 ? 4 : 8, DT = HD / 16;
-  constexpr float NEG_BIG = -1.0e30f;
   __shared__ float4 s_o[NW][DT][64];
   __shared__ float2 s_ml[NW][16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m16 = lane & 15, quad = lane >> 4;
@@ -459,7 +458,13 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
   const uint64_t* mrow = mask + (int64_t)r * 4;
   const uint64_t w0 = mrow[0], w1 = mrow[1], w2 = mrow[2], w3 = mrow[3];
   const float scale = 1.0f / sqrtf((float)HD);
-  float m_run = NEG_BIG, l_run = 0.f;  // l_run: this lane's keys only
+  // Whether a key counts is decided by the mask alone, never by its score's value: every finite score takes part, and a
+  // NaN one has to reach the output (the maximum passes over it, its exponential does not).
+  float m_run = -INFINITY, l_run = 0.f;  // l_run: this lane's keys only
+  auto exponent_from = [](float v, float m) {
+#pragma clang fp contract(off)  // (a product fused into the difference would leave the maximum's own rounding error there)
+    return v - (m == -INFINITY ? 0.f : m);
+  };
   v4f acc[DT];
 #pragma unroll
   for (int c = 0; c < DT; ++c) acc[c] = v4f{0.f, 0.f, 0.f, 0.f};
@@ -483,23 +488,24 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
         sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j], qf[c][j], sa, 0, 0, 0);
         sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j + 1], qf[c][j + 1], sb, 0, 0, 0);
       }
-    float p[4], mx = NEG_BIG;
+    float p[4], mx = -INFINITY;
+    bool vis[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int key = k0 + quad * 4 + i, t = key - P;
       const uint64_t word = t < 64 ? w0 : t < 128 ? w1 : t < 192 ? w2 : w3;
-      const bool vis = key < P || (key < T && ((word >> (t & 63)) & 1ull));
-      p[i] = vis ? (sa[i] + sb[i]) * scale : NEG_BIG;
-      mx = fmaxf(mx, p[i]);
+      vis[i] = key < P || (key < T && ((word >> (t & 63)) & 1ull));
+      p[i] = (sa[i] + sb[i]) * scale;
+      mx = vis[i] ? fmaxf(mx, p[i]) : mx;
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float m_new = fmaxf(m_run, mx), alpha = expf(m_run - m_new);
+    const float m_new = fmaxf(m_run, mx), alpha = expf(exponent_from(m_run, m_new));
     m_run = m_new;
     float sum = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      p[i] = p[i] > 0.5f * NEG_BIG ? expf(p[i] - m_new) : 0.f;
+      p[i] = vis[i] ? expf(exponent_from(p[i], m_new)) : 0.f;
       sum += p[i];
     }
     l_run = l_run * alpha + sum;
@@ -516,13 +522,13 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
 #pragma unroll
   for (int c = 0; c < DT; ++c) s_o[wave][c][lane] = make_float4(acc[c][0], acc[c][1], acc[c][2], acc[c][3]);
   __syncthreads();
-  float M = NEG_BIG, L = 0.f, f[NW];
+  float M = -INFINITY, L = 0.f, f[NW];
 #pragma unroll
   for (int w = 0; w < NW; ++w) M = fmaxf(M, s_ml[w][m16].x);
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
     const float2 ml = s_ml[w][m16];
-    f[w] = expf(ml.x - M);
+    f[w] = expf(exponent_from(ml.x, M));
     L += ml.y * f[w];
   }
   const float inv = 1.0f / L;

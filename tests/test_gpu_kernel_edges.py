@@ -193,3 +193,76 @@ def test_a_row_has_the_same_bits_in_a_small_tree_and_a_larger_one():
     ver.close()
     assert torch.isfinite(rows[0]).all() and rows[0].abs().max() > 0
     assert torch.equal(rows[0], rows[1]) and torch.equal(rows[0], rows[2])
+
+
+@pytest.mark.parametrize("hd", [8, 16, 64, 128, 256])
+def test_fp32_attention_weighs_every_visible_key(hd):
+    """A key counts by the mask, not by its score's value: a NaN key of the prefix or of an ancestor reaches the output of
+    every row that sees it and of no other, scores of -1e32 are weighed like any others, a score of -infinity weighs nothing.
+    Bound for the finite rows: fp32 sums of at most 41 values of O(1), 1e-5."""
+    import torch
+    P, n, cap = 37, 4, 64
+    cfg = di.ModelConfig(f"f32-attn{hd}", 1, 64, 2, 1, hd, 64, 64, dtype="fp32")
+    ver = _verifier(cfg, di.make_weights(cfg, seed=3), max_batch=1, kv_capacity=cap, max_nodes=n)
+    g = torch.Generator(device="cuda").manual_seed(hd)
+    rand = lambda *shape: torch.randn(*shape, device="cuda", generator=g)
+    k, v = rand(1, P, hd), rand(1, P, hd)
+    q, kt, vt = rand(1, n, 2, hd), rand(1, 1, n, hd), rand(1, 1, n, hd)
+    parent = [-1, 0, 0, 1]
+    sees = np.array([[1, 0, 0, 0], [1, 1, 0, 0], [1, 0, 1, 0], [1, 1, 0, 1]], bool)
+
+    def run(k, q, kt):
+        ver.kv_store(0, 0, 0, k, v)
+        return ver.tree_attention(0, [P], [parent], q, kt, vt)[0].cpu().numpy().astype(np.float64)
+
+    def ref(k, q, kt):
+        K, V = (torch.cat([a[0], b[0, 0]]).double().cpu().numpy() for a, b in ((k, kt), (v, vt)))
+        out = np.zeros((n, 2, hd))
+        for i in range(n):
+            see = np.concatenate([np.ones(P, bool), sees[i]])
+            for h in range(2):
+                s = K[see] @ q[0, i, h].double().cpu().numpy() / np.sqrt(hd)
+                w = np.exp(s - s.max())
+                out[i, h] = w @ V[see] / w.sum()
+        return out
+
+    assert np.abs(run(k, q, kt) - ref(k, q, kt)).max() <= 1e-5
+    for at in (0, 15, 36):
+        bad = k.clone()
+        bad[0, at, hd // 2] = float("nan")
+        assert np.isnan(run(bad, q, kt)).all(), at
+    bad = kt.clone()
+    bad[0, 0, 1, 3] = float("nan")
+    out = run(k, q, bad)
+    assert np.isnan(out[[1, 3]]).all() and np.abs(out[[0, 2]] - ref(k, q, kt)[[0, 2]]).max() <= 1e-5
+    # every visible score below -1e32, two keys tied at the top
+    ones, far = torch.ones_like(q), torch.full_like(k, -4e32 / hd ** 0.5)
+    far[0, [2, 30]] /= 2
+    far_t = torch.full_like(kt, -4e32 / hd ** 0.5)
+    assert np.abs(run(far, ones, far_t) - ref(far, ones, far_t)).max() <= 1e-5
+    gone = k.clone()
+    gone[0, :33, 0] = float("-inf")
+    assert np.abs(run(gone, ones, kt) - ref(gone, ones, kt)).max() <= 1e-5
+    ver.close()
+
+
+def test_fp32_step_reports_a_nan_key_of_the_prefix():
+    """A restored prefix with one bad key and finite values: no tokens, an error."""
+    from paper_2407_12021_amd.binding import DED_ENONFINITE, DedError
+    cfg = di.ModelConfig("f32-nan-key", 2, 64, 2, 1, 32, 64, 96, dtype="fp32")
+    ver = _verifier(cfg, di.make_weights(cfg, seed=3), max_batch=1, kv_capacity=64, max_nodes=16)
+    r = np.random.default_rng(2)
+    k, v = (r.standard_normal((1, 20, 32)).astype(np.float32) for _ in range(2))
+    for bad in (False, True):
+        k[0, 7, 5] = np.nan if bad else 0.5
+        for layer in range(2):
+            ver.kv_store(layer, 0, 0, k, v)
+        ver.verify_step([20], [di.random_tree(9, None, seed=1)], [di.zipf_tokens(96, 9, seed=1)])
+        if not bad:
+            ver.accept(mode=0)
+            continue
+        for call in (ver.get_argmax, ver.accept):
+            with pytest.raises(DedError) as e:
+                call()
+            assert e.value.code == DED_ENONFINITE
+    ver.close()
