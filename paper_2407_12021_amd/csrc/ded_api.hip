@@ -548,7 +548,8 @@ int clear_step_slots(ded_ctx* c) {
 }
 
 // Rows that decide into which k ranges a step's projections are summed: those of its trees padded to the largest, so that
-// the sums of a tree do not depend on how much its neighbours in the batch fall short of it.
+// the sums of a tree do not depend on how much its neighbours in the batch fall short of it.  (They do depend on the room
+// that the context, sized by its max_batch and max_nodes, has for split sums.)
 int sum_rows(const ded_ctx* c) { return round_up(c->batch * c->n_step, 64); }
 GemmPlan plan_gemm(const ded_ctx* c, int rows_pad, int N, int K, int planes) {
   const int rows = sum_rows(c);

@@ -1455,8 +1455,8 @@ bool tile_plan_ok(const GemmPlan& p, int rows_pad, int N, int K, int64_t part_el
 }
 
 // Into how many k ranges a product of 256 and more rows is summed: the first x_main groups of 256 features in `main`, the
-// others in `rem`.  The shape alone decides it, not the workgroup tile, so that a result has the same bits whichever tile
-// runs.  The ranges are counted so that 256 x 128 (from 512 rows on also 256 x 256) tiles fill the chip's last round of
+// others in `rem`.  The shape (and what the context has room for) decides it, not the workgroup tile, so that a result has
+// the same bits whichever tile runs.  The ranges are counted so that 256 x 128 (from 512 rows on also 256 x 256) tiles fill the chip's last round of
 // one workgroup per CU: as few as it takes, or whole rounds unsplit and only a mostly empty last one split.
 struct KRanges {
   int x_main, main, rem;
@@ -1582,8 +1582,11 @@ GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, in
   const int NG = (N + 16 * TN - 1) / (16 * TN), groups = K / (32 * PD), rg = sum_rows / 64;
   const int64_t w_bytes = (int64_t)NG * 64 * K * 2, slice = (int64_t)sum_rows * N * 4;
   if (sum_rows >= 256) {
-    const GemmPlan p = plan_tiles(k_ranges(sum_rows, N, K, planes, max_splits), rows_pad, N, K, planes, part_elems);
-    return p.tile ? p : plan_tiles(k_ranges(sum_rows, N, K, planes, 1), rows_pad, N, K, planes, part_elems);  // no room for slices
+    // No room for the slices: unsplit.  Asked for sum_rows, so that a ragged batch is summed like a full one: a tile whose
+    // slices fit sum_rows fits fewer rows as well.
+    KRanges r = k_ranges(sum_rows, N, K, planes, max_splits);
+    if (!plan_tiles(r, sum_rows, N, K, planes, part_elems).tile) r = k_ranges(sum_rows, N, K, planes, 1);
+    return plan_tiles(r, rows_pad, N, K, planes, part_elems);
   }
   GemmPlan best{0, 1, 1};
   double best_cost = 1e300;

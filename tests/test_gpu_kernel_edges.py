@@ -266,3 +266,33 @@ def test_fp32_step_reports_a_nan_key_of_the_prefix():
                 call()
             assert e.value.code == DED_ENONFINITE
     ver.close()
+
+
+# (d, H, Hkv, F, V) of one layer; a batch of full trees and a ragged one that share the first tree.  320 padded rows whose
+# gate / up slices have no room in the context where those of the 208 packed rows would
+RAGGED = [
+    ((4096, 32, 32, 11008, 32000), [64] * 5, [64, 33, 16, 20, 40]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(RAGGED)))
+def test_a_tree_has_the_same_bits_beside_full_trees_and_beside_small_ones(case):
+    """The k ranges of a product come from the trees padded to the largest, whatever runs: the logits of the first tree do
+    not depend on how far its neighbours fall short of it."""
+    import torch
+    (d, H, Hkv, F, V), full, ragged = RAGGED[case]
+    cfg = di.ModelConfig(f"ragged-bits{case}", 1, d, H, Hkv, 128, F, V, dtype="bf16")
+    w = di.make_weights(cfg, seed=5, gain_jitter=0.1, threads=16)
+    ver = _verifier(cfg, w, max_batch=len(full), kv_capacity=128, max_nodes=max(full))
+    r = np.random.default_rng(7)
+    k, v = (torch.from_numpy(r.standard_normal((Hkv, 20, 128)).astype(np.float32)).bfloat16() for _ in range(2))
+    rows = []
+    for nodes in (full, ragged):
+        for b in range(len(nodes)):
+            ver.kv_store(0, b, 0, k, v)
+        parents = [di.random_tree(n, None, seed=b) for b, n in enumerate(nodes)]
+        tokens = [di.zipf_tokens(V, n, seed=6, stream=b) for b, n in enumerate(nodes)]
+        rows.append(ver.verify_step([20] * len(nodes), parents, tokens, want_logits=True)[0].clone())
+    ver.close()
+    assert torch.isfinite(rows[0]).all() and rows[0].abs().max() > 0
+    assert torch.equal(rows[0], rows[1])
