@@ -182,3 +182,23 @@ def test_host_api_from_plain_c(b, tmp_path):
     assert r.returncode == 0, r.stderr[-3000:]
     r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), (r.stdout[-2000:], r.stderr[-2000:])
+
+
+def test_cache_copies_are_done_when_the_call_returns(b, monkeypatch):
+    """kv_store / kv_load enqueue an asynchronous copy; the caller may use the tensors on any stream afterwards, so the binding
+    waits for the device behind the copy, also when torch's current stream is the context's."""
+    import types
+
+    import torch
+    log, stream = [], object()
+    fake_cuda = types.SimpleNamespace(current_stream=lambda device=None: stream, synchronize=lambda device=None: log.append("wait"))
+    fake_torch = types.SimpleNamespace(cuda=fake_cuda, empty=torch.empty, empty_like=torch.empty_like, float32=torch.float32)
+    ver = object.__new__(b.Verifier)
+    ver.torch, ver.device, ver.dtype, ver.stream, ver.ctx = fake_torch, torch.device("cpu"), "fp32", stream, None
+    ver.mc = types.SimpleNamespace(n_kv_heads=2, head_dim=64)
+    monkeypatch.setattr(b, "ded_kv_store", lambda *a: log.append("store") or b.DED_OK)
+    monkeypatch.setattr(b, "ded_kv_load", lambda *a: log.append("load") or b.DED_OK)
+    rows = torch.zeros(2, 3, 64)
+    ver.kv_store(0, 0, 0, rows, rows)
+    ver.kv_load(0, 0, 0, 3)
+    assert log == ["store", "wait", "load", "wait"]

@@ -296,3 +296,28 @@ def test_a_tree_has_the_same_bits_beside_full_trees_and_beside_small_ones(case):
     ver.close()
     assert torch.isfinite(rows[0]).all() and rows[0].abs().max() > 0
     assert torch.equal(rows[0], rows[1])
+
+
+def test_cache_copies_are_done_for_every_stream():
+    """The tensors of kv_store and kv_load are used on another stream right after the call, behind a long queue of work on
+    the context's own."""
+    import torch
+    cfg = di.ModelConfig("kv-streams", 1, 128, 4, 2, 128, 128, 64, dtype="bf16")
+    ver = _verifier(cfg, di.make_weights(cfg, seed=3), max_batch=1, kv_capacity=4096, max_nodes=16)
+    other = torch.cuda.Stream()
+    a = torch.randn(2, 4000, 128, device="cuda").bfloat16().clamp(0.5, 4.0)
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    staging = a.clone()
+    for _ in range(20):
+        busy @ busy
+    ver.kv_store(0, 0, 0, staging, staging)
+    with torch.cuda.stream(other):
+        staging.zero_()
+    for _ in range(20):
+        busy @ busy
+    k, v = ver.kv_load(0, 0, 0, 4000)
+    with torch.cuda.stream(other):
+        same = torch.equal(k, a) and torch.equal(v, a)
+    assert same
+    ver.close()
