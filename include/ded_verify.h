@@ -88,7 +88,10 @@ typedef struct {
 /* KV cache: HOST arrays of n_layers device buffers, each ded_kv_layer_bytes(cfg) bytes, holding
  * max_batch sequences of kv_capacity slots.  The element layout inside a buffer belongs to the
  * library (bf16 caches are stored as matrix-core operand fragments); use ded_kv_store / ded_kv_load
- * to move plain [Hkv][n][hd] rows in and out.  Keys are stored after the rotary embedding. */
+ * to move plain [Hkv][n][hd] rows in and out.  Keys are stored after the rotary embedding.
+ * Alignment: the cache buffers (and the weight matrices) of a DED_BF16 context are 16-byte aligned; those of a
+ * DED_F32 context, and every other array that a call takes (q, tree K/V, out, plain rows, logits), are aligned
+ * to their elements. */
 typedef struct {
   void *const *k;
   void *const *v;

@@ -223,10 +223,10 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
     if (QP == 1 && plain.q) {
       // the caller's bf16 rows, widened here (exact): a lane's eight dims are 16 contiguous bytes of its row
       const int64_t row = ((int64_t)b * plain.max_nodes + min(node_of[rb], N - 1)) * H + kvh * G + g_of[rb];
-      const uint4* src = reinterpret_cast<const uint4*>(plain.q + row * 128) + quad;
+      const bf16_t* src = plain.q + row * 128 + quad * 8;
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
-        const uint4 v = src[kk * 4];
+        const uint4 v = load_row16(src + kk * 32);
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
         for (int j = 0; j < 8; ++j)
@@ -558,8 +558,8 @@ __global__ __launch_bounds__(NW * 64, 2) void tree_attn_tiled_kernel(
       bf16_t* dst = plain.out + (((int64_t)b * plain.max_nodes + node_of[rb]) * H + h) * 128 + quad * 4;
 #pragma unroll
       for (int hb = 0; hb < 8; ++hb)
-        *reinterpret_cast<uint2*>(dst + hb * 16) =
-            pack4_bf16(o[rb][hb][0] * inv, o[rb][hb][1] * inv, o[rb][hb][2] * inv, o[rb][hb][3] * inv);
+        store_row8(dst + hb * 16,
+                   pack4_bf16(o[rb][hb][0] * inv, o[rb][hb][1] * inv, o[rb][hb][2] * inv, o[rb][hb][3] * inv));
       continue;
     }
     if (o_final) {
@@ -634,8 +634,8 @@ __global__ __launch_bounds__(256) void tree_attn_merge_kernel(bf16_t* __restrict
   const float v[4] = {acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv};
   if (plain.out) {
     if (node < seq_n[b])
-      *reinterpret_cast<uint2*>(plain.out + (((int64_t)b * plain.max_nodes + node) * H + h) * 128 + d4 * 4) =
-          pack4_bf16(v[0], v[1], v[2], v[3]);
+      store_row8(plain.out + (((int64_t)b * plain.max_nodes + node) * H + h) * 128 + d4 * 4,
+                 pack4_bf16(v[0], v[1], v[2], v[3]));
     return;
   }
   uint16_t hi[4], lo[4];

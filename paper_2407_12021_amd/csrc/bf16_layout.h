@@ -60,6 +60,19 @@ __host__ __device__ inline int64_t packvt_index(int key, int hdim) {
   return ((frag << 6) + lane) * 8 + (kl & 7);
 }
 
+// The plain rows of a caller (queries, tree K/V, cache rows in and out) are aligned to their elements and no further:
+// vectors of them are declared so.  (The same global_load_dwordx4 / global_store_dwordx4 as for aligned ones.)
+typedef uint32_t row_u32x4_t __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t row_u32x2_t __attribute__((ext_vector_type(2), aligned(2)));
+__device__ inline uint4 load_row16(const uint16_t* p) {
+  const row_u32x4_t v = *reinterpret_cast<const row_u32x4_t*>(p);
+  return make_uint4(v[0], v[1], v[2], v[3]);
+}
+__device__ inline void store_row16(uint16_t* p, uint4 v) {
+  *reinterpret_cast<row_u32x4_t*>(p) = row_u32x4_t{v.x, v.y, v.z, v.w};
+}
+__device__ inline void store_row8(uint16_t* p, uint2 v) { *reinterpret_cast<row_u32x2_t*>(p) = row_u32x2_t{v.x, v.y}; }
+
 __device__ inline uint16_t f32_to_bf16(float f) {  // round to nearest even
   uint32_t u = __float_as_uint(f);
   u += 0x7FFFu + ((u >> 16) & 1u);

@@ -226,9 +226,9 @@ __device__ inline void kv_group_copy(bf16_t* kc, bf16_t* vc, bf16_t* kp, bf16_t*
       const int u = tid + i * 256, lane = u & 63, m = lane & 15;
       const int slot = slot0 + (m >> 2) * 8 + ((u >> 8) & 1) * 4 + (m & 3), dim = ((u >> 6) & 3) * 32 + (lane >> 4) * 8;
       if (!inside(slot)) continue;
-      uint4* plain = reinterpret_cast<uint4*>(kp + (int64_t)(slot - first) * 128 + dim);
-      if (TO_CACHE) units[u] = bf16_to_f16x8(*plain);
-      else *plain = f16_to_bf16x8(units[u]);
+      bf16_t* plain = kp + (int64_t)(slot - first) * 128 + dim;
+      if (TO_CACHE) units[u] = bf16_to_f16x8(load_row16(plain));
+      else store_row16(plain, f16_to_bf16x8(units[u]));
     }
   }
   if (!vp) return;
@@ -239,7 +239,7 @@ __device__ inline void kv_group_copy(bf16_t* kc, bf16_t* vc, bf16_t* kp, bf16_t*
     for (int i = 0; i < 2; ++i) {
       const int u = tid + i * 256, row = u >> 4, dim = (u & 15) * 8;
       uint4 v = make_uint4(0, 0, 0, 0);
-      if (inside(slot0 + row)) v = bf16_to_f16x8(*reinterpret_cast<const uint4*>(vp + (int64_t)(slot0 + row - first) * 128 + dim));
+      if (inside(slot0 + row)) v = bf16_to_f16x8(load_row16(vp + (int64_t)(slot0 + row - first) * 128 + dim));
       uint32_t* d = l32 + (row * KV_LDS_ROW + dim) / 2;
       d[0] = v.x, d[1] = v.y, d[2] = v.z, d[3] = v.w;
     }
@@ -274,7 +274,7 @@ __device__ inline void kv_group_copy(bf16_t* kc, bf16_t* vc, bf16_t* kp, bf16_t*
       const int u = tid + i * 256, row = u >> 4, dim = (u & 15) * 8;
       if (!inside(slot0 + row)) continue;
       const uint32_t* d = l32 + (row * KV_LDS_ROW + dim) / 2;
-      *reinterpret_cast<uint4*>(vp + (int64_t)(slot0 + row - first) * 128 + dim) = make_uint4(d[0], d[1], d[2], d[3]);
+      store_row16(vp + (int64_t)(slot0 + row - first) * 128 + dim, make_uint4(d[0], d[1], d[2], d[3]));
     }
   }
 }

@@ -10,6 +10,7 @@
 namespace ded {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float cache_v4f __attribute__((ext_vector_type(4), aligned(4)));  // the caller's cache: aligned to its elements only
 
 __device__ inline float wave_sum(float v) {
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
@@ -251,8 +252,8 @@ __global__ __launch_bounds__(512) void f32_mfma_gemm_kernel(F32Gemm g) {
       dst = (hs < g.H + g.Hkv ? g.kc : g.vc) + (((int64_t)b * g.Hkv + kvh) * g.cap + g.m.seq_p[b] + node) * g.hd;
     }
     if (dst) {
-      put(dst + d0, lo, 0, 4, true);
-      put(dst + d0 + half, hi, 0, 4, true);
+      *reinterpret_cast<cache_v4f*>(dst + d0) = cache_v4f{lo[0], lo[1], lo[2], lo[3]};
+      *reinterpret_cast<cache_v4f*>(dst + d0 + half) = cache_v4f{hi[0], hi[1], hi[2], hi[3]};
     }
   }
 }
@@ -472,7 +473,7 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
     const float* kr = K + (int64_t)min(k0 + m16, T - 1) * HD + quad * 4;
     v4f kf[DT];
 #pragma unroll
-    for (int c = 0; c < DT; ++c) kf[c] = *reinterpret_cast<const v4f*>(kr + c * 16);
+    for (int c = 0; c < DT; ++c) kf[c] = *reinterpret_cast<const cache_v4f*>(kr + c * 16);
     float vf[DT][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {

@@ -321,3 +321,51 @@ def test_cache_copies_are_done_for_every_stream():
         same = torch.equal(k, a) and torch.equal(v, a)
     assert same
     ver.close()
+
+
+def _off_by_one(x):
+    """The same values one element past an allocation's start."""
+    import torch
+    y = torch.empty(x.numel() + 1, dtype=x.dtype, device=x.device)[1:].view(x.shape)
+    y.copy_(x)
+    return y
+
+
+@pytest.mark.parametrize("dtype,prefix,n", [("bf16", 40, 16), ("bf16", 1500, 40), ("fp32", 40, 16)])
+def test_rows_of_a_caller_are_aligned_to_their_elements_only(dtype, prefix, n, monkeypatch):
+    """Queries, tree K/V, output and plain cache rows (fp32: the cache itself too) that start one element past a 16-byte
+    boundary give the bits of aligned ones, with one key range and with several."""
+    import torch
+    from paper_2407_12021_amd import binding
+    hd = 128 if dtype == "bf16" else 64
+    cfg = di.ModelConfig("align-" + dtype, 1, 128, 4, 2, hd, 128, 64, dtype=dtype)
+    w = di.make_weights(cfg, seed=3)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda").manual_seed(n)
+    rand = lambda *shape: torch.randn(*shape, device="cuda", generator=g).to(dt)
+    k, v, q = rand(2, prefix, hd), rand(2, prefix, hd), rand(1, n, 4, hd)
+    kt, vt = rand(1, 2, n, hd), rand(1, 2, n, hd)
+    parent, token = di.random_tree(n, None, seed=n), di.zipf_tokens(64, n, seed=n)
+    got = []
+    for shift in (lambda x: x, _off_by_one):
+        if dtype == "fp32" and shift is _off_by_one:
+            init, size = binding.ded_verify_init, binding.ded_kv_layer_bytes
+
+            def init_off(cfg, weights, kv, *rest):
+                kv.k[0] += 4
+                kv.v[0] += 4
+                return init(cfg, weights, kv, *rest)
+
+            monkeypatch.setattr(binding, "ded_kv_layer_bytes", lambda c: size(c) + 4)
+            monkeypatch.setattr(binding, "ded_verify_init", init_off)
+        ver = _verifier(cfg, w, max_batch=1, kv_capacity=prefix + 64, max_nodes=n)
+        ver.kv_store(0, 0, 0, shift(k), shift(v))
+        out = ver.tree_attention(0, [prefix], [parent], shift(q), shift(kt), shift(vt), out=shift(torch.zeros_like(q)))
+        lk, lv = shift(torch.zeros_like(k)), shift(torch.zeros_like(v))
+        assert binding.ded_kv_load(ver.ctx, 0, 0, 0, prefix, lk.data_ptr(), lv.data_ptr()) == binding.DED_OK
+        logits = ver.verify_step([prefix], [parent], [token], want_logits=True)
+        torch.cuda.synchronize()
+        got.append([x.clone() for x in (out, lk, lv, logits)])
+        ver.close()
+    for a, b in zip(*got):
+        assert a.any() and torch.equal(a, b)
