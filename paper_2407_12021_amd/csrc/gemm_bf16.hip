@@ -1495,7 +1495,7 @@ KRanges k_ranges(int rows, int N, int K, int planes, int max_splits) {
 // (measured, in us: 7B- and 8B-width projections, 128 - 2048 rows, random operands); with fewer workgroups a slot is
 // faster, because it is the chip's power and memory that bound it more than the CU.  A hand-over costs about 3 us and
 // 1.5 us per 64 KB slice beyond the first.
-GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, int64_t part_elems) {
+GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, int64_t part_elems, double* us = nullptr) {
   constexpr double slot_us[2][6] = {{0.97, 0.74, 0.52, 0.50, 0.40, 0.31}, {1.80, 1.25, 0.86, 0.94, 0.70, 0.51}};
   const int parts = r.main > 1 ? r.main : r.rem;
   GemmPlan best{0, 1, 1, 0, 0};
@@ -1521,7 +1521,15 @@ GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, in
       best = p;
     }
   }
+  if (us) *us = best_cost;
   return best;
+}
+
+// Time of an unsplit wide launch of `wgs` workgroups, in us: 8 us around the loop, and a turn of it (64 of k) that is longer
+// the more of the chip streams weights.
+double wide_us(int nwn, int wgs, int K) {
+  constexpr double turn_us[5] = {0.0, 0.0, 0.905, 1.04, 1.24};
+  return (wgs + kCUs - 1) / kCUs * 8.0 + K / 64 * turn_us[nwn] * wgs / kCUs;
 }
 
 template <int PLANES, int EPI>
@@ -1615,13 +1623,18 @@ GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, in
       }
     }
   }
-  // 65 - 255 rows, an unsplit wide kernel: the halves of its k range as the two ranges of the tile kernel, added in the same
-  // order.  Three trees of 144 rows on the 8B shape 10.4 -> 9.36 ms; the 97-row step of the 7B shape (gate/up, LM head)
-  // unchanged.
+  // 65 - 255 rows, an unsplit wide kernel: the halves of its k range can run as the two ranges of the tile kernel, added in
+  // the same order.  Worth it where the wide kernel reads the weights in several rounds, or k is long against the tile
+  // kernel's start-up and hand-over (5 us and 4.5 us per 64 features of the tile beyond plan_tiles' estimate).  Both sides
+  // measured, wide / tile, us: 97 rows, gate/up of the 7B shape 68 / 73 and of the 8B shape 77 / 81, the same of the 13B
+  // shape (K = 5120) 95 / 92 and its QKV 76 / 62, LM heads of 32000 tokens with K = 2048 49 / 55, K = 4096 87 / 86, K = 8192
+  // 161 / 144, of 128256 tokens 390 / 293; 144 rows, gate/up of the 8B shape 123 / 102.
   if (rows_pad > 64 && best.nwn && best.splits == 1 && groups % 2 == 0) {
-    GemmPlan p = plan_tiles(KRanges{0, 2, 1}, rows_pad, N, K, planes, part_elems);
+    double tile_us;
+    GemmPlan p = plan_tiles(KRanges{0, 2, 1}, rows_pad, N, K, planes, part_elems, &tile_us);
+    const int wgs = (NG + best.nwn - 1) / best.nwn * (rows_pad / 64);
     p.ssq_waves = 2 * best.nwn;
-    if (p.tile) return p;
+    if (p.tile && tile_us + 5.0 + 4.5 * tile_dims(p.tile).groups < wide_us(best.nwn, wgs, K)) return p;
   }
   return best;
 }

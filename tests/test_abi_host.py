@@ -202,3 +202,25 @@ def test_cache_copies_are_done_when_the_call_returns(b, monkeypatch):
     ver.kv_store(0, 0, 0, rows, rows)
     ver.kv_load(0, 0, 0, 3)
     assert log == ["store", "wait", "load", "wait"]
+
+
+@pytest.mark.parametrize("sum_rows,rows_pad,N,K,tile", [
+    (128, 128, 22016, 4096, False),   # gate / up of the 7B shape, 97 rows: one round of the wide kernel, 68 us against 73
+    (128, 128, 28672, 4096, False),   # of the 8B shape: 77 us against 81
+    (128, 128, 32000, 2048, False),   # an LM head with short k: 49 us against 55
+    (128, 128, 15360, 5120, True),    # QKV of the 13B shape: 76 us against 62
+    (128, 128, 128256, 4096, True),   # LM head of the 8B shape, four rounds: 390 us against 293
+    (192, 192, 28672, 4096, True),    # gate / up of the 8B shape, 144 rows: 123 us against 102
+    (64, 64, 22016, 4096, False),     # one 64-row group
+])
+def test_kernel_of_65_to_255_rows(b, sum_rows, rows_pad, N, K, tile):
+    """Where both can add the same k ranges in the same order, the faster of the skinny and the tile kernel runs."""
+    import ctypes as C
+
+    class Plan(C.Structure):
+        _fields_ = [(n, C.c_int) for n in ("nwn", "nw", "splits", "tile", "whole", "ssq_waves")]
+
+    plan = b.lib()["_ZN3ded14bf16_gemm_planEiiiiiil"]  # ded::bf16_gemm_plan(int x 6, int64_t)
+    plan.restype, plan.argtypes = Plan, [C.c_int] * 6 + [C.c_int64]
+    p = plan(sum_rows, rows_pad, N, K, 2, 4, N * 512)
+    assert bool(p.tile) == tile, [getattr(p, n) for n, _ in Plan._fields_]

@@ -269,9 +269,13 @@ def test_fp32_step_reports_a_nan_key_of_the_prefix():
 
 
 # (d, H, Hkv, F, V) of one layer; a batch of full trees and a ragged one that share the first tree.  320 padded rows whose
-# gate / up slices have no room in the context where those of the 208 packed rows would
+# gate / up slices have no room in the context where those of the 208 packed rows would; 192 and 144 padded rows, whose QKV
+# or gate / up run in the tile kernel beside full trees and in the wide kernel (128 packed rows) beside small ones, the LM
+# head in two shapes of tile
 RAGGED = [
     ((4096, 32, 32, 11008, 32000), [64] * 5, [64, 33, 16, 20, 40]),
+    ((4096, 32, 32, 11008, 32000), [64] * 3, [64, 16, 17]),
+    ((4096, 32, 8, 14336, 32000), [48] * 3, [48, 16, 1]),
 ]
 
 
