@@ -1066,13 +1066,17 @@ __global__ __launch_bounds__(NWMAX * 64) void gemm_slim_kernel(const uint4* __re
 // wavefront tile: every wavefront position has a last arriver of its own and no barrier is needed.  The first slots of
 // the next item are requested before a tile's epilogue runs.
 // What bounds it: at 512 rows and more the matrix cores at the chip's power limit (LM head of a 7B shape, 512 rows:
-// 225 us = 1.19 PFLOP/s executed, and no more than 1.26 with operands that never leave the caches); at 256 rows the
-// operand stream, ~55 GB/s into each CU (gate/up of a 7B shape 119 -> 101 us, QKV 73 -> 61, O 48 -> 27, down 78 -> 44).
+// 225 us with two planes = 1.19 PFLOP/s executed, and no more than 1.26 with operands that never leave the caches; gate/up
+// of the 13B shape, 216 tiles of 256 x 256 in one round: 225 us between launches that draw less power, 250 in a step); at
+// 256 rows the operand stream, ~55 GB/s into each CU (gate/up of a 7B shape 119 -> 101 us, QKV 73 -> 61, O 48 -> 27, down 78 -> 44).
 // ------------------------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void glb_void_t;
-__device__ __forceinline__ void load_to_lds(const char* src, uint4* dst) {  // lane i: 16 bytes at its src -> dst[i]
-  __builtin_amdgcn_global_load_lds((glb_void_t*)src, (lds_void_t*)dst, 16, 0, 0);
+// lane i: 16 bytes at base + its offset -> dst[i].  (The offset is kept from view, as 32 bits: the compiler otherwise holds
+// a 64-bit one per load across the loop, or spills it.)
+__device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint4* dst) {
+  asm volatile("" : "+v"(offset));
+  __builtin_amdgcn_global_load_lds((glb_void_t*)(base + offset), (lds_void_t*)dst, 16, 0, 0);
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {  // all but the last N vector-memory operations, and every LDS read, are done
@@ -1179,10 +1183,10 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
   };
   auto request = [&](uint4* slot) {
 #pragma unroll
-    for (int j = 0; j < WJ; ++j) load_to_lds(wbase + woff[j], slot + (j * TILE_WAVES + wave) * 64);
+    for (int j = 0; j < WJ; ++j) load_to_lds(wbase, woff[j], slot + (j * TILE_WAVES + wave) * 64);
 #pragma unroll
     for (int j = 0; j < XJ; ++j)
-      load_to_lds(xbase + xoff[j], slot + (WF + min(j * TILE_WAVES + wave, XF - 1)) * 64);
+      load_to_lds(xbase, xoff[j], slot + (WF + min(j * TILE_WAVES + wave, XF - 1)) * 64);
     // (past the segment's end its last slot is read again, so that the loads in flight stay countable)
     --req_left;
     wbase += req_left > 0 ? 1 << 12 : 0;
@@ -1235,14 +1239,32 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
     if (live) compute(now);
     __builtin_amdgcn_sched_barrier(0);
   };
-  // Otherwise (large wavefront tiles): read and multiplied in the same step; the slot of the step before is free.
+  // Otherwise (large wavefront tiles): read and multiplied in the same step; the slot of the step before is free.  The
+  // activations stay in registers, the weights pass through two, one fragment ahead of its products.  (The fences hold the
+  // compiler to that: with a slot's fragments all in registers it spilled the load addresses, and fetching those inside the
+  // loop waited for every load in flight, two of three slots.)
   auto step_direct = [&](const uint4* slot, uint4* freed, bool live) {
     wait_loads<IN_FLIGHT>();
     barrier_only();
     request(freed);
-    if (live) {
-      read(slot, fa);
-      compute(fa);
+    if (!live) return;
+    const uint4* lw = slot + fg * (GPW * TN) * 64 + lane;
+    const uint4* lx = slot + (WF + rg * (RBW * PLANES)) * 64 + lane;
+    f16x8_t w[2], x[RBW * PLANES];
+    w[0] = __builtin_bit_cast(f16x8_t, lw[0]);
+#pragma unroll
+    for (int i = 0; i < RBW * PLANES; ++i) x[i] = __builtin_bit_cast(f16x8_t, lx[i << 6]);
+#pragma unroll
+    for (int i = 0; i < GPW * TN; ++i) {
+      if (i + 1 < GPW * TN) w[(i + 1) & 1] = __builtin_bit_cast(f16x8_t, lw[(i + 1) << 6]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int p = 0; p < PLANES; ++p)
+#pragma unroll
+        for (int rb = 0; rb < RBW; ++rb)
+          acc[i / TN][i % TN][rb] =
+              __builtin_amdgcn_mfma_f32_16x16x32_f16(w[i & 1], x[rb * PLANES + p], acc[i / TN][i % TN][rb], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
 
@@ -1492,11 +1514,18 @@ KRanges k_ranges(int rows, int N, int K, int planes, int max_splits) {
 }
 
 // Tile of a launch whose sums have k ranges `r`.  Every tile shape is weighed with the time of one ring slot on a full chip
-// (measured, in us: 7B- and 8B-width projections, 128 - 2048 rows, random operands); with fewer workgroups a slot is
-// faster, because it is the chip's power and memory that bound it more than the CU.  A hand-over costs about 3 us and
-// 1.5 us per 64 KB slice beyond the first.
+// (measured, in us: 7B-, 8B- and 13B-width projections, 128 - 2048 rows, random operands).  With fewer workgroups a slot is
+// faster where the chip's memory bounds it more than the CU; with two planes and 256 rows and more it is not, and a partly
+// filled round takes as long as a full one (gate/up in a step, us, by tile 256 x 256 / x 192 / x 128, 128 x 256 / x 192 /
+// x 128: 7B shape, 512 rows 193 / 284 / 207, 221 / 221 / 177; 13B, 512 rows 250 / 383 / 262, 272 / 303 / 286, 2048 rows
+// 976 / 962 / 894, 926 / 1001 / 1009).  A hand-over costs about 3 us and 1.5 us per 64 KB slice beyond
+// the first, and 25 us more with 128 accumulators per lane (the other part is fetched eight fragments at a time: QKV of a
+// 7B shape, 2048 rows, a third of it split, 350 us with 256 x 256 tiles, 337 with 256 x 128).
 GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, int64_t part_elems, double* us = nullptr) {
-  constexpr double slot_us[2][6] = {{0.97, 0.74, 0.52, 0.50, 0.40, 0.31}, {1.80, 1.25, 0.86, 0.94, 0.70, 0.51}};
+  constexpr double slot_us[3][6] = {{0.97, 0.74, 0.52, 0.50, 0.40, 0.31},    // one plane
+                                    {1.80, 1.25, 0.86, 0.94, 0.70, 0.51},    // two planes, fewer than 256 rows
+                                    {1.50, 1.19, 0.79, 0.84, 0.63, 0.47}};   // two planes, 256 rows and more
+  const int kind = planes == 1 ? 0 : rows_pad < 256 ? 1 : 2;
   const int parts = r.main > 1 ? r.main : r.rem;
   GemmPlan best{0, 1, 1, 0, 0};
   double best_cost = 1e300;
@@ -1505,17 +1534,17 @@ GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, in
     const int64_t tiles = tile_count(tile, rows_pad, N);
     const int64_t whole = r.main > 1 ? 0 : std::min<int64_t>(tiles, (int64_t)r.x_main * (4 / t.groups) * row_tile_count(tile, rows_pad));
     const int slots = K / 32;
-    const double slot = slot_us[planes - 1][tile - TILE_256x256], slice_64k = t.groups * t.row_blocks / 16.0;
+    const double slot = slot_us[kind][tile - TILE_256x256], slice_64k = t.groups * t.row_blocks / 16.0;
     const GemmPlan p{0, 1, parts, tile, (int)whole};
     if (!tile_plan_ok(p, rows_pad, N, K, part_elems)) continue;
     double cost = 0.0;
     auto rounds = [&](int64_t items, int len) {
       const double fill = (double)(items % kCUs) / kCUs;
-      cost += (double)(items / kCUs) * len * slot + (fill > 0 ? len * slot * (0.4 + 0.6 * fill) : 0.0);
+      cost += len * slot * ((double)(items / kCUs) + (fill > 0 ? kind == 2 ? 1.0 : 0.4 + 0.6 * fill : 0.0));
     };
     rounds(whole, slots);
     rounds((tiles - whole) * parts, (slots + parts - 1) / parts);
-    if (parts > 1) cost += 3.0 + 1.5 * (parts - 1) * slice_64k;
+    if (parts > 1) cost += 3.0 + 1.5 * (parts - 1) * slice_64k + (tile == TILE_256x256 ? 25.0 : 0.0);
     if (cost < best_cost) {
       best_cost = cost;
       best = p;
