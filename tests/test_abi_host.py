@@ -219,16 +219,16 @@ def test_kernel_of_65_to_255_rows(b, sum_rows, rows_pad, N, K, tile):
     assert bool(p.tile) == tile
 
 
-@pytest.mark.parametrize("rows,N,K,tile", [  # 1: 256 features x 256 rows, 3: 256 x 128, 6: 128 x 128
-    (512, 22016, 4096, 6),    # gate / up of the 7B shape: 177 us (256 x 128: 207)
-    (512, 27648, 5120, 1),    # of the 13B shape: 250 us (256 x 128: 262)
-    (512, 28672, 4096, 1),    # of the 8B shape: 205 us (256 x 128: 211)
-    (512, 15360, 5120, 3),    # QKV of the 13B shape: 138 us (256 x 256: 237)
-    (2048, 27648, 5120, 3),   # gate / up of the 13B shape: 894 us (256 x 256: 976)
-    (256, 6144, 4096, 3),     # QKV of the 8B shape in four k ranges: 50 us (128 x 128: 60)
+@pytest.mark.parametrize("rows,N,K,room,tile", [  # room: slices the context has room for; 1: 256 features x 256 rows, 3: 256 x 128, 6: 128 x 128
+    (512, 22016, 4096, 1, 6),    # gate / up of the 7B shape: 177 us (256 x 128: 207)
+    (512, 27648, 5120, 1, 1),    # of the 13B shape: 250 us (256 x 128: 262)
+    (512, 28672, 4096, 1, 1),    # of the 8B shape: 205 us (256 x 128: 211)
+    (512, 15360, 5120, 1, 3),    # QKV of the 13B shape: 138 us (256 x 256: 237)
+    (2048, 27648, 5120, 1, 3),   # gate / up of the 13B shape: 894 us (256 x 256: 976)
+    (256, 6144, 4096, 4, 3),     # QKV of the 8B shape in four k ranges: 50 us (128 x 128: 60)
 ])
-def test_workgroup_tile_of_two_planes(b, rows, N, K, tile):
-    p = _gemm_plan(b, rows, rows, N, K, 2, 4, N * max(rows, 512) * 4)
+def test_workgroup_tile_of_two_planes(b, rows, N, K, room, tile):
+    p = _gemm_plan(b, rows, rows, N, K, 2, room, N * rows * room)
     assert p.tile == tile
 
 
