@@ -265,7 +265,7 @@ int ded_tree_attention(ded_ctx *ctx, int32_t layer, int32_t batch, const int32_t
 /* ded_tree_attention for callers that cannot allocate device memory and have no workspace region to spare for
  * it: code under HIP graph capture, tight serving loops, harnesses that forbid allocation.  Same arguments,
  * same kernels and bit-identical output, but every transient device buffer of the call (the uploaded tree
- * description, the re-laid-out queries and output, the split-KV partial results) lives in an array that is
+ * description, the split-KV partial results, and room for the queries and the output) lives in an array that is
  * part of the library's own device image: ded_static_scratch_bytes() bytes (32 MiB) per GPU, held from the
  * first ded_verify_init on that GPU until the process ends.  The call allocates nothing and frees nothing.
  * The context's device must be current.  A call whose buffers would not fit the array (roughly

@@ -23,14 +23,13 @@ inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline int round_up(int v, int a) { return (v + a - 1) / a * a; }
 
 enum KClass {
-  KC_META = 0, KC_ROPE_TABLE, KC_EMBED, KC_RMSNORM, KC_GEMM_QKV, KC_QKV_EPILOGUE, KC_TREE_ATTN, KC_ATTN_MERGE,
-  KC_GEMM_O, KC_GEMM_GATE_UP, KC_SILU_MUL, KC_GEMM_DOWN, KC_GEMM_LM_HEAD, KC_ARGMAX, KC_EXPORT, KC_WALK,
-  KC_COMPACT, KC_LAYOUT, KC_SAMPLE, KC_TOP2_REDUCE, KC_COUNT
+  KC_META = 0, KC_ROPE_TABLE, KC_EMBED, KC_GEMM_QKV, KC_QKV_EPILOGUE, KC_TREE_ATTN, KC_GEMM_O, KC_GEMM_GATE_UP,
+  KC_GEMM_DOWN, KC_GEMM_LM_HEAD, KC_ARGMAX, KC_EXPORT, KC_WALK, KC_COMPACT, KC_LAYOUT, KC_SAMPLE, KC_TOP2_REDUCE, KC_COUNT
 };
 const char* const kClassNames[KC_COUNT] = {
-    "meta_upload", "rope_table", "embed", "add_rmsnorm", "gemm_qkv", "qkv_rope_epilogue", "tree_attention",
-    "attention_merge", "gemm_o", "gemm_gate_up", "silu_mul", "gemm_down", "gemm_lm_head", "argmax",
-    "export_logits", "accept_walk", "kv_compact", "layout_convert", "sample_top_p", "top2_reduce"};
+    "meta_upload", "rope_table", "embed", "gemm_qkv", "qkv_rope_epilogue", "tree_attention", "gemm_o", "gemm_gate_up",
+    "gemm_down", "gemm_lm_head", "argmax", "export_logits", "accept_walk", "kv_compact", "layout_convert", "sample_top_p",
+    "top2_reduce"};
 
 struct Carve {  // bump allocator over the workspace (base may be null when only sizing)
   char* base;
@@ -1063,7 +1062,8 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
       const int64_t part_rows = (int64_t)batch * md.H * ns * shape.n_step;
       Carve w(reinterpret_cast<char*>(c->static_scratch));
       ws.d_meta = w.take<char>(c->meta_bytes);
-      // part of the documented size of a call: room for the queries and the output in operand-fragment form
+      // counted with every call as documented, though the queries and the output are no longer re-laid-out: what is refused
+      // does not change
       w.take<bf16_t>((int64_t)round_up(shape.rows, 64) * md.H * md.hd * 4);
       ws.part_o = w.take<float>(part_rows * md.hd);
       ws.part_ml = w.take<float2>(part_rows);

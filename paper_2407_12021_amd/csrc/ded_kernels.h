@@ -140,10 +140,6 @@ struct GemmEpilogue {
   float* ssq_out;
 };
 
-// Skinny GEMM on the matrix cores with a fused epilogue.  planes = 2 uses X = hi + lo, planes = 1 only the
-// hi plane.  rows_pad % 64 == 0, N % 16 == 0 (N % 64 for the paired epilogues), K % 128 == 0.  `part` holds
-// plan.splits slices of part_stride >= rows_pad * round_up(N, 64) floats, `counters` one zeroed int per output tile (left zeroed).
-// Returns false (nothing launched) on an unsupported shape.
 // Workgroup tiles of the tile kernel (features x rows).
 enum {
   TILE_256x256 = 1, TILE_256x192, TILE_256x128, TILE_128x256, TILE_128x192, TILE_128x128
@@ -159,6 +155,11 @@ struct GemmPlan {
 // sum_rows (a multiple of 64, >= rows_pad) decides into which k ranges the sums are split, rows_pad how they are run.
 GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems);
 int bf16_gemm_tiles(int rows_pad, int N, const GemmPlan& plan);
+// GEMM on the matrix cores with a fused epilogue (skinny and tile kernels).  planes = 2 uses X = hi + lo, planes = 1 only
+// the hi plane.  rows_pad % 64 == 0, N % 16 == 0 (N % 64 for the paired epilogues), K % 128 == 0.  `part` (part_elems floats)
+// takes the split sums: plan.splits slices of part_stride >= rows_pad * round_up(N, 64) floats, or the tile kernel's own
+// slices; `counters` one zeroed int per output tile, eight per split tile of the tile kernel (left zeroed).  Returns false
+// (nothing launched) on an unsupported shape.
 bool bf16_gemm(float* part, int64_t part_stride, int64_t part_elems, const bf16_t* x_packed, const bf16_t* w_packed,
                int rows_pad, int N, int K, int planes, const GemmPlan& plan, int* counters, const GemmEpilogue& epi,
                hipStream_t s);

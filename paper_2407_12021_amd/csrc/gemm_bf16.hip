@@ -1491,7 +1491,7 @@ bool tile_plan_ok(const GemmPlan& p, int rows_pad, int N, int K, int64_t part_el
 struct KRanges {
   int x_main, main, rem;
 };
-KRanges k_ranges(int rows, int N, int K, int planes, int max_splits) {
+KRanges k_ranges(int rows, int N, int K, int max_splits) {
   const int NG = (N + 16 * TN - 1) / (16 * TN), groups = K / (32 * PD), X = (NG + 3) / 4;
   KRanges best{X, 1, 1};
   double best_cost = 1e300;
@@ -1629,8 +1629,8 @@ GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, in
   if (sum_rows >= 256) {
     // No room for the slices: unsplit.  Asked for sum_rows, so that a ragged batch is summed like a full one: a tile whose
     // slices fit sum_rows fits fewer rows as well.
-    KRanges r = k_ranges(sum_rows, N, K, planes, max_splits);
-    if (!plan_tiles(r, sum_rows, N, K, planes, part_elems).tile) r = k_ranges(sum_rows, N, K, planes, 1);
+    KRanges r = k_ranges(sum_rows, N, K, max_splits);
+    if (!plan_tiles(r, sum_rows, N, K, planes, part_elems).tile) r = k_ranges(sum_rows, N, K, 1);
     return plan_tiles(r, rows_pad, N, K, planes, part_elems);
   }
   GemmPlan best{0, 1, 1};

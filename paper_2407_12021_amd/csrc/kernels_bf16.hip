@@ -37,11 +37,6 @@ __device__ inline void store8(float* p, const F8& r) {
   *reinterpret_cast<float4*>(p + 4) = make_float4(r.v[4], r.v[5], r.v[6], r.v[7]);
 }
 __device__ inline uint32_t pk(uint16_t lo, uint16_t hi) { return (uint32_t)lo | ((uint32_t)hi << 16); }
-// eight floats -> eight f16 (one 16-byte unit)
-__device__ inline uint4 to_f16x8(const F8& r) {
-  return make_uint4(pk(f32_to_f16(r.v[0]), f32_to_f16(r.v[1])), pk(f32_to_f16(r.v[2]), f32_to_f16(r.v[3])),
-                    pk(f32_to_f16(r.v[4]), f32_to_f16(r.v[5])), pk(f32_to_f16(r.v[6]), f32_to_f16(r.v[7])));
-}
 // eight floats -> hi and lo planes
 __device__ inline void to_f16x8_split(const F8& r, uint4& hi, uint4& lo) {
   uint16_t h[8], l[8];
@@ -49,16 +44,6 @@ __device__ inline void to_f16x8_split(const F8& r, uint4& hi, uint4& lo) {
   for (int i = 0; i < 8; ++i) split_f16(r.v[i], h[i], l[i]);
   hi = make_uint4(pk(h[0], h[1]), pk(h[2], h[3]), pk(h[4], h[5]), pk(h[6], h[7]));
   lo = make_uint4(pk(l[0], l[1]), pk(l[2], l[3]), pk(l[4], l[5]), pk(l[6], l[7]));
-}
-// sum over split-K slices in slice order (fixed order -> deterministic)
-__device__ inline F8 sum_parts8(const float* part, int n_part, int64_t part_stride, int64_t off) {
-  F8 acc = load8(part + off);
-  for (int s = 1; s < n_part; ++s) {
-    F8 t = load8(part + (int64_t)s * part_stride + off);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) acc.v[i] += t.v[i];
-  }
-  return acc;
 }
 
 }  // namespace
