@@ -13,6 +13,24 @@ def pytest_configure(config):
 
 
 @pytest.fixture(scope="session")
+def gemm_plan():
+    """ded::bf16_gemm_plan(sum_rows, rows_pad, N, K, planes, max_splits, part_elems): which kernel runs a projection (host code)."""
+    import ctypes as C
+
+    from paper_2407_12021_amd import binding
+
+    class Plan(C.Structure):
+        _fields_ = [(n, C.c_int) for n in ("nwn", "nw", "splits", "tile", "whole", "ssq_waves")]
+
+    def plan(*args):
+        f = binding.lib()["_ZN3ded14bf16_gemm_planEiiiiiil"]
+        f.restype, f.argtypes = Plan, [C.c_int] * 6 + [C.c_int64]
+        return f(*args)
+
+    return plan
+
+
+@pytest.fixture(scope="session")
 def small_cfg():
     from ded_inputs import ModelConfig
     return ModelConfig("pin-small", 2, 32, 4, 2, 8, 48, 50, dtype="fp32")

@@ -213,9 +213,9 @@ def test_cache_copies_are_done_when_the_call_returns(b, monkeypatch):
     (192, 192, 28672, 4096, True),    # gate / up of the 8B shape, 144 rows: 123 us against 102
     (64, 64, 22016, 4096, False),     # one 64-row group
 ])
-def test_kernel_of_65_to_255_rows(b, sum_rows, rows_pad, N, K, tile):
+def test_kernel_of_65_to_255_rows(b, gemm_plan, sum_rows, rows_pad, N, K, tile):
     """Where both can add the same k ranges in the same order, the faster of the skinny and the tile kernel runs."""
-    p = _gemm_plan(b, sum_rows, rows_pad, N, K, 2, 4, N * 512)
+    p = gemm_plan(sum_rows, rows_pad, N, K, 2, 4, N * 512)
     assert bool(p.tile) == tile
 
 
@@ -227,17 +227,6 @@ def test_kernel_of_65_to_255_rows(b, sum_rows, rows_pad, N, K, tile):
     (2048, 27648, 5120, 1, 3),   # gate / up of the 13B shape: 894 us (256 x 256: 976)
     (256, 6144, 4096, 4, 3),     # QKV of the 8B shape in four k ranges: 50 us (128 x 128: 60)
 ])
-def test_workgroup_tile_of_two_planes(b, rows, N, K, room, tile):
-    p = _gemm_plan(b, rows, rows, N, K, 2, room, N * rows * room)
+def test_workgroup_tile_of_two_planes(b, gemm_plan, rows, N, K, room, tile):
+    p = gemm_plan(rows, rows, N, K, 2, room, N * rows * room)
     assert p.tile == tile
-
-
-def _gemm_plan(b, *args):
-    import ctypes as C
-
-    class Plan(C.Structure):
-        _fields_ = [(n, C.c_int) for n in ("nwn", "nw", "splits", "tile", "whole", "ssq_waves")]
-
-    plan = b.lib()["_ZN3ded14bf16_gemm_planEiiiiiil"]  # ded::bf16_gemm_plan(int x 6, int64_t)
-    plan.restype, plan.argtypes = Plan, [C.c_int] * 6 + [C.c_int64]
-    return plan(*args)

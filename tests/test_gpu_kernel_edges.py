@@ -154,6 +154,40 @@ def test_projections_at_tile_edges(case):
     assert err <= 2e-2
 
 
+# (d, H, Hkv, F, V) of one layer, prefix lengths, tree sizes, (N, K) of the projections that the tile kernel runs: steps of 97,
+# 144 and 70 rows whose unsplit products run as two k ranges of the tile kernel, rows that fill no whole tile, a vocabulary
+# that ends inside a feature group
+MID_EDGES = [
+    ((2048, 16, 4, 8192, 65552), [5], [97], [(16384, 2048), (65552, 2048)]),
+    ((4096, 32, 8, 14336, 32016), [3, 0, 40], [37, 21, 50], [(28672, 4096), (32016, 4096)]),
+    ((5120, 40, 40, 1408, 1040), [9], [70], [(15360, 5120)]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(MID_EDGES)))
+def test_projections_of_65_to_255_rows(case, gemm_plan):
+    """Bound: the 16-bit path's 2e-2 logit tolerance, as above; tokens and margins without logits equal those with them."""
+    (d, H, Hkv, F, V), prefix_len, nodes, tiled = MID_EDGES[case]
+    rows = -(-len(nodes) * (-(-max(nodes) // 16) * 16) // 64) * 64
+    for N, K in tiled:
+        assert gemm_plan(rows, rows, N, K, 2, 4, N * 512).tile
+    cfg = di.ModelConfig(f"mid-edge{case}", 1, d, H, Hkv, 128, F, V, dtype="bf16")
+    w = di.make_weights(cfg, seed=100 + case, gain_jitter=0.1, threads=16)
+    err = _step_error(cfg, w, prefix_len, nodes, seed=110 + case)
+    print(f"max |logit error| {err:.2e}")
+    assert err <= 2e-2
+    ver = _verifier(cfg, w, max_batch=len(nodes), kv_capacity=128, max_nodes=max(nodes))
+    parents = [di.random_tree(n, None, seed=b) for b, n in enumerate(nodes)]
+    tokens = [di.zipf_tokens(V, n, seed=6, stream=b) for b, n in enumerate(nodes)]
+    got = []
+    for logits in (True, False):
+        ver.verify_step([0] * len(nodes), parents, tokens, want_logits=logits)
+        got.append(ver.get_argmax())
+    ver.close()
+    for b, n in enumerate(nodes):
+        assert np.array_equal(got[0][0][b, :n], got[1][0][b, :n]) and np.array_equal(got[0][1][b, :n], got[1][1][b, :n])
+
+
 # (layers, d, H, Hkv, F, V), prefix lengths, tree sizes: steps of 16 and 32 padded rows; k ranges of one step of 128, ranges that
 # are no multiple of the ring, half groups and whole groups (160 feature groups and more), 2 to 16 ranges per workgroup, a
 # vocabulary that ends inside a group
@@ -271,11 +305,13 @@ def test_fp32_step_reports_a_nan_key_of_the_prefix():
 # (d, H, Hkv, F, V) of one layer; a batch of full trees and a ragged one that share the first tree.  320 padded rows whose
 # gate / up slices have no room in the context where those of the 208 packed rows would; 192 and 144 padded rows, whose QKV
 # or gate / up run in the tile kernel beside full trees and in the wide kernel (128 packed rows) beside small ones, the LM
-# head in two shapes of tile
+# head in two shapes of tile; 512 padded rows beside 192 and 384 packed ones, which between them take every shape of tile
 RAGGED = [
     ((4096, 32, 32, 11008, 32000), [64] * 5, [64, 33, 16, 20, 40]),
     ((4096, 32, 32, 11008, 32000), [64] * 3, [64, 16, 17]),
     ((4096, 32, 8, 14336, 32000), [48] * 3, [48, 16, 1]),
+    ((4096, 32, 8, 14336, 32000), [64] * 8, [64] + [16] * 7),
+    ((4096, 32, 8, 14336, 32000), [64] * 8, [64] * 4 + [32] * 4),
 ]
 
 
