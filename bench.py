@@ -350,20 +350,21 @@ def profile_workload(di, mode):
     if mode == "c2":
         attention_only_bench(di, iters=16)
         return
-    if mode == "large":
-        cfg, batch, nodes, P = di.WORKLOADS["c3"].model.with_layers(2), 8, 256, 0
+    shapes = {"large": (8, 256, 0), "chunk": (1, 256, 768), "decode": (1, 1, 1024)}  # batch, nodes, prefix of the 7B shape
+    if mode in shapes:
+        cfg, (batch, nodes, P) = di.WORKLOADS["c3"].model.with_layers(2), shapes[mode]
     else:
         cfg, batch, nodes, P = di.WORKLOADS["c5"].model.with_layers(2), 8, 256, 16384
     w = di.make_weights(cfg, seed=0, threads=16)
     ver = Verifier(cfg, w, max_batch=batch, kv_capacity=P + nodes + 64, max_nodes=nodes)
     del w
     g = np.random.default_rng(5)
-    for s0 in range(0, P, nodes):
+    for s0 in range(0, P if mode == "c5attn" else 0, nodes):
         ver.verify_step([s0] * batch, [di.chain_tree(nodes)] * batch, [g.integers(0, cfg.vocab, size=nodes) for _ in range(batch)])
         ver.accept(mode=1)
-    parent = di.random_tree(nodes, None, seed=3)
+    parent = di.random_tree(nodes, None, seed=3) if nodes > 1 else [-1]
     toks = [g.integers(0, cfg.vocab, size=nodes) for _ in range(batch)]
-    for _ in range(4 if mode == "large" else 3):
+    for _ in range({"large": 4, "c5attn": 3}.get(mode, 20)):
         ver.verify_step([P] * batch, [parent] * batch, toks)
         ver.accept(mode=0)
     torch.cuda.synchronize()
@@ -457,11 +458,11 @@ def main():
     ap.add_argument("--no-attn", action="store_true")
     ap.add_argument("--no-large-rows", action="store_true")
     ap.add_argument("--no-batched", action="store_true", help="skip the c4 / c5 step timings (26 GB and 15 GB of weights)")
-    ap.add_argument("--profile-mode", choices=["c3", "c2", "large", "c5attn"],
+    ap.add_argument("--profile-mode", choices=["c3", "c2", "large", "chunk", "decode", "c5attn"],
                     help="a minimal workload for rocprofv3 runs (kernel trace or one --pmc counter set), no timing: "
                          "c3 = a 1 GiB device copy (counter calibration) + 4 verification steps of the benchmark workload; "
                          "c2 = 24 attention-only launches of configuration 2; large = 4 steps of a 2-layer 7B-shape model "
-                         "on 8 x 256-node trees (2048 rows); c5attn = 3 steps of a 2-layer Llama-3-8B-shape model, batch 8, "
+                         "on 8 x 256-node trees (2048 rows); chunk / decode = 20 steps of the same model on one 256-node tree / one node; c5attn = 3 steps of a 2-layer Llama-3-8B-shape model, batch 8, "
                          "prefix 16384, 256-node trees")
     args = ap.parse_args()
     if args.gpus != 1:
