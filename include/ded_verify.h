@@ -210,6 +210,7 @@ int ded_verify_step(ded_ctx *ctx, int32_t batch, const int32_t *prefix_len, cons
  *   p_i = softmax(logits / temperature); the nucleus is the smallest set of most probable tokens whose
  *   probabilities reach top_p (ties with its last member included); the token is the smallest id j of
  *   the nucleus with  sum_{i in nucleus, i <= j} p_i > u * sum_{nucleus} p.
+ *   Weights below 2^-40 of the most probable token's count as zero.
  *   temperature > 0, 0 < top_p <= 1
  *   uniform  host [batch][max_nodes], one number in [0, 1) per node, drawn by the caller
  * Synchronises the stream.  ded_get_argmax afterwards returns the sampled tokens (margins unchanged).
