@@ -462,8 +462,9 @@ def main():
                     help="a minimal workload for rocprofv3 runs (kernel trace or one --pmc counter set), no timing: "
                          "c3 = a 1 GiB device copy (counter calibration) + 4 verification steps of the benchmark workload; "
                          "c2 = 24 attention-only launches of configuration 2; large = 4 steps of a 2-layer 7B-shape model "
-                         "on 8 x 256-node trees (2048 rows); chunk / decode = 20 steps of the same model on one 256-node tree / one node; c5attn = 3 steps of a 2-layer Llama-3-8B-shape model, batch 8, "
-                         "prefix 16384, 256-node trees")
+                         "on 8 x 256-node trees (2048 rows); chunk / decode = 20 steps of the same model on one 256-node "
+                         "tree / one node; c5attn = 3 steps of a 2-layer Llama-3-8B-shape model, batch 8, prefix 16384, "
+                         "256-node trees")
     args = ap.parse_args()
     if args.gpus != 1:
         print("bench.py: this build runs on ONE GPU only (no collectives, no sharding); use --gpus 1", file=sys.stderr)
