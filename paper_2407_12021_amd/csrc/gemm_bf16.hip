@@ -28,6 +28,7 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
+#include <type_traits>
 
 #include "bf16_layout.h"
 #include "ded_kernels.h"
@@ -50,13 +51,12 @@ __device__ unsigned long long* g_trace = nullptr;  // [workgroup][wave][8] wall-
 #define DED_STAMP(i)
 #endif
 
-typedef f32x4_t Acc[TN][4];  // one wavefront's tile: 4 feature tiles x 4 row blocks
+typedef f32x4_t Acc[TN][4];  // 4 feature tiles x 4 row blocks
 
 // With a single 64-row group the weights of a skinny GEMM are read exactly once per launch (ONCE): loaded with the
 // non-temporal hint they stream through the caches without displacing anything, which measured ~12 % more read
 // bandwidth on a plain streaming kernel (6.8 against 6.0 TB/s).  With two or three row groups the later rounds of
-// the launch find the weights in the last-level cache, and the hint would cost that.  The volatile flavour is for
-// prefetches that must stay where they are written.
+// the launch find the weights in the last-level cache, and the hint would cost that.
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 template <bool ONCE>
 __device__ inline uint4 load_weights(const uint4* q) {
@@ -67,18 +67,11 @@ __device__ inline uint4 load_weights(const uint4* q) {
     return *q;
   }
 }
-template <bool ONCE>
-__device__ inline uint4 load_weights_pinned(const uint4* q) {
-  if constexpr (ONCE) {
-    const u32x4_t r = __builtin_nontemporal_load(reinterpret_cast<const volatile u32x4_t*>(q));
-    return make_uint4(r.x, r.y, r.z, r.w);
-  } else {
-    // (component-wise: a volatile load of the whole vector is compiled to an uncached system-scope access)
-    const volatile uint4* c = q;
-    uint4 r;
-    r.x = c->x, r.y = c->y, r.z = c->z, r.w = c->w;
-    return r;
-  }
+// Loads stay on their side of this: the compiler may not move them across a memory clobber (the pointers are not __restrict__)
+// nor the scheduler across its own barrier.  Otherwise it sinks a prefetch to where its value is used.
+__device__ __forceinline__ void pin_loads() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Split-K slices travel between workgroups of one launch, which may sit on different XCDs with separate
@@ -107,29 +100,31 @@ __device__ inline unsigned long long slice_load(unsigned long long* p) {
 __device__ inline unsigned long long pack2(float a, float b) {
   return ((unsigned long long)__float_as_uint(b) << 32) | __float_as_uint(a);
 }
-__device__ inline int64_t slice_tile_offset(int rb0, int NG, int ng) { return ((int64_t)(rb0 >> 2) * NG + ng) * (TN * 4 * 256); }
+__device__ inline int64_t slice_tile_offset(int NG, int ng) { return ((int64_t)blockIdx.z * NG + ng) * (TN * 4 * 256); }
 
-__device__ inline void store_slice(float* slice, int NG, int ng, int rb0, int lane, const Acc& acc) {
-  unsigned long long* q = reinterpret_cast<unsigned long long*>(slice + slice_tile_offset(rb0, NG, ng)) + lane;
+// Row blocks rb_lo .. rb_lo + RBN - 1 of the tile, which the wavefront holds in acc[t][0 .. RBN-1].
+template <int RBN, typename A>
+__device__ inline void store_slice(float* slice, int NG, int ng, int rb_lo, int lane, const A& acc) {
+  unsigned long long* q = reinterpret_cast<unsigned long long*>(slice + slice_tile_offset(NG, ng) + rb_lo * 256) + lane;
 #pragma unroll
   for (int t = 0; t < TN; ++t)
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) {
-      const f32x4_t v = acc[t][rb];
-      slice_store(q + (t * 4 + rb) * 128, pack2(v[0], v[1]));
-      slice_store(q + (t * 4 + rb) * 128 + 64, pack2(v[2], v[3]));
+    for (int j = 0; j < RBN; ++j) {
+      const f32x4_t v = acc[t][j];
+      slice_store(q + (t * 4 + j) * 128, pack2(v[0], v[1]));
+      slice_store(q + (t * 4 + j) * 128 + 64, pack2(v[2], v[3]));
     }
 }
 
 // acc[t][j] = sum over slices 0..splits-1 (in slice order) of row block rb_lo + j of the tile, j < RBN
-template <int RBN>
-__device__ inline void load_slices(const float* part, int64_t part_stride, int splits, int NG, int ng, int rb0,
-                                   int rb_lo, int lane, Acc& acc) {
+template <int RBN, typename A>
+__device__ inline void load_slices(const float* part, int64_t part_stride, int splits, int NG, int ng, int rb_lo, int lane,
+                                   A& acc) {
 #pragma unroll
   for (int t = 0; t < TN; ++t)
 #pragma unroll
     for (int j = 0; j < RBN; ++j) acc[t][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  const float* base = part + slice_tile_offset(rb0, NG, ng) + rb_lo * 256;
+  const float* base = part + slice_tile_offset(NG, ng) + rb_lo * 256;
 #pragma unroll 4
   for (int s = 0; s < splits; ++s) {
     unsigned long long* q =
@@ -146,28 +141,13 @@ __device__ inline void load_slices(const float* part, int64_t part_stride, int s
   }
 }
 
-// The same for a wavefront that holds only RBN row blocks of its tile (first one: rb_lo) in acc[t][0 .. RBN-1].
-template <int RBN>
-__device__ inline void store_slice_rows(float* slice, int NG, int ng, int rb0, int rb_lo, int lane, const Acc& acc) {
-  unsigned long long* q =
-      reinterpret_cast<unsigned long long*>(slice + slice_tile_offset(rb0, NG, ng) + rb_lo * 256) + lane;
-#pragma unroll
-  for (int t = 0; t < TN; ++t)
-#pragma unroll
-    for (int j = 0; j < RBN; ++j) {
-      const f32x4_t v = acc[t][j];
-      slice_store(q + (t * 4 + j) * 128, pack2(v[0], v[1]));
-      slice_store(q + (t * 4 + j) * 128 + 64, pack2(v[2], v[3]));
-    }
-}
-
 // acc[t][j] (in: this workgroup's own slice values, which it still holds) = sum over slices 0..S-1 in slice order,
 // the own values standing in for slice `split`: only the S - 1 other slices are fetched, all loads in flight
 // together.  The result does not depend on which workgroup arrived last.
-template <int RBN, int S>
-__device__ inline void sum_other_slices(const float* part, int64_t part_stride, int split, int NG, int ng, int rb0,
-                                        int rb_lo, int lane, Acc& acc) {
-  const float* base = part + slice_tile_offset(rb0, NG, ng) + rb_lo * 256;
+template <int RBN, int S, typename A>
+__device__ inline void sum_other_slices(const float* part, int64_t part_stride, int split, int NG, int ng, int rb_lo, int lane,
+                                        A& acc) {
+  const float* base = part + slice_tile_offset(NG, ng) + rb_lo * 256;
   unsigned long long a[S - 1][TN][RBN], b[S - 1][TN][RBN];
 #pragma unroll
   for (int k = 0; k < S - 1; ++k) {
@@ -206,17 +186,17 @@ __device__ inline void sum_other_slices(const float* part, int64_t part_stride, 
   }
 }
 
-template <int RBN>
-__device__ inline void sum_slices_keep_own(const float* part, int64_t part_stride, int split, int splits, int NG,
-                                           int ng, int rb0, int rb_lo, int lane, Acc& acc) {
+template <int RBN, typename A>
+__device__ inline void sum_slices_keep_own(const float* part, int64_t part_stride, int split, int splits, int NG, int ng,
+                                           int rb_lo, int lane, A& acc) {
   if (splits == 2) {
-    sum_other_slices<RBN, 2>(part, part_stride, split, NG, ng, rb0, rb_lo, lane, acc);
+    sum_other_slices<RBN, 2>(part, part_stride, split, NG, ng, rb_lo, lane, acc);
   } else if (splits == 4) {
-    sum_other_slices<RBN, 4>(part, part_stride, split, NG, ng, rb0, rb_lo, lane, acc);
+    sum_other_slices<RBN, 4>(part, part_stride, split, NG, ng, rb_lo, lane, acc);
   } else if (splits == 3) {
-    sum_other_slices<RBN, 3>(part, part_stride, split, NG, ng, rb0, rb_lo, lane, acc);
+    sum_other_slices<RBN, 3>(part, part_stride, split, NG, ng, rb_lo, lane, acc);
   } else {
-    load_slices<RBN>(part, part_stride, splits, NG, ng, rb0, rb_lo, lane, acc);  // all slices, the own one included
+    load_slices<RBN>(part, part_stride, splits, NG, ng, rb_lo, lane, acc);  // all slices, the own one included
   }
 }
 
@@ -481,94 +461,130 @@ __device__ inline bool take_ticket(int splits, int* counters, int* s_flag) {
   return *s_flag != 0;
 }
 
-// Hand-over of whole tiles: the wavefronts that hold a complete workgroup tile (`owner`) write it as this
-// workgroup's slice; the last-arriving workgroup then re-reads all slices in slice order (load_slices, any of its
-// wavefronts) and runs the epilogue.
-__device__ inline bool finish_split(float* part, int64_t part_stride, int split, int splits, int* counters, int NG,
-                                    int ng, int rb0, int lane, bool owner, const Acc& acc, int* s_flag) {
-  if (owner) store_slice(part + (int64_t)split * part_stride, NG, ng, rb0, lane, acc);
-  return take_ticket(splits, counters, s_flag);
-}
+// The row blocks of a launch are dealt to its groups (blockIdx.z) as evenly as they go: at most four each, sizes that differ by
+// one at most, and a kernel instance for the larger groups of 4 or of 3 (smaller ones take the branch with one block less).
+// Groups that always ran as four fetched and multiplied blocks nobody reads, out of what bounds these kernels, ~50 GB/s into
+// each CU.  In steps, us, always four / as dealt: 48 rows (7B shape) gate/up 43.0 / 38.4, QKV 32.0 / 30.0, O and down
+// together 38.5 / 36.8; 97 rows 65.9 / 62.8, 42.1 / 40.0, 54.2 / 52.9; 144 rows of the 8B shape, QKV 35.2 / 31.4, O and down 92.7 /
+// 88.6.  (With every load held in its place, see pin_loads: half of the gain of the 97 rows, 64 rows 43.1 -> 41.9 in gate/up.)
+__device__ inline int group_first(int rbs) { return blockIdx.z * rbs / gridDim.z; }
+__device__ inline int group_size(int rbs) { return (blockIdx.z + 1) * rbs / gridDim.z - group_first(rbs); }
 
 // ------------------------------------------------------------------------------------------
 // Stream kernel: one feature group per workgroup, NW wavefronts split the k range.
 // ------------------------------------------------------------------------------------------
-template <int NW, int PLANES, int EPI, bool ONCE>
-__global__ __launch_bounds__(NW * 64, 2) void gemm_stream_kernel(float* __restrict__ part, int64_t part_stride,
-                                                                 const uint4* __restrict__ xp,
-                                                                 const uint4* __restrict__ wp, int RB, int N, int KT,
-                                                                 int splits, int* __restrict__ counters,
-                                                                 GemmEpilogue epi) {
-  __shared__ float4 red[(NW > 1 ? NW / 2 : 1) * TN * 4 * 64];
-  __shared__ float s_ssq[NW * 64];
-  __shared__ int s_flag;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <int NW, int RBG>
+struct StreamShared {
+  float4 red[(NW > 1 ? NW / 2 : 1) * TN * RBG * 64];
+  float ssq[NW * 64];
+  int flag;
+};
+template <int NW, int PLANES, int EPI, bool ONCE, int RBG, typename SH>
+__device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, int64_t part_stride, const uint4* xp,
+                                             const uint4* wp, int RB, int rb0, int N, int KT, int splits,
+                                             int* __restrict__ counters, const GemmEpilogue& epi) {
+  float4* const red = sh.red;
+  float* const s_ssq = sh.ssq;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ng = blockIdx.x;
   const int split = blockIdx.y;
-  const int rb0 = blockIdx.z * 4;
   // this wavefront's k range, in units of RING steps (the finest grain the loop allows: K = 11008 over 16
   // wavefronts is 21 or 22 steps each, where whole groups of PD steps would give 20 or 24)
   const int units = KT / RING;
   const int parts = splits * NW;
   const int gi = split * NW + wave;
-  const int g_begin = (int)((int64_t)gi * units / parts);
-  const int g_end = (int)((int64_t)(gi + 1) * units / parts);
+  const int k0 = gi * units / parts * RING, k1 = (gi + 1) * units / parts * RING;  // (32 bits: a 64-bit division takes 0.2 us)
 
-  Acc acc;
+  f32x4_t acc[TN][RBG];
 #pragma unroll
   for (int t = 0; t < TN; ++t)
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) acc[t][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < RBG; ++rb) acc[t][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   DED_STAMP(0)
   SsqPart ssq;
   ssq_clear(ssq);
-  if (g_begin < g_end) {
-    const uint4* wsrc = wp + (((int64_t)ng * KT * TN) << 6) + lane;
-    // per k step the activations of the 4 row blocks x 2 planes (hi, lo) are 8 KiB of contiguous memory
-    const uint4* xsrc = xp + ((int64_t)rb0 << 7) + lane;
-    const int64_t xstep = (int64_t)RB << 7;
-
-    uint4 wr[RING][TN], xr[RING][4 * PLANES];
-    auto issue = [&](int slot, int kt) {
+  // The ring: D steps' fragments in fixed registers, a step's refilled as soon as it is used up (the loads held there).  Straight
+  // code from the first load to the last: a load under a condition makes the compiler's waits assume that it did not happen.
+  constexpr int D = PLANES == 1 && ONCE ? 4 : 2;
+  static_assert(D == RING || D == 2 * RING, "a range is whole units of RING steps");
+  const int n = k1 - k0;
+  const char* wsrc = reinterpret_cast<const char*>(wp) + (((int64_t)ng * KT + k0) * TN << 10);  // (uniform; the lane's offset apart)
+  // per k step the activations of the group's row blocks x 2 planes (hi, lo) are one run of memory
+  const char* xsrc = reinterpret_cast<const char*>(xp) + (int64_t)k0 * ((int64_t)RB << 11) + ((int64_t)rb0 << 11);
+  const int64_t xstep = (int64_t)RB << 11;
+  const uint32_t lane16 = lane << 4;
+  uint4 wr[D][TN], xr[D][RBG * PLANES];
+  auto issue = [&](int slot) {
+    pin_loads();
 #pragma unroll
-      for (int t = 0; t < TN; ++t) wr[slot][t] = load_weights<ONCE>(wsrc + (((int64_t)kt * TN + t) << 6));
+    for (int t = 0; t < TN; ++t) wr[slot][t] = load_weights<ONCE>(reinterpret_cast<const uint4*>(wsrc + (t << 10) + lane16));
 #pragma unroll
-      for (int rb = 0; rb < 4; ++rb)
+    for (int rb = 0; rb < RBG; ++rb)
 #pragma unroll
-        for (int p = 0; p < PLANES; ++p) xr[slot][rb * PLANES + p] = xsrc[kt * xstep + ((rb * 2 + p) << 6)];
-    };
-    auto compute = [&](int slot) {
+      for (int p = 0; p < PLANES; ++p) xr[slot][rb * PLANES + p] = *reinterpret_cast<const uint4*>(xsrc + ((rb * 2 + p) << 10) + lane16);
+    wsrc += TN << 10;
+    xsrc += xstep;
+    pin_loads();
+  };
+  auto compute = [&](int slot) {
 #pragma unroll
-      for (int p = 0; p < PLANES; ++p)  // 16 independent accumulators between dependent products
+    for (int p = 0; p < PLANES; ++p)  // 4 RBG independent accumulators between dependent products
 #pragma unroll
-        for (int t = 0; t < TN; ++t) {
-          f16x8_t a = __builtin_bit_cast(f16x8_t, wr[slot][t]);
+      for (int t = 0; t < TN; ++t) {
+        f16x8_t a = __builtin_bit_cast(f16x8_t, wr[slot][t]);
 #pragma unroll
-          for (int rb = 0; rb < 4; ++rb)
-            acc[t][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                a, __builtin_bit_cast(f16x8_t, xr[slot][rb * PLANES + p]), acc[t][rb], 0, 0, 0);
-        }
-    };
-
-    int kt = g_begin * RING;
-    const int kt_last = g_end * RING - RING;  // first step of the last ring-full
-#pragma unroll
-    for (int j = 0; j < RING; ++j) issue(j, kt + j);
-    const int kt_ssq = kt_last - 8 * RING > kt ? kt_last - 8 * RING : kt;  // 8 ring turns before the end
-    if (kt >= kt_last) ssq_issue(epi, rb0, lane, wave, NW, ssq);
-    for (; kt < kt_last; kt += RING) {
-#pragma unroll
-      for (int j = 0; j < RING; ++j) {
-        compute(j);
-        issue(j, kt + RING + j);
+        for (int rb = 0; rb < RBG; ++rb)
+          acc[t][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+              a, __builtin_bit_cast(f16x8_t, xr[slot][rb * PLANES + p]), acc[t][rb], 0, 0, 0);
       }
-      if (kt == kt_ssq) ssq_issue(epi, rb0, lane, wave, NW, ssq);
-    }
+  };
+  constexpr bool SSQ = EPI != EPI_RESIDUAL;
+  if (n >= D) {
+    int left = n - D;  // steps not requested yet
+    if (left % D) {    // what is beyond whole turns goes first; either way the places are in order after it
+      constexpr int R = D - RING;
 #pragma unroll
-    for (int j = 0; j < RING; ++j) compute(j);
+      for (int j = 0; j < D; ++j) issue((j + R) % D);
+#pragma unroll
+      for (int j = R; j < D; ++j) {
+        compute(j);
+        issue(j);
+      }
+      left -= RING;
+    } else {
+#pragma unroll
+      for (int j = 0; j < D; ++j) issue(j);
+    }
+    auto turns_to = [&](int rest) {
+      for (; left > rest; left -= D) {
+        if (!ONCE) {
+#pragma unroll
+          for (int j = 0; j < D; ++j) compute(j);
+#pragma unroll
+          for (int j = 0; j < D; ++j) issue(j);
+        } else {
+#pragma unroll
+          for (int j = 0; j < D; ++j) {
+            compute(j);
+            issue(j);
+          }
+        }
+      }
+    };
+    if constexpr (SSQ) {
+      turns_to(12);
+      ssq_issue(epi, rb0, lane, wave, NW, ssq);  // the row sums, a dozen steps before the end
+    }
+    turns_to(0);
+#pragma unroll
+    for (int j = 0; j < D; ++j) compute(j);
   } else {
-    ssq_issue(epi, rb0, lane, wave, NW, ssq);
+    if constexpr (SSQ) ssq_issue(epi, rb0, lane, wave, NW, ssq);
+    for (int i = 0; i < n; ++i) {
+      issue(0);
+      compute(0);
+    }
   }
   ssq_publish(epi, rb0, lane, wave, NW, ssq, s_ssq);
   if (NW == 1) __syncthreads();
@@ -579,23 +595,23 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_kernel(float* __restri
 #pragma unroll
     for (int stride = NW / 2; stride >= 1; stride >>= 1) {
       if (wave >= stride && wave < 2 * stride) {
-        float4* dst = red + (int64_t)(wave - stride) * TN * 4 * 64 + lane;
+        float4* dst = red + (int64_t)(wave - stride) * TN * RBG * 64 + lane;
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-          for (int rb = 0; rb < 4; ++rb) {
+          for (int rb = 0; rb < RBG; ++rb) {
             f32x4_t v = acc[t][rb];
-            dst[(t * 4 + rb) * 64] = make_float4(v[0], v[1], v[2], v[3]);
+            dst[(t * RBG + rb) * 64] = make_float4(v[0], v[1], v[2], v[3]);
           }
       }
       __syncthreads();
       if (wave < stride) {
-        const float4* src = red + (int64_t)wave * TN * 4 * 64 + lane;
+        const float4* src = red + (int64_t)wave * TN * RBG * 64 + lane;
 #pragma unroll
         for (int t = 0; t < TN; ++t)
 #pragma unroll
-          for (int rb = 0; rb < 4; ++rb) {
-            float4 v = src[(t * 4 + rb) * 64];
+          for (int rb = 0; rb < RBG; ++rb) {
+            float4 v = src[(t * RBG + rb) * 64];
             acc[t][rb] += f32x4_t{v.x, v.y, v.z, v.w};
           }
       }
@@ -605,14 +621,38 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_kernel(float* __restri
   DED_STAMP(3)
   const float row_scale = ssq_scale(epi, lane, NW, s_ssq);  // the reduction above had at least one barrier
   if (splits == 1) {
-    if (wave == 0) run_epilogue<EPI, 4>(epi, ng, N, rb0, rb0, row_scale, lane, acc);
-  } else if (finish_split(part, part_stride, split, splits, counters, gridDim.x, ng, rb0, lane, wave == 0, acc, &s_flag)) {
-    constexpr int RBN = 4 / NW;  // the wavefronts of the last workgroup share the tile's row blocks
-    load_slices<RBN>(part, part_stride, splits, gridDim.x, ng, rb0, wave * RBN, lane, acc);
-    DED_STAMP(6)
-    run_epilogue<EPI, RBN>(epi, ng, N, rb0, rb0 + wave * RBN, row_scale, lane, acc);
+    if (wave == 0) run_epilogue<EPI, RBG>(epi, ng, N, rb0, rb0, row_scale, lane, acc);
+  } else {
+    if (wave == 0) store_slice<RBG>(part + (int64_t)split * part_stride, gridDim.x, ng, 0, lane, acc);
+    // the wavefronts of the last workgroup share the tile's row blocks
+    constexpr int RBN = (RBG + NW - 1) / NW;
+    const int rb_lo = wave * RBN;
+    if (take_ticket(splits, counters, &sh.flag) && rb_lo < RBG) {
+      if (RBG % RBN == 0 || rb_lo + RBN <= RBG) {
+        load_slices<RBN>(part, part_stride, splits, gridDim.x, ng, rb_lo, lane, acc);
+        DED_STAMP(6)
+        run_epilogue<EPI, RBN>(epi, ng, N, rb0, rb0 + rb_lo, row_scale, lane, acc);
+      } else if constexpr (RBG % RBN) {
+        load_slices<RBG % RBN>(part, part_stride, splits, gridDim.x, ng, rb_lo, lane, acc);
+        run_epilogue<EPI, RBG % RBN>(epi, ng, N, rb0, rb0 + rb_lo, row_scale, lane, acc);
+      }
+    }
   }
   DED_STAMP(7)
+}
+// RBG: row blocks of the larger groups; others have one less
+template <int NW, int PLANES, int EPI, bool ONCE, int RBG>
+__global__ __launch_bounds__(NW * 64, 2) void gemm_stream_kernel(float* __restrict__ part, int64_t part_stride,
+                                                                 const uint4* xp,
+                                                                 const uint4* wp, int RB, int rbs, int N, int KT,
+                                                                 int splits, int* __restrict__ counters,
+                                                                 GemmEpilogue epi) {
+  __shared__ StreamShared<NW, RBG> sh;
+  const int rb0 = group_first(rbs);
+  if (ONCE || group_size(rbs) == RBG)
+    stream_group<NW, PLANES, EPI, ONCE, RBG>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
+  else
+    stream_group<NW, PLANES, EPI, ONCE, RBG - 1>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -623,41 +663,47 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_kernel(float* __restri
 // 1/NWN of what they would if every wavefront fetched its own.  Two wavefronts per SIMD overlap each
 // other's LDS waits and barriers; the halves are added through LDS at the end (fixed order).
 // ------------------------------------------------------------------------------------------
-template <int NWN, int PLANES, int EPI, bool ONCE>
-__global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restrict__ part, int64_t part_stride,
-                                                                 const uint4* __restrict__ xp,
-                                                                 const uint4* __restrict__ wp, int RB, int N, int KT,
-                                                                 int splits, int* __restrict__ counters,
-                                                                 GemmEpilogue epi) {
-  constexpr int TH = NWN * 64;                    // threads per half
-  constexpr int CH = (NWN == 4 || PLANES == 1) ? 2 : 1;  // k steps per activation chunk (<= 4 staged units / thread)
-  constexpr int STEP_U4 = 4 * PLANES * 64;        // uint4 units of activations per k step
-  constexpr int CHUNK_U4 = CH * STEP_U4;
+template <int NWN, int PLANES, int RBG>
+struct WideShape {
+  static constexpr int CH = (NWN == 4 || PLANES == 1) ? 2 : 1;  // k steps per activation chunk (<= 4 staged units / thread)
+  static constexpr int STEP_U4 = RBG * PLANES * 64;             // uint4 units of activations per k step
+  static constexpr int CHUNK_U4 = CH * STEP_U4;
+  static constexpr int RED_U4 = 2 * NWN * TN * ((RBG + 1) / 2) * 64;  // what the halves exchange
+  static constexpr int LDS_U4 = 2 * 2 * CHUNK_U4 > RED_U4 ? 2 * 2 * CHUNK_U4 : RED_U4;
+};
+template <int NWN, int PLANES, int RBG>
+struct WideShared {
+  uint4 lds[WideShape<NWN, PLANES, RBG>::LDS_U4];  // [half][buffer][chunk]; reused for the final reduction
+  float ssq[2 * NWN * 64];
+  int flag;
+};
+template <int NWN, int PLANES, int EPI, bool ONCE, int RBG, typename SH>
+__device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int64_t part_stride, const uint4* xp, const uint4* wp,
+                                           int RB, int rb0, int N, int KT, int splits,
+                                           int* __restrict__ counters, const GemmEpilogue& epi) {
+  using W = WideShape<NWN, PLANES, RBG>;
+  constexpr int TH = NWN * 64;  // threads per half
+  constexpr int CH = W::CH, STEP_U4 = W::STEP_U4, CHUNK_U4 = W::CHUNK_U4;
   constexpr int PER_THREAD = (CHUNK_U4 + TH - 1) / TH;
-  constexpr int ACC_U4 = TN * 4 * 64;             // float4 units of one wavefront's accumulators
-  constexpr int LDS_U4 = (2 * 2 * CHUNK_U4 > NWN * ACC_U4) ? 2 * 2 * CHUNK_U4 : NWN * ACC_U4;
-  __shared__ uint4 lds[LDS_U4];                   // [half][buffer][chunk]; reused for the final reduction
-  __shared__ float s_ssq[2 * NWN * 64];
-  __shared__ int s_flag;
-  const int half = threadIdx.x / TH;
+  uint4* const lds = sh.lds;
+  float* const s_ssq = sh.ssq;
+  const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / TH);
   const int tid = threadIdx.x - half * TH, lane = tid & 63, wn = tid >> 6;
   uint4* xs = lds + half * 2 * CHUNK_U4;
   const int NG = (N + 16 * TN - 1) / (16 * TN);
   const int ng_raw = blockIdx.x * NWN + wn;
   const int ng = ng_raw < NG ? ng_raw : NG - 1;  // surplus wavefront of the last tile: valid reads, no store
   const int split = blockIdx.y;
-  const int rb0 = blockIdx.z * 4;
   const int groups = KT / PD;
-  const int g_begin = (int)((int64_t)split * groups / splits);
-  const int g_end = (int)((int64_t)(split + 1) * groups / splits);
+  const int g_begin = split * groups / splits, g_end = (split + 1) * groups / splits;
   const int n_chunks = (g_end - g_begin) * (PD / CH) / 2;  // per half; the range holds an even number of chunks
   const int kt0 = g_begin * PD + half * n_chunks * CH;
 
-  Acc acc;
+  f32x4_t acc[TN][RBG];
 #pragma unroll
   for (int t = 0; t < TN; ++t)
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb) acc[t][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int rb = 0; rb < RBG; ++rb) acc[t][rb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   const uint4* wsrc = wp + (((int64_t)ng * KT * TN) << 6) + lane;
   const uint4* xsrc = xp + ((int64_t)rb0 << 7);
@@ -701,9 +747,9 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
   auto compute = [&](const WChunk& w, int buf) {
 #pragma unroll
     for (int s = 0; s < CH; ++s) {
-      f16x8_t b[4 * PLANES];
+      f16x8_t b[RBG * PLANES];
 #pragma unroll
-      for (int i = 0; i < 4 * PLANES; ++i)
+      for (int i = 0; i < RBG * PLANES; ++i)
         b[i] = __builtin_bit_cast(f16x8_t, xs[buf * CHUNK_U4 + s * STEP_U4 + (i << 6) + lane]);
 #pragma unroll
       for (int p = 0; p < PLANES; ++p)
@@ -711,7 +757,7 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
         for (int t = 0; t < TN; ++t) {
           f16x8_t a = __builtin_bit_cast(f16x8_t, w.f[s][t]);
 #pragma unroll
-          for (int rb = 0; rb < 4; ++rb)
+          for (int rb = 0; rb < RBG; ++rb)
             acc[t][rb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b[rb * PLANES + p], acc[t][rb], 0, 0, 0);
         }
     }
@@ -734,20 +780,16 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
   if constexpr (DEEP) {
     // Weights three chunks ahead, activations two.  The ring slots are fixed registers (the loop is unrolled by the
     // ring length and leaves from the middle): a copy between slots would have to wait for the load that still
-    // writes its source.  The loads go through volatile accesses: the compiler otherwise sinks a prefetch to the
-    // block of its first use, i.e. issues it one iteration before it is needed whatever the source says.  Fetches
-    // past the range re-read its last chunk (in bounds, never used).
+    // writes its source.  The loads are pinned, activations in front of weights, and the LDS stores behind the products: the
+    // compiler otherwise sinks a prefetch to the block of its first use, or waits for activations of one iteration back before
+    // the products (48 rows, gate/up of a 7B shape: 49.0 us so, 38.4 pinned).  Fetches past the range re-read its last chunk
+    // (in bounds, never used).
     const int c_max = n_chunks - 1;
     auto cl = [&](int c) { return c < c_max ? c : c_max; };
-    auto ldv = [](const volatile uint4* q) {
-      uint4 r;
-      r.x = q->x, r.y = q->y, r.z = q->z, r.w = q->w;
-      return r;
-    };
     auto load_w_pinned = [&](int c) {
       WChunk w;
 #pragma unroll
-      for (int t = 0; t < TN; ++t) w.f[0][t] = load_weights_pinned<ONCE>(wsrc + (((int64_t)(kt0 + c) * TN + t) << 6));
+      for (int t = 0; t < TN; ++t) w.f[0][t] = load_weights<ONCE>(wsrc + (((int64_t)(kt0 + c) * TN + t) << 6));
       return w;
     };
     auto load_x_pinned = [&](int c) {
@@ -756,7 +798,7 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
       for (int i = 0; i < PER_THREAD; ++i) {
         int u = tid + i * TH;
         if (CHUNK_U4 % TH != 0 && u >= CHUNK_U4) u = CHUNK_U4 - 1;  // surplus threads fetch the last unit again
-        x.u[i] = ldv(xsrc + (int64_t)(kt0 + c) * xstep + u);        // CH == 1, two planes: unit u of the step
+        x.u[i] = xsrc[(int64_t)(kt0 + c) * xstep + u];              // CH == 1, two planes: unit u of the step
       }
       return x;
     };
@@ -774,26 +816,38 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
     for (int c = 0;;) {
       if (c == c_ssq4) ssq_issue(epi, rb0, lane, wv, 2 * NWN, ssq);
       xa = load_x_pinned(cl(c + 2));
+      pin_loads();
       w3 = load_w_pinned(cl(c + 3));
+      pin_loads();
       compute(w0, 0);
+      __builtin_amdgcn_sched_barrier(0);
       store_x(1, xb);
       __syncthreads();
       if (++c >= n_chunks) break;
       xb = load_x_pinned(cl(c + 2));
+      pin_loads();
       w0 = load_w_pinned(cl(c + 3));
+      pin_loads();
       compute(w1, 1);
+      __builtin_amdgcn_sched_barrier(0);
       store_x(0, xa);
       __syncthreads();
       if (++c >= n_chunks) break;
       xa = load_x_pinned(cl(c + 2));
+      pin_loads();
       w1 = load_w_pinned(cl(c + 3));
+      pin_loads();
       compute(w2, 0);
+      __builtin_amdgcn_sched_barrier(0);
       store_x(1, xb);
       __syncthreads();
       if (++c >= n_chunks) break;
       xb = load_x_pinned(cl(c + 2));
+      pin_loads();
       w2 = load_w_pinned(cl(c + 3));
+      pin_loads();
       compute(w3, 1);
+      __builtin_amdgcn_sched_barrier(0);
       store_x(0, xa);
       __syncthreads();
       if (++c >= n_chunks) break;
@@ -826,46 +880,72 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
   }
   DED_STAMP(2)
   ssq_publish(epi, rb0, lane, threadIdx.x >> 6, 2 * NWN, ssq, s_ssq);
-  // the halves are added through LDS: half h ends up with row blocks 2h, 2h + 1 of its feature group, in
-  // acc[t][0..1]; each half hands the other the two row blocks it does not finish
+  // the halves are added through LDS: half 0 ends up with the first H0 row blocks of its feature group, half 1 with the others,
+  // in acc[t][0..]; each half hands the other what it does not finish
+  constexpr int H0 = (RBG + 1) / 2, H1 = RBG - H0;
   __syncthreads();
   {
-    constexpr int HALF_U4 = TN * 2 * 64;  // two row blocks of one wavefront's accumulators
+    constexpr int HALF_U4 = TN * H0 * 64;
     float4* out = reinterpret_cast<float4*>(lds) + (half * NWN + wn) * HALF_U4 + lane;
 #pragma unroll
     for (int t = 0; t < TN; ++t)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const f32x4_t v = half == 0 ? acc[t][2 + j] : acc[t][j];
-        out[(t * 2 + j) * 64] = make_float4(v[0], v[1], v[2], v[3]);
+      for (int j = 0; j < H0; ++j) {
+        const f32x4_t v = half == 0 ? acc[t][H0 + j < RBG ? H0 + j : RBG - 1] : acc[t][j];
+        if (j < H1 || half == 1) out[(t * H0 + j) * 64] = make_float4(v[0], v[1], v[2], v[3]);
       }
     __syncthreads();
     const float4* in = reinterpret_cast<const float4*>(lds) + ((1 - half) * NWN + wn) * HALF_U4 + lane;
 #pragma unroll
     for (int t = 0; t < TN; ++t)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const float4 v = in[(t * 2 + j) * 64];
-        const f32x4_t mine = half == 0 ? acc[t][j] : acc[t][2 + j];
-        acc[t][j] = mine + f32x4_t{v.x, v.y, v.z, v.w};
+      for (int j = 0; j < H0; ++j) {
+        if (j < H1 || half == 0) {
+          const float4 v = in[(t * H0 + j) * 64];
+          const f32x4_t mine = half == 0 ? acc[t][j] : acc[t][H0 + j < RBG ? H0 + j : RBG - 1];
+          acc[t][j] = mine + f32x4_t{v.x, v.y, v.z, v.w};
+        }
       }
   }
   DED_STAMP(3)
   const float row_scale = ssq_scale(epi, lane, 2 * NWN, s_ssq);
   const bool store_ok = ng_raw < NG;
-  if (splits == 1) {
-    if (store_ok) run_epilogue<EPI, 2>(epi, ng, N, rb0, rb0 + half * 2, row_scale, lane, acc);
-  } else {
-    // every wavefront writes the two row blocks it holds; in the last workgroup it fetches the same two row
-    // blocks of the other slices and finishes them
-    if (store_ok) store_slice_rows<2>(part + (int64_t)split * part_stride, NG, ng, rb0, half * 2, lane, acc);
-    if (take_ticket(splits, counters, &s_flag) && store_ok) {
-      sum_slices_keep_own<2>(part, part_stride, split, splits, NG, ng, rb0, half * 2, lane, acc);
-      DED_STAMP(6)
-      run_epilogue<EPI, 2>(epi, ng, N, rb0, rb0 + half * 2, row_scale, lane, acc);
+  // every wavefront finishes the row blocks it holds, or writes them as this workgroup's slice; in the last workgroup it then
+  // fetches the same row blocks of the other slices and finishes those
+  float* slice = part + (int64_t)split * part_stride;
+  if (splits > 1) {
+    if (store_ok) {
+      if (H0 == H1) store_slice<H0>(slice, NG, ng, half * H0, lane, acc);
+      else if (half == 0) store_slice<H0>(slice, NG, ng, 0, lane, acc);
+      else store_slice<H1>(slice, NG, ng, H0, lane, acc);
     }
+    if (!take_ticket(splits, counters, &sh.flag)) return;
   }
+  if (!store_ok) return;
+  auto finish = [&](auto held, int rb_lo) {
+    constexpr int RBN = decltype(held)::value;
+    if (splits > 1) sum_slices_keep_own<RBN>(part, part_stride, split, splits, NG, ng, rb_lo, lane, acc);
+    DED_STAMP(6)
+    run_epilogue<EPI, RBN>(epi, ng, N, rb0, rb0 + rb_lo, row_scale, lane, acc);
+  };
+  if (H0 == H1) finish(std::integral_constant<int, H0>(), half * H0);
+  else if (half == 0) finish(std::integral_constant<int, H0>(), 0);
+  else finish(std::integral_constant<int, H1>(), H0);
   DED_STAMP(7)
+}
+// RBG: row blocks of the larger groups; others have one less
+template <int NWN, int PLANES, int EPI, bool ONCE, int RBG>
+__global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restrict__ part, int64_t part_stride,
+                                                                 const uint4* xp,
+                                                                 const uint4* wp, int RB, int rbs, int N, int KT,
+                                                                 int splits, int* __restrict__ counters,
+                                                                 GemmEpilogue epi) {
+  __shared__ WideShared<NWN, PLANES, RBG> sh;
+  const int rb0 = group_first(rbs);
+  if (ONCE || group_size(rbs) == RBG)
+    wide_group<NWN, PLANES, EPI, ONCE, RBG>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
+  else
+    wide_group<NWN, PLANES, EPI, ONCE, RBG - 1>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1574,7 +1654,7 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
                   const uint4* xp, const uint4* wp, int RB, int N, int KT, int* counters, const GemmEpilogue& epi,
                   int nw, hipStream_t s) {
   const int splits = plan.splits;
-#define DED_ARGS part, part_stride, xp, wp, RB, N, KT, splits, counters, epi
+#define DED_ARGS part, part_stride, xp, wp, RB, rbs, N, KT, splits, counters, epi
   if (plan.tile) {
     const TileDims t = tile_dims(plan.tile);
     const int row_tiles = (RB + t.row_blocks - 1) / t.row_blocks;
@@ -1600,10 +1680,14 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
   if constexpr (PLANES == 1 && (EPI == EPI_LOGITS || EPI == EPI_TOP2)) {
     return false;
   } else {
-  const bool once = RB == 4;  // one 64-row group: every weight byte is read once
-#define DED_SKINNY(KERNEL, A, GRID, THREADS)                                                          \
-  if (once) hipLaunchKernelGGL((KERNEL<A, PLANES, EPI, true>), GRID, dim3(THREADS), 0, s, DED_ARGS);   \
-  else hipLaunchKernelGGL((KERNEL<A, PLANES, EPI, false>), GRID, dim3(THREADS), 0, s, DED_ARGS);
+  const int rbs = (epi.rows + 15) / 16, groups = RB / 4;
+  const bool once = groups == 1;  // every weight byte is read once
+#define DED_SKINNY_ROWS(KERNEL, A, RBG, GRID, THREADS)                                                     \
+  if (once) hipLaunchKernelGGL((KERNEL<A, PLANES, EPI, true, RBG>), GRID, dim3(THREADS), 0, s, DED_ARGS);   \
+  else hipLaunchKernelGGL((KERNEL<A, PLANES, EPI, false, RBG>), GRID, dim3(THREADS), 0, s, DED_ARGS);
+#define DED_SKINNY(KERNEL, A, GRID, THREADS)                      \
+  if (rbs > 3 * groups) { DED_SKINNY_ROWS(KERNEL, A, 4, GRID, THREADS) } \
+  else { DED_SKINNY_ROWS(KERNEL, A, 3, GRID, THREADS) }
   if (plan.nwn == 0) {
     if (nw == 4) { DED_SKINNY(gemm_stream_kernel, 4, grid_stream, 256) }
     else if (nw == 2) { DED_SKINNY(gemm_stream_kernel, 2, grid_stream, 128) }
@@ -1615,6 +1699,7 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
   else if (plan.nwn == 2) { DED_SKINNY(gemm_wide_kernel, 2, grid_wide, 256) }
   else return false;
 #undef DED_SKINNY
+#undef DED_SKINNY_ROWS
 #undef DED_ARGS
   return true;
   }

@@ -211,6 +211,23 @@ def test_projections_of_few_rows(case):
     assert err <= 2e-2
 
 
+# (d, H, Hkv, F, V), tree size: 3 - 11 row blocks in one to three groups of 2, 3 and 4; k ranges of no, one and two steps, of
+# whole turns of the ring and half a turn more, in one slice and several
+GROUP_EDGES = [((128, 1, 1, 128, 80), 33)] + [((640, 5, 5, 896, 1040), n) for n in (48, 49, 65, 81, 97, 129, 145, 161)] + [
+    ((4096, 32, 8, 11008, 4112), 40), ((4096, 32, 32, 11008, 4112), 145)]
+
+
+@pytest.mark.parametrize("case", range(len(GROUP_EDGES)))
+def test_projections_of_uneven_row_groups(case):
+    """Bound: the 16-bit path's 2e-2 logit tolerance, as above."""
+    (d, H, Hkv, F, V), n = GROUP_EDGES[case]
+    cfg = di.ModelConfig(f"group-edge{case}", 1, d, H, Hkv, 128, F, V, dtype="bf16")
+    w = di.make_weights(cfg, seed=120 + case, gain_jitter=0.1, threads=16)
+    err = _step_error(cfg, w, [7], [n], seed=140 + case)
+    print(f"max |logit error| {err:.2e}")
+    assert err <= 2e-2
+
+
 def test_a_row_has_the_same_bits_in_a_small_tree_and_a_larger_one():
     """The projections of one and two row blocks add the k ranges of the larger steps in their order: the root's logits of a
     chain of 1, 17 and 40 nodes are equal bit for bit (one key tile each, so attention sums the same keys too)."""
