@@ -67,6 +67,13 @@ __device__ inline uint4 load_weights(const uint4* q) {
     return *q;
   }
 }
+// A load that the compiler may move as it likes (nothing in the launch writes what it reads).
+template <bool ONCE>
+__device__ inline uint4 load_free(const uint4* q) {
+  typedef const __attribute__((address_space(4))) u32x4_t invariant_t;
+  const u32x4_t r = ONCE ? __builtin_nontemporal_load((invariant_t*)q) : *(invariant_t*)q;
+  return make_uint4(r.x, r.y, r.z, r.w);
+}
 // Loads stay on their side of this: the compiler may not move them across a memory clobber (the pointers are not __restrict__)
 // nor the scheduler across its own barrier.  Otherwise it sinks a prefetch to where its value is used.
 __device__ __forceinline__ void pin_loads() {
@@ -648,7 +655,7 @@ __global__ __launch_bounds__(NW * 64, 2) void gemm_stream_kernel(float* __restri
                                                                  int splits, int* __restrict__ counters,
                                                                  GemmEpilogue epi) {
   __shared__ StreamShared<NW, RBG> sh;
-  const int rb0 = group_first(rbs);
+  const int rb0 = ONCE ? 0 : group_first(rbs);
   if (ONCE || group_size(rbs) == RBG)
     stream_group<NW, PLANES, EPI, ONCE, RBG>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
   else
@@ -687,7 +694,7 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
   constexpr int PER_THREAD = (CHUNK_U4 + TH - 1) / TH;
   uint4* const lds = sh.lds;
   float* const s_ssq = sh.ssq;
-  const int half = __builtin_amdgcn_readfirstlane(threadIdx.x / TH);
+  const int half = threadIdx.x / TH;
   const int tid = threadIdx.x - half * TH, lane = tid & 63, wn = tid >> 6;
   uint4* xs = lds + half * 2 * CHUNK_U4;
   const int NG = (N + 16 * TN - 1) / (16 * TN);
@@ -720,7 +727,7 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
 #pragma unroll
     for (int s = 0; s < CH; ++s)
 #pragma unroll
-      for (int t = 0; t < TN; ++t) w.f[s][t] = load_weights<ONCE>(wsrc + (((int64_t)(kt0 + c * CH + s) * TN + t) << 6));
+      for (int t = 0; t < TN; ++t) w.f[s][t] = load_free<ONCE>(wsrc + (((int64_t)(kt0 + c * CH + s) * TN + t) << 6));
     return w;
   };
   // unit u of a chunk: step s = u / STEP_U4, inside the step (rb, plane, lane) in memory order
@@ -732,7 +739,7 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
       if (CHUNK_U4 % TH == 0 || u < CHUNK_U4) {
         int s = u / STEP_U4, v = u - s * STEP_U4;
         int src = PLANES == 2 ? v : ((v >> 6) * 128 + (v & 63));  // one plane: skip the lo fragments
-        x.u[i] = xsrc[(int64_t)(kt0 + c * CH + s) * xstep + src];
+        x.u[i] = load_free<false>(xsrc + (int64_t)(kt0 + c * CH + s) * xstep + src);
       }
     }
     return x;
@@ -813,44 +820,36 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
     store_x(0, xa);
     __syncthreads();
     DED_STAMP(1)
-    for (int c = 0;;) {
-      if (c == c_ssq4) ssq_issue(epi, rb0, lane, wv, 2 * NWN, ssq);
-      xa = load_x_pinned(cl(c + 2));
+    int c = 0;
+    auto stage = [&](XStage& xl, WChunk& wl, const WChunk& w, int buf, const XStage& xs_) {
+      xl = load_x_pinned(cl(c + 2));
       pin_loads();
-      w3 = load_w_pinned(cl(c + 3));
+      wl = load_w_pinned(cl(c + 3));
       pin_loads();
-      compute(w0, 0);
+      compute(w, buf);
       __builtin_amdgcn_sched_barrier(0);
-      store_x(1, xb);
+      store_x(buf ^ 1, xs_);
       __syncthreads();
-      if (++c >= n_chunks) break;
-      xb = load_x_pinned(cl(c + 2));
-      pin_loads();
-      w0 = load_w_pinned(cl(c + 3));
-      pin_loads();
-      compute(w1, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      store_x(0, xa);
-      __syncthreads();
-      if (++c >= n_chunks) break;
-      xa = load_x_pinned(cl(c + 2));
-      pin_loads();
-      w1 = load_w_pinned(cl(c + 3));
-      pin_loads();
-      compute(w2, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      store_x(1, xb);
-      __syncthreads();
-      if (++c >= n_chunks) break;
-      xb = load_x_pinned(cl(c + 2));
-      pin_loads();
-      w2 = load_w_pinned(cl(c + 3));
-      pin_loads();
-      compute(w3, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      store_x(0, xa);
-      __syncthreads();
-      if (++c >= n_chunks) break;
+      ++c;
+    };
+    // (whole turns, the row sums, the rest: with the row sums' loads under a condition inside the loop the compiler waited for
+    // every load in flight once per turn)
+    while (c < c_ssq4) {
+      stage(xa, w3, w0, 0, xb);
+      stage(xb, w0, w1, 1, xa);
+      stage(xa, w1, w2, 0, xb);
+      stage(xb, w2, w3, 1, xa);
+    }
+    ssq_issue(epi, rb0, lane, wv, 2 * NWN, ssq);
+    for (;;) {
+      stage(xa, w3, w0, 0, xb);
+      if (c >= n_chunks) break;
+      stage(xb, w0, w1, 1, xa);
+      if (c >= n_chunks) break;
+      stage(xa, w1, w2, 0, xb);
+      if (c >= n_chunks) break;
+      stage(xb, w2, w3, 1, xa);
+      if (c >= n_chunks) break;
     }
   } else {
     WChunk w0 = load_w(0);
@@ -941,7 +940,7 @@ __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restri
                                                                  int splits, int* __restrict__ counters,
                                                                  GemmEpilogue epi) {
   __shared__ WideShared<NWN, PLANES, RBG> sh;
-  const int rb0 = group_first(rbs);
+  const int rb0 = ONCE ? 0 : group_first(rbs);
   if (ONCE || group_size(rbs) == RBG)
     wide_group<NWN, PLANES, EPI, ONCE, RBG>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
   else
