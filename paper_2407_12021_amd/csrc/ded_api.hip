@@ -571,7 +571,7 @@ bool slim_step(const ded_ctx* c) {
 // LM head of the 16-bit path on the final residual stream (c->y_p / c->ssq as the last layer left them).  With
 // want_logits the fp32 logits are written to the workspace; without, only the per-group top-2 candidates that the
 // per-node argmax needs (the logits never reach memory).
-bool lm_head_bf16(ded_ctx* c, bool want_logits) {
+bool lm_head_bf16(ded_ctx* c, bool want_logits, float* logits_out = nullptr) {
   const ModelDims& md = c->md;
   const int rows = c->rows, rows_pad = round_up(rows, 64), d = md.d;
   GemmEpilogue e = {};
@@ -586,11 +586,17 @@ bool lm_head_bf16(ded_ctx* c, bool want_logits) {
     e.kind = EPI_LOGITS;
     e.out = c->logits;
     e.out_stride = md.V;
+    e.logits_out = logits_out;
+    e.max_nodes = c->cfg.max_nodes;
+    const StepMeta m = c->meta();
+    e.seq_n = m.seq_n;
+    e.row0 = m.row0;
+    e.blk_seq = m.blk_seq;
   } else {
     e.kind = EPI_TOP2;
-    e.top2_part = c->top2_part;
-    e.top2_groups = (md.V + 63) / 64;
   }
+  e.top2_part = c->top2_part;
+  e.top2_groups = (md.V + 63) / 64;
   // From 256 rows on the projection is bound by the matrix cores and reads the hi plane of its input alone: the lo
   // plane matters for what is carried through the layers, not here, where one rounding of the final normalised input
   // (2^-12 relative) moves a logit by ~2e-4.  Below, the weight stream bounds it and the lo product is free.
@@ -602,7 +608,7 @@ bool lm_head_bf16(ded_ctx* c, bool want_logits) {
                    rows_pad, md.V, d, planes, plan, c->counters, e, c->stream);
 }
 
-int forward_bf16(ded_ctx* c, bool want_logits) {
+int forward_bf16(ded_ctx* c, bool want_logits, float* logits_out) {
   const ModelDims& md = c->md;
   StepMeta m = c->meta();
   hipStream_t s = c->stream;
@@ -684,7 +690,7 @@ int forward_bf16(ded_ctx* c, bool want_logits) {
       gemm(KC_GEMM_DOWN, c->h_p, c->wdown[l], d, F, 1, e);
     }
   }
-  ok = lm_head_bf16(c, want_logits) && ok;
+  ok = lm_head_bf16(c, want_logits, logits_out) && ok;
   if (!ok) return DED_EINVAL;
   return launch_status();
 }
@@ -867,21 +873,22 @@ int ded_verify_step(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const 
   // the fp32 logits are materialised only for a caller that asks for them or samples from them
   const bool want_logits = !c->bf16 || logits_out != nullptr || c->sampling_seen;
   c->have_logits = false;
-  rc = c->bf16 ? forward_bf16(c, want_logits) : forward_f32(c);
+  rc = c->bf16 ? forward_bf16(c, want_logits, logits_out) : forward_f32(c);
   if (rc != DED_OK) return rc;
   StepMeta m = c->meta();
-  if (want_logits) {
-    ProfScope p(c, KC_ARGMAX);
-    launch_argmax(c->logits, c->md.V, m.rows, c->md.V, c->d_amax, c->d_margin, c->d_rowflag, c->stream);
-  } else {
+  if (c->bf16) {
+    // the LM head has left every row's candidates, and the logits where they are wanted, the caller's rows among them
     ProfScope p(c, KC_TOP2_REDUCE);
     launch_top2_reduce(c->top2_part, (c->md.V + 63) / 64, m.rows, c->d_amax, c->d_margin, c->d_rowflag, c->stream);
+  } else {
+    { ProfScope p(c, KC_ARGMAX);
+      launch_argmax(c->logits, c->md.V, m.rows, c->md.V, c->d_amax, c->d_margin, c->d_rowflag, c->stream); }
+    if (logits_out) {
+      ProfScope p(c, KC_EXPORT);
+      launch_export_logits(logits_out, c->logits, c->md.V, m, c->cfg.max_nodes, c->md.V, c->stream);
+    }
   }
   c->have_logits = want_logits;
-  if (logits_out) {
-    ProfScope p(c, KC_EXPORT);
-    launch_export_logits(logits_out, c->logits, c->md.V, m, c->cfg.max_nodes, c->md.V, c->stream);
-  }
   rc = launch_status();
   if (rc != DED_OK) return rc;
   c->pending = true;

@@ -121,9 +121,12 @@ struct GemmEpilogue {
   float inv_k, eps;
   int rows;      // real rows (the rest up to rows_pad is padding)
   int rb_total;  // rows_pad / 16 of the PackX buffers
-  // EPI_LOGITS: out[r][n] = scale * Y
+  // EPI_LOGITS: out[r][n] = scale * Y, and the rows of real nodes (seq_n, row0, blk_seq) in the caller's logits_out
+  // [batch][max_nodes][N] too if it is not null; and what EPI_TOP2 leaves
   float* out;
   int64_t out_stride;
+  float* logits_out;
+  int max_nodes;
   // EPI_TOP2: instead of the logits, per (row, 64-feature group) the best value, its feature index, the second
   // best value and a non-finite flag: top2_part[r * top2_groups + group] (16 bytes each)
   void* top2_part;

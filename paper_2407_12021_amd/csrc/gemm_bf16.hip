@@ -51,6 +51,7 @@ __device__ unsigned long long* g_trace = nullptr;  // [workgroup][wave][8] wall-
 #define DED_STAMP(i)
 #endif
 
+typedef float caller_f32x4_t __attribute__((ext_vector_type(4), aligned(4)));  // a caller's floats: aligned to themselves
 typedef f32x4_t Acc[TN][4];  // 4 feature tiles x 4 row blocks
 
 // With a single 64-row group the weights of a skinny GEMM are read exactly once per launch (ONCE): loaded with the
@@ -279,20 +280,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
 #pragma unroll
   for (int j = 0; j < RBN; ++j) scale[j] = __shfl(row_scale, (rbase - rb0 + j) * 16 + row_in);
 
-  if (EPI == EPI_LOGITS) {
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const int n = (ng * TN + t0 + t) * 16 + quad * 4;
-      if (n >= N) continue;
-#pragma unroll
-      for (int rb = 0; rb < RBN; ++rb) {
-        if (RAGGED && rbase + rb >= e.rb_total) continue;
-        const int64_t r = (int64_t)(rbase + rb) * 16 + row_in;
-        f32x4_t v = acc[t][rb] * scale[rb];
-        *reinterpret_cast<float4*>(e.out + r * e.out_stride + n) = make_float4(v[0], v[1], v[2], v[3]);
-      }
-    }
-  } else if (EPI == EPI_TOP2) {
+  if (EPI == EPI_LOGITS || EPI == EPI_TOP2) {
     // what the approval walk needs of a logits row, without the row: the best value of this 64-feature group, its
     // feature index (lowest on ties), the second best value, and whether any value is NaN or infinite
     uint4* dst = reinterpret_cast<uint4*>(e.top2_part);
@@ -302,11 +290,24 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
       const int64_t r = (int64_t)(rbase + rb) * 16 + row_in;
       float v1 = -INFINITY, v2 = -INFINITY;
       int i1 = 0x7fffffff, bad = 0;
+      // the row itself too, where it is asked for: into the workspace and, for a real node, into the caller's [batch][max_nodes][V]
+      float *own = nullptr, *out = nullptr;
+      if constexpr (EPI == EPI_LOGITS) {
+        own = e.out + r * e.out_stride;
+        if (e.logits_out && r < e.rows) {
+          const int b = e.blk_seq[r >> 4], node = (int)r - e.row0[b];
+          if (node < e.seq_n[b]) out = e.logits_out + ((int64_t)b * e.max_nodes + node) * N;
+        }
+      }
 #pragma unroll
       for (int t = 0; t < TN; ++t) {
         const int n = (ng * TN + t) * 16 + quad * 4;
         if (n >= N) continue;
         const f32x4_t v = acc[t][rb] * scale[rb];
+        if constexpr (EPI == EPI_LOGITS) {
+          *reinterpret_cast<f32x4_t*>(own + n) = v;
+          if (out) *reinterpret_cast<caller_f32x4_t*>(out + n) = v;
+        }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {  // ascending feature index: a later equal value never replaces the first
           const float x = v[i];
