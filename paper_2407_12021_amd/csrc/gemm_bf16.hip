@@ -868,6 +868,10 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
       compute(w0, buf);
       store_x(buf ^ 1, xn);
       __syncthreads();
+      // (held behind the barrier: in the instance of three row blocks the copies, which wait for every weight load in flight, were
+      // moved in front of it, with the LDS stores behind them.  48 rows, us, moved / held: 8B shape gate/up 50.4 / 46.6, LM head
+      // 175.9 / 171.1; 13B shape gate/up 58.9 / 54.7, QKV 37.6 / 36.6)
+      __builtin_amdgcn_sched_barrier(0);
       w0 = w1;
       w1 = w2;
       buf ^= 1;
