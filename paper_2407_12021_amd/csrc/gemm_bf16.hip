@@ -648,13 +648,13 @@ __device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, i
   }
   DED_STAMP(7)
 }
-// RBG: row blocks of the larger groups; others have one less
+// RBG: row blocks of the larger groups; others have one less.  (Two to three wavefronts per SIMD: for a fourth, which three blocks
+// would fit, the compiler fetched the slices two at a time.  us, so / now: d = 2048, 80 rows O 13.1 / 10.1, down 20.0 / 17.1; d = 1024,
+// K = 2816, 144 rows 12.9 / 9.9)
 template <int NW, int PLANES, int EPI, bool ONCE, int RBG>
-__global__ __launch_bounds__(NW * 64, 2) void gemm_stream_kernel(float* __restrict__ part, int64_t part_stride,
-                                                                 const uint4* xp,
-                                                                 const uint4* wp, int RB, int rbs, int N, int KT,
-                                                                 int splits, int* __restrict__ counters,
-                                                                 GemmEpilogue epi) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 3)))
+void gemm_stream_kernel(float* __restrict__ part, int64_t part_stride, const uint4* xp, const uint4* wp, int RB, int rbs, int N,
+                        int KT, int splits, int* __restrict__ counters, GemmEpilogue epi) {
   __shared__ StreamShared<NW, RBG> sh;
   const int rb0 = ONCE ? 0 : group_first(rbs);
   if (ONCE || group_size(rbs) == RBG)
