@@ -475,8 +475,13 @@ __device__ inline bool take_ticket(int splits, int* counters, int* s_flag) {
 // each CU.  In steps, us, always four / as dealt: 48 rows (7B shape) gate/up 43.0 / 38.4, QKV 32.0 / 30.0, O and down
 // together 38.5 / 36.8; 97 rows 65.9 / 62.8, 42.1 / 40.0, 54.2 / 52.9; 144 rows of the 8B shape, QKV 35.2 / 31.4, O and down 92.7 /
 // 88.6.  (With every load held in its place, see pin_loads: half of the gain of the 97 rows, 64 rows 43.1 -> 41.9 in gate/up.)
-__device__ inline int group_first(int rbs) { return blockIdx.z * rbs / gridDim.z; }
-__device__ inline int group_size(int rbs) { return (blockIdx.z + 1) * rbs / gridDim.z - group_first(rbs); }
+// The first `larger` groups have RBG blocks, the others RBG - 1 (a division in the kernel would cost it 0.2 us).
+template <int RBG>
+__device__ inline int group_first(int larger) { return (int)blockIdx.z * (RBG - 1) + min((int)blockIdx.z, larger); }
+
+// How a launch reads its weights, and with that the order of its loads: once (a single group); by several groups; by several
+// groups in more workgroups than CUs.
+enum { READ_ONCE, READ_SHARED, READ_ROUNDS };
 
 // ------------------------------------------------------------------------------------------
 // Stream kernel: one feature group per workgroup, NW wavefronts split the k range.
@@ -487,10 +492,11 @@ struct StreamShared {
   float ssq[NW * 64];
   int flag;
 };
-template <int NW, int PLANES, int EPI, bool ONCE, int RBG, typename SH>
+template <int NW, int PLANES, int EPI, int READS, int RBG, typename SH>
 __device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, int64_t part_stride, const uint4* xp,
                                              const uint4* wp, int RB, int rb0, int N, int KT, int splits,
                                              int* __restrict__ counters, const GemmEpilogue& epi) {
+  constexpr bool ONCE = READS == READ_ONCE;
   float4* const red = sh.red;
   float* const s_ssq = sh.ssq;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -564,9 +570,12 @@ __device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, i
 #pragma unroll
       for (int j = 0; j < D; ++j) issue(j);
     }
+    // A step's place is refilled at once, or all of a turn's together where other workgroups on the CU have their loads in flight
+    // meanwhile.  O and down together, us, at once / together: 7B shape, 128 rows 53.9 / 55.2, 13B, 192 rows 97.5 / 100.6 (at most one
+    // workgroup per CU); down alone, more of them: 7B, 192 rows 57.9 / 54.3, 13B, 97 rows 55.2 / 53.7.
     auto turns_to = [&](int rest) {
       for (; left > rest; left -= D) {
-        if (!ONCE) {
+        if (READS == READ_ROUNDS) {
 #pragma unroll
           for (int j = 0; j < D; ++j) compute(j);
 #pragma unroll
@@ -651,16 +660,16 @@ __device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, i
 // RBG: row blocks of the larger groups; others have one less.  (Two to three wavefronts per SIMD: for a fourth, which three blocks
 // would fit, the compiler fetched the slices two at a time.  us, so / now: d = 2048, 80 rows O 13.1 / 10.1, down 20.0 / 17.1; d = 1024,
 // K = 2816, 144 rows 12.9 / 9.9)
-template <int NW, int PLANES, int EPI, bool ONCE, int RBG>
+template <int NW, int PLANES, int EPI, int READS, int RBG>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 3)))
-void gemm_stream_kernel(float* __restrict__ part, int64_t part_stride, const uint4* xp, const uint4* wp, int RB, int rbs, int N,
-                        int KT, int splits, int* __restrict__ counters, GemmEpilogue epi) {
+void gemm_stream_kernel(float* __restrict__ part, int64_t part_stride, const uint4* xp, const uint4* wp, int RB, int larger,
+                        int N, int KT, int splits, int* __restrict__ counters, GemmEpilogue epi) {
   __shared__ StreamShared<NW, RBG> sh;
-  const int rb0 = ONCE ? 0 : group_first(rbs);
-  if (ONCE || group_size(rbs) == RBG)
-    stream_group<NW, PLANES, EPI, ONCE, RBG>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
+  const int rb0 = READS == READ_ONCE ? 0 : group_first<RBG>(larger);
+  if (READS == READ_ONCE || (int)blockIdx.z < larger)
+    stream_group<NW, PLANES, EPI, READS, RBG>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
   else
-    stream_group<NW, PLANES, EPI, ONCE, RBG - 1>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
+    stream_group<NW, PLANES, EPI, READS, RBG - 1>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -941,12 +950,12 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
 template <int NWN, int PLANES, int EPI, bool ONCE, int RBG>
 __global__ __launch_bounds__(NWN * 128, 2) void gemm_wide_kernel(float* __restrict__ part, int64_t part_stride,
                                                                  const uint4* xp,
-                                                                 const uint4* wp, int RB, int rbs, int N, int KT,
+                                                                 const uint4* wp, int RB, int larger, int N, int KT,
                                                                  int splits, int* __restrict__ counters,
                                                                  GemmEpilogue epi) {
   __shared__ WideShared<NWN, PLANES, RBG> sh;
-  const int rb0 = ONCE ? 0 : group_first(rbs);
-  if (ONCE || group_size(rbs) == RBG)
+  const int rb0 = ONCE ? 0 : group_first<RBG>(larger);
+  if (ONCE || (int)blockIdx.z < larger)
     wide_group<NWN, PLANES, EPI, ONCE, RBG>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
   else
     wide_group<NWN, PLANES, EPI, ONCE, RBG - 1>(sh, part, part_stride, xp, wp, RB, rb0, N, KT, splits, counters, epi);
@@ -1658,7 +1667,7 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
                   const uint4* xp, const uint4* wp, int RB, int N, int KT, int* counters, const GemmEpilogue& epi,
                   int nw, hipStream_t s) {
   const int splits = plan.splits;
-#define DED_ARGS part, part_stride, xp, wp, RB, rbs, N, KT, splits, counters, epi
+#define DED_ARGS part, part_stride, xp, wp, RB, larger, N, KT, splits, counters, epi
   if (plan.tile) {
     const TileDims t = tile_dims(plan.tile);
     const int row_tiles = (RB + t.row_blocks - 1) / t.row_blocks;
@@ -1684,26 +1693,41 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
   if constexpr (PLANES == 1 && (EPI == EPI_LOGITS || EPI == EPI_TOP2)) {
     return false;
   } else {
-  const int rbs = (epi.rows + 15) / 16, groups = RB / 4;
+  const int rbs = (epi.rows + 15) / 16, groups = RB / 4, most = rbs > 3 * groups ? 4 : 3;
   const bool once = groups == 1;  // every weight byte is read once
-#define DED_SKINNY_ROWS(KERNEL, A, RBG, GRID, THREADS)                                                     \
-  if (once) hipLaunchKernelGGL((KERNEL<A, PLANES, EPI, true, RBG>), GRID, dim3(THREADS), 0, s, DED_ARGS);   \
-  else hipLaunchKernelGGL((KERNEL<A, PLANES, EPI, false, RBG>), GRID, dim3(THREADS), 0, s, DED_ARGS);
-#define DED_SKINNY(KERNEL, A, GRID, THREADS)                      \
-  if (rbs > 3 * groups) { DED_SKINNY_ROWS(KERNEL, A, 4, GRID, THREADS) } \
-  else { DED_SKINNY_ROWS(KERNEL, A, 3, GRID, THREADS) }
+  const int larger = rbs - groups * (most - 1);
+#define DED_STREAM(NW, READS)                                                                                                        \
+  {                                                                                                                                  \
+    if (most == 4) hipLaunchKernelGGL((gemm_stream_kernel<NW, PLANES, EPI, READS, 4>), grid_stream, dim3(NW * 64), 0, s, DED_ARGS);  \
+    else hipLaunchKernelGGL((gemm_stream_kernel<NW, PLANES, EPI, READS, 3>), grid_stream, dim3(NW * 64), 0, s, DED_ARGS);            \
+  }
+#define DED_WIDE(NWN, ONCE)                                                                                                          \
+  {                                                                                                                                  \
+    if (most == 4) hipLaunchKernelGGL((gemm_wide_kernel<NWN, PLANES, EPI, ONCE, 4>), grid_wide, dim3(NWN * 128), 0, s, DED_ARGS);    \
+    else hipLaunchKernelGGL((gemm_wide_kernel<NWN, PLANES, EPI, ONCE, 3>), grid_wide, dim3(NWN * 128), 0, s, DED_ARGS);              \
+  }
   if (plan.nwn == 0) {
-    if (nw == 4) { DED_SKINNY(gemm_stream_kernel, 4, grid_stream, 256) }
-    else if (nw == 2) { DED_SKINNY(gemm_stream_kernel, 2, grid_stream, 128) }
-    else { DED_SKINNY(gemm_stream_kernel, 1, grid_stream, 64) }
+    const bool rounds = (int64_t)grid_stream.x * grid_stream.y * grid_stream.z > kCUs;
+    if (nw == 4) {
+      if (once) DED_STREAM(4, READ_ONCE) else if (rounds) DED_STREAM(4, READ_ROUNDS) else DED_STREAM(4, READ_SHARED)
+    } else if (nw == 2) {
+      if (once) DED_STREAM(2, READ_ONCE) else DED_STREAM(2, READ_SHARED)
+    } else {
+      if (once) DED_STREAM(1, READ_ONCE) else DED_STREAM(1, READ_SHARED)
+    }
     return true;
   }
-  if (plan.nwn == 4) { DED_SKINNY(gemm_wide_kernel, 4, grid_wide, 512) }
-  else if (plan.nwn == 3) { DED_SKINNY(gemm_wide_kernel, 3, grid_wide, 384) }
-  else if (plan.nwn == 2) { DED_SKINNY(gemm_wide_kernel, 2, grid_wide, 256) }
-  else return false;
-#undef DED_SKINNY
-#undef DED_SKINNY_ROWS
+  if (plan.nwn == 4) {
+    if (once) DED_WIDE(4, true) else DED_WIDE(4, false)
+  } else if (plan.nwn == 3) {
+    if (once) DED_WIDE(3, true) else DED_WIDE(3, false)
+  } else if (plan.nwn == 2) {
+    if (once) DED_WIDE(2, true) else DED_WIDE(2, false)
+  } else {
+    return false;
+  }
+#undef DED_STREAM
+#undef DED_WIDE
 #undef DED_ARGS
   return true;
   }
