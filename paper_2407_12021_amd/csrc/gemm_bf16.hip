@@ -797,10 +797,12 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
   if constexpr (DEEP) {
     // Weights three chunks ahead, activations two.  The ring slots are fixed registers (the loop is unrolled by the
     // ring length and leaves from the middle): a copy between slots would have to wait for the load that still
-    // writes its source.  The loads are pinned, activations in front of weights, and the LDS stores behind the products: the
-    // compiler otherwise sinks a prefetch to the block of its first use, or waits for activations of one iteration back before
-    // the products (48 rows, gate/up of a 7B shape: 49.0 us so, 38.4 pinned).  Fetches past the range re-read its last chunk
-    // (in bounds, never used).
+    // writes its source.  Of a single row group, whose weights all come from memory, the loads are pinned, activations in front of
+    // weights, and the LDS stores behind the products: the compiler otherwise sinks a prefetch to the block of its first use, or
+    // waits for activations of one iteration back before the products (48 rows, gate/up of a 7B shape: 49.0 us so, 38.4 pinned).
+    // Several groups find the weights in the caches and take the compiler's order, loads between the products (gate/up of the 7B
+    // shape, us, pinned / not: 128 rows 65.4 / 64.2, 176 rows 109.8 / 105.0, 192 rows 113.2 / 108.9; up to 97 rows within the noise
+    // of a card).  Fetches past the range re-read its last chunk (in bounds, never used).
     const int c_max = n_chunks - 1;
     auto cl = [&](int c) { return c < c_max ? c : c_max; };
     auto load_w_pinned = [&](int c) {
@@ -833,11 +835,11 @@ __device__ __forceinline__ void wide_group(SH& sh, float* __restrict__ part, int
     int c = 0;
     auto stage = [&](XStage& xl, WChunk& wl, const WChunk& w, int buf, const XStage& xs_) {
       xl = load_x_pinned(cl(c + 2));
-      pin_loads();
+      if (ONCE) pin_loads();
       wl = load_w_pinned(cl(c + 3));
-      pin_loads();
+      if (ONCE) pin_loads();
       compute(w, buf);
-      __builtin_amdgcn_sched_barrier(0);
+      if (ONCE) __builtin_amdgcn_sched_barrier(0);
       store_x(buf ^ 1, xs_);
       __syncthreads();
       ++c;
