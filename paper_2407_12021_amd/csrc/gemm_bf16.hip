@@ -507,7 +507,8 @@ __device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, i
   const int units = KT / RING;
   const int parts = splits * NW;
   const int gi = split * NW + wave;
-  const int k0 = gi * units / parts * RING, k1 = (gi + 1) * units / parts * RING;  // (32 bits: a 64-bit division takes 0.2 us)
+  // (32 bits: a 64-bit division takes 0.2 us.  At least 4 steps: the host launches no more wavefronts than K has groups of PD)
+  const int k0 = gi * units / parts * RING, k1 = (gi + 1) * units / parts * RING;
 
   f32x4_t acc[TN][RBG];
 #pragma unroll
@@ -520,8 +521,13 @@ __device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, i
   ssq_clear(ssq);
   // The ring: D steps' fragments in fixed registers, a step's refilled as soon as it is used up (the loads held there).  Straight
   // code from the first load to the last: a load under a condition makes the compiler's waits assume that it did not happen.
+  // D = 4 where the registers of one plane allow it and no second workgroup wants them (one group: at most one workgroup per CU in
+  // the measured shapes; 232 registers, two wavefronts per SIMD, against 152 and three).  us, D = 2 / 4: O and down together, 64 rows,
+  // 7B shape 38.4 / 38.4, 13B 52.4 / 52.7; with two wavefronts (O of d = 2048, 64 rows) 25.0 / 11.9, since with fewer registers the
+  // compiler fetches the slices two at a time.  Several groups, 2 / 4: 7B, 128 rows 54.3 / 53.7, 192 rows 79.8 / 84.9 (three
+  // workgroups per CU).  Two planes: four steps of both do not fit.
   constexpr int D = PLANES == 1 && ONCE ? 4 : 2;
-  static_assert(D == RING || D == 2 * RING, "a range is whole units of RING steps");
+  static_assert((D == RING || D == 2 * RING) && D <= PD, "a range is whole units of RING steps, and at least PD steps");
   const int n = k1 - k0;
   const char* wsrc = reinterpret_cast<const char*>(wp) + (((int64_t)ng * KT + k0) * TN << 10);  // (uniform; the lane's offset apart)
   // per k step the activations of the group's row blocks x 2 planes (hi, lo) are one run of memory
@@ -554,55 +560,47 @@ __device__ __forceinline__ void stream_group(SH& sh, float* __restrict__ part, i
       }
   };
   constexpr bool SSQ = EPI != EPI_RESIDUAL;
-  if (n >= D) {
-    int left = n - D;  // steps not requested yet
-    if (left % D) {    // what is beyond whole turns goes first; either way the places are in order after it
-      constexpr int R = D - RING;
+  int left = n - D;  // steps not requested yet
+  if (D > RING && left % D) {  // what is beyond whole turns goes first; either way the places are in order after it
+    constexpr int R = D - RING;
 #pragma unroll
-      for (int j = 0; j < D; ++j) issue((j + R) % D);
+    for (int j = 0; j < D; ++j) issue((j + R) % D);
 #pragma unroll
-      for (int j = R; j < D; ++j) {
-        compute(j);
-        issue(j);
-      }
-      left -= RING;
-    } else {
-#pragma unroll
-      for (int j = 0; j < D; ++j) issue(j);
+    for (int j = R; j < D; ++j) {
+      compute(j);
+      issue(j);
     }
-    // A step's place is refilled at once, or all of a turn's together where other workgroups on the CU have their loads in flight
-    // meanwhile.  O and down together, us, at once / together: 7B shape, 128 rows 53.9 / 55.2, 13B, 192 rows 97.5 / 100.6 (at most one
-    // workgroup per CU); down alone, more of them: 7B, 192 rows 57.9 / 54.3, 13B, 97 rows 55.2 / 53.7.
-    auto turns_to = [&](int rest) {
-      for (; left > rest; left -= D) {
-        if (READS == READ_ROUNDS) {
+    left -= RING;
+  } else {
 #pragma unroll
-          for (int j = 0; j < D; ++j) compute(j);
+    for (int j = 0; j < D; ++j) issue(j);
+  }
+  // A step's place is refilled at once, or all of a turn's together where other workgroups on the CU have their loads in flight
+  // meanwhile.  O and down together, us, at once / together: 7B shape, 128 rows 53.9 / 55.2, 13B, 192 rows 97.5 / 100.6 (at most one
+  // workgroup per CU); down alone, more of them: 7B, 192 rows 57.9 / 54.3, 13B, 97 rows 55.2 / 53.7.
+  auto turns_to = [&](int rest) {
+    for (; left > rest; left -= D) {
+      if (READS == READ_ROUNDS) {
 #pragma unroll
-          for (int j = 0; j < D; ++j) issue(j);
-        } else {
+        for (int j = 0; j < D; ++j) compute(j);
 #pragma unroll
-          for (int j = 0; j < D; ++j) {
-            compute(j);
-            issue(j);
-          }
+        for (int j = 0; j < D; ++j) issue(j);
+      } else {
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          compute(j);
+          issue(j);
         }
       }
-    };
-    if constexpr (SSQ) {
-      turns_to(12);
-      ssq_issue(epi, rb0, lane, wave, NW, ssq);  // the row sums, a dozen steps before the end
     }
-    turns_to(0);
-#pragma unroll
-    for (int j = 0; j < D; ++j) compute(j);
-  } else {
-    if constexpr (SSQ) ssq_issue(epi, rb0, lane, wave, NW, ssq);
-    for (int i = 0; i < n; ++i) {
-      issue(0);
-      compute(0);
-    }
+  };
+  if constexpr (SSQ) {
+    turns_to(12);
+    ssq_issue(epi, rb0, lane, wave, NW, ssq);  // the row sums, a dozen steps before the end
   }
+  turns_to(0);
+#pragma unroll
+  for (int j = 0; j < D; ++j) compute(j);
   ssq_publish(epi, rb0, lane, wave, NW, ssq, s_ssq);
   if (NW == 1) __syncthreads();
 
