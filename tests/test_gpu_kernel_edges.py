@@ -13,8 +13,19 @@ def _verifier(*a, **k):
     return Verifier(*a, **k)
 
 
+def _check_argmax(logits, tokens, margins, nodes):
+    """Tokens and margins of a step's real nodes are those of its fp32 logits, bit for bit: lowest id of the largest, largest minus
+    second largest."""
+    for b, n in enumerate(nodes):
+        rows = logits[b, :n]
+        top2 = np.partition(rows, -2, axis=1)[:, -2:]
+        assert np.array_equal(tokens[b, :n], np.argmax(rows, axis=1)), b
+        assert np.array_equal(margins[b, :n], top2[:, 1] - top2[:, 0]), b
+
+
 def _step_error(cfg, w, prefix_len, nodes, seed):
-    """Largest logit error of one ragged batch step whose prefixes were computed by the library and the oracle each."""
+    """Largest logit error of one ragged batch step whose prefixes were computed by the library and the oracle each; its tokens
+    and margins have to be those of its logits."""
     B, most = len(nodes), max(nodes)
     ver = _verifier(cfg, w, max_batch=B, kv_capacity=max(prefix_len) + most + 64, max_nodes=most)
     prefixes = [di.zipf_tokens(cfg.vocab, max(p, 1), seed=seed, stream=b)[:p] for b, p in enumerate(prefix_len)]
@@ -27,7 +38,9 @@ def _step_error(cfg, w, prefix_len, nodes, seed):
             ver.kv_store(l, b, 0, k, v)
     parents = [di.random_tree(n, None, seed=seed + b) for b, n in enumerate(nodes)]
     tokens = [di.zipf_tokens(cfg.vocab, n, seed=seed + 1, stream=b) for b, n in enumerate(nodes)]
-    logits = ver.verify_step(prefix_len, parents, tokens, want_logits=True).cpu().numpy().astype(np.float64)
+    logits = ver.verify_step(prefix_len, parents, tokens, want_logits=True).cpu().numpy()
+    _check_argmax(logits, *ver.get_argmax(), nodes)
+    logits = logits.astype(np.float64)
     ver.accept(mode=0)
     ver.close()
     worst = 0.0
@@ -166,7 +179,7 @@ MID_EDGES = [
 
 @pytest.mark.parametrize("case", range(len(MID_EDGES)))
 def test_projections_of_65_to_255_rows(case, gemm_plan):
-    """Bound: the 16-bit path's 2e-2 logit tolerance, as above; tokens and margins without logits equal those with them."""
+    """Bound: the 16-bit path's 2e-2 logit tolerance, as above; tokens and margins, with logits and without, are those of the logits."""
     (d, H, Hkv, F, V), prefix_len, nodes, tiled = MID_EDGES[case]
     rows = -(-len(nodes) * (-(-max(nodes) // 16) * 16) // 64) * 64
     for N, K in tiled:
@@ -179,13 +192,11 @@ def test_projections_of_65_to_255_rows(case, gemm_plan):
     ver = _verifier(cfg, w, max_batch=len(nodes), kv_capacity=128, max_nodes=max(nodes))
     parents = [di.random_tree(n, None, seed=b) for b, n in enumerate(nodes)]
     tokens = [di.zipf_tokens(V, n, seed=6, stream=b) for b, n in enumerate(nodes)]
-    got = []
-    for logits in (True, False):
-        ver.verify_step([0] * len(nodes), parents, tokens, want_logits=logits)
-        got.append(ver.get_argmax())
+    logits = ver.verify_step([0] * len(nodes), parents, tokens, want_logits=True).cpu().numpy()
+    _check_argmax(logits, *ver.get_argmax(), nodes)
+    ver.verify_step([0] * len(nodes), parents, tokens)
+    _check_argmax(logits, *ver.get_argmax(), nodes)
     ver.close()
-    for b, n in enumerate(nodes):
-        assert np.array_equal(got[0][0][b, :n], got[1][0][b, :n]) and np.array_equal(got[0][1][b, :n], got[1][1][b, :n])
 
 
 # (layers, d, H, Hkv, F, V), prefix lengths, tree sizes: steps of 16 and 32 padded rows; k ranges of one step of 128, ranges that
@@ -211,10 +222,11 @@ def test_projections_of_few_rows(case):
     assert err <= 2e-2
 
 
-# (d, H, Hkv, F, V), tree size: 3 - 11 row blocks in one to three groups of 2, 3 and 4; k ranges of no, one and two steps, of
-# whole turns of the ring and half a turn more, in one slice and several
+# (d, H, Hkv, F, V), tree size: 3 - 11 row blocks in one to three groups of 2, 3 and 4; k ranges of four steps and more, of whole
+# turns of the stream kernel's ring and half a turn more, in one slice and several; the last two in more workgroups than CUs too
+# (down 768; gate/up 768 and down 480).  The wide kernel: WIDE_EDGES
 GROUP_EDGES = [((128, 1, 1, 128, 80), 33)] + [((640, 5, 5, 896, 1040), n) for n in (48, 49, 65, 81, 97, 129, 145, 161)] + [
-    ((4096, 32, 8, 11008, 4112), 40), ((4096, 32, 32, 11008, 4112), 145)]
+    ((4096, 32, 8, 11008, 4112), 40), ((4096, 32, 32, 11008, 4112), 145), ((2048, 16, 8, 8192, 1040), 145)]
 
 
 @pytest.mark.parametrize("case", range(len(GROUP_EDGES)))
@@ -226,6 +238,88 @@ def test_projections_of_uneven_row_groups(case):
     err = _step_error(cfg, w, [7], [n], seed=140 + case)
     print(f"max |logit error| {err:.2e}")
     assert err <= 2e-2
+
+
+# (d, H, Hkv, F, V), tree size, {(N, K): (feature groups per workgroup, slices)} of the projections that the wide kernel runs: row
+# blocks 3 (one group), 3 + 2, 4 + 3, 3 + 3 + 3, 4 + 3 + 3 and 4 + 4 + 3; two, three and four feature groups, the last ones surplus or
+# ending inside a group; one slice and several, at most one workgroup per CU and more
+WIDE_EDGES = [
+    ((1024, 8, 8, 2816, 8208), 40, {(8208, 1024): (2, 3)}),
+    ((1024, 8, 8, 2816, 8208), 65, {(8208, 1024): (2, 1)}),
+    ((1024, 8, 8, 2816, 32016), 80, {(32016, 1024): (4, 1)}),
+    ((1024, 8, 8, 2816, 32016), 97, {(32016, 1024): (4, 1)}),
+    ((1024, 8, 8, 2816, 32016), 144, {(32016, 1024): (3, 1), (5632, 1024): (2, 1)}),
+    ((1024, 8, 8, 2816, 32016), 160, {(32016, 1024): (3, 1), (5632, 1024): (2, 1)}),
+    ((4096, 32, 32, 11008, 4112), 65, {(12288, 4096): (3, 2), (22016, 4096): (3, 1), (4112, 4096): (3, 5)}),
+    ((4096, 32, 32, 11008, 4112), 176, {(22016, 4096): (3, 2)}),
+    ((4096, 32, 8, 14336, 1040), 40, {(6144, 4096): (3, 8), (28672, 4096): (4, 2)}),
+    ((4096, 32, 8, 14336, 1040), 97, {(6144, 4096): (3, 4), (28672, 4096): (4, 1)}),
+    ((4096, 32, 8, 14336, 1040), 150, {(6144, 4096): (4, 3)}),
+]
+
+
+@pytest.mark.parametrize("case", range(len(WIDE_EDGES)))
+def test_wide_projections_of_uneven_row_groups(case, gemm_plan):
+    """Bound: the 16-bit path's 2e-2 logit tolerance, as above."""
+    (d, H, Hkv, F, V), n, wide = WIDE_EDGES[case]
+    rows, up = -(-n // 64) * 64, lambda x: -(-x // 64) * 64
+    part = max((H + 2 * Hkv) * 128, 2 * F, d, up(V)) * max(512, rows)  # the context's room for split sums
+    for (N, K), want in wide.items():
+        plan = gemm_plan(rows, rows, N, K, 2, min(8, part // (rows * up(N))), part)
+        assert (plan.nwn, plan.splits, plan.tile) == (*want, 0), (N, K)
+    cfg = di.ModelConfig(f"wide-edge{case}", 1, d, H, Hkv, 128, F, V, dtype="bf16")
+    w = di.make_weights(cfg, seed=160 + case, gain_jitter=0.1, threads=16)
+    err = _step_error(cfg, w, [7], [n], seed=180 + case)
+    print(f"max |logit error| {err:.2e}")
+    assert err <= 2e-2
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("n", [1, 2, 64, 65, 256])
+def test_a_kept_chain_is_returned_whole(dtype, n):
+    """accept(mode=1): the path is the chain, the tokens are those of its nodes after the first and the last node's argmax; for
+    the second sequence of a batch too, whose rows start further down."""
+    cfg = di.ModelConfig("chain-" + dtype, 1, 128, 1, 1, 128 if dtype == "bf16" else 64, 128, 512, dtype=dtype)
+    ver = _verifier(cfg, di.make_weights(cfg, seed=4, gain_jitter=0.1), max_batch=2, kv_capacity=576, max_nodes=max(n, 21))
+    prefix = [0, 0]
+    for turn, nodes in enumerate(([21, n], [n, 21])):
+        tokens = [di.zipf_tokens(cfg.vocab, m, seed=n + turn, stream=b) for b, m in enumerate(nodes)]
+        ver.verify_step(prefix, [di.chain_tree(m) for m in nodes], tokens)
+        best, _ = ver.get_argmax()
+        kept, path, after = ver.accept(mode=1)
+        for b, m in enumerate(nodes):
+            assert path[b] == list(range(m)) and after[b] == prefix[b] + m
+            assert kept[b] == [int(t) for t in tokens[b][1:]] + [int(best[b, m - 1])]
+        prefix = after
+    ver.close()
+
+
+# tree sizes, widths: the slim kernel, the stream and wide kernels, the tile kernel (256 and more rows), and the fp32 export
+@pytest.mark.parametrize("dtype,nodes,d,V", [("bf16", [3, 9], 128, 1040), ("bf16", [40, 7, 20], 256, 1040), ("bf16", [33, 50], 1024, 8208),
+                                             ("bf16", [64, 65, 130], 256, 1040), ("fp32", [5, 17], 128, 101)])
+def test_logits_go_to_real_nodes_of_an_array_aligned_to_its_elements(dtype, nodes, d, V):
+    """logits_out one element past a 16-byte boundary: real nodes' rows have the bits of the aligned array's, rows of absent nodes and
+    what lies before and behind the array keep what was there."""
+    import torch
+    from paper_2407_12021_amd import binding
+    cfg = di.ModelConfig("logits-out-" + dtype, 1, d, 2, 1, 128 if dtype == "bf16" else 64, 256, V, dtype=dtype)
+    B, most = len(nodes), max(nodes) + 3
+    ver = _verifier(cfg, di.make_weights(cfg, seed=6, gain_jitter=0.1), max_batch=B, kv_capacity=256, max_nodes=most)
+    parents = [di.random_tree(n, None, seed=b) for b, n in enumerate(nodes)]
+    tokens = [di.zipf_tokens(V, n, seed=6, stream=b) for b, n in enumerate(nodes)]
+    want = ver.verify_step([0] * B, parents, tokens, want_logits=True)
+    size, mark = B * most * V, 12345.0
+    flat = torch.full((size + 64,), mark, device="cuda")
+    assert flat.data_ptr() % 16 == 0
+    rc = binding.ded_verify_step(ver.ctx, [0] * B, nodes, ver._pad(parents, -1), ver._pad(tokens, 0), flat[1:].data_ptr())
+    assert rc == binding.DED_OK
+    torch.cuda.synchronize()
+    got = flat[1:1 + size].view(B, most, V)
+    for b, n in enumerate(nodes):
+        assert torch.isfinite(got[b, :n]).all() and torch.equal(got[b, :n], want[b, :n])
+        assert (got[b, n:] == mark).all()
+    assert flat[0] == mark and (flat[1 + size:] == mark).all()
+    ver.close()
 
 
 def test_a_row_has_the_same_bits_in_a_small_tree_and_a_larger_one():

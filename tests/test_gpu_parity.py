@@ -511,10 +511,11 @@ def test_zero_layer_bf16_gemm_path():
 
 @pytest.mark.parametrize("shape", ["ragged-vocab", "32000", "large-rows"])
 def test_fused_argmax_equals_argmax_of_materialised_logits(shape):
-    """Without a logits request the LM-head GEMM hands the argmax its per-tile candidates and the [rows][vocab]
-    logits never reach memory; with one they are written and reduced by the stand-alone kernel.  Tokens and
-    margins must be equal bit for bit (the merge rule is order-independent), on a vocabulary with a ragged last
-    feature group, on the benchmark's vocabulary, and through the large-row GEMM (batched trees, split-K)."""
+    """The LM-head GEMM hands the argmax its per-tile candidates; without a logits request the [rows][vocab] logits
+    never reach memory, with one the same epilogue stores them too.  Tokens and margins of both must be those that
+    numpy finds in the stored logits, bit for bit (the merge rule is order-independent), on a vocabulary with a
+    ragged last feature group, on the benchmark's vocabulary, and through the large-row GEMM (batched trees,
+    split-K)."""
     if shape == "ragged-vocab":
         cfg, batch, nodes = di.ModelConfig("t2-a", 1, 256, 2, 2, 128, 128, 1008, dtype="bf16"), 2, 40
     elif shape == "32000":
