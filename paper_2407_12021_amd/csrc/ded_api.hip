@@ -568,9 +568,9 @@ bool slim_step(const ded_ctx* c) {
                                                       fits(md.d, md.F, 1)));
 }
 
-// LM head of the 16-bit path on the final residual stream (c->y_p / c->ssq as the last layer left them).  With
-// want_logits the fp32 logits are written to the workspace; without, only the per-group top-2 candidates that the
-// per-node argmax needs (the logits never reach memory).
+// LM head of the 16-bit path on the final residual stream (c->y_p / c->ssq as the last layer left them): the per-group top-2
+// candidates that the per-node argmax needs and, with want_logits, the fp32 logits, into the workspace and the rows of real nodes
+// into the caller's logits_out too if it is not null (otherwise no logits reach memory).
 bool lm_head_bf16(ded_ctx* c, bool want_logits, float* logits_out = nullptr) {
   const ModelDims& md = c->md;
   const int rows = c->rows, rows_pad = round_up(rows, 64), d = md.d;

@@ -472,9 +472,8 @@ __device__ inline bool take_ticket(int splits, int* counters, int* s_flag) {
 // The row blocks of a launch are dealt to its groups (blockIdx.z) as evenly as they go: at most four each, sizes that differ by
 // one at most, and a kernel instance for the larger groups of 4 or of 3 (smaller ones take the branch with one block less).
 // Groups that always ran as four fetched and multiplied blocks nobody reads, out of what bounds these kernels, ~50 GB/s into
-// each CU.  In steps, us, always four / as dealt: 48 rows (7B shape) gate/up 43.0 / 38.4, QKV 32.0 / 30.0, O and down
-// together 38.5 / 36.8; 97 rows 65.9 / 62.8, 42.1 / 40.0, 54.2 / 52.9; 144 rows of the 8B shape, QKV 35.2 / 31.4, O and down 92.7 /
-// 88.6.  (With every load held in its place, see pin_loads: half of the gain of the 97 rows, 64 rows 43.1 -> 41.9 in gate/up.)
+// each CU.  In steps, us, always four / as dealt: 48 rows (7B shape) gate/up 43.0 / 38.3, QKV 31.6 / 29.8, O and down together
+// 38.4 / 36.1; 97 rows 66.0 / 61.0, 41.3 / 38.9, 54.1 / 52.2; 144 rows of the 8B shape, QKV 34.4 / 30.1, O and down 92.5 / 84.5.
 // The first `larger` groups have RBG blocks, the others RBG - 1 (a division in the kernel would cost it 0.2 us).
 template <int RBG>
 __device__ inline int group_first(int larger) { return (int)blockIdx.z * (RBG - 1) + min((int)blockIdx.z, larger); }
@@ -1655,8 +1654,9 @@ GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, in
   return best;
 }
 
-// Time of an unsplit wide launch of `wgs` workgroups, in us: 8 us around the loop, and a turn of it (64 of k) that is longer
-// the more of the chip streams weights.
+// Time of an unsplit wide launch of `wgs` workgroups whose row groups all have four blocks, in us: 8 us around the loop, and a turn
+// of it (64 of k) that is longer the more of the chip streams weights.  Groups of three are faster: 80 and 144 rows cost it what 128
+// and 192 do.
 double wide_us(int nwn, int wgs, int K) {
   constexpr double turn_us[5] = {0.0, 0.0, 0.905, 1.04, 1.24};
   return (wgs + kCUs - 1) / kCUs * 8.0 + K / 64 * turn_us[nwn] * wgs / kCUs;
@@ -1776,9 +1776,20 @@ GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, in
   // 65 - 255 rows, an unsplit wide kernel: the halves of its k range can run as the two ranges of the tile kernel, added in
   // the same order.  Worth it where the wide kernel reads the weights in several rounds, or k is long against the tile
   // kernel's start-up and hand-over (5 us and 4.5 us per 64 features of the tile beyond plan_tiles' estimate).  Both sides
-  // measured, wide / tile, us: 97 rows, gate/up of the 7B shape 68 / 73 and of the 8B shape 77 / 81, the same of the 13B
-  // shape (K = 5120) 95 / 92 and its QKV 76 / 62, LM heads of 32000 tokens with K = 2048 49 / 55, K = 4096 87 / 86, K = 8192
-  // 161 / 144, of 128256 tokens 390 / 293; 144 rows, gate/up of the 8B shape 123 / 102.
+  // measured in steps, wide / tile, us, 80 - 97 - 128 rows and 144 - 176 - 192; * what the rule takes:
+  //   gate/up  7B   57* - 60* - 63* / 69 - 70 - 70                (144 rows and more: split, the rule does not apply)
+  //            8B   68* - 72* - 75* / 78 - 79 - 79                109 - 118 - 117 / 95* - 97* - 99*
+  //            13B  85 - 89 - 92 / 89* - 90* - 91*                137 - 142 - 144 / 112* - 116* - 118*
+  //            d = 2048, F = 8192  25 - 26 - 27 / 31* - 31* - 31*
+  //   QKV      7B                                                 51 - 52 - 55 / 54* - 54* - 55*
+  //            13B  53 - 56 - 58 / 58* - 59* - 60*                63 - 64 - 68 / 70* - 70* - 70*
+  //   LM head of 32000 tokens
+  //     d = 2048    45* - 47* - 47* / 49 - 50 - 51                67 - 72 - 73 / 65* - 67* - 68*
+  //     d = 4096    83 - 83 - 84 / 79* - 84* - 85*                123 - 129 - 130 / 106* - 107* - 110*
+  //     d = 5120    96 - 99 - 100 / 102* - 100* - 100*            157 - 161 - 158 / 121* - 124* - 125*
+  //   of 128256     380 - 385 - 389 / 284* - 288* - 292*          548 - 557 - 558 / 380* - 389* - 395*
+  // The estimates know groups of four only, so the rule takes the tile kernel too early where groups have three (QKV of the 13B
+  // shape, 80 and 144 rows 10 %) and at d = 2048.
   if (rows_pad > 64 && best.nwn && best.splits == 1 && groups % 2 == 0) {
     double tile_us;
     GemmPlan p = plan_tiles(KRanges{0, 2, 1}, rows_pad, N, K, planes, part_elems, &tile_us);
