@@ -36,12 +36,12 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # f16 and bf16 dense MFMA peak
 PMC_FETCH_FACTOR = 2.0
 PMC_WRITE_FACTOR = 1.0
 PMC_KIB = {  # class: (FETCH_SIZE, WRITE_SIZE) mean per launch
-    "gemm_qkv": (63005.0, 14346.0),
-    "gemm_o": (21083.0, 6282.0),
-    "gemm_gate_up": (98621.0, 12395.0),
-    "gemm_down": (52187.0, 6282.0),
-    "gemm_lm_head": (136299.0, 16512.0),
-    "tree_attention_c2": (33615.0 + 4249.0, 8320.0 + 2048.0),  # split-KV kernel + merge kernel
+    "gemm_qkv": (62999.0, 14346.0),
+    "gemm_o": (21087.0, 6282.0),
+    "gemm_gate_up": (98720.0, 12395.0),
+    "gemm_down": (52191.0, 6282.0),
+    "gemm_lm_head": (136273.0, 16512.0),
+    "tree_attention_c2": (33621.0 + 4246.0, 8320.0 + 512.0),  # split-KV kernel + merge kernel
 }
 
 
