@@ -1655,8 +1655,8 @@ GemmPlan plan_tiles(const KRanges& r, int rows_pad, int N, int K, int planes, in
 }
 
 // Time of an unsplit wide launch of `wgs` workgroups whose row groups all have four blocks, in us: 8 us around the loop, and a turn
-// of it (64 of k) that is longer the more of the chip streams weights.  Groups of three are faster: 80 and 144 rows cost it what 128
-// and 192 do.
+// of it (64 of k) that is longer the more of the chip streams weights.  (Groups of three are faster; 80 and 144 rows are taken for
+// 128 and 192 here.)
 double wide_us(int nwn, int wgs, int K) {
   constexpr double turn_us[5] = {0.0, 0.0, 0.905, 1.04, 1.24};
   return (wgs + kCUs - 1) / kCUs * 8.0 + K / 64 * turn_us[nwn] * wgs / kCUs;
@@ -1707,6 +1707,7 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
     else hipLaunchKernelGGL((gemm_wide_kernel<NWN, PLANES, EPI, ONCE, 3>), grid_wide, dim3(NWN * 128), 0, s, DED_ARGS);              \
   }
   if (plan.nwn == 0) {
+    // (one or two wavefronts: short k, refilled at once whatever the launch; O of d = 1024, 192 rows, us, together / at once 10.6 / 10.3)
     const bool rounds = (int64_t)grid_stream.x * grid_stream.y * grid_stream.z > kCUs;
     if (nw == 4) {
       if (once) DED_STREAM(4, READ_ONCE) else if (rounds) DED_STREAM(4, READ_ROUNDS) else DED_STREAM(4, READ_SHARED)
