@@ -230,9 +230,9 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
   const int L = c.n_layers;
   auto bytes = [&](int64_t n) { return (size_t)n * z.elem; };
 
-  // bf16 matrices are re-laid-out with the feature count padded to a multiple of 64
+  // matrices are re-laid-out: bf16 with the feature count padded to a multiple of 64, fp32 to whole tiles of 16 x 16
   auto wbytes = [&](int64_t n_out, int64_t k_in) {
-    return bytes((c.dtype == DED_BF16 ? (n_out + 63) / 64 * 64 : n_out) * k_in);
+    return c.dtype == DED_BF16 ? bytes((n_out + 63) / 64 * 64 * k_in) : (size_t)f32_packed_floats(n_out, k_in) * 4;
   };
   char* emb = w.take<char>(bytes(V * d));
   char* lm = w.take<char>(wbytes(V, d));
@@ -251,7 +251,7 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
   for (int l = 0; l < L; ++l) {
     char* a = w.take<char>(wbytes(qkv_n, d));
     char* b = w.take<char>(wbytes(d, qd));
-    char* g = w.take<char>(wbytes(2 * F, d));
+    char* g = w.take<char>(c.dtype == DED_BF16 ? wbytes(2 * F, d) : 2 * wbytes(F, d));
     char* dn = w.take<char>(wbytes(d, F));
     float* na = w.take<float>(d);
     float* nf = w.take<float>(d);
@@ -266,7 +266,7 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
   }
   void** dkc = w.take<void*>(std::max(L, 1));
   void** dvc = w.take<void*>(std::max(L, 1));
-  float* x = w.take<float>((int64_t)z.max_rows_pad * d);
+  float* x = w.take<float>(c.dtype == DED_BF16 ? (int64_t)z.max_rows_pad * d : f32_packed_floats(z.max_rows_pad, d));
   float* logits = w.take<float>((int64_t)z.max_rows_pad * V);
   float2* tab = w.take<float2>((int64_t)z.max_rows * (c.head_dim / 2));
   if (ctx) {
@@ -278,8 +278,8 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
   }
   if (c.dtype == DED_F32) {
     float* qkv = w.take<float>((int64_t)z.max_rows_pad * qkv_n);
-    float* o = w.take<float>((int64_t)z.max_rows_pad * qd);
-    float* h = w.take<float>((int64_t)z.max_rows_pad * F);
+    float* o = w.take<float>(f32_packed_floats(z.max_rows_pad, qd));
+    float* h = w.take<float>(f32_packed_floats(z.max_rows_pad, F));
     if (ctx) {
       ctx->f_qkv = qkv;
       ctx->f_o = o;
@@ -505,10 +505,10 @@ int forward_f32(ded_ctx* c) {
   const int d = md.d, qd = md.H * md.hd, kvd = md.Hkv * md.hd, qkv_n = qd + 2 * kvd, F = md.F;
   { ProfScope p(c, KC_ROPE_TABLE); launch_rope_table(c->rope_tab, m.pos, m.rows, md.hd, md.rope_base, s); }
   { ProfScope p(c, KC_EMBED); f32_embed(c->x, (const float*)c->emb, m, d, s); }
-  auto gemm = [&](int cls, int kind, float* y, const float* x, const void* w, const float* gain, int N, int K, int l) {
+  auto gemm = [&](int cls, int kind, float* y, const float* x, const void* w, int N, int K, int l) {
     F32Gemm g = {};
     g.kind = kind;
-    g.Y = y, g.X = x, g.W = (const float*)w, g.gain = gain;
+    g.Y = y, g.X = x, g.W = (const float*)w;
     g.eps = md.eps;
     g.rows = m.rows, g.N = N, g.K = K;
     if (kind == F32_QKV) {
@@ -522,14 +522,14 @@ int forward_f32(ded_ctx* c) {
   };
   for (int l = 0; l < md.n_layers; ++l) {
     const bool fused = md.hd % 32 == 0;
-    gemm(KC_GEMM_QKV, fused ? F32_QKV : F32_STORE, c->f_qkv, c->x, c->wqkv[l], c->norm_attn[l], qkv_n, d, l);
+    gemm(KC_GEMM_QKV, fused ? F32_QKV : F32_STORE, c->f_qkv, c->x, c->wqkv[l], qkv_n, d, l);
     if (!fused) { ProfScope p(c, KC_QKV_EPILOGUE); f32_rope_kv(c->f_qkv, (float*)c->kc[l], (float*)c->vc[l], c->rope_tab, m, md, s); }
     { ProfScope p(c, KC_TREE_ATTN); f32_tree_attention(c->f_o, c->f_qkv, qkv_n, (const float*)c->kc[l], (const float*)c->vc[l], m, md, s); }
-    gemm(KC_GEMM_O, F32_RESIDUAL, c->x, c->f_o, c->wo[l], nullptr, d, qd, l);
-    gemm(KC_GEMM_GATE_UP, F32_SILU, c->f_h, c->x, c->wgu[l], c->norm_ffn[l], 2 * F, d, l);
-    gemm(KC_GEMM_DOWN, F32_RESIDUAL, c->x, c->f_h, c->wdown[l], nullptr, d, F, l);
+    gemm(KC_GEMM_O, F32_RESIDUAL, c->x, c->f_o, c->wo[l], d, qd, l);
+    gemm(KC_GEMM_GATE_UP, F32_SILU, c->f_h, c->x, c->wgu[l], 2 * F, d, l);
+    gemm(KC_GEMM_DOWN, F32_RESIDUAL, c->x, c->f_h, c->wdown[l], d, F, l);
   }
-  gemm(KC_GEMM_LM_HEAD, F32_STORE, c->logits, c->x, c->lm_head, c->final_norm, md.V, d, 0);
+  gemm(KC_GEMM_LM_HEAD, F32_STORE, c->logits, c->x, c->lm_head, md.V, d, 0);
   return launch_status();
 }
 
@@ -823,15 +823,19 @@ int ded_verify_init(const ded_config* cfg, const ded_weights* w, const ded_kv* k
   INIT_TRY(copy_gain(c->final_norm, w->final_norm));
   INIT_TRY(hipMemcpyAsync(c->emb, w->emb, (size_t)V * d * z.elem, hipMemcpyDeviceToDevice, s));
   if (!c->bf16) {
-    INIT_TRY(hipMemcpyAsync(c->lm_head, w->lm_head, (size_t)V * d * 4, hipMemcpyDeviceToDevice, s));
+    // (packed with the gain of the norm before the projection)
+    auto pack = [&](void* dst, const void* src, const float* gain, int64_t n, int64_t k) {
+      f32_pack_weight((float*)dst, (const float*)src, gain, (int)n, (int)k, s);
+    };
+    pack(c->lm_head, w->lm_head, w->final_norm, V, d);
     for (int l = 0; l < L; ++l) {
-      INIT_TRY(hipMemcpyAsync(c->wqkv[l], w->wqkv[l], (size_t)qkv_n * d * 4, hipMemcpyDeviceToDevice, s));
-      INIT_TRY(hipMemcpyAsync(c->wo[l], w->wo[l], (size_t)d * qd * 4, hipMemcpyDeviceToDevice, s));
-      INIT_TRY(hipMemcpyAsync(c->wgu[l], w->wgate_up[l], (size_t)2 * F * d * 4, hipMemcpyDeviceToDevice, s));
-      INIT_TRY(hipMemcpyAsync(c->wdown[l], w->wdown[l], (size_t)d * F * 4, hipMemcpyDeviceToDevice, s));
-      INIT_TRY(copy_gain(c->norm_attn[l], w->norm_attn[l]));
-      INIT_TRY(copy_gain(c->norm_ffn[l], w->norm_ffn[l]));
+      pack(c->wqkv[l], w->wqkv[l], w->norm_attn[l], qkv_n, d);
+      pack(c->wo[l], w->wo[l], nullptr, d, qd);
+      pack(c->wgu[l], w->wgate_up[l], w->norm_ffn[l], F, d);
+      pack((float*)c->wgu[l] + f32_packed_floats(F, d), (const float*)w->wgate_up[l] + F * d, w->norm_ffn[l], F, d);
+      pack(c->wdown[l], w->wdown[l], nullptr, d, F);
     }
+    INIT_TRY(hipGetLastError());
   } else {
     bf16_pack_weight((bf16_t*)c->lm_head, (const bf16_t*)w->lm_head, (int)V, (int)d, PERM_NONE, s);
     for (int l = 0; l < L; ++l) {

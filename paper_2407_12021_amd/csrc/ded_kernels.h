@@ -52,20 +52,25 @@ void launch_export_logits(float* dst, const float* src, int64_t src_stride, cons
 void launch_accept_walk(const StepMeta& m, const int32_t* amax, const int32_t* row_flag, int mode, int32_t* out_n,
                         int32_t* out_flag, int32_t* out_path, int32_t* out_tok, int stride, hipStream_t s);
 
-// ---- fp32 path (plain row-major everywhere; cache [B][Hkv][cap][hd]) ---------------------
+// ---- fp32 path (cache [B][Hkv][cap][hd], queries and logits row-major; weights and projection inputs "packed": tiles of
+// 16 rows x 16 k, see kernels_f32.hip) ------------------------------------------------------
+// floats of a packed matrix
+inline int64_t f32_packed_floats(int64_t rows, int64_t k) { return (rows + 15) / 16 * ((k + 15) / 16) * 256; }
+// dst = packed W[N][K] * gain[k] (gain null: 1)
+void f32_pack_weight(float* dst, const float* src, const float* gain, int N, int K, hipStream_t s);
 void f32_embed(float* x, const float* emb, const StepMeta& m, int d, hipStream_t s);
 // Y[r][n] = sum_k X[r][k] W[n][k] with a fused neighbour on either side.  All kinds but F32_RESIDUAL normalise their
-// input rows: X[r] is taken as x * gain / sqrt(mean(x^2) + eps).
+// input rows, X[r] / sqrt(mean(x^2) + eps); the norm's gain is part of W.  X and W are packed.
 enum {
   F32_STORE = 0,     // Y = result, row stride N
-  F32_RESIDUAL = 1,  // Y += result
-  F32_SILU = 2,      // W holds gate and up features one after the other: Y = silu(gate) * up, row stride N / 2
+  F32_RESIDUAL = 1,  // Y += result, packed
+  F32_SILU = 2,      // W = packed gate features, then packed up features, N / 2 each: Y = silu(gate) * up, packed
   F32_QKV = 3        // queries rotated into Y (row stride N), keys rotated / values into the cache; hd % 32 == 0
 };
 struct F32Gemm {
   int kind;
   float* Y;
-  const float *X, *W, *gain;
+  const float *X, *W;
   float eps;
   int rows, N, K;  // rows % 16 == 0
   // F32_QKV
@@ -87,7 +92,7 @@ void f32_kv_copy(float* cache, float* plain, bool to_cache, int seq, int first, 
 void f32_kv_clear(float* kc, float* vc, int seq, int first, int n, const ModelDims& md, hipStream_t s);
 void f32_scatter_tree_kv(float* kc, float* vc, const float* k_tree, const float* v_tree,
                          const StepMeta& m, const ModelDims& md, int max_nodes, hipStream_t s);
-// q [B][max_nodes][H][hd] -> qkv-style rows [R][H*hd]; and back for the output
+// q [B][max_nodes][H][hd] -> qkv-style rows [R][H*hd]; and the packed attention output -> [B][max_nodes][H][hd]
 void f32_gather_rows(float* dst, const float* src, const StepMeta& m, int max_nodes, int width,
                      bool to_padded, hipStream_t s);
 

@@ -38,210 +38,234 @@ __device__ inline float block_max_256(float v, float* sh) {
 }
 
 // ------------------------------------------------------------------------------------------
-__global__ void f32_embed_kernel(float* __restrict__ x, const float* __restrict__ emb,
-                                 const int32_t* __restrict__ token, int d) {
-  int r = blockIdx.x;
-  const float* src = emb + (int64_t)token[r] * d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) x[(int64_t)r * d + i] = src[i];
+// Operands of the projections lie in memory as the matrix instructions read them ("packed"): a matrix of R rows (features of
+// a weight, tree rows of an activation) and K columns is cut into tiles of 16 rows x 16 k, 1 KiB each, the tiles of 16 rows
+// one after the other along k.  Inside a tile lane = (k / 4 % 4) * 16 + row % 16 holds four consecutive k, so one load
+// instruction of a wavefront fetches a whole tile from 1 KiB of contiguous memory, and a result tile of the 16x16x4
+// instruction (lane = (feature / 4 % 4) * 16 + row) is stored as the next projection's input without a shuffle.  Row-major
+// operands cost 16 rows x 64 bytes per load instruction, all 16 on the same memory channel where the row stride is a
+// power of two.  K and the features are padded with zeros to whole tiles.
+__host__ __device__ inline int tiles16(int n) { return (n + 15) / 16; }
+__device__ inline int64_t packed_unit(int r, int k, int kt) {  // in units of four floats; kt = tiles16(K)
+  return ((int64_t)(r >> 4) * kt + (k >> 4)) * 64 + ((k >> 2) & 3) * 16 + (r & 15);
+}
+
+// dst = packed W[n][k] * gain[k] (gain null: 1).  The RMSNorm gain of a projection's input multiplies here, once, instead of
+// every input element in every workgroup: one fp32 rounding per product either way.
+__global__ __launch_bounds__(256) void f32_pack_weight_kernel(float4* __restrict__ dst, const float* __restrict__ src,
+                                                              const float* __restrict__ gain, int N, int K, int kt) {
+  const int lane = threadIdx.x & 63, k = ((blockIdx.x * 4 + (threadIdx.x >> 6)) * 4 + (lane >> 4)) * 4;
+  const int n = blockIdx.y * 16 + (lane & 15);
+  if (k >= kt * 16) return;
+  float v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v[i] = n < N && k + i < K ? src[(int64_t)n * K + k + i] : 0.f;
+    if (gain && k + i < K) v[i] *= gain[k + i];
+  }
+  dst[((int64_t)blockIdx.y * kt + (k >> 4)) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+}
+void f32_pack_weight(float* dst, const float* src, const float* gain, int N, int K, hipStream_t s) {
+  const int kt = tiles16(K), nt = tiles16(N);
+  for (int n0 = 0; n0 < nt; n0 += 32768) {  // (grid limit of the second dimension)
+    const int n = std::min(nt - n0, 32768);
+    hipLaunchKernelGGL(f32_pack_weight_kernel, dim3((kt + 3) / 4, n), dim3(256), 0, s,
+                       reinterpret_cast<float4*>(dst) + (int64_t)n0 * kt * 64, src + (int64_t)n0 * 16 * K, gain, N - n0 * 16, K, kt);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// x (packed) = emb[token]; a wavefront takes one tile of 16 rows x 16 dims
+__global__ __launch_bounds__(256) void f32_embed_kernel(float4* __restrict__ x, const float* __restrict__ emb,
+                                                        const int32_t* __restrict__ token, int d, int kt) {
+  const int lane = threadIdx.x & 63, c = blockIdx.y * 4 + (threadIdx.x >> 6), k = c * 16 + (lane >> 4) * 4;
+  if (c >= kt) return;
+  const float* src = emb + (int64_t)token[blockIdx.x * 16 + (lane & 15)] * d + k;
+  float v[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = k + i < d ? src[i] : 0.f;
+  x[((int64_t)blockIdx.x * kt + c) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
 }
 void f32_embed(float* x, const float* emb, const StepMeta& m, int d, hipStream_t s) {
-  hipLaunchKernelGGL(f32_embed_kernel, dim3(m.rows), dim3(256), 0, s, x, emb, m.token, d);
+  hipLaunchKernelGGL(f32_embed_kernel, dim3(m.rows / 16, (tiles16(d) + 3) / 4), dim3(256), 0, s, reinterpret_cast<float4*>(x),
+                     emb, m.token, d, tiles16(d));
 }
 
 // ------------------------------------------------------------------------------------------
 // Projections with fused neighbours:  Y[r][n] = sum_k X[r][k] W[n][k], X optionally RMS-normalised on the way in, Y
-// going into what the decoder does with it (F32_* in ded_kernels.h).
+// going into what the decoder does with it (F32_* in ded_kernels.h).  X and W are packed (above).
 //
-// A workgroup owns FT x RT tiles of 16 features x 16 rows; its 8 wavefronts split k in chunks of 32, taken in turn, and
-// meet in LDS.  Operands go straight from memory to registers: a lane fetches 16 bytes of its feature (row), so four
-// lanes cover 64 contiguous bytes of it, and component j of those registers is the operand of the j-th matrix
-// instruction (both operands permute k alike).  Splitting k over the wavefronts is what fills the chip at the sizes of
-// this path (a d = 256 model has 16 feature tiles per projection) and keeps the chain of dependent loads short.
-// RMSNorm is applied as (x * gain) . W * (1 / rms): the wavefronts form sum(x^2) from the operands they load anyway.
-// Bound by latency and L2 reads at these sizes, not by the matrix instructions.  Measured at 160 rows, gate/up of
-// N = 5632, K = 1024: 34.5 us (about 480 us for one wavefront per feature walking the rows by vector arithmetic).
-template <int FT, int RT, int EPI, bool VEC>
-__global__ __launch_bounds__(512) void f32_mfma_gemm_kernel(F32Gemm g) {
+// A workgroup owns FT x RT tiles of 16 features x 16 rows; its 8 wavefronts take the k tiles in turn and meet in LDS.
+// Operands go straight from memory to registers, D k tiles ahead; component j of a lane's 16 bytes is the operand of the
+// j-th matrix instruction (both operands permute k alike).  Splitting k over the wavefronts is what fills the chip at the
+// sizes of this path (a d = 256 model has 16 feature tiles per projection) and keeps the chain of dependent loads short.
+// RMSNorm is applied as (W * gain) . x * (1 / rms): the wavefronts form sum(x^2) from the operands they load anyway.
+// Bound by the fp32 matrix instructions (64 flop per cycle and SIMD) and, the smaller the tile the more, by the operands into
+// each CU: 2 KiB per 32 cycles of matrix work with 1 x 1 tiles, 6 KiB per 256 with 4 x 2.  160 rows, K = 1024, us with
+// row-major operands and the gain multiplied into every input / now: gate/up of N = 5632 37.6 / 17.2 (matrix instructions
+// alone: 11.7), QKV of N = 3072 22.2 / 9.8, LM head of N = 8192 45.4 / 24.  Deeper rings are slower: 448 rows, gate/up,
+// 4 x 2 tiles, 2 / 3 / 4 k tiles ahead: 42.5 / 44.9 / 98 (spilled); 2 x 2, 3 / 4 / 6: 45.4 / 50.7 / 54.6.
+template <int FT, int RT, int D, int EPI>
+__global__ __launch_bounds__(512, 4) void f32_mfma_gemm_kernel(F32Gemm g) {
   constexpr int NW = 8;
-  constexpr bool NORM = EPI != F32_RESIDUAL;
+  constexpr bool NORM = EPI != F32_RESIDUAL, PAIRED = EPI == F32_SILU || EPI == F32_QKV;
+  constexpr int UF = PAIRED ? FT / 2 : FT;  // a unit = a feature tile, or a pair of partner tiles (t, t + UF)
+  static_assert(!PAIRED || FT % 2 == 0, "partner tiles come in pairs");
+  static_assert(UF * RT <= NW, "one wavefront finishes one unit of one row block");
   __shared__ float4 red[NW][FT * RT][64];
   __shared__ float s_ss[NORM ? NW : 1][RT][16];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m16 = lane & 15, quad = lane >> 4;
-  const int bx = blockIdx.x, rb0 = blockIdx.y * RT, nrb = g.rows / 16, K = g.K;
-  const int half = g.hd / 2;
-  int n0[FT], n_end[FT];  // first feature of each tile and the end of its matrix part
-#pragma unroll
-  for (int t = 0; t < FT; ++t) {
-    if (EPI == F32_SILU) {
-      n0[t] = t * (g.N / 2) + bx * 16;
-      n_end[t] = (t + 1) * (g.N / 2);
-    } else if (EPI == F32_QKV) {
-      const int per = half / 16, hs = bx / per, p = bx - hs * per;
-      n0[t] = hs * g.hd + p * 16 + t * half;
-      n_end[t] = g.N;
-    } else {
-      n0[t] = (bx * FT + t) * 16;
-      n_end[t] = g.N;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // (scalar: addresses are a scalar base and the lane)
+  const unsigned lane = threadIdx.x & 63, m16 = lane & 15, quad = lane >> 4;
+  const int nrb = g.rows / 16, kt = tiles16(g.K), half = g.hd / 2;
+  // Workgroups go to the 8 XCDs in turn: every XCD gets a contiguous share of the feature units, the row groups of a unit
+  // next to each other, so that a unit's weights come into one L2 only.
+  const int n_rg = (nrb + RT - 1) / RT, xcd = blockIdx.x & 7, share = gridDim.x >> 3, rest = gridDim.x & 7;
+  const int lin = xcd * share + min(xcd, rest) + (blockIdx.x >> 3);
+  const int u0 = lin / n_rg * UF, rb0 = (lin - lin / n_rg * n_rg) * RT;
+  const int n_units = EPI == F32_SILU ? tiles16(g.N / 2) : EPI == F32_QKV ? g.N / 32 : tiles16(g.N);
+  // the feature tile of unit u (PAIRED: of its first partner) and its partner's
+  auto tile_of = [&](int u, int second) {
+    if (EPI == F32_SILU) return second * n_units + u;
+    if (EPI == F32_QKV) {
+      const int per = half / 16, hs = u / per;
+      return hs * 2 * per + (u - hs * per) + second * per;
     }
-  }
-  const float *wp[FT], *xp[RT];
-#pragma unroll
-  for (int t = 0; t < FT; ++t) wp[t] = g.W + (int64_t)min(n0[t] + m16, n_end[t] - 1) * K;
-#pragma unroll
-  for (int t = 0; t < RT; ++t) xp[t] = g.X + (int64_t)(min(rb0 + t, nrb - 1) * 16 + m16) * K;
-  // four consecutive k of one row (VEC: K % 4 == 0, one 16-byte load); TAIL: zero past the row's end
-  auto load4 = [&](const float* q, int k, auto tail) {
-    constexpr bool TAIL = decltype(tail)::value;
-    v4f v = v4f{0.f, 0.f, 0.f, 0.f};
-    if constexpr (VEC) {
-      if (!TAIL || k < K) v = *reinterpret_cast<const v4f*>(q + k);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (!TAIL || k + i < K) v[i] = q[k + i];
-    }
-    return v;
+    return u;
   };
+  const char *wp[FT], *xp[RT];
+#pragma unroll
+  for (int t = 0; t < FT; ++t)
+    wp[t] = reinterpret_cast<const char*>(g.W) + (int64_t)tile_of(min(u0 + t % UF, n_units - 1), t / UF) * kt * 1024;
+#pragma unroll
+  for (int t = 0; t < RT; ++t) xp[t] = reinterpret_cast<const char*>(g.X) + (int64_t)min(rb0 + t, nrb - 1) * kt * 1024;
+  // what this wavefront finishes after the reduction
+  const int fu = wave % UF, rt = wave / UF, u = u0 + fu, rb = rb0 + rt, r = rb * 16 + m16;
+  const bool finishes = wave < UF * RT && u < n_units && rb < nrb;
+  // (the residual's old values are requested first: they have arrived by then)
+  const int64_t at = ((int64_t)rb * tiles16(g.N) + u) * 64 + lane;
+  v4f old = v4f{0.f, 0.f, 0.f, 0.f};
+  if (EPI == F32_RESIDUAL && finishes) old = reinterpret_cast<const v4f*>(g.Y)[at];
   v4f acc[FT][RT];
   float ss[RT];
 #pragma unroll
-  for (int r = 0; r < RT; ++r) {
-    ss[r] = 0.f;
+  for (int i = 0; i < RT; ++i) {
+    ss[i] = 0.f;
 #pragma unroll
-    for (int t = 0; t < FT; ++t) acc[t][r] = v4f{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < FT; ++t) acc[t][i] = v4f{0.f, 0.f, 0.f, 0.f};
   }
   struct Chunk {
-    v4f w[FT][2], x[RT][2], gain[2];
+    v4f w[FT], x[RT];
   };
-  auto load = [&](int c, auto tail) {
-    Chunk q;
+  auto load = [&](Chunk& q, int c) {
+    const uint32_t off = (uint32_t)c * 1024 + lane * 16;
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int k = c * 32 + j * 16 + quad * 4;
+    for (int t = 0; t < FT; ++t) q.w[t] = *reinterpret_cast<const v4f*>(wp[t] + off);
 #pragma unroll
-      for (int t = 0; t < FT; ++t) q.w[t][j] = load4(wp[t], k, tail);
+    for (int t = 0; t < RT; ++t) q.x[t] = *reinterpret_cast<const v4f*>(xp[t] + off);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  auto compute = [&](const Chunk& q) {
+    if (NORM) {
 #pragma unroll
-      for (int t = 0; t < RT; ++t) q.x[t][j] = load4(xp[t], k, tail);
-      if (NORM) q.gain[j] = load4(g.gain, k, tail);
+      for (int i = 0; i < RT; ++i) {
+        const v4f x = q.x[i];
+        ss[i] += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+      }
     }
-    return q;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int t = 0; t < FT; ++t)
+#pragma unroll
+        for (int j = 0; j < RT; ++j)
+          acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(q.w[t][i], q.x[j][i], acc[t][j], 0, 0, 0);
   };
-  auto compute = [&](Chunk& q) {
+  // k tiles wave, wave + 8, ...: D in flight; the last turns load only what there is
+  if (wave < kt) {
+    const int n = (kt - wave + NW - 1) / NW;
+    Chunk st[D];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      if (NORM) {
+    for (int i = 0; i < D; ++i) load(st[i], wave + min(i, n - 1) * NW);
+    int c = 0;
+    for (; c + 2 * D <= n; c += D) {
 #pragma unroll
-        for (int r = 0; r < RT; ++r) {
-          const v4f x = q.x[r][j];
-          ss[r] += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
-          q.x[r][j] = x * q.gain[j];
-        }
+      for (int i = 0; i < D; ++i) {
+        compute(st[i]);
+        load(st[i], wave + (c + D + i) * NW);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i)
+      if (c + i < n) {
+        compute(st[i]);
+        if (c + D + i < n) load(st[i], wave + (c + D + i) * NW);
       }
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int t = 0; t < FT; ++t)
-#pragma unroll
-          for (int r = 0; r < RT; ++r)
-            acc[t][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(q.w[t][j][i], q.x[r][j][i], acc[t][r], 0, 0, 0);
-    }
-  };
-  // whole chunks: two in flight per wavefront (fetches past the share re-read its last chunk); what K leaves over goes
-  // to the wavefront whose turn it would be
-  const int n_full = K / 32, last = n_full - 1 - (n_full - 1 - wave) % NW;
-  if (wave < n_full) {
-    Chunk a = load(wave, std::false_type{});
-    for (int c = wave;;) {
-      Chunk b = load(min(c + NW, last), std::false_type{});
-      compute(a);
-      if ((c += NW) > last) break;
-      a = load(min(c + NW, last), std::false_type{});
-      compute(b);
-      if ((c += NW) > last) break;
-    }
-  }
-  if (K % 32 && wave == n_full % NW) {
-    Chunk t = load(n_full, std::true_type{});
-    compute(t);
+    for (int i = 0; i < D; ++i)
+      if (c + D + i < n) compute(st[i]);
   }
   // the wavefronts' k shares meet in LDS, added in wavefront order
 #pragma unroll
   for (int t = 0; t < FT; ++t)
 #pragma unroll
-    for (int r = 0; r < RT; ++r) red[wave][t * RT + r][lane] = make_float4(acc[t][r][0], acc[t][r][1], acc[t][r][2], acc[t][r][3]);
+    for (int j = 0; j < RT; ++j) red[wave][t * RT + j][lane] = make_float4(acc[t][j][0], acc[t][j][1], acc[t][j][2], acc[t][j][3]);
   if (NORM) {
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      float v = ss[r];
+    for (int i = 0; i < RT; ++i) {
+      float v = ss[i];
       v += __shfl_xor(v, 16);
       v += __shfl_xor(v, 32);
-      if (quad == 0) s_ss[wave][r][m16] = v;
+      if (quad == 0) s_ss[wave][i][m16] = v;
     }
   }
   __syncthreads();
-  if (wave >= RT || rb0 + wave >= nrb) return;
-  const int rt = wave, r = (rb0 + rt) * 16 + m16;
+  if (!finishes) return;
   float scale = 1.f;
   if (NORM) {
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) v += s_ss[w][rt][m16];
-    scale = 1.0f / sqrtf(v / (float)K + g.eps);
+    scale = 1.0f / sqrtf(v / (float)g.K + g.eps);
   }
-  float y[FT][4];
+  v4f y[PAIRED ? 2 : 1];
 #pragma unroll
-  for (int t = 0; t < FT; ++t) {
+  for (int t = 0; t < (PAIRED ? 2 : 1); ++t) {
     v4f v = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float4 q = red[w][t * RT + rt][lane];
+      const float4 q = red[w][(t * UF + fu) * RT + rt][lane];
       v += v4f{q.x, q.y, q.z, q.w};
     }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) y[t][i] = NORM ? v[i] * scale : v[i];
+    y[t] = NORM ? v * scale : v;
   }
-  // four consecutive outputs; 16-byte accesses where the row stride allows them
-  auto put = [&](float* dst, const float (&v)[4], int n, int limit, bool aligned) {
-    if (aligned && n + 3 < limit) {
-      *reinterpret_cast<float4*>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+  if (EPI == F32_RESIDUAL) {  // packed, like the old values
+    reinterpret_cast<v4f*>(g.Y)[at] = y[0] + old;
+  } else if (EPI == F32_STORE) {  // row-major
+    const int n = u * 16 + quad * 4;
+    float* dst = g.Y + (int64_t)r * g.N + n;
+    if ((g.N & 3) == 0) {
+      if (n < g.N) *reinterpret_cast<v4f*>(dst) = y[0];
     } else {
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        if (n + i < limit) dst[i] = v[i];
+        if (n + i < g.N) dst[i] = y[0][i];
     }
-  };
-  if (EPI == F32_STORE || EPI == F32_RESIDUAL) {
-    const bool aligned = (g.N & 3) == 0;
+  } else if (EPI == F32_SILU) {  // packed: the down projection's input (features past F come out as 0)
+    v4f h;
 #pragma unroll
-    for (int t = 0; t < FT; ++t) {
-      const int n = n0[t] + quad * 4;
-      float* dst = g.Y + (int64_t)r * g.N + n;
-      if (EPI == F32_RESIDUAL) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (n + i < g.N) y[t][i] += dst[i];
-      }
-      put(dst, y[t], n, g.N, aligned);
-    }
-  } else if (EPI == F32_SILU) {
-    const int F = g.N / 2, f = bx * 16 + quad * 4;
-    float h[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) h[i] = y[0][i] / (1.0f + expf(-y[0][i])) * y[FT - 1][i];
-    put(g.Y + (int64_t)r * F + f, h, f, F, (F & 3) == 0);
+    for (int i = 0; i < 4; ++i) h[i] = y[0][i] / (1.0f + expf(-y[0][i])) * y[PAIRED][i];
+    reinterpret_cast<v4f*>(g.Y)[((int64_t)rb * n_units + u) * 64 + lane] = h;
   } else {  // F32_QKV: rotate queries and keys, queries stay in the row, keys and values go to cache slot P + node
-    const int per = half / 16, hs = bx / per, d0 = (bx - hs * per) * 16 + quad * 4;
-    const int b = g.m.blk_seq[r >> 4], node = r - g.m.row0[b];
+    const int per = half / 16, hs = u / per, d0 = (u - hs * per) * 16 + quad * 4;
+    const int b = g.m.blk_seq[rb], node = r - g.m.row0[b];
     const bool real = node < g.m.seq_n[b];
-    float lo[4], hi[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) lo[i] = y[0][i], hi[i] = y[FT - 1][i];
+    v4f lo = y[0], hi = y[PAIRED];
     if (hs < g.H + g.Hkv) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float2 cs = g.tab[(int64_t)r * half + d0 + i];
-        lo[i] = y[0][i] * cs.x - y[FT - 1][i] * cs.y;
-        hi[i] = y[FT - 1][i] * cs.x + y[0][i] * cs.y;
+        lo[i] = y[0][i] * cs.x - y[PAIRED][i] * cs.y;
+        hi[i] = y[PAIRED][i] * cs.x + y[0][i] * cs.y;
       }
     }
     float* dst = nullptr;
@@ -252,49 +276,45 @@ __global__ __launch_bounds__(512) void f32_mfma_gemm_kernel(F32Gemm g) {
       dst = (hs < g.H + g.Hkv ? g.kc : g.vc) + (((int64_t)b * g.Hkv + kvh) * g.cap + g.m.seq_p[b] + node) * g.hd;
     }
     if (dst) {
-      *reinterpret_cast<cache_v4f*>(dst + d0) = cache_v4f{lo[0], lo[1], lo[2], lo[3]};
-      *reinterpret_cast<cache_v4f*>(dst + d0 + half) = cache_v4f{hi[0], hi[1], hi[2], hi[3]};
+      *reinterpret_cast<cache_v4f*>(dst + d0) = lo;
+      *reinterpret_cast<cache_v4f*>(dst + d0 + half) = hi;
     }
   }
 }
 
-// Tiles per workgroup by a cost fitted to a sweep (16 - 512 rows, the six shapes of the models above and the tiny one):
-// a workgroup alone on its CU takes 3 us + K / 1024 * (1.1 us per operand tile it fetches + 0.85 us per tile product),
-// and w workgroups per CU (counted in halves: the larger tiles run two at a time) take max(1, 0.95 w) times that.  160 rows: QKV (N = 3072, K = 1024) 34.6 us with 1 x 1 tiles,
-// 18.7 with 2 x 2, 15.5 with 4 x 2; O (1024, 1024) 13.7 / 10.3 / 16.8; 512 rows, gate/up (5632, 1024): 88 us with 2 x 2,
-// 74 with 2 x 4.  16 rows, d = 256: 3.7 us with 1 x 1, 5.1 with 2 x 2.
+// Tiles per workgroup: the shape whose busiest CU is done first.  A workgroup takes `us` microseconds per 1024 of K of its CU
+// (fitted to 16 - 448 rows, N = 256 - 16000, K = 256 - 3200; most launches within 10 %).  160 rows, us with 1 x 1 / 2 x 1 /
+// 2 x 2 / 4 x 2 tiles: gate/up (N = 5632, K = 1024) - / 18.0 / 19.0 / 17.2, O (1024, 1024) 4.6 / 4.8 / 4.8 / 8.0, down
+// (1024, 2816) 12.6 / 12.7 / 10.9 / 20, LM head (8192, 1024) 31 / 27.7 / 23.9 / 26.5; 448 rows, LM head 79 / 68.7 / 63.4 / 60.
 void f32_gemm(const F32Gemm& g, hipStream_t s) {
   if (g.rows <= 0) return;
   const int nrb = g.rows / 16;
-  const bool vec = g.K % 4 == 0, paired = g.kind == F32_SILU || g.kind == F32_QKV;
-  auto units = [&](int ft) {
-    return g.kind == F32_SILU ? (g.N / 2 + 15) / 16 : g.kind == F32_QKV ? g.N / 32 : (g.N + 16 * ft - 1) / (16 * ft);
+  const bool paired = g.kind == F32_SILU || g.kind == F32_QKV;
+  const int units = g.kind == F32_SILU ? tiles16(g.N / 2) : g.kind == F32_QKV ? g.N / 32 : tiles16(g.N);
+  auto groups = [&](int ft, int rt) {  // workgroups of ft x rt tiles
+    const int uf = paired ? ft / 2 : ft;
+    return (units + uf - 1) / uf * ((nrb + rt - 1) / rt);
   };
-  int FT = 2, RT = 2;
-  if (vec) {
-    static const int shapes[][2] = {{1, 1}, {2, 1}, {2, 2}, {2, 4}, {4, 2}};
-    double best = 1e300;
-    for (const auto& sh : shapes) {
-      if (paired ? sh[0] != 2 : sh[0] == 2 && sh[1] == 1) continue;
-      const double one = 3.0 + g.K / 1024.0 * (1.1 * (sh[0] + sh[1]) + 0.85 * sh[0] * sh[1]);
-      const double per_cu = std::ceil(units(sh[0]) * ((nrb + sh[1] - 1) / sh[1]) / 128.0) / 2;
-      const double cost = one * std::max(1.0, 0.95 * per_cu);
-      if (cost < best) best = cost, FT = sh[0], RT = sh[1];
-    }
+  static const struct {
+    int ft, rt;
+    double us;
+  } shapes[] = {{1, 1, 1.55}, {2, 1, 2.45}, {2, 2, 4.45}, {4, 2, 8.3}};
+  int FT = 2, RT = 1;
+  double best = 1e300;
+  for (const auto& sh : shapes) {
+    if (paired && sh.ft == 1) continue;
+    const double cost = sh.us * ((groups(sh.ft, sh.rt) + 255) / 256);
+    if (cost < best) best = cost, FT = sh.ft, RT = sh.rt;
   }
-#define DED_F32_GO(FT, RT, EPI, VEC) \
-  hipLaunchKernelGGL((f32_mfma_gemm_kernel<FT, RT, EPI, VEC>), dim3(units(FT), (nrb + RT - 1) / RT), dim3(512), 0, s, g)
-#define DED_F32_PAIRED(EPI)                        \
-  if (!vec) DED_F32_GO(2, 2, EPI, false);          \
-  else if (RT == 1) DED_F32_GO(2, 1, EPI, true);   \
-  else if (RT == 2) DED_F32_GO(2, 2, EPI, true);   \
-  else DED_F32_GO(2, 4, EPI, true)
-#define DED_F32_PLAIN(EPI)                         \
-  if (!vec) DED_F32_GO(2, 2, EPI, false);          \
-  else if (FT == 1) DED_F32_GO(1, 1, EPI, true);   \
-  else if (FT == 4) DED_F32_GO(4, 2, EPI, true);   \
-  else if (RT == 2) DED_F32_GO(2, 2, EPI, true);   \
-  else DED_F32_GO(2, 4, EPI, true)
+#define DED_F32_GO(FT, RT, D, EPI) \
+  hipLaunchKernelGGL((f32_mfma_gemm_kernel<FT, RT, D, EPI>), dim3(groups(FT, RT)), dim3(512), 0, s, g)
+#define DED_F32_PAIRED(EPI)                    \
+  if (FT == 4) DED_F32_GO(4, 2, 2, EPI);       \
+  else if (RT == 2) DED_F32_GO(2, 2, 3, EPI);  \
+  else DED_F32_GO(2, 1, 4, EPI)
+#define DED_F32_PLAIN(EPI)                     \
+  if (FT == 1) DED_F32_GO(1, 1, 4, EPI);       \
+  else DED_F32_PAIRED(EPI)
   switch (g.kind) {
     case F32_STORE: DED_F32_PLAIN(F32_STORE); break;
     case F32_RESIDUAL: DED_F32_PLAIN(F32_RESIDUAL); break;
@@ -364,10 +384,13 @@ __global__ __launch_bounds__(256) void f32_tree_attention_kernel(
   __shared__ float sacc[256];
   int r = blockIdx.x, h = blockIdx.y;
   int b = blk_seq[r >> 4], node = r - row0[b];
-  float* out = o + ((int64_t)r * H + h) * hd;
+  auto put = [&](int i, float v) {  // packed, the O projection's input
+    const int k = h * hd + i;
+    o[packed_unit(r, k, tiles16(H * hd)) * 4 + (k & 3)] = v;
+  };
   int nb = seq_n[b];
   if (node >= nb) {
-    for (int i = threadIdx.x; i < hd; i += 256) out[i] = 0.f;
+    for (int i = threadIdx.x; i < hd; i += 256) put(i, 0.f);
     return;
   }
   int P = seq_p[b];
@@ -428,7 +451,7 @@ __global__ __launch_bounds__(256) void f32_tree_attention_kernel(
   if (threadIdx.x < hd) {
     float t = 0.f;
     for (int p = 0; p < parts; ++p) t += sacc[p * hd + threadIdx.x];
-    out[threadIdx.x] = t / l_run;
+    put(threadIdx.x, t / l_run);
   }
 }
 // Matrix-core form for head dims of 16 and more.  One workgroup per (16-row block, query head); its NW wavefronts take
@@ -540,7 +563,7 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
       const float4 t = s_o[w][c][lane];
       v += v4f{t.x, t.y, t.z, t.w} * f[w];
     }
-    *reinterpret_cast<float4*>(o + ((int64_t)r * H + h) * HD + c * 16 + quad * 4) =
+    reinterpret_cast<float4*>(o)[((int64_t)blockIdx.x * (H * DT) + h * DT + c) * 64 + lane] =  // packed, the O projection's input
         make_float4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
   }
 }
@@ -645,7 +668,8 @@ void f32_scatter_tree_kv(float* kc, float* vc, const float* k_tree, const float*
                      k_tree, v_tree, m.seq_p, m.seq_n, md.Hkv, md.hd, md.cap, max_nodes);
 }
 
-// rows of real nodes between the caller's [B][max_nodes][width] and the padded [R][width] buffers
+// rows of real nodes from the caller's [B][max_nodes][width] to the padded [R][width] queries, and of the packed attention
+// output to the caller
 __global__ void f32_gather_rows_kernel(float* __restrict__ dst, const float* __restrict__ src,
                                        const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
                                        const int32_t* __restrict__ blk_seq, int max_nodes, int width, int to_padded) {
@@ -655,7 +679,7 @@ __global__ void f32_gather_rows_kernel(float* __restrict__ dst, const float* __r
   int64_t pad = (int64_t)r * width, ext = ((int64_t)b * max_nodes + node) * width;
   for (int i = threadIdx.x; i < width; i += blockDim.x) {
     if (to_padded) dst[pad + i] = real ? src[ext + i] : 0.f;
-    else if (real) dst[ext + i] = src[pad + i];
+    else if (real) dst[ext + i] = src[packed_unit(r, i, tiles16(width)) * 4 + (i & 3)];
   }
 }
 void f32_gather_rows(float* dst, const float* src, const StepMeta& m, int max_nodes, int width,

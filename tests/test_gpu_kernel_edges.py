@@ -81,6 +81,26 @@ def test_fp32_projections_and_attention_at_tile_edges(case):
     assert err <= 1e-4
 
 
+# the packed operands' larger tiles, with feature and row tiles that do not divide into them: 4 x 2 in gate/up and LM head over
+# fewer k tiles than wavefronts (K = 52); 4 x 2, then 2 x 2, over an odd number of k tiles (K = 1040)
+FP32_TILES = [
+    ((52, 4, 2, 32, 2810, 16003), [7, 40, 3], [33, 61, 17]),
+    ((1040, 2, 2, 64, 48, 8190), [5, 20], [16, 48]),
+    ((1040, 2, 1, 64, 100, 4090), [9], [50]),
+]
+
+
+@pytest.mark.parametrize("case", range(len(FP32_TILES)))
+def test_fp32_projections_of_every_tile(case):
+    """Bound: sums of at most 2810 products of O(1) terms round to ~1e-5; the fp32 path's 1e-4 logit tolerance."""
+    (d, H, Hkv, hd, F, V), prefix_len, nodes = FP32_TILES[case]
+    cfg = di.ModelConfig(f"f32-tile{case}", 2, d, H, Hkv, hd, F, V, dtype="fp32")
+    w = di.make_weights(cfg, seed=70 + case, gain_jitter=0.1, std=0.05)
+    err = _step_error(cfg, w, prefix_len, nodes, seed=80 + case)
+    print(f"max |logit error| {err:.2e}")
+    assert err <= 1e-4
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 def test_cache_rows_come_back_and_neighbours_stay(dtype):
     """Ranges that start, end or lie inside a 32-slot group of the cache: rows come back bit for bit (bf16 values widen to
