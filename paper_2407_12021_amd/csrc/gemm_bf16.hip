@@ -274,7 +274,7 @@ __device__ inline float ssq_scale(const GemmEpilogue& e, int lane, int nwv, cons
 template <int EPI, int RBN, int T = TN, bool RAGGED = false, typename A>
 __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb0, int rbase, float row_scale, int lane,
                                     A& acc, int t0 = 0) {
-  // (RAGGED: row blocks from e.rb_total on are surplus ones of a last row tile, nothing is written for them)
+  // (RAGGED: rows from e.rows on are surplus ones of a last row tile, nothing is written for them)
   const int row_in = lane & 15, quad = lane >> 4;
   float scale[RBN];
 #pragma unroll
@@ -286,7 +286,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     uint4* dst = reinterpret_cast<uint4*>(e.top2_part);
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (RAGGED && rbase + rb >= e.rb_total) continue;
+      if (RAGGED && (rbase + rb) * 16 >= e.rows) continue;
       const int64_t r = (int64_t)(rbase + rb) * 16 + row_in;
       float v1 = -INFINITY, v2 = -INFINITY;
       int i1 = 0x7fffffff, bad = 0;
@@ -341,7 +341,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     // x += Y;  next GEMM input = (x * gain) as hi/lo f16 (its 1/rms is applied by the consumer);  sum(x^2) per group
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (RAGGED && rbase + rb >= e.rb_total) continue;
+      if (RAGGED && (rbase + rb) * 16 >= e.rows) continue;
       const int r = (rbase + rb) * 16 + row_in;
       float ss = 0.f;
 #pragma unroll
@@ -369,7 +369,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     // group ng = gate features [32 ng, 32 ng + 32) in tiles 0, 1 and the matching up features in tiles 2, 3
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (RAGGED && rbase + rb >= e.rb_total) continue;
+      if (RAGGED && (rbase + rb) * 16 >= e.rows) continue;
       const int r = (rbase + rb) * 16 + row_in;
 #pragma unroll
       for (int t = 0; t < T / 2; ++t) {
@@ -390,7 +390,7 @@ __device__ inline void run_epilogue(const GemmEpilogue& e, int ng, int N, int rb
     const int G = e.H / e.Hkv;
 #pragma unroll
     for (int rb = 0; rb < RBN; ++rb) {
-      if (RAGGED && rbase + rb >= e.rb_total) continue;
+      if (RAGGED && (rbase + rb) * 16 >= e.rows) continue;
       const int r = (rbase + rb) * 16 + row_in;
       if (r >= e.rows) continue;
       const int b = e.blk_seq[r >> 4], node = r - e.row0[b];
@@ -1164,11 +1164,22 @@ __global__ __launch_bounds__(NWMAX * 64) void gemm_slim_kernel(const uint4* __re
 // ------------------------------------------------------------------------------------------
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) const void glb_void_t;
-// lane i: 16 bytes at base + its offset -> dst[i].  (The offset is kept from view, as 32 bits: the compiler otherwise holds
-// a 64-bit one per load across the loop, or spills it.)
+// lane i: 16 bytes at base + its offset -> dst[i].  (The offset is kept from view, as 32 bits: the compiler otherwise holds a
+// 64-bit one per load across the loop, or spills it.)
+// BUFFER: nothing where the offset is NO_LOAD, past the buffer's end, which the hardware checks.  With global loads to LDS in
+// flight the compiler waits for every LDS read before it uses the first, which is what costs the tiles that read and multiply
+// in one step (gate/up of the 8B shape, 2048 rows, us, global / buffer: 776 / 759).  The tiles that read a step ahead wait for
+// all reads anyway, and setting up the buffer costs them (gate/up of the 7B shape, 256 rows: 100 / 103).
+constexpr uint32_t NO_LOAD = 0xf0000000u;
+template <bool BUFFER>
 __device__ __forceinline__ void load_to_lds(const char* base, uint32_t offset, uint4* dst) {
   asm volatile("" : "+v"(offset));
-  __builtin_amdgcn_global_load_lds((glb_void_t*)(base + offset), (lds_void_t*)dst, 16, 0, 0);
+  if constexpr (BUFFER) {
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, NO_LOAD, 0x00020000);
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)dst, 16, offset, 0, 0, 0);
+  } else {
+    __builtin_amdgcn_global_load_lds((glb_void_t*)(base + offset), (lds_void_t*)dst, 16, 0, 0);
+  }
 }
 template <int N>
 __device__ __forceinline__ void wait_loads() {  // all but the last N vector-memory operations, and every LDS read, are done
@@ -1249,6 +1260,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
   }
   if (item >= end) return;
   const int64_t xstep = (int64_t)RB << 11;  // bytes of activations per k step
+  const int real_rb = epi.rows >> 4;        // row blocks that exist: the operands are padded to 64 rows, and the last row tile may reach past them
 
   // The segment whose slots are being requested: tile, k range in slots, slots left to request; operand addresses as a
   // wavefront-uniform base that moves with k and a lane offset per load that is fixed inside a tile.
@@ -1271,22 +1283,23 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
 #pragma unroll
     for (int j = 0; j < WJ; ++j) {
       const int f = j * TILE_WAVES + wave;
-      const int g = min(f >> 2, NG - 1 - tf * FG);  // surplus feature groups / row blocks re-read a valid one
+      const int g = min(f >> 2, NG - 1 - tf * FG);  // surplus feature groups re-read a valid one
       woff[j] = (((uint32_t)g * KT) << 12) + ((f & 3) << 10) + (lane << 4);
     }
 #pragma unroll
     for (int j = 0; j < XJ; ++j) {
       const int f = min(j * TILE_WAVES + wave, XF - 1);
-      const int rb = min(f / PLANES, RB - 1 - rb_tile), p = f % PLANES;
-      xoff[j] = ((uint32_t)rb << 11) + (p << 10) + (lane << 4);
+      // (surplus row blocks are not fetched, or, by global loads, a valid one again; what becomes of them is not stored)
+      const int rb = f / PLANES, p = f % PLANES, valid = min(rb, real_rb - 1 - rb_tile);
+      xoff[j] = AHEAD || rb == valid ? ((uint32_t)valid << 11) + (p << 10) + (lane << 4) : NO_LOAD;
     }
   };
   auto request = [&](uint4* slot) {
 #pragma unroll
-    for (int j = 0; j < WJ; ++j) load_to_lds(wbase, woff[j], slot + (j * TILE_WAVES + wave) * 64);
+    for (int j = 0; j < WJ; ++j) load_to_lds<!AHEAD>(wbase, woff[j], slot + (j * TILE_WAVES + wave) * 64);
 #pragma unroll
     for (int j = 0; j < XJ; ++j)
-      load_to_lds(xbase, xoff[j], slot + (WF + min(j * TILE_WAVES + wave, XF - 1)) * 64);
+      load_to_lds<!AHEAD>(xbase, xoff[j], slot + (WF + min(j * TILE_WAVES + wave, XF - 1)) * 64);
     // (past the segment's end its last slot is read again, so that the loads in flight stay countable)
     --req_left;
     wbase += req_left > 0 ? 1 << 12 : 0;
@@ -1372,7 +1385,8 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
   request_first();
   for (int par = 0;; par ^= 1) {
     const int cur_tile = tile, cur_part = part_id, n = kp_end - kp;
-    const int tf = cur_tile / row_tiles, rb_tile = (cur_tile - tf * row_tiles) * RBT;
+    const int tf = cur_tile / row_tiles, rb_tile = (cur_tile - tf * row_tiles) * RBT, rbw = rb_tile + rg * RBW;
+    const bool any_rows = rbw < real_rb;  // (otherwise this wavefront has nothing to store)
     // (lane numbers of their own for what happens once per tile: the addresses derived from them would otherwise be
     // formed ahead of the loop over tiles and held, or spilled, across the products)
     int ltid = tid, llane = lane;
@@ -1426,12 +1440,12 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
       }
     } else {
       for (int c = 0; c < n; c += ST) {
-        step_direct(ring0, ST == 3 ? ring2 : ST == 4 ? ring3 : ring5, true);
-        step_direct(ring1, ring0, c + 1 < n);
-        step_direct(ring2, ring1, c + 2 < n);
-        if constexpr (ST > 3) step_direct(ring3, ring2, c + 3 < n);
-        if constexpr (ST > 4) step_direct(ring4, ring3, c + 4 < n);
-        if constexpr (ST > 4) step_direct(ring5, ring4, c + 5 < n);
+        step_direct(ring0, ST == 3 ? ring2 : ST == 4 ? ring3 : ring5, any_rows);
+        step_direct(ring1, ring0, any_rows && c + 1 < n);
+        step_direct(ring2, ring1, any_rows && c + 2 < n);
+        if constexpr (ST > 3) step_direct(ring3, ring2, any_rows && c + 3 < n);
+        if constexpr (ST > 4) step_direct(ring4, ring3, any_rows && c + 4 < n);
+        if constexpr (ST > 4) step_direct(ring5, ring4, any_rows && c + 5 < n);
       }
     }
     wait_loads<0>();
@@ -1445,8 +1459,7 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
     }
 
     // finish the tile, or hand this workgroup's part of it over
-    const int rbw = rb_tile + rg * RBW;
-    bool finish = rbw < RB;
+    bool finish = any_rows;
     if (cur_part >= 0 && finish) {
       constexpr int WT_ELEMS = GPW * TN * RBW * 256;  // a wavefront tile, in accumulator order
       constexpr int NF = GPW * TN * RBW, CF = S::ACC_REGS > 64 ? 2 : 4;  // its fragments; fragments summed together

@@ -188,12 +188,13 @@ def test_projections_at_tile_edges(case):
 
 
 # (d, H, Hkv, F, V) of one layer, prefix lengths, tree sizes, (N, K) of the projections that the tile kernel runs: steps of 97,
-# 144 and 70 rows whose unsplit products run as two k ranges of the tile kernel, rows that fill no whole tile, a vocabulary
-# that ends inside a feature group
+# 144, 70 and 176 rows whose unsplit products run as two k ranges of the tile kernel, rows that fill no whole tile (wavefronts
+# without rows, and with a surplus block), a vocabulary that ends inside a feature group
 MID_EDGES = [
     ((2048, 16, 4, 8192, 65552), [5], [97], [(16384, 2048), (65552, 2048)]),
     ((4096, 32, 8, 14336, 32016), [3, 0, 40], [37, 21, 50], [(28672, 4096), (32016, 4096)]),
     ((5120, 40, 40, 1408, 1040), [9], [70], [(15360, 5120)]),
+    ((4096, 32, 8, 14336, 32016), [7, 0, 9], [64, 50, 48], [(28672, 4096), (32016, 4096)]),
 ]
 
 
