@@ -4,6 +4,7 @@
 #include "ded_kernels.h"
 
 #include <algorithm>
+#include <cmath>
 #include <cstring>
 #include <mutex>
 #include <new>
@@ -17,6 +18,7 @@ namespace {
 constexpr int kMaskWords = 4;   // ancestor bitmask words per row (max_nodes <= 256)
 constexpr int kMaxNodes = 256;
 constexpr int64_t kAttnPartRows = 1 << 17;  // split-KV partial rows the workspace reserves at least
+constexpr size_t kMetaMirrorBytes = 1 << 20;  // of pinned slots for step descriptions (at least two slots, at most 16)
 constexpr int kGemmCounters = 1 << 16;      // split-K arrival tickets (a GEMM with more output tiles runs unsplit)
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
@@ -26,6 +28,7 @@ enum KClass {
   KC_META = 0, KC_ROPE_TABLE, KC_EMBED, KC_GEMM_QKV, KC_QKV_EPILOGUE, KC_TREE_ATTN, KC_GEMM_O, KC_GEMM_GATE_UP,
   KC_GEMM_DOWN, KC_GEMM_LM_HEAD, KC_ARGMAX, KC_EXPORT, KC_WALK, KC_COMPACT, KC_LAYOUT, KC_SAMPLE, KC_TOP2_REDUCE, KC_COUNT
 };
+// (rope_table and export_logits count no launches: the embedding and the argmax do that work)
 const char* const kClassNames[KC_COUNT] = {
     "meta_upload", "rope_table", "embed", "gemm_qkv", "qkv_rope_epilogue", "tree_attention", "gemm_o", "gemm_gate_up",
     "gemm_down", "gemm_lm_head", "argmax", "export_logits", "accept_walk", "kv_compact", "layout_convert", "sample_top_p",
@@ -125,21 +128,24 @@ struct ded_ctx {
   float2* attn_part_ml = nullptr;
   int64_t attn_part_rows = 0;
   void* top2_part = nullptr;  // [rows_pad][ceil(V / 64)] x 16 B: per-group candidates of the fused LM-head argmax
-  // step meta (device + pinned host mirror, one contiguous block)
+  // step meta (device + pinned host mirror, one contiguous block).  The mirror has several slots that calls take in turn, in
+  // two halves: entering a half, a call waits for the calls that used it the last time round.
   char* d_meta = nullptr;
-  char* h_meta = nullptr;
+  char* h_meta = nullptr;  // the present slot
   size_t meta_bytes = 0;
-  hipEvent_t meta_ev = nullptr;  // completion of the last upload from h_meta
-  bool meta_inflight = false;
+  char *h_meta_slots = nullptr, *h_meta_slots_dev = nullptr;
+  int meta_slots = 0, meta_slot = 0;
+  char* h_meta_dev = nullptr;  // the present slot as kernels address it: the first kernel of a call reads it there
+  hipEvent_t meta_ev[2] = {};  // what had been enqueued when the half was left
+  bool meta_left[2] = {};
   MetaOffsets off;  // of the pending step: the block is packed to the step's own row count
   // results
+  // (the three lie one after the other, packed to the step's rows: one copy brings them to the host)
   int32_t* d_amax = nullptr;
   float* d_margin = nullptr;
   int32_t* d_rowflag = nullptr;  // [rows] != 0: the row's logits hold a NaN or an infinity
-  int32_t* d_seqflag = nullptr;  // [max_batch] the same per sequence (real nodes only), written by the walk
-  float* d_uniform = nullptr;  // [rows] uniform numbers of ded_sample
-  int32_t *d_nacc = nullptr, *d_path = nullptr, *d_acctok = nullptr;
-  char* h_res = nullptr;  // pinned: amax | margin | row flags, or nacc | seqflag | path | acctok
+  // pinned: amax | margin | row flags, or uniform numbers | row flags, or nacc | seqflag | path | acctok
+  char *h_res = nullptr, *h_res_dev = nullptr;
   size_t res_bytes = 0;
   // state of the pending step
   bool pending = false;
@@ -176,6 +182,19 @@ struct ded_ctx {
     m.n_step = n_step;
     m.rows = rows;
     return m;
+  }
+  size_t meta_units() const { return (off.bytes + 15) / 16; }  // (the blocks end on a multiple of 256 bytes)
+  StepFront front() const {
+    const StepMeta h = meta_at(h_meta_dev);
+    StepFront f;
+    f.meta_src = reinterpret_cast<const uint4*>(h_meta_dev);
+    f.meta_dst = reinterpret_cast<uint4*>(d_meta);
+    f.units = (int)meta_units();
+    f.token = h.token, f.pos = h.pos;
+    f.tab = rope_tab;
+    f.rows = rows, f.half = md.hd / 2;
+    f.neg2_over_hd_log2base = -2.0 / (double)md.hd * log2((double)md.rope_base);
+    return f;
   }
 };
 
@@ -319,28 +338,11 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
   // step meta block
   const size_t m = align_up(MetaOffsets(z.max_rows, c.max_batch).bytes, 256);
   char* dmeta = w.take<char>(m);
-  int stride = c.max_nodes + 1;
-  int32_t* amax = w.take<int32_t>(z.max_rows_pad);
-  float* margin = w.take<float>(z.max_rows_pad);
-  float* uniform = w.take<float>(z.max_rows_pad);
-  int32_t* rowflag = w.take<int32_t>(z.max_rows_pad);
-  // one block, so that a single copy brings a step's verdict to the host: nacc | seqflag | path | acctok
-  int32_t* nacc = w.take<int32_t>((int64_t)c.max_batch * (2 + 2 * stride));
-  // (no arithmetic on the null pointers of a sizing pass)
-  int32_t* seqflag = nacc ? nacc + c.max_batch : nullptr;
-  int32_t* path = nacc ? seqflag + c.max_batch : nullptr;
-  int32_t* acct = nacc ? path + (int64_t)c.max_batch * stride : nullptr;
+  int32_t* amax = w.take<int32_t>((int64_t)z.max_rows_pad * 3);  // and margins and flags, see ingest
   if (ctx) {
     ctx->d_meta = dmeta;
     ctx->meta_bytes = m;
     ctx->d_amax = amax;
-    ctx->d_margin = margin;
-    ctx->d_uniform = uniform;
-    ctx->d_rowflag = rowflag;
-    ctx->d_seqflag = seqflag;
-    ctx->d_nacc = nacc;
-    ctx->d_path = path;
-    ctx->d_acctok = acct;
   }
   return align_up(w.off, 256);
 }
@@ -418,8 +420,9 @@ int validate_step(const ded_config& cfg, int32_t batch, const int32_t* prefix_le
   return DED_OK;
 }
 
-int ingest_and_upload(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const int32_t* n_nodes,
-                      const int32_t* parent, const int32_t* token, char* d_meta_dst = nullptr) {
+// The description of a call, into the next slot of the pinned mirror.
+int ingest(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const int32_t* n_nodes, const int32_t* parent,
+           const int32_t* token) {
   const ded_config& cfg = c->cfg;
   int nmax = 0, pmax = 0, rows = 0;
   c->s_row0.resize(batch);
@@ -429,14 +432,22 @@ int ingest_and_upload(ded_ctx* c, int32_t batch, const int32_t* prefix_len, cons
     c->s_row0[b] = rows;
     rows += round_up(n_nodes[b], 16);
   }
-  if (c->meta_inflight) {  // the pinned mirror may still be feeding the previous upload
-    HIP_TRY(hipEventSynchronize(c->meta_ev));
-    c->meta_inflight = false;
+  const int half = c->meta_slots / 2;
+  c->meta_slot = (c->meta_slot + 1) % c->meta_slots;
+  if (c->meta_slot % half == 0) {
+    const int now = c->meta_slot / half, left = 1 - now;
+    HIP_TRY(hipEventRecord(c->meta_ev[left], c->stream));
+    c->meta_left[left] = true;
+    if (c->meta_left[now]) HIP_TRY(hipEventSynchronize(c->meta_ev[now]));
   }
+  c->h_meta = c->h_meta_slots + c->meta_slot * c->meta_bytes;
+  c->h_meta_dev = c->h_meta_slots_dev + c->meta_slot * c->meta_bytes;
   c->batch = batch;
   c->n_step = round_up(nmax, 16);
   c->rows = rows;
   c->off = MetaOffsets(rows, batch);
+  c->d_margin = reinterpret_cast<float*>(c->d_amax + rows);
+  c->d_rowflag = c->d_amax + 2 * (size_t)rows;
   c->max_p = pmax;
   c->s_p.assign(prefix_len, prefix_len + batch);
   c->s_n.assign(n_nodes, n_nodes + batch);
@@ -485,13 +496,6 @@ int ingest_and_upload(ded_ctx* c, int32_t batch, const int32_t* prefix_len, cons
       h_pos[r] = P + h_depth[r];
     }
   }
-  {
-    ProfScope ps(c, KC_META);
-    HIP_TRY(hipMemcpyAsync(d_meta_dst ? d_meta_dst : c->d_meta, c->h_meta, c->off.bytes, hipMemcpyHostToDevice,
-                           c->stream));
-  }
-  HIP_TRY(hipEventRecord(c->meta_ev, c->stream));
-  c->meta_inflight = true;
   return DED_OK;
 }
 
@@ -503,8 +507,7 @@ int forward_f32(ded_ctx* c) {
   StepMeta m = c->meta();
   hipStream_t s = c->stream;
   const int d = md.d, qd = md.H * md.hd, kvd = md.Hkv * md.hd, qkv_n = qd + 2 * kvd, F = md.F;
-  { ProfScope p(c, KC_ROPE_TABLE); launch_rope_table(c->rope_tab, m.pos, m.rows, md.hd, md.rope_base, s); }
-  { ProfScope p(c, KC_EMBED); f32_embed(c->x, (const float*)c->emb, m, d, s); }
+  { ProfScope p(c, KC_EMBED); f32_embed(c->x, (const float*)c->emb, c->front(), d, s); }
   auto gemm = [&](int cls, int kind, float* y, const float* x, const void* w, int N, int K, int l) {
     F32Gemm g = {};
     g.kind = kind;
@@ -639,8 +642,7 @@ int forward_bf16(ded_ctx* c, bool want_logits, float* logits_out) {
     e.inv_k = 1.0f / (float)d;
   };
   auto next_gain = [&](int l) { return l < L ? c->norm_attn[l] : c->final_norm; };
-  { ProfScope p(c, KC_ROPE_TABLE); launch_rope_table(c->rope_tab, m.pos, m.rows, md.hd, md.rope_base, s); }
-  { ProfScope p(c, KC_EMBED); bf16_embed(c->x, c->y_p, c->ssq, (const bf16_t*)c->emb, next_gain(0), m, rows_pad, d, s); }
+  { ProfScope p(c, KC_EMBED); bf16_embed(c->x, c->y_p, c->ssq, (const bf16_t*)c->emb, next_gain(0), c->front(), rows_pad, d, s); }
   for (int l = 0; l < L; ++l) {
     {
       GemmEpilogue e = base;
@@ -781,13 +783,19 @@ int ded_verify_init(const ded_config* cfg, const ded_weights* w, const ded_kv* k
   };
   int stride = cfg->max_nodes + 1;
   c->res_bytes = align_up((size_t)z.max_rows_pad * 12 + (size_t)cfg->max_batch * 4 * (2 + 2 * stride), 256);
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_meta), c->meta_bytes, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&c->h_res), c->res_bytes, hipHostMallocDefault) != hipSuccess) {
+  // (coherent: kernels read and write them while they run)
+  const unsigned kind = hipHostMallocMapped | hipHostMallocCoherent;
+  c->meta_slots = (int)std::max<size_t>(2, std::min<size_t>(16, kMetaMirrorBytes / c->meta_bytes) / 2 * 2);
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_meta_slots), c->meta_bytes * c->meta_slots, kind) != hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&c->h_res), c->res_bytes, kind) != hipSuccess ||
+      hipHostGetDevicePointer(reinterpret_cast<void**>(&c->h_meta_slots_dev), c->h_meta_slots, 0) != hipSuccess ||
+      hipHostGetDevicePointer(reinterpret_cast<void**>(&c->h_res_dev), c->h_res, 0) != hipSuccess) {
     (void)hipGetLastError();
     return fail(DED_EHIP);
   }
-  memset(c->h_meta, 0, c->meta_bytes);
-  if (hipEventCreateWithFlags(&c->meta_ev, hipEventDisableTiming) != hipSuccess) {
+  memset(c->h_meta_slots, 0, c->meta_bytes * c->meta_slots);
+  if (hipEventCreateWithFlags(&c->meta_ev[0], hipEventDisableTiming) != hipSuccess ||
+      hipEventCreateWithFlags(&c->meta_ev[1], hipEventDisableTiming) != hipSuccess) {
     (void)hipGetLastError();
     return fail(DED_EHIP);
   }
@@ -858,8 +866,9 @@ void ded_verify_free(ded_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
   for (hipEvent_t e : c->ev_pool) (void)hipEventDestroy(e);
-  if (c->meta_ev) (void)hipEventDestroy(c->meta_ev);
-  if (c->h_meta) (void)hipHostFree(c->h_meta);
+  for (hipEvent_t e : c->meta_ev)
+    if (e) (void)hipEventDestroy(e);
+  if (c->h_meta_slots) (void)hipHostFree(c->h_meta_slots);
   if (c->h_res) (void)hipHostFree(c->h_res);
   delete c;
 }
@@ -870,7 +879,7 @@ int ded_verify_step(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const 
   int rc = validate_step(c->cfg, batch, prefix_len, n_nodes, parent, token, true);
   if (rc != DED_OK) return rc;
   if (c->poisoned && (rc = clear_step_slots(c)) != DED_OK) return rc;
-  rc = ingest_and_upload(c, batch, prefix_len, n_nodes, parent, token);
+  rc = ingest(c, batch, prefix_len, n_nodes, parent, token);
   if (rc != DED_OK) return rc;
   c->pending = false;
   c->have_argmax = false;
@@ -885,12 +894,8 @@ int ded_verify_step(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const 
     ProfScope p(c, KC_TOP2_REDUCE);
     launch_top2_reduce(c->top2_part, (c->md.V + 63) / 64, m.rows, c->d_amax, c->d_margin, c->d_rowflag, c->stream);
   } else {
-    { ProfScope p(c, KC_ARGMAX);
-      launch_argmax(c->logits, c->md.V, m.rows, c->md.V, c->d_amax, c->d_margin, c->d_rowflag, c->stream); }
-    if (logits_out) {
-      ProfScope p(c, KC_EXPORT);
-      launch_export_logits(logits_out, c->logits, c->md.V, m, c->cfg.max_nodes, c->md.V, c->stream);
-    }
+    ProfScope p(c, KC_ARGMAX);
+    launch_argmax(c->logits, m, c->md.V, c->d_amax, c->d_margin, c->d_rowflag, logits_out, c->cfg.max_nodes, c->stream);
   }
   c->have_logits = want_logits;
   rc = launch_status();
@@ -913,25 +918,22 @@ int ded_accept(ded_ctx* c, int32_t mode, int32_t* accepted_tokens, int32_t* n_ac
   }
   StepMeta m = c->meta();
   hipStream_t s = c->stream;
-  { ProfScope p(c, KC_WALK);
-    launch_accept_walk(m, c->d_amax, c->d_rowflag, mode, c->d_nacc, c->d_seqflag, c->d_path, c->d_acctok, stride, s); }
+  // nacc | seqflag | path | acctok, written by the kernel and read below
+  const int MB = c->cfg.max_batch;
+  int32_t* h_n = reinterpret_cast<int32_t*>(c->h_res);
+  int32_t *h_flag = h_n + MB, *h_path = h_flag + MB, *h_tok = h_path + (size_t)MB * stride;
+  auto on_device = [&](int32_t* p) { return reinterpret_cast<int32_t*>(c->h_res_dev + (reinterpret_cast<char*>(p) - c->h_res)); };
+  const ApprovalWalk w = {m.token, m.parent, m.seq_n, m.row0, c->d_amax, c->d_rowflag, B, mode, stride,
+                          on_device(h_n), on_device(h_flag), on_device(h_path), on_device(h_tok)};
   if (c->md.n_layers > 0 && mode == 0) {
     ProfScope p(c, KC_COMPACT);
-    if (c->bf16)
-      bf16_kv_compact((bf16_t* const*)c->d_kc, (bf16_t* const*)c->d_vc, c->d_path, c->d_nacc, m, c->md, stride, s);
-    else
-      f32_kv_compact((float* const*)c->d_kc, (float* const*)c->d_vc, c->d_path, c->d_nacc, m, c->md, stride, s);
+    if (c->bf16) bf16_kv_compact((bf16_t* const*)c->d_kc, (bf16_t* const*)c->d_vc, w, m, c->md, s);
+    else f32_kv_compact((float* const*)c->d_kc, (float* const*)c->d_vc, w, m, c->md, s);
+  } else {
+    ProfScope p(c, KC_WALK);
+    launch_accept_walk(w, s);
   }
   if (launch_status() != DED_OK) return DED_EHIP;
-  int32_t* h_n = reinterpret_cast<int32_t*>(c->h_res);
-  const int MB = c->cfg.max_batch;
-  int32_t* h_flag = h_n + MB;
-  int32_t* h_path = h_flag + MB;
-  int32_t* h_tok = h_path + (size_t)MB * stride;
-  // nacc | seqflag | path | acctok are one device block with the same layout: path and acctok of the live
-  // sequences end before (2 MB + (MB + B) * stride) words
-  HIP_TRY(hipMemcpyAsync(h_n, c->d_nacc, sizeof(int32_t) * (2 * (size_t)MB + (size_t)(MB + B) * stride),
-                         hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
   c->pending = false;
   for (int b = 0; b < B; ++b)
@@ -962,7 +964,6 @@ int ded_sample(ded_ctx* c, float temperature, float top_p, const float* uniform)
       if (!(u >= 0.f) || !(u < 1.f)) return DED_EINVAL;
       h_u[c->s_row0[b] + i] = u;
     }
-  HIP_TRY(hipMemcpyAsync(c->d_uniform, h_u, sizeof(float) * rows, hipMemcpyHostToDevice, c->stream));
   // A step keeps its logits only if the caller asked for them or the context has sampled before; the first
   // sampled step of a context recomputes them from the final residual stream, which is still in place.
   c->sampling_seen = true;
@@ -970,11 +971,11 @@ int ded_sample(ded_ctx* c, float temperature, float top_p, const float* uniform)
     if (!lm_head_bf16(c, true)) return DED_EINVAL;
     c->have_logits = true;
   }
+  const int32_t* h_f = reinterpret_cast<int32_t*>(c->h_res) + rows;  // written by the kernel
   { ProfScope p(c, KC_SAMPLE);
-    launch_sample_top_p(c->logits, c->md.V, c->meta(), c->md.V, temperature, top_p, c->d_uniform, c->d_amax, c->stream); }
+    launch_sample_top_p(c->logits, c->md.V, c->meta(), c->md.V, temperature, top_p, reinterpret_cast<const float*>(c->h_res_dev),
+                        c->d_rowflag, c->d_amax, reinterpret_cast<int32_t*>(c->h_res_dev) + rows, c->stream); }
   if (launch_status() != DED_OK) return DED_EHIP;
-  int32_t* h_f = reinterpret_cast<int32_t*>(c->h_res) + c->max_rows_pad;
-  HIP_TRY(hipMemcpyAsync(h_f, c->d_rowflag, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));  // h_res is free again
   for (int b = 0; b < c->batch; ++b)
     for (int i = 0; i < c->s_n[b]; ++i)
@@ -989,12 +990,10 @@ int ded_get_argmax(ded_ctx* c, int32_t* argmax, float* margin) {
   if (!c || !argmax) return DED_EINVAL;
   if (!c->have_argmax) return DED_ESTATE;
   const int rows = c->rows, mn = c->cfg.max_nodes;
-  int32_t* h_a = reinterpret_cast<int32_t*>(c->h_res);
-  float* h_m = reinterpret_cast<float*>(c->h_res) + c->max_rows_pad;
-  HIP_TRY(hipMemcpyAsync(h_a, c->d_amax, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(hipMemcpyAsync(h_m, c->d_margin, sizeof(float) * rows, hipMemcpyDeviceToHost, c->stream));
-  int32_t* h_f = reinterpret_cast<int32_t*>(c->h_res) + 2 * (size_t)c->max_rows_pad;
-  HIP_TRY(hipMemcpyAsync(h_f, c->d_rowflag, sizeof(int32_t) * rows, hipMemcpyDeviceToHost, c->stream));
+  const int32_t* h_a = reinterpret_cast<int32_t*>(c->h_res);
+  const float* h_m = reinterpret_cast<float*>(c->h_res) + rows;
+  const int32_t* h_f = h_a + 2 * (size_t)rows;
+  HIP_TRY(hipMemcpyAsync(c->h_res, c->d_amax, sizeof(int32_t) * 3 * (size_t)rows, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
   for (int b = 0; b < c->batch; ++b)
     for (int i = 0; i < c->s_n[b]; ++i)
@@ -1084,7 +1083,7 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
   } else if (st) {
     return DED_EINVAL;  // the fp32 path has no transient buffers of this kind
   }
-  rc = ingest_and_upload(c, batch, prefix_len, n_nodes, parent, nullptr, ws.d_meta);
+  rc = ingest(c, batch, prefix_len, n_nodes, parent, nullptr);
   if (rc != DED_OK) return rc;
   c->pending = false;
   c->have_argmax = false;
@@ -1094,11 +1093,14 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
   if (c->bf16) {
     const int rows_pad = round_up(m.rows, 64);
     { ProfScope p(c, KC_LAYOUT);
-      bf16_scatter_tree_kv((bf16_t*)c->kc[layer], (bf16_t*)c->vc[layer], (const bf16_t*)k_tree, (const bf16_t*)v_tree, m, md, mn, s); }
+      bf16_scatter_tree_kv((bf16_t*)c->kc[layer], (bf16_t*)c->vc[layer], (const bf16_t*)k_tree, (const bf16_t*)v_tree,
+                           c->meta_at(c->h_meta_dev), c->h_meta_dev, ws.d_meta, (int)c->meta_units(), md, mn, s); }
     { ProfScope p(c, KC_TREE_ATTN);
       bf16_tree_attention(nullptr, rows_pad, nullptr, (const bf16_t*)c->kc[layer], (const bf16_t*)c->vc[layer], ws.part_o,
                           ws.part_ml, ns, 1, m, md, s, (const bf16_t*)q, (bf16_t*)out, mn); }
   } else {
+    { ProfScope p(c, KC_META);
+      HIP_TRY(hipMemcpyAsync(ws.d_meta, c->h_meta, c->off.bytes, hipMemcpyHostToDevice, s)); }
     { ProfScope p(c, KC_LAYOUT);
       f32_scatter_tree_kv((float*)c->kc[layer], (float*)c->vc[layer], (const float*)k_tree, (const float*)v_tree, m, md, mn, s);
       f32_gather_rows(c->f_qkv, (const float*)q, m, mn, qd, true, s); }

@@ -29,28 +29,44 @@ struct ModelDims {
   float rope_base, eps;
 };
 
+// What the embedding kernels do beside the embedding (step_ends.h): the rotary table tab[r][i] = cos, sin of pos[r] *
+// base^(-2i/hd), i < half = hd/2, and the copy of the step's description from pinned host memory to the device.  token and
+// pos are read from the host's block, everything after from the device's.
+struct StepFront {
+  const uint4* meta_src;  // pinned host memory
+  uint4* meta_dst;
+  int units;  // 16 bytes each
+  const int32_t *token, *pos;
+  float2* tab;
+  int rows, half;
+  double neg2_over_hd_log2base;
+};
+// Approval walk (mode 0 greedy, mode 1 keep the whole chain), done by the kernels that compact the cache (step_ends.h).  The out_
+// arrays are pinned host memory: out_n, out_flag [B], out_path, out_tok [B][stride].  If a real row of any sequence is
+// flagged, every sequence gets out_n = 0, out_flag = 1.
+struct ApprovalWalk {
+  const int32_t *token, *parent, *seq_n, *row0, *amax, *row_flag;
+  int batch, mode, stride;
+  int32_t *out_n, *out_flag, *out_path, *out_tok;
+};
+
 // ---- shared (both dtypes) --------------------------------------------------------------
-// cos/sin of pos[r] * base^(-2i/hd), i < hd/2, angles formed in fp64.  tab: [R][hd/2] float2.
-void launch_rope_table(float2* tab, const int32_t* pos, int rows, int hd, float base, hipStream_t s);
 // Measurement aid: streams `bytes` (multiple of 16) of device memory through the CUs once.
 void launch_stream_read(const void* src, size_t bytes, uint32_t* sink, hipStream_t s);
 // Per-row argmax (lowest index on exact ties) and top-1 minus top-2 over V fp32 logits; flag[r] != 0 when the
-// row holds a NaN or an infinity.
-void launch_argmax(const float* logits, int64_t row_stride, int rows, int V, int32_t* amax,
-                   float* margin, int32_t* flag, hipStream_t s);
+// row holds a NaN or an infinity.  The rows of real nodes go to the caller's export_to [batch][max_nodes][V] too if it is not null.
+void launch_argmax(const float* logits, const StepMeta& m, int V, int32_t* amax, float* margin, int32_t* flag, float* export_to,
+                   int max_nodes, hipStream_t s);
 // The same from the candidates the LM-head GEMM leaves with EPI_TOP2: part [rows][groups] x 16 bytes.
 void launch_top2_reduce(const void* part, int groups, int rows, int32_t* amax, float* margin, int32_t* flag,
                         hipStream_t s);
 // Temperature / top-p sample of every real row (inverse CDF of uniform[r] over the nucleus in id order) -> token_out[r].
+// uniform and flag_out (the rows' flags once more) are pinned host memory.
 void launch_sample_top_p(const float* logits, int64_t row_stride, const StepMeta& m, int V, float temperature,
-                         float top_p, const float* uniform, int32_t* token_out, hipStream_t s);
-// Copy rows of real nodes to the caller's [batch][max_nodes][V] logits buffer.
-void launch_export_logits(float* dst, const float* src, int64_t src_stride, const StepMeta& m,
-                          int max_nodes, int V, hipStream_t s);
-// Approval walk (one wavefront per sequence).  mode 0 greedy, mode 1 keep the whole chain.
-// out_n [B], out_path / out_tok [B][stride].  If a real row of any sequence is flagged, every sequence gets out_n = 0, out_flag = 1.
-void launch_accept_walk(const StepMeta& m, const int32_t* amax, const int32_t* row_flag, int mode, int32_t* out_n,
-                        int32_t* out_flag, int32_t* out_path, int32_t* out_tok, int stride, hipStream_t s);
+                         float top_p, const float* uniform, const int32_t* flag, int32_t* token_out, int32_t* flag_out,
+                         hipStream_t s);
+// The walk alone, where there is nothing to compact.
+void launch_accept_walk(const ApprovalWalk& w, hipStream_t s);
 
 // ---- fp32 path (cache [B][Hkv][cap][hd], queries and logits row-major; weights and projection inputs "packed": tiles of
 // 16 rows x 16 k, see kernels_f32.hip) ------------------------------------------------------
@@ -58,7 +74,7 @@ void launch_accept_walk(const StepMeta& m, const int32_t* amax, const int32_t* r
 inline int64_t f32_packed_floats(int64_t rows, int64_t k) { return (rows + 15) / 16 * ((k + 15) / 16) * 256; }
 // dst = packed W[N][K] * gain[k] (gain null: 1)
 void f32_pack_weight(float* dst, const float* src, const float* gain, int N, int K, hipStream_t s);
-void f32_embed(float* x, const float* emb, const StepMeta& m, int d, hipStream_t s);
+void f32_embed(float* x, const float* emb, const StepFront& f, int d, hipStream_t s);
 // Y[r][n] = sum_k X[r][k] W[n][k] with a fused neighbour on either side.  All kinds but F32_RESIDUAL normalise their
 // input rows, X[r] / sqrt(mean(x^2) + eps); the norm's gain is part of W.  X and W are packed.
 enum {
@@ -84,8 +100,7 @@ void f32_rope_kv(float* qkv, float* kc, float* vc, const float2* tab, const Step
                  const ModelDims& md, hipStream_t s);
 void f32_tree_attention(float* o, const float* qkv, int q_stride, const float* kc, const float* vc,
                         const StepMeta& m, const ModelDims& md, hipStream_t s);
-void f32_kv_compact(float* const* kc, float* const* vc, const int32_t* path, const int32_t* n_acc,
-                    const StepMeta& m, const ModelDims& md, int stride, hipStream_t s);
+void f32_kv_compact(float* const* kc, float* const* vc, const ApprovalWalk& w, const StepMeta& m, const ModelDims& md, hipStream_t s);
 // plain [Hkv][n][hd] <-> cache
 void f32_kv_copy(float* cache, float* plain, bool to_cache, int seq, int first, int n,
                  const ModelDims& md, hipStream_t s);
@@ -112,7 +127,7 @@ typedef uint16_t bf16_t;
 enum { PERM_NONE = 0, PERM_ROPE = 1 /* per head: dims i and i + 64 */, PERM_GATE_UP = 2 /* gate f and up f */ };
 void bf16_pack_weight(bf16_t* dst, const bf16_t* src, int N, int K, int perm, hipStream_t s);
 // x = emb[token]; y = (x * gain) as hi/lo f16 in PackX; ssq[r][g] = sum of x^2 over feature group g (64 wide)
-void bf16_embed(float* x, bf16_t* y_packed, float* ssq, const bf16_t* emb, const float* gain, const StepMeta& m,
+void bf16_embed(float* x, bf16_t* y_packed, float* ssq, const bf16_t* emb, const float* gain, const StepFront& f,
                 int rows_pad, int d, hipStream_t s);
 
 // What a GEMM does with its result tile (fused epilogue).  RMSNorm is deferred: producers write
@@ -195,12 +210,12 @@ void bf16_tree_attention(bf16_t* o_packed, int rows_pad, const bf16_t* q_packed,
                          float* part_o, float2* part_ml, int n_splits, int q_planes, const StepMeta& m,
                          const ModelDims& md, hipStream_t s, const bf16_t* q_plain = nullptr,
                          bf16_t* out_plain = nullptr, int max_nodes = 0);
-void bf16_kv_compact(bf16_t* const* kc, bf16_t* const* vc, const int32_t* path, const int32_t* n_acc,
-                     const StepMeta& m, const ModelDims& md, int stride, hipStream_t s);
+void bf16_kv_compact(bf16_t* const* kc, bf16_t* const* vc, const ApprovalWalk& w, const StepMeta& m, const ModelDims& md, hipStream_t s);
 void bf16_kv_copy(bf16_t* kcache, bf16_t* vcache, bf16_t* k_plain, bf16_t* v_plain, bool to_cache,
                   int seq, int first, int n, const ModelDims& md, hipStream_t s);
 void bf16_kv_clear(bf16_t* kcache, bf16_t* vcache, int seq, int first, int n, const ModelDims& md, hipStream_t s);
-void bf16_scatter_tree_kv(bf16_t* kc, bf16_t* vc, const bf16_t* k_tree, const bf16_t* v_tree,
-                          const StepMeta& m, const ModelDims& md, int max_nodes, hipStream_t s);
+// m: the step's description in pinned host memory, `units` x 16 bytes of which go from meta_src to meta_dst beside the scatter
+void bf16_scatter_tree_kv(bf16_t* kc, bf16_t* vc, const bf16_t* k_tree, const bf16_t* v_tree, const StepMeta& m,
+                          const void* meta_src, void* meta_dst, int units, const ModelDims& md, int max_nodes, hipStream_t s);
 
 }  // namespace ded

@@ -4,6 +4,7 @@
 
 #include "bf16_layout.h"
 #include "ded_kernels.h"
+#include "step_ends.h"
 
 namespace ded {
 
@@ -94,14 +95,18 @@ void bf16_pack_weight(bf16_t* dst, const bf16_t* src, int N, int K, int perm, hi
 
 // ------------------------------------------------------------------------------------------
 // Embedding gather: x = emb[token] (fp32 residual stream), y = (x * gain) as hi/lo f16 in PackX for the first
-// GEMM, ssq[r][g] = sum of x^2 over the 64 features of group g (the consumer turns that into 1/rms).
+// GEMM, ssq[r][g] = sum of x^2 over the 64 features of group g (the consumer turns that into 1/rms).  The workgroups behind
+// those of the rows do the step's front work.
 __global__ __launch_bounds__(256) void bf16_embed_kernel(float* __restrict__ x, uint4* __restrict__ y,
                                                          float* __restrict__ ssq, const bf16_t* __restrict__ emb,
-                                                         const float* __restrict__ gain,
-                                                         const int32_t* __restrict__ token, int rows, int RB, int d) {
+                                                         const float* __restrict__ gain, StepFront f, int RB, int d) {
   int r = blockIdx.x;
-  const bool real = r < rows;  // padding rows (up to the 64-row granule of the GEMMs) are cleared
-  const bf16_t* src = emb + (int64_t)(real ? token[r] : 0) * d;
+  if (r >= RB * 16) {
+    step_front(f, r - RB * 16);
+    return;
+  }
+  const bool real = r < f.rows;  // padding rows (up to the 64-row granule of the GEMMs) are cleared
+  const bf16_t* src = emb + (int64_t)(real ? f.token[r] : 0) * d;
   for (int u = threadIdx.x; u < d / 8; u += 256) {  // d % 64 == 0: whole wavefront iterations only
     uint4 in = real ? *reinterpret_cast<const uint4*>(src + u * 8) : make_uint4(0, 0, 0, 0);
     uint32_t w[4] = {in.x, in.y, in.z, in.w};
@@ -128,26 +133,27 @@ __global__ __launch_bounds__(256) void bf16_embed_kernel(float* __restrict__ x, 
     y[packx_index(r, u * 8, RB, 1) >> 3] = lo;
   }
 }
-void bf16_embed(float* x, bf16_t* y_packed, float* ssq, const bf16_t* emb, const float* gain, const StepMeta& m,
+void bf16_embed(float* x, bf16_t* y_packed, float* ssq, const bf16_t* emb, const float* gain, const StepFront& f,
                 int rows_pad, int d, hipStream_t s) {
-  hipLaunchKernelGGL(bf16_embed_kernel, dim3(rows_pad), dim3(256), 0, s, x, reinterpret_cast<uint4*>(y_packed), ssq, emb,
-                     gain, m.token, m.rows, rows_pad / 16, d);
+  hipLaunchKernelGGL(bf16_embed_kernel, dim3(rows_pad + step_front_blocks(f)), dim3(256), 0, s, x,
+                     reinterpret_cast<uint4*>(y_packed), ssq, emb, gain, f, rows_pad / 16, d);
 }
 
 // ------------------------------------------------------------------------------------------
 // Compaction in the fragment layouts.  Threads 0..15 move the sixteen 16-byte key units of a slot,
-// threads 16..143 one value element each; every thread walks the path upwards (see the fp32 kernel).
-__global__ __launch_bounds__(192) void bf16_kv_compact_kernel(bf16_t* const* __restrict__ kc,
-                                                              bf16_t* const* __restrict__ vc,
-                                                              const int32_t* __restrict__ path,
-                                                              const int32_t* __restrict__ n_acc,
-                                                              const int32_t* __restrict__ seq_p, int Hkv, int cap,
-                                                              int stride) {
+// threads 16..143 one value element each; every thread walks the path upwards (see the fp32 kernel).  Every workgroup does
+// the approval walk of its sequence itself; the first of the sequence reports it.
+__global__ __launch_bounds__(256) void bf16_kv_compact_kernel(bf16_t* const* __restrict__ kc, bf16_t* const* __restrict__ vc,
+                                                              ApprovalWalk w, const int32_t* __restrict__ seq_p, int Hkv,
+                                                              int cap) {
+  __shared__ WalkShared sh;
   const int hd = 128;
   int layer = blockIdx.x, bh = blockIdx.y;
   int b = bh / Hkv;
-  int len = n_acc[b], P = seq_p[b];
-  const int32_t* pth = path + (int64_t)b * stride;
+  int P = seq_p[b];
+  const int len = approval_walk(w, b, sh);
+  if (layer == 0 && bh == b * Hkv) report_walk(w, b, sh, len);
+  const int32_t* pth = sh.path;
   int t = threadIdx.x;
   if (t < 16) {
     bf16_t* K = kc[layer] + (int64_t)bh * cap * hd;
@@ -166,10 +172,9 @@ __global__ __launch_bounds__(192) void bf16_kv_compact_kernel(bf16_t* const* __r
     }
   }
 }
-void bf16_kv_compact(bf16_t* const* kc, bf16_t* const* vc, const int32_t* path, const int32_t* n_acc,
-                     const StepMeta& m, const ModelDims& md, int stride, hipStream_t s) {
-  hipLaunchKernelGGL(bf16_kv_compact_kernel, dim3(md.n_layers, m.batch * md.Hkv), dim3(192), 0, s, kc, vc, path,
-                     n_acc, m.seq_p, md.Hkv, md.cap, stride);
+void bf16_kv_compact(bf16_t* const* kc, bf16_t* const* vc, const ApprovalWalk& w, const StepMeta& m, const ModelDims& md, hipStream_t s) {
+  hipLaunchKernelGGL(bf16_kv_compact_kernel, dim3(md.n_layers, m.batch * md.Hkv), dim3(256), 0, s, kc, vc, w, m.seq_p, md.Hkv,
+                     md.cap);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -300,24 +305,32 @@ void bf16_kv_clear(bf16_t* kcache, bf16_t* vcache, int seq, int first, int n, co
   hipLaunchKernelGGL(bf16_kv_clear_kernel, dim3(n, md.Hkv), dim3(128), 0, s, kcache, vcache, seq, first, md.Hkv, md.cap);
 }
 
-// tree K / V [B][Hkv][max_nodes][hd] -> cache slots P + node
+// tree K / V [B][Hkv][max_nodes][hd] -> cache slots P + node.  The step's description is still in host memory (seq_p, seq_n); the
+// last workgroups of each row of the grid copy it to the device for the kernels that follow.
 __global__ __launch_bounds__(256) void bf16_scatter_tree_kv_kernel(bf16_t* __restrict__ kc, bf16_t* __restrict__ vc,
                                                                    const bf16_t* __restrict__ kt,
                                                                    const bf16_t* __restrict__ vt,
                                                                    const int32_t* __restrict__ seq_p,
-                                                                   const int32_t* __restrict__ seq_n, int Hkv, int cap,
+                                                                   const int32_t* __restrict__ seq_n,
+                                                                   const uint4* __restrict__ meta_src,
+                                                                   uint4* __restrict__ meta_dst, int units, int Hkv, int cap,
                                                                    int max_nodes) {
   __shared__ __align__(16) uint16_t lds[32 * KV_LDS_ROW];
+  if (blockIdx.x == gridDim.x - 1) {
+    for (int u = blockIdx.y * 256 + threadIdx.x; u < units; u += gridDim.y * 256) meta_dst[u] = meta_src[u];
+    return;
+  }
   const int bh = blockIdx.y, b = bh / Hkv, P = seq_p[b], n = seq_n[b], kb = P / 32 + blockIdx.x;
   if (kb * 32 >= P + n) return;
   const int64_t plain = (int64_t)bh * max_nodes * 128, base = (int64_t)bh * cap * 128;
   kv_group_copy<true>(kc + base, vc + base, const_cast<bf16_t*>(kt) + plain, const_cast<bf16_t*>(vt) + plain, P, n, kb, lds);
 }
 void bf16_scatter_tree_kv(bf16_t* kc, bf16_t* vc, const bf16_t* k_tree, const bf16_t* v_tree, const StepMeta& m,
-                          const ModelDims& md, int max_nodes, hipStream_t s) {
+                          const void* meta_src, void* meta_dst, int units, const ModelDims& md, int max_nodes, hipStream_t s) {
   // a tree of n nodes touches at most (n + 30) / 32 + 1 groups
-  hipLaunchKernelGGL(bf16_scatter_tree_kv_kernel, dim3((m.n_step + 30) / 32 + 1, m.batch * md.Hkv), dim3(256), 0, s, kc,
-                     vc, k_tree, v_tree, m.seq_p, m.seq_n, md.Hkv, md.cap, max_nodes);
+  hipLaunchKernelGGL(bf16_scatter_tree_kv_kernel, dim3((m.n_step + 30) / 32 + 2, m.batch * md.Hkv), dim3(256), 0, s, kc,
+                     vc, k_tree, v_tree, m.seq_p, m.seq_n, reinterpret_cast<const uint4*>(meta_src),
+                     reinterpret_cast<uint4*>(meta_dst), units, md.Hkv, md.cap, max_nodes);
 }
 
 }  // namespace ded

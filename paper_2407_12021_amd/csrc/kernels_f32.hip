@@ -6,6 +6,7 @@
 #include <type_traits>
 
 #include "ded_kernels.h"
+#include "step_ends.h"
 
 namespace ded {
 
@@ -75,20 +76,27 @@ void f32_pack_weight(float* dst, const float* src, const float* gain, int N, int
 }
 
 // ------------------------------------------------------------------------------------------
-// x (packed) = emb[token]; a wavefront takes one tile of 16 rows x 16 dims
-__global__ __launch_bounds__(256) void f32_embed_kernel(float4* __restrict__ x, const float* __restrict__ emb,
-                                                        const int32_t* __restrict__ token, int d, int kt) {
-  const int lane = threadIdx.x & 63, c = blockIdx.y * 4 + (threadIdx.x >> 6), k = c * 16 + (lane >> 4) * 4;
+// x (packed) = emb[token]; a wavefront takes one tile of 16 rows x 16 dims.  The workgroups behind those of the embedding do
+// the step's front work.
+__global__ __launch_bounds__(256) void f32_embed_kernel(float4* __restrict__ x, const float* __restrict__ emb, StepFront f, int d,
+                                                        int kt, int groups) {
+  const int lane = threadIdx.x & 63, rb = blockIdx.x / groups;
+  if (rb * 16 >= f.rows) {
+    step_front(f, blockIdx.x - f.rows / 16 * groups);
+    return;
+  }
+  const int c = (blockIdx.x - rb * groups) * 4 + (threadIdx.x >> 6), k = c * 16 + (lane >> 4) * 4;
   if (c >= kt) return;
-  const float* src = emb + (int64_t)token[blockIdx.x * 16 + (lane & 15)] * d + k;
+  const float* src = emb + (int64_t)f.token[rb * 16 + (lane & 15)] * d + k;
   float v[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) v[i] = k + i < d ? src[i] : 0.f;
-  x[((int64_t)blockIdx.x * kt + c) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+  x[((int64_t)rb * kt + c) * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
 }
-void f32_embed(float* x, const float* emb, const StepMeta& m, int d, hipStream_t s) {
-  hipLaunchKernelGGL(f32_embed_kernel, dim3(m.rows / 16, (tiles16(d) + 3) / 4), dim3(256), 0, s, reinterpret_cast<float4*>(x),
-                     emb, m.token, d, tiles16(d));
+void f32_embed(float* x, const float* emb, const StepFront& f, int d, hipStream_t s) {
+  const int groups = (tiles16(d) + 3) / 4;
+  hipLaunchKernelGGL(f32_embed_kernel, dim3(f.rows / 16 * groups + step_front_blocks(f)), dim3(256), 0, s,
+                     reinterpret_cast<float4*>(x), emb, f, d, tiles16(d), groups);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -587,15 +595,18 @@ void f32_tree_attention(float* o, const float* qkv, int q_stride, const float* k
 
 // ------------------------------------------------------------------------------------------
 // Compaction: slot P + path[j] -> slot P + j for j = 0..len-1.  path is increasing with path[j] >= j,
-// so each thread walks j upwards and only ever overwrites slots it has already consumed.
-__global__ void f32_kv_compact_kernel(float* const* __restrict__ kc, float* const* __restrict__ vc,
-                                      const int32_t* __restrict__ path, const int32_t* __restrict__ n_acc,
-                                      const int32_t* __restrict__ seq_p, int Hkv, int hd, int cap, int stride) {
+// so each thread walks j upwards and only ever overwrites slots it has already consumed.  Every workgroup does the approval walk
+// of its sequence itself; the first of the sequence reports it.
+__global__ __launch_bounds__(256) void f32_kv_compact_kernel(float* const* __restrict__ kc, float* const* __restrict__ vc,
+                                                             ApprovalWalk w, const int32_t* __restrict__ seq_p, int Hkv,
+                                                             int hd, int cap) {
+  __shared__ WalkShared sh;
   int layer = blockIdx.x, bh = blockIdx.y;
   int b = bh / Hkv;
-  int len = n_acc[b];
   int P = seq_p[b];
-  const int32_t* pth = path + (int64_t)b * stride;
+  const int len = approval_walk(w, b, sh);
+  if (layer == 0 && bh == b * Hkv) report_walk(w, b, sh, len);
+  const int32_t* pth = sh.path;
   float* K = kc[layer] + (int64_t)bh * cap * hd;
   float* V = vc[layer] + (int64_t)bh * cap * hd;
   for (int i = threadIdx.x; i < hd; i += blockDim.x) {
@@ -608,10 +619,9 @@ __global__ void f32_kv_compact_kernel(float* const* __restrict__ kc, float* cons
     }
   }
 }
-void f32_kv_compact(float* const* kc, float* const* vc, const int32_t* path, const int32_t* n_acc,
-                    const StepMeta& m, const ModelDims& md, int stride, hipStream_t s) {
-  hipLaunchKernelGGL(f32_kv_compact_kernel, dim3(md.n_layers, m.batch * md.Hkv), dim3(64), 0, s, kc, vc, path,
-                     n_acc, m.seq_p, md.Hkv, md.hd, md.cap, stride);
+void f32_kv_compact(float* const* kc, float* const* vc, const ApprovalWalk& w, const StepMeta& m, const ModelDims& md, hipStream_t s) {
+  hipLaunchKernelGGL(f32_kv_compact_kernel, dim3(md.n_layers, m.batch * md.Hkv), dim3(256), 0, s, kc, vc, w, m.seq_p, md.Hkv,
+                     md.hd, md.cap);
 }
 
 // ------------------------------------------------------------------------------------------

@@ -1,29 +1,8 @@
-// Kernels used by both storage types: rotary table, per-node argmax, logits export, approval walk.
+// Kernels used by both storage types: per-node argmax (with the logits' export), sampler, approval walk.
 #include "ded_kernels.h"
+#include "step_ends.h"
 
 namespace ded {
-
-// ------------------------------------------------------------------------------------------
-// Rotary table.  The angle pos * base^(-2i/hd) is formed in fp64 so that long contexts do not lose
-// phase accuracy; the rotation itself is applied in fp32 by the consumers.
-// ------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(float2* __restrict__ tab, const int32_t* __restrict__ pos, int rows,
-                                  int half, double neg2_over_hd_log2base) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= rows * half) return;
-  int r = idx / half, i = idx - r * half;
-  double theta = exp2((double)i * neg2_over_hd_log2base);
-  double ang = (double)pos[r] * theta;
-  tab[idx] = make_float2((float)cos(ang), (float)sin(ang));
-}
-
-void launch_rope_table(float2* tab, const int32_t* pos, int rows, int hd, float base, hipStream_t s) {
-  int half = hd / 2;
-  int n = rows * half;
-  if (n <= 0) return;
-  double c = -2.0 / (double)hd * log2((double)base);
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, tab, pos, rows, half, c);
-}
 
 // ------------------------------------------------------------------------------------------
 // Measurement aid: a plain streaming read of a device buffer: every wavefront walks a contiguous region of its own
@@ -129,16 +108,28 @@ __device__ inline void top2_block_finish(Top2 t, int bad, int32_t* amax, float* 
   }
 }
 
-__global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ logits, int64_t row_stride,
-                                                     int V, int32_t* __restrict__ amax,
-                                                     float* __restrict__ margin, int32_t* __restrict__ flag) {
-  const float* row = logits + (int64_t)blockIdx.x * row_stride;
+typedef float caller_f32x4_t __attribute__((ext_vector_type(4), aligned(4)));  // the caller's array: aligned to its elements only
+
+// (the row goes to the caller from the same registers: as a launch of its own the copy read it once more)
+__global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ logits, int V, int32_t* __restrict__ amax,
+                                                     float* __restrict__ margin, int32_t* __restrict__ flag,
+                                                     float* __restrict__ export_to, int max_nodes,
+                                                     const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
+                                                     const int32_t* __restrict__ blk_seq) {
+  const int r = blockIdx.x;
+  const float* row = logits + (int64_t)r * V;
+  float* out = nullptr;
+  if (export_to) {
+    const int b = blk_seq[r >> 4], node = r - row0[b];
+    if (node < seq_n[b]) out = export_to + ((int64_t)b * max_nodes + node) * V;
+  }
   Top2 t = {-INFINITY, 0x7fffffff, -INFINITY};
   int bad = 0;
   int nv4 = ((reinterpret_cast<uintptr_t>(row) & 15) == 0) ? (V / 4) : 0;
   const float4* row4 = reinterpret_cast<const float4*>(row);
   for (int i = threadIdx.x; i < nv4; i += 256) {
     float4 v = row4[i];
+    if (out) *reinterpret_cast<caller_f32x4_t*>(out + 4 * i) = caller_f32x4_t{v.x, v.y, v.z, v.w};
     bad |= nonfinite(v.x) | nonfinite(v.y) | nonfinite(v.z) | nonfinite(v.w);
     top2_push(t, v.x, 4 * i);
     top2_push(t, v.y, 4 * i + 1);
@@ -146,16 +137,19 @@ __global__ __launch_bounds__(256) void argmax_kernel(const float* __restrict__ l
     top2_push(t, v.w, 4 * i + 3);
   }
   for (int i = nv4 * 4 + threadIdx.x; i < V; i += 256) {
-    bad |= nonfinite(row[i]);
-    top2_push(t, row[i], i);
+    const float v = row[i];
+    if (out) out[i] = v;
+    bad |= nonfinite(v);
+    top2_push(t, v, i);
   }
   top2_block_finish(t, bad, amax, margin, flag);
 }
 
-void launch_argmax(const float* logits, int64_t row_stride, int rows, int V, int32_t* amax,
-                   float* margin, int32_t* flag, hipStream_t s) {
-  if (rows <= 0) return;
-  hipLaunchKernelGGL(argmax_kernel, dim3(rows), dim3(256), 0, s, logits, row_stride, V, amax, margin, flag);
+void launch_argmax(const float* logits, const StepMeta& m, int V, int32_t* amax, float* margin, int32_t* flag, float* export_to,
+                   int max_nodes, hipStream_t s) {
+  if (m.rows <= 0) return;
+  hipLaunchKernelGGL(argmax_kernel, dim3(m.rows), dim3(256), 0, s, logits, V, amax, margin, flag, export_to, max_nodes,
+                     m.seq_n, m.row0, m.blk_seq);
 }
 
 // The same verdict from per-(row, 64-feature group) candidates that the LM-head GEMM's epilogue left instead of
@@ -243,7 +237,8 @@ __device__ inline unsigned long long block_exclusive_u64(unsigned long long v, u
 __global__ __launch_bounds__(SAMPLE_THREADS) void sample_top_p_kernel(
     const float* __restrict__ logits, int64_t row_stride, int V, float inv_temp, float top_p,
     const float* __restrict__ uniform, const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0,
-    const int32_t* __restrict__ blk_seq, int32_t* __restrict__ token_out) {
+    const int32_t* __restrict__ blk_seq, const int32_t* __restrict__ flag, int32_t* __restrict__ token_out,
+    int32_t* __restrict__ flag_out) {
   __shared__ unsigned long long hist[SAMPLE_COPIES * SAMPLE_BINS];
   __shared__ unsigned long long sh[SAMPLE_WAVES];
   __shared__ float sh_f[SAMPLE_WAVES];
@@ -253,6 +248,8 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_top_p_kernel(
   if (r - row0[seq] >= seq_n[seq]) return;  // padding row
   const float* row = logits + (int64_t)r * row_stride;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (tid == 0) flag_out[r] = flag[r];
+  const float u = uniform[r];  // (host memory: requested here, needed at the end)
   const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
   auto load4 = [&](int i, float (&l)[4]) {  // past the end: no weight
     if (vec && i + 3 < V) {
@@ -370,7 +367,7 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_top_p_kernel(
   __syncthreads();
   unsigned long long total;
   const unsigned long long mine = hist[tid], before = block_exclusive_u64(mine, sh, total);
-  unsigned long long target = (unsigned long long)((double)uniform[r] * (double)total);
+  unsigned long long target = (unsigned long long)((double)u * (double)total);
   target = target < total ? target : total - 1;
   if (before <= target && target < before + mine) {
     sh_sub = tid;
@@ -401,116 +398,22 @@ __global__ __launch_bounds__(SAMPLE_THREADS) void sample_top_p_kernel(
 }
 
 void launch_sample_top_p(const float* logits, int64_t row_stride, const StepMeta& m, int V, float temperature,
-                         float top_p, const float* uniform, int32_t* token_out, hipStream_t s) {
+                         float top_p, const float* uniform, const int32_t* flag, int32_t* token_out, int32_t* flag_out,
+                         hipStream_t s) {
   if (m.rows <= 0) return;
   hipLaunchKernelGGL(sample_top_p_kernel, dim3(m.rows), dim3(SAMPLE_THREADS), 0, s, logits, row_stride, V,
-                     1.0f / temperature, top_p, uniform, m.seq_n, m.row0, m.blk_seq, token_out);
+                     1.0f / temperature, top_p, uniform, m.seq_n, m.row0, m.blk_seq, flag, token_out, flag_out);
 }
 
 // ------------------------------------------------------------------------------------------
-__global__ void export_logits_kernel(float* __restrict__ dst, const float* __restrict__ src,
-                                     int64_t src_stride, const int32_t* __restrict__ seq_n,
-                                     const int32_t* __restrict__ row0, const int32_t* __restrict__ blk_seq,
-                                     int max_nodes, int V) {
-  int r = blockIdx.x;
-  int b = blk_seq[r >> 4], node = r - row0[b];
-  if (node >= seq_n[b]) return;
-  const float* s = src + (int64_t)r * src_stride;
-  float* d = dst + ((int64_t)b * max_nodes + node) * V;
-  for (int i = threadIdx.x; i < V; i += blockDim.x) d[i] = s[i];
+// One workgroup per sequence.
+__global__ __launch_bounds__(256) void accept_walk_kernel(ApprovalWalk w) {
+  __shared__ WalkShared sh;
+  const int len = approval_walk(w, blockIdx.x, sh);
+  report_walk(w, blockIdx.x, sh, len);
 }
-
-void launch_export_logits(float* dst, const float* src, int64_t src_stride, const StepMeta& m,
-                          int max_nodes, int V, hipStream_t s) {
-  hipLaunchKernelGGL(export_logits_kernel, dim3(m.rows), dim3(256), 0, s, dst, src, src_stride, m.seq_n,
-                     m.row0, m.blk_seq, max_nodes, V);
-}
-
-// ------------------------------------------------------------------------------------------
-// Approval walk, one wavefront per sequence.  Node i is approved iff every node v on the path
-// root..i (v != root) carries the model's token of its parent.  The end node is the deepest
-// approved node, lowest index among equals.
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void accept_walk_kernel(const int32_t* __restrict__ token,
-                                                         const int32_t* __restrict__ parent,
-                                                         const int32_t* __restrict__ depth,
-                                                         const int32_t* __restrict__ seq_n,
-                                                         const int32_t* __restrict__ amax,
-                                                         const int32_t* __restrict__ row_flag,
-                                                         const int32_t* __restrict__ row0, int mode, int32_t* __restrict__ out_n,
-                                                         int32_t* __restrict__ out_flag,
-                                                         int32_t* __restrict__ out_path,
-                                                         int32_t* __restrict__ out_tok, int stride) {
-  int b = blockIdx.x;
-  int n = seq_n[b];
-  const int32_t* tok = token + row0[b];
-  const int32_t* par = parent + row0[b];
-  const int32_t* dep = depth + row0[b];
-  const int32_t* am = amax + row0[b];
-  // a step with a non-finite logit at a real node of any sequence has no verdict: every sequence gets path
-  // length 0 (nothing is compacted) and its flag raised
-  int bad = 0;
-  for (int b2 = 0; b2 < gridDim.x; ++b2)
-    for (int i = threadIdx.x; i < seq_n[b2]; i += 64) bad |= row_flag[row0[b2] + i];
-  bad = __any(bad != 0);
-  if (bad) {
-    if (threadIdx.x == 0) {
-      out_n[b] = 0;
-      out_flag[b] = 1;
-    }
-    return;
-  }
-  int32_t* path = out_path + (int64_t)b * stride;
-  int32_t* acc = out_tok + (int64_t)b * stride;
-  if (mode == 1) {  // a chain, as the caller has checked: its nodes in order (one lane that walks up 256 parents took 62 us)
-    for (int j = threadIdx.x; j < n; j += 64) {
-      path[j] = j;
-      acc[j] = j + 1 < n ? tok[j + 1] : am[j];
-    }
-    if (threadIdx.x == 0) {
-      out_n[b] = n;
-      out_flag[b] = 0;
-    }
-    return;
-  }
-  int best = -1;  // key = depth * 1024 + (1023 - node)
-  for (int i = threadIdx.x; i < n; i += 64) {
-    bool ok = true;
-    int v = i;
-    for (int guard = 0; guard < n && ok; ++guard) {
-      int p = par[v];
-      if (p < 0) break;
-      ok = (tok[v] == am[p]);
-      v = p;
-    }
-    if (ok) {
-      int key = dep[i] * 1024 + (1023 - i);
-      best = key > best ? key : best;
-    }
-  }
-  for (int off = 32; off >= 1; off >>= 1) {
-    int o = __shfl_xor(best, off);
-    best = o > best ? o : best;
-  }
-  if (threadIdx.x == 0) {
-    int end = 1023 - (best & 1023);
-    int len = dep[end] + 1;
-    int v = end;
-    for (int j = len - 1; j >= 0; --j) {
-      path[j] = v;
-      if (j > 0) acc[j - 1] = tok[v];
-      v = par[v];
-    }
-    acc[len - 1] = am[end];
-    out_n[b] = len;
-    out_flag[b] = 0;
-  }
-}
-
-void launch_accept_walk(const StepMeta& m, const int32_t* amax, const int32_t* row_flag, int mode, int32_t* out_n,
-                        int32_t* out_flag, int32_t* out_path, int32_t* out_tok, int stride, hipStream_t s) {
-  hipLaunchKernelGGL(accept_walk_kernel, dim3(m.batch), dim3(64), 0, s, m.token, m.parent, m.depth,
-                     m.seq_n, amax, row_flag, m.row0, mode, out_n, out_flag, out_path, out_tok, stride);
+void launch_accept_walk(const ApprovalWalk& w, hipStream_t s) {
+  hipLaunchKernelGGL(accept_walk_kernel, dim3(w.batch), dim3(256), 0, s, w);
 }
 
 }  // namespace ded

@@ -541,3 +541,42 @@ def test_rows_of_a_caller_are_aligned_to_their_elements_only(dtype, prefix, n, m
         ver.close()
     for a, b in zip(*got):
         assert a.any() and torch.equal(a, b)
+
+
+@pytest.mark.parametrize("dtype,max_nodes", [("bf16", 33), ("fp32", 33), ("bf16", 256)])
+def test_calls_in_a_row_keep_their_own_descriptions(dtype, max_nodes):
+    """Forty attention calls and ten steps that nobody waits for in between, each with its own tree and prefix length (more calls
+    than the pinned mirror has slots): every output has the bits of the same call waited for."""
+    import torch
+    hd, batch = 128 if dtype == "bf16" else 64, 2
+    cfg = di.ModelConfig("in-a-row-" + dtype, 1, 128, 4, 2, hd, 256, 96, dtype=dtype)
+    ver = _verifier(cfg, di.make_weights(cfg, seed=3), max_batch=batch, kv_capacity=640, max_nodes=max_nodes)
+    kind = torch.bfloat16 if dtype == "bf16" else torch.float32
+    draw = lambda *shape: torch.randn(*shape, device="cuda").to(kind)
+    for b in range(batch):
+        ver.kv_store(0, b, 0, draw(2, 300, hd), draw(2, 300, hd))
+    r = np.random.default_rng(11)
+    calls = []
+    for i in range(50):
+        nodes = [int(r.integers(1, max_nodes + 1)) for _ in range(batch)]
+        calls.append(([int(r.integers(0, 301)) for _ in nodes], [di.random_tree(n, None, seed=i) for n in nodes],
+                      draw(batch, max_nodes, 4, hd), draw(batch, 2, max_nodes, hd), draw(batch, 2, max_nodes, hd),
+                      [di.zipf_tokens(96, n, seed=i, stream=b) for b, n in enumerate(nodes)]))
+    runs = []
+    for wait in (True, False):
+        for b in range(batch):
+            k = torch.linspace(-1, 1, 2 * 300 * hd, device="cuda").view(2, 300, hd).to(kind)
+            ver.kv_store(0, b, 0, k, k.flip(1).contiguous())
+        outs = []
+        for i, (prefix, parents, q, k, v, tokens) in enumerate(calls):
+            if i % 5:
+                outs.append(ver.tree_attention(0, prefix, parents, q, k, v))
+            else:
+                outs.append(ver.verify_step(prefix, parents, tokens, want_logits=True))
+            if wait:
+                torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        runs.append(outs)
+    ver.close()
+    for i, (a, b) in enumerate(zip(*runs)):
+        assert torch.isfinite(a).all() and torch.equal(a, b), i
