@@ -18,6 +18,7 @@ namespace {
 constexpr int kMaskWords = 4;   // ancestor bitmask words per row (max_nodes <= 256)
 constexpr int kMaxNodes = 256;
 constexpr int64_t kAttnPartRows = 1 << 17;  // split-KV partial rows the workspace reserves at least
+constexpr int64_t kF32AttnPartFloats = 16 << 20;  // partial results of the fp32 attention: at most
 constexpr size_t kMetaMirrorBytes = 1 << 20;  // of pinned slots for step descriptions (at least two slots, at most 16)
 constexpr int kGemmCounters = 1 << 16;      // split-K arrival tickets (a GEMM with more output tiles runs unsplit)
 
@@ -51,9 +52,9 @@ struct Carve {  // bump allocator over the workspace (base may be null when only
 
 // Where the parts of a step's description sit inside the uploaded block, for `rows` tree rows of `batch` sequences.
 struct MetaOffsets {
-  size_t token = 0, parent = 0, depth = 0, pos = 0, mask = 0, p = 0, n = 0, row0 = 0, blk_seq = 0, bytes = 0;
+  size_t token = 0, parent = 0, depth = 0, pos = 0, mask = 0, p = 0, n = 0, row0 = 0, blk_seq = 0, attn_items = 0, bytes = 0;
   MetaOffsets() = default;
-  MetaOffsets(int rows, int batch) {
+  MetaOffsets(int rows, int batch, bool f32) {
     auto take = [&](size_t count) {
       const size_t at = bytes;
       bytes = align_up(bytes + count, 64);
@@ -63,6 +64,7 @@ struct MetaOffsets {
     pos = take((size_t)rows * 4), mask = take((size_t)rows * 8 * kMaskWords);
     p = take((size_t)batch * 4), n = take((size_t)batch * 4), row0 = take((size_t)batch * 4);
     blk_seq = take((size_t)rows / 16 * 4);
+    if (f32) attn_items = take((size_t)rows / 16 * F32_ATTN_SPLITS * 4);
   }
 };
 
@@ -117,7 +119,10 @@ struct ded_ctx {
   float* logits = nullptr;
   float2* rope_tab = nullptr;
   // fp32 path
-  float *f_qkv = nullptr, *f_o = nullptr, *f_h = nullptr;
+  float *f_qkv = nullptr, *f_o = nullptr, *f_h = nullptr, *f_part_o = nullptr, *f_part_ml = nullptr;
+  int* f_tickets = nullptr;
+  int f_splits = 1;  // key ranges that f_part_o has room for
+  int f_items = 0;   // of the pending step: workgroups per head of its attention
   // bf16 path
   bf16_t *y_p = nullptr, *o_p = nullptr, *h_p = nullptr, *q_p = nullptr;
   float* part = nullptr;
@@ -178,6 +183,7 @@ struct ded_ctx {
     m.seq_n = reinterpret_cast<const int32_t*>(base + off.n);
     m.row0 = reinterpret_cast<const int32_t*>(base + off.row0);
     m.blk_seq = reinterpret_cast<const int32_t*>(base + off.blk_seq);
+    m.attn_items = reinterpret_cast<const int32_t*>(base + off.attn_items);
     m.batch = batch;
     m.n_step = n_step;
     m.rows = rows;
@@ -299,10 +305,19 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
     float* qkv = w.take<float>((int64_t)z.max_rows_pad * qkv_n);
     float* o = w.take<float>(f32_packed_floats(z.max_rows_pad, qd));
     float* h = w.take<float>(f32_packed_floats(z.max_rows_pad, F));
+    const int64_t range = (int64_t)z.max_rows * c.n_heads;  // (row, head) pairs of one key range
+    const int splits = (int)std::max<int64_t>(1, std::min<int64_t>(F32_ATTN_SPLITS, kF32AttnPartFloats / (range * (c.head_dim + 2))));
+    float* part_o = w.take<float>(splits > 1 ? range * splits * c.head_dim : 1);
+    float* part_ml = w.take<float>(splits > 1 ? range * splits * 2 : 1);
+    int* tickets = w.take<int>(range / 16);
     if (ctx) {
       ctx->f_qkv = qkv;
       ctx->f_o = o;
       ctx->f_h = h;
+      ctx->f_part_o = part_o;
+      ctx->f_part_ml = part_ml;
+      ctx->f_tickets = tickets;
+      ctx->f_splits = splits;
     }
   } else {
     // GEMM inputs and queries are kept as hi/lo pairs of f16: two planes each
@@ -336,7 +351,7 @@ size_t carve_workspace(const ded_config& c, char* base, ded_ctx* ctx) {
     }
   }
   // step meta block
-  const size_t m = align_up(MetaOffsets(z.max_rows, c.max_batch).bytes, 256);
+  const size_t m = align_up(MetaOffsets(z.max_rows, c.max_batch, c.dtype == DED_F32).bytes, 256);
   char* dmeta = w.take<char>(m);
   int32_t* amax = w.take<int32_t>((int64_t)z.max_rows_pad * 3);  // and margins and flags, see ingest
   if (ctx) {
@@ -445,7 +460,7 @@ int ingest(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const int32_t* 
   c->batch = batch;
   c->n_step = round_up(nmax, 16);
   c->rows = rows;
-  c->off = MetaOffsets(rows, batch);
+  c->off = MetaOffsets(rows, batch, !c->bf16);
   c->d_margin = reinterpret_cast<float*>(c->d_amax + rows);
   c->d_rowflag = c->d_amax + 2 * (size_t)rows;
   c->max_p = pmax;
@@ -461,6 +476,8 @@ int ingest(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const int32_t* 
   int32_t* h_n = reinterpret_cast<int32_t*>(c->h_meta + c->off.n);
   int32_t* h_row0 = reinterpret_cast<int32_t*>(c->h_meta + c->off.row0);
   int32_t* h_blk = reinterpret_cast<int32_t*>(c->h_meta + c->off.blk_seq);
+  int32_t* h_items = reinterpret_cast<int32_t*>(c->h_meta + c->off.attn_items);
+  c->f_items = 0;
   for (int b = 0; b < batch; ++b) {
     const int32_t* par = parent + (int64_t)b * cfg.max_nodes;
     const int32_t* tok = token ? token + (int64_t)b * cfg.max_nodes : nullptr;
@@ -469,6 +486,10 @@ int ingest(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const int32_t* 
     h_n[b] = n;
     h_row0[b] = row0;
     for (int i = 0; i < n_pad; i += 16) h_blk[(row0 + i) / 16] = b;
+    if (!c->bf16)
+      for (int i = 0; i < n_pad; i += 16)
+        for (int z = 0; z < f32_attention_splits(P + n, c->f_splits); ++z)
+          h_items[c->f_items++] = (row0 + i) / 16 * F32_ATTN_SPLITS + z;
     for (int i = 0; i < n_pad; ++i) {
       const int r = row0 + i;
       uint64_t* mr = h_mask + (size_t)r * kMaskWords;
@@ -502,6 +523,11 @@ int ingest(ded_ctx* c, int32_t batch, const int32_t* prefix_len, const int32_t* 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? DED_OK : DED_EHIP; }
 
 // ---------------------------------------------------------------------------------------------
+void f32_attention(ded_ctx* c, const float* q, int q_stride, int layer, const StepMeta& m, hipStream_t s) {
+  f32_tree_attention(c->f_o, q, q_stride, (const float*)c->kc[layer], (const float*)c->vc[layer], m, c->md, c->f_items, c->f_splits,
+                     c->f_part_o, c->f_part_ml, c->f_tickets, s);
+}
+
 int forward_f32(ded_ctx* c) {
   const ModelDims& md = c->md;
   StepMeta m = c->meta();
@@ -527,7 +553,7 @@ int forward_f32(ded_ctx* c) {
     const bool fused = md.hd % 32 == 0;
     gemm(KC_GEMM_QKV, fused ? F32_QKV : F32_STORE, c->f_qkv, c->x, c->wqkv[l], qkv_n, d, l);
     if (!fused) { ProfScope p(c, KC_QKV_EPILOGUE); f32_rope_kv(c->f_qkv, (float*)c->kc[l], (float*)c->vc[l], c->rope_tab, m, md, s); }
-    { ProfScope p(c, KC_TREE_ATTN); f32_tree_attention(c->f_o, c->f_qkv, qkv_n, (const float*)c->kc[l], (const float*)c->vc[l], m, md, s); }
+    { ProfScope p(c, KC_TREE_ATTN); f32_attention(c, c->f_qkv, qkv_n, l, m, s); }
     gemm(KC_GEMM_O, F32_RESIDUAL, c->x, c->f_o, c->wo[l], d, qd, l);
     gemm(KC_GEMM_GATE_UP, F32_SILU, c->f_h, c->x, c->wgu[l], 2 * F, d, l);
     gemm(KC_GEMM_DOWN, F32_RESIDUAL, c->x, c->f_h, c->wdown[l], d, F, l);
@@ -1105,7 +1131,7 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
       f32_scatter_tree_kv((float*)c->kc[layer], (float*)c->vc[layer], (const float*)k_tree, (const float*)v_tree, m, md, mn, s);
       f32_gather_rows(c->f_qkv, (const float*)q, m, mn, qd, true, s); }
     { ProfScope p(c, KC_TREE_ATTN);
-      f32_tree_attention(c->f_o, c->f_qkv, qd, (const float*)c->kc[layer], (const float*)c->vc[layer], m, md, s); }
+      f32_attention(c, c->f_qkv, qd, layer, m, s); }
     { ProfScope p(c, KC_LAYOUT); f32_gather_rows((float*)out, c->f_o, m, mn, qd, false, s); }
   }
   return launch_status();

@@ -21,6 +21,7 @@ struct StepMeta {
   const int32_t* seq_n;   // [B]   real tree rows per sequence
   const int32_t* row0;    // [B]   first row of the sequence (multiple of 16)
   const int32_t* blk_seq; // [rows / 16] sequence of each 16-row block
+  const int32_t* attn_items;  // fp32 path: (16-row block, key range) pairs, block * F32_ATTN_SPLITS + range
   int32_t batch, n_step, rows;  // rows = sum of the padded tree sizes
 };
 
@@ -98,8 +99,20 @@ struct F32Gemm {
 void f32_gemm(const F32Gemm& g, hipStream_t s);
 void f32_rope_kv(float* qkv, float* kc, float* vc, const float2* tab, const StepMeta& m,
                  const ModelDims& md, hipStream_t s);
+// Sequences of more than 256 keys are cut into up to `most` <= F32_ATTN_SPLITS key ranges (head dims of 16 and more); m.attn_items
+// lists the n_items pairs of a 16-row block and one of its sequence's ranges.  part_o holds rows * H * most * hd floats,
+// part_ml rows * H * most * 2, tickets rows / 16 * H zeroed ints (left zeroed); the first two are not used with most = 1.
+// The sequence alone decides about its ranges (and the room the context has), not how full the chip is: a row's sums do not
+// depend on its neighbours.  A range is one block of 16 keys per wavefront; two blocks in a row are faster than the hand-over
+// (144 keys, 4 heads x 64: 7.0 us whole, 8.8 in two ranges; 560 keys, 8 heads x 128: 21 and 13.3 in five).
+constexpr int F32_ATTN_SPLITS = 8;
+__host__ __device__ inline int f32_attention_splits(int keys, int most) {
+  const int s = keys > 256 ? (keys + 127) / 128 : 1;
+  return s < most ? s : most;
+}
 void f32_tree_attention(float* o, const float* qkv, int q_stride, const float* kc, const float* vc,
-                        const StepMeta& m, const ModelDims& md, hipStream_t s);
+                        const StepMeta& m, const ModelDims& md, int n_items, int most, float* part_o, float* part_ml, int* tickets,
+                        hipStream_t s);
 void f32_kv_compact(float* const* kc, float* const* vc, const ApprovalWalk& w, const StepMeta& m, const ModelDims& md, hipStream_t s);
 // plain [Hkv][n][hd] <-> cache
 void f32_kv_copy(float* cache, float* plain, bool to_cache, int seq, int first, int n,

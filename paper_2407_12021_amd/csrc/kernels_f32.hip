@@ -462,31 +462,83 @@ __global__ __launch_bounds__(256) void f32_tree_attention_kernel(
     put(threadIdx.x, t / l_run);
   }
 }
+// Partial results of the kernel below travel between workgroups of one launch, which may sit on different XCDs: device-scope
+// relaxed accesses that go through to the point of coherence, stores waited for before the ticket is taken, loads behind the
+// ticket's return value (-DDED_SPLITK_FENCES: fences instead, as for the 16-bit path's split sums).
+__device__ inline void part_store(float* p, float a, float b) {
+  const unsigned long long v = (unsigned long long)__float_as_uint(b) << 32 | __float_as_uint(a);
+#ifdef DED_SPLITK_FENCES
+  *reinterpret_cast<unsigned long long*>(p) = v;
+#else
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#endif
+}
+__device__ inline float2 part_load(const float* p) {
+#ifdef DED_SPLITK_FENCES
+  const unsigned long long v = *reinterpret_cast<const unsigned long long*>(p);
+#else
+  const unsigned long long v = __hip_atomic_load(reinterpret_cast<unsigned long long*>(const_cast<float*>(p)), __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+#endif
+  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+}
+// whether this workgroup is the last of `splits` whose partial results lie in memory
+__device__ inline bool last_of(int splits, int* ticket, int* s_flag) {
+#ifdef DED_SPLITK_FENCES
+  __atomic_thread_fence(__ATOMIC_RELEASE);
+#else
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int prev = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (prev == splits - 1) __hip_atomic_store(ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_flag = prev == splits - 1;
+  }
+  __syncthreads();
+#ifdef DED_SPLITK_FENCES
+  if (*s_flag) __atomic_thread_fence(__ATOMIC_ACQUIRE);
+#endif
+  return *s_flag != 0;
+}
 // Matrix-core form for head dims of 16 and more.  One workgroup per (16-row block, query head); its NW wavefronts take
 // 16-key blocks in turn, each with an online soft-max of its own, and merge through LDS at the end.  S^T = K . Q^T leaves
 // the scores of four consecutive keys (4 quad + i) of one row in a lane, which is the operand layout of the second
 // product O^T = V^T . P^T when its i-th instruction takes keys 4 quad + i: no cross-lane traffic but the row maximum.
 // The kernel above walks one row per workgroup, every lane along a key of its own (64 separate rows per load), and
-// fetches K and V once per row; this one fetches them once per 16 rows.  Measured: four trees on prefixes of up to 512
-// keys, 8 heads x 128, per layer 261 us before, 22 us now.
+// fetches K and V once per row; this one fetches them once per 16 rows.
+// A workgroup takes one of up to F32_ATTN_SPLITS ranges of about 128 keys, one 16-key block per wavefront; the last one to finish
+// adds the ranges in their order.  Bound by latencies (6 us from start to end for a single range of 24 keys: operands 2.8,
+// products and soft-max 2.4, meeting of the wavefronts and hand-over) and, where a CU runs several ranges after one another, by
+// the fp32 matrix instructions (2048 cycles per block for a head dim of 128).  Hence the list of items in place of a grid with
+// empty workgroups, which the dispatcher spread so unevenly that some CUs ran two, and registers for two workgroups per CU:
+// the values are requested behind the keys' products, the queries stay in LDS.
+// us, per layer, 8 heads x 128, four trees of 160 rows: on prefixes of 512, 131, 300 and 17 keys unsplit 21, so 13.3 (12.4 with one
+// workgroup per CU), on four prefixes of 512 keys 21 and 18.3 (21).
+// A lane's feature m of value tiles 4 c .. 4 c + 3 stands for dims 64 c + 4 m .. + 3, so that it loads 16 bytes of a value row (one
+// float per load instruction otherwise, 32 for a head dim of 128).
 template <int HD>
-__global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kernel(
+__global__ __launch_bounds__(HD == 256 ? 256 : 512, HD == 256 ? 1 : 4) void f32_mfma_attention_kernel(
     float* __restrict__ o, const float* __restrict__ qkv, int q_stride, const float* __restrict__ kc,
     const float* __restrict__ vc, const uint64_t* __restrict__ mask, const int32_t* __restrict__ seq_p,
-    const int32_t* __restrict__ seq_n, const int32_t* __restrict__ row0, const int32_t* __restrict__ blk_seq, int H,
-    int Hkv, int cap) {
-  constexpr int NW = HD == 256 ? 4 : 8, DT = HD / 16;
+    const int32_t* __restrict__ seq_n, const int32_t* __restrict__ blk_seq, const int32_t* __restrict__ items, int H, int Hkv,
+    int cap, int most,
+    float* part_o, float* part_ml, int* tickets) {
+  constexpr int NW = HD == 256 ? 4 : 8, DT = HD / 16, VEC = DT < 4 ? DT : 4;
+  typedef float vec __attribute__((ext_vector_type(VEC), aligned(4)));
   __shared__ float4 s_o[NW][DT][64];
   __shared__ float2 s_ml[NW][16];
+  __shared__ float4 s_q[DT][64];
+  __shared__ int s_last;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m16 = lane & 15, quad = lane >> 4;
-  const int h = blockIdx.y, r = blockIdx.x * 16 + m16, b = blk_seq[blockIdx.x];
+  const int h = blockIdx.x, item = items[blockIdx.y], rb = item / F32_ATTN_SPLITS, range = item % F32_ATTN_SPLITS;
+  const int r = rb * 16 + m16, b = blk_seq[rb];
   const int P = seq_p[b], T = P + seq_n[b], kvh = h / (H / Hkv);
+  const int splits = f32_attention_splits(T, most), blocks = (T + 15) / 16;
+  const int k_begin = range * blocks / splits * 16, k_end = (range + 1) * blocks / splits * 16;
   const float* K = kc + ((int64_t)b * Hkv + kvh) * cap * HD;
   const float* V = vc + ((int64_t)b * Hkv + kvh) * cap * HD;
   const float* q = qkv + (int64_t)r * q_stride + (int64_t)h * HD;
-  v4f qf[DT];
-#pragma unroll
-  for (int c = 0; c < DT; ++c) qf[c] = *reinterpret_cast<const v4f*>(q + c * 16 + quad * 4);
   const uint64_t* mrow = mask + (int64_t)r * 4;
   const uint64_t w0 = mrow[0], w1 = mrow[1], w2 = mrow[2], w3 = mrow[3];
   const float scale = 1.0f / sqrtf((float)HD);
@@ -500,26 +552,39 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
   v4f acc[DT];
 #pragma unroll
   for (int c = 0; c < DT; ++c) acc[c] = v4f{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = wave * 16; k0 < T; k0 += NW * 16) {
+  v4f kf[DT];
+  auto load_keys = [&](int k0) {
     const float* kr = K + (int64_t)min(k0 + m16, T - 1) * HD + quad * 4;
-    v4f kf[DT];
 #pragma unroll
     for (int c = 0; c < DT; ++c) kf[c] = *reinterpret_cast<const cache_v4f*>(kr + c * 16);
-    float vf[DT][4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const float* vr = V + (int64_t)min(k0 + quad * 4 + j, T - 1) * HD + m16;
-#pragma unroll
-      for (int c = 0; c < DT; ++c) vf[c][j] = vr[c * 16];
-    }
+  };
+  load_keys(k_begin + wave * 16);
+  // the queries, the same for all wavefronts, stay in LDS: held by each they left registers for one workgroup per CU
+  for (int c = wave; c < DT; c += NW) s_q[c][lane] = *reinterpret_cast<const float4*>(q + c * 16 + quad * 4);
+  __syncthreads();
+  for (int k0 = k_begin + wave * 16; k0 < k_end; k0 += NW * 16) {
     v4f sa = v4f{0.f, 0.f, 0.f, 0.f}, sb = sa;
 #pragma unroll
-    for (int c = 0; c < DT; ++c)
+    for (int c = 0; c < DT; ++c) {
+      const float4 qc = s_q[c][lane];
+      sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][0], qc.x, sa, 0, 0, 0);
+      sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][1], qc.y, sb, 0, 0, 0);
+      sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][2], qc.z, sa, 0, 0, 0);
+      sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][3], qc.w, sb, 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    float vf[4][DT];
 #pragma unroll
-      for (int j = 0; j < 4; j += 2) {
-        sa = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j], qf[c][j], sa, 0, 0, 0);
-        sb = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][j + 1], qf[c][j + 1], sb, 0, 0, 0);
+    for (int j = 0; j < 4; ++j) {
+      const float* vr = V + (int64_t)min(k0 + quad * 4 + j, T - 1) * HD + m16 * VEC;
+#pragma unroll
+      for (int c = 0; c < DT; c += VEC) {
+        const vec v = *reinterpret_cast<const vec*>(vr + c * 16);
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) vf[j][c + e] = v[e];
       }
+    }
+    __builtin_amdgcn_sched_barrier(0);
     float p[4], mx = -INFINITY;
     bool vis[4];
 #pragma unroll
@@ -545,8 +610,9 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
     for (int c = 0; c < DT; ++c) {
       acc[c] *= alpha;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[c][j], p[j], acc[c], 0, 0, 0);
+      for (int j = 0; j < 4; ++j) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[j][c], p[j], acc[c], 0, 0, 0);
     }
+    load_keys(k0 + NW * 16);  // (past the end the last key again)
   }
   l_run += __shfl_xor(l_run, 16);
   l_run += __shfl_xor(l_run, 32);
@@ -563,24 +629,68 @@ __global__ __launch_bounds__(HD == 256 ? 256 : 512) void f32_mfma_attention_kern
     f[w] = expf(exponent_from(ml.x, M));
     L += ml.y * f[w];
   }
-  const float inv = 1.0f / L;
+  float inv = 1.0f / L;
+  const int64_t group = (int64_t)rb * H + h, part = group * most + range;
   for (int c = wave; c < DT; c += NW) {
     v4f v = v4f{0.f, 0.f, 0.f, 0.f};
+    // dims c * 16 + quad * 4 + i, from where the wavefronts left them
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      const float4 t = s_o[w][c][lane];
-      v += v4f{t.x, t.y, t.z, t.w} * f[w];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int dim = c * 16 + quad * 4 + i, m = dim % (16 * VEC) / VEC, t = dim / (16 * VEC) * VEC + dim % VEC;
+        v[i] += reinterpret_cast<const float*>(&s_o[w][t][m / 4 * 16 + m16])[m % 4] * f[w];
+      }
     }
-    reinterpret_cast<float4*>(o)[((int64_t)blockIdx.x * (H * DT) + h * DT + c) * 64 + lane] =  // packed, the O projection's input
+    float4* out = reinterpret_cast<float4*>(o) + ((int64_t)rb * (H * DT) + h * DT + c) * 64 + lane;  // packed, the O projection's input
+    if (splits == 1) {
+      *out = make_float4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
+    } else {
+      float* p = part_o + ((part * DT + c) * 64 + lane) * 4;
+      part_store(p, v[0], v[1]);
+      part_store(p + 2, v[2], v[3]);
+    }
+  }
+  if (splits == 1) return;
+  if (wave == 0 && quad == 0) part_store(part_ml + (part * 16 + m16) * 2, M, L);
+  if (!last_of(splits, tickets + group, &s_last)) return;
+  float g[F32_ATTN_SPLITS];
+  M = -INFINITY, L = 0.f;
+  float2 ml[F32_ATTN_SPLITS];
+#pragma unroll
+  for (int z = 0; z < F32_ATTN_SPLITS; ++z)  // (past the last range it is read again, with no weight)
+    ml[z] = part_load(part_ml + ((group * most + min(z, splits - 1)) * 16 + m16) * 2);
+#pragma unroll
+  for (int z = 0; z < F32_ATTN_SPLITS; ++z) M = fmaxf(M, ml[z].x);
+#pragma unroll
+  for (int z = 0; z < F32_ATTN_SPLITS; ++z) {
+    g[z] = expf(exponent_from(ml[z].x, M));
+    if (z < splits) L += ml[z].y * g[z];
+  }
+  inv = 1.0f / L;
+  for (int c = wave; c < DT; c += NW) {
+    float2 lo[F32_ATTN_SPLITS], hi[F32_ATTN_SPLITS];
+#pragma unroll
+    for (int z = 0; z < F32_ATTN_SPLITS; ++z) {
+      const float* p = part_o + (((group * most + min(z, splits - 1)) * DT + c) * 64 + lane) * 4;
+      lo[z] = part_load(p), hi[z] = part_load(p + 2);
+    }
+    v4f v = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int z = 0; z < F32_ATTN_SPLITS; ++z)
+      if (z < splits) v += v4f{lo[z].x, lo[z].y, hi[z].x, hi[z].y} * g[z];
+    reinterpret_cast<float4*>(o)[((int64_t)rb * (H * DT) + h * DT + c) * 64 + lane] =
         make_float4(v[0] * inv, v[1] * inv, v[2] * inv, v[3] * inv);
   }
 }
 
 void f32_tree_attention(float* o, const float* qkv, int q_stride, const float* kc, const float* vc,
-                        const StepMeta& m, const ModelDims& md, hipStream_t s) {
+                        const StepMeta& m, const ModelDims& md, int n_items, int most, float* part_o, float* part_ml, int* tickets,
+                        hipStream_t s) {
 #define DED_F32_ATTN(HD)                                                                                          \
-  hipLaunchKernelGGL((f32_mfma_attention_kernel<HD>), dim3(m.rows / 16, md.H), dim3(HD == 256 ? 256 : 512), 0, s, o, \
-                     qkv, q_stride, kc, vc, m.mask, m.seq_p, m.seq_n, m.row0, m.blk_seq, md.H, md.Hkv, md.cap)
+  hipLaunchKernelGGL((f32_mfma_attention_kernel<HD>), dim3(md.H, n_items), dim3(HD == 256 ? 256 : 512), 0, s, o, \
+                     qkv, q_stride, kc, vc, m.mask, m.seq_p, m.seq_n, m.blk_seq, m.attn_items, md.H, md.Hkv, md.cap, most, part_o, part_ml, \
+                     tickets)
   switch (md.hd) {
     case 16: DED_F32_ATTN(16); return;
     case 32: DED_F32_ATTN(32); return;

@@ -59,7 +59,7 @@ def _step_error(cfg, w, prefix_len, nodes, seed):
 
 # (d, H, Hkv, hd, F, V), prefix lengths, tree sizes: k not a multiple of 4 (scalar loads) or of 32, features not a
 # multiple of the tile, head dims on both sides of the fused rotary projection (32) and of the matrix-core attention (16),
-# one and several row tiles, more feature tiles than one per CU
+# one and several row tiles, more feature tiles than one per CU, 256 keys (the most in one range) and 257, more than 8 ranges of 128
 FP32_EDGES = [
     ((33, 2, 2, 8, 17, 50), [0, 5], [1, 16]),
     ((36, 2, 1, 16, 50, 101), [33], [17]),
@@ -67,6 +67,8 @@ FP32_EDGES = [
     ((132, 2, 2, 64, 340, 97), [127, 64, 1, 130], [1, 16, 17, 48]),
     ((256, 3, 1, 128, 688, 4096), [129], [16]),
     ((320, 2, 1, 256, 96, 6000), [31, 300], [65, 130]),
+    ((64, 2, 1, 32, 44, 500), [240, 241, 1100], [16, 16, 20]),
+    ((256, 2, 2, 128, 64, 97), [1010, 500, 245], [5, 33, 12]),
 ]
 
 
