@@ -1120,7 +1120,8 @@ static int tree_attention_common(ded_ctx* c, int32_t layer, int32_t batch, const
     const int rows_pad = round_up(m.rows, 64);
     { ProfScope p(c, KC_LAYOUT);
       bf16_scatter_tree_kv((bf16_t*)c->kc[layer], (bf16_t*)c->vc[layer], (const bf16_t*)k_tree, (const bf16_t*)v_tree,
-                           c->meta_at(c->h_meta_dev), c->h_meta_dev, ws.d_meta, (int)c->meta_units(), md, mn, s); }
+                           c->meta_at(c->h_meta_dev), c->h_meta_dev, ws.d_meta, (int)c->meta_units(), c->s_p.data(), c->s_n.data(),
+                           md, mn, s); }
     { ProfScope p(c, KC_TREE_ATTN);
       bf16_tree_attention(nullptr, rows_pad, nullptr, (const bf16_t*)c->kc[layer], (const bf16_t*)c->vc[layer], ws.part_o,
                           ws.part_ml, ns, 1, m, md, s, (const bf16_t*)q, (bf16_t*)out, mn); }

@@ -227,8 +227,10 @@ void bf16_kv_compact(bf16_t* const* kc, bf16_t* const* vc, const ApprovalWalk& w
 void bf16_kv_copy(bf16_t* kcache, bf16_t* vcache, bf16_t* k_plain, bf16_t* v_plain, bool to_cache,
                   int seq, int first, int n, const ModelDims& md, hipStream_t s);
 void bf16_kv_clear(bf16_t* kcache, bf16_t* vcache, int seq, int first, int n, const ModelDims& md, hipStream_t s);
-// m: the step's description in pinned host memory, `units` x 16 bytes of which go from meta_src to meta_dst beside the scatter
+// m: the step's description in pinned host memory, `units` x 16 bytes of which go from meta_src to meta_dst beside the scatter;
+// host_p, host_n: its prefix lengths and tree sizes for the host
 void bf16_scatter_tree_kv(bf16_t* kc, bf16_t* vc, const bf16_t* k_tree, const bf16_t* v_tree, const StepMeta& m,
-                          const void* meta_src, void* meta_dst, int units, const ModelDims& md, int max_nodes, hipStream_t s);
+                          const void* meta_src, void* meta_dst, int units, const int32_t* host_p, const int32_t* host_n,
+                          const ModelDims& md, int max_nodes, hipStream_t s);
 
 }  // namespace ded

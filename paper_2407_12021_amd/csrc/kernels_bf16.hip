@@ -179,8 +179,8 @@ void bf16_kv_compact(bf16_t* const* kc, bf16_t* const* vc, const ApprovalWalk& w
 
 // ------------------------------------------------------------------------------------------
 // plain bf16 rows [n][hd] of one (sequence, kv head)  <->  slots [first, first + n) of its f16 cache fragments (to the
-// cache: exact widening; back: round to bf16).  A workgroup takes one 32-slot group of the cache, i.e. 8 KiB of key
-// fragments and 8 KiB of value fragments, in 16-byte units: a key unit is eight dims of one slot (a 16-byte piece of a
+// cache: exact widening; back: round to bf16).  A workgroup takes the keys or the values of one 32-slot group of the cache, 8 KiB
+// of fragments (both, one after the other, are two round trips to memory), in 16-byte units: a key unit is eight dims of one slot (a 16-byte piece of a
 // plain row), a value unit eight slots of one dim, so values go through LDS.  Slots outside the range keep their
 // contents (a group's first and last slots may belong to other tokens).
 // Bound by memory traffic (plain + cache bytes once each).  One thread per element, with two-byte scattered accesses to
@@ -276,13 +276,14 @@ __global__ __launch_bounds__(256) void bf16_kv_copy_kernel(bf16_t* __restrict__ 
   __shared__ __align__(16) uint16_t lds[32 * KV_LDS_ROW];
   const int g = blockIdx.y;
   const int64_t base = ((int64_t)seq * Hkv + g) * cap * 128, plain = (int64_t)g * n * 128;
-  kv_group_copy<TO_CACHE>(kcache + base, vcache + base, kp ? kp + plain : nullptr, vp ? vp + plain : nullptr, first, n,
-                          first / 32 + blockIdx.x, lds);
+  const bool keys = blockIdx.z == 0;  // or values
+  kv_group_copy<TO_CACHE>(kcache + base, vcache + base, keys && kp ? kp + plain : nullptr, !keys && vp ? vp + plain : nullptr,
+                          first, n, first / 32 + blockIdx.x, lds);
 }
 void bf16_kv_copy(bf16_t* kcache, bf16_t* vcache, bf16_t* k_plain, bf16_t* v_plain, bool to_cache, int seq,
                   int first, int n, const ModelDims& md, hipStream_t s) {
   if (n <= 0) return;
-  const dim3 grid((first + n - 1) / 32 - first / 32 + 1, md.Hkv);
+  const dim3 grid((first + n - 1) / 32 - first / 32 + 1, md.Hkv, 2);
   if (to_cache)
     hipLaunchKernelGGL((bf16_kv_copy_kernel<true>), grid, dim3(256), 0, s, kcache, vcache, k_plain, v_plain, seq, first, n,
                        md.Hkv, md.cap);
@@ -306,30 +307,49 @@ void bf16_kv_clear(bf16_t* kcache, bf16_t* vcache, int seq, int first, int n, co
 }
 
 // tree K / V [B][Hkv][max_nodes][hd] -> cache slots P + node.  The step's description is still in host memory (seq_p, seq_n); the
-// last workgroups of each row of the grid copy it to the device for the kernels that follow.
+// last workgroups of each row of the grid copy it to the device for the kernels that follow.  What the scatter itself needs of
+// it travels with the launch for up to eight sequences: a round trip to the host at its head is 1.5 us of 5.
+struct FewSequences {
+  int32_t count, p[8], n[8];  // count 0: more of them, read the arrays
+};
 __global__ __launch_bounds__(256) void bf16_scatter_tree_kv_kernel(bf16_t* __restrict__ kc, bf16_t* __restrict__ vc,
                                                                    const bf16_t* __restrict__ kt,
                                                                    const bf16_t* __restrict__ vt,
                                                                    const int32_t* __restrict__ seq_p,
-                                                                   const int32_t* __restrict__ seq_n,
+                                                                   const int32_t* __restrict__ seq_n, FewSequences few,
                                                                    const uint4* __restrict__ meta_src,
                                                                    uint4* __restrict__ meta_dst, int units, int Hkv, int cap,
                                                                    int max_nodes) {
   __shared__ __align__(16) uint16_t lds[32 * KV_LDS_ROW];
   if (blockIdx.x == gridDim.x - 1) {
+    if (blockIdx.z) return;
     for (int u = blockIdx.y * 256 + threadIdx.x; u < units; u += gridDim.y * 256) meta_dst[u] = meta_src[u];
     return;
   }
-  const int bh = blockIdx.y, b = bh / Hkv, P = seq_p[b], n = seq_n[b], kb = P / 32 + blockIdx.x;
+  const int bh = blockIdx.y, b = bh / Hkv;
+  int P = few.p[0], n = few.n[0];
+#pragma unroll
+  for (int i = 1; i < 8; ++i)
+    if (b == i) P = few.p[i], n = few.n[i];
+  if (!few.count) P = seq_p[b], n = seq_n[b];
+  const int kb = P / 32 + blockIdx.x;
   if (kb * 32 >= P + n) return;
   const int64_t plain = (int64_t)bh * max_nodes * 128, base = (int64_t)bh * cap * 128;
-  kv_group_copy<true>(kc + base, vc + base, const_cast<bf16_t*>(kt) + plain, const_cast<bf16_t*>(vt) + plain, P, n, kb, lds);
+  const bool keys = blockIdx.z == 0;  // or values
+  kv_group_copy<true>(kc + base, vc + base, keys ? const_cast<bf16_t*>(kt) + plain : nullptr,
+                      keys ? nullptr : const_cast<bf16_t*>(vt) + plain, P, n, kb, lds);
 }
 void bf16_scatter_tree_kv(bf16_t* kc, bf16_t* vc, const bf16_t* k_tree, const bf16_t* v_tree, const StepMeta& m,
-                          const void* meta_src, void* meta_dst, int units, const ModelDims& md, int max_nodes, hipStream_t s) {
+                          const void* meta_src, void* meta_dst, int units, const int32_t* host_p, const int32_t* host_n,
+                          const ModelDims& md, int max_nodes, hipStream_t s) {
+  FewSequences few = {};
+  if (m.batch <= 8) {
+    few.count = m.batch;
+    for (int b = 0; b < m.batch; ++b) few.p[b] = host_p[b], few.n[b] = host_n[b];
+  }
   // a tree of n nodes touches at most (n + 30) / 32 + 1 groups
-  hipLaunchKernelGGL(bf16_scatter_tree_kv_kernel, dim3((m.n_step + 30) / 32 + 2, m.batch * md.Hkv), dim3(256), 0, s, kc,
-                     vc, k_tree, v_tree, m.seq_p, m.seq_n, reinterpret_cast<const uint4*>(meta_src),
+  hipLaunchKernelGGL(bf16_scatter_tree_kv_kernel, dim3((m.n_step + 30) / 32 + 2, m.batch * md.Hkv, 2), dim3(256), 0, s, kc,
+                     vc, k_tree, v_tree, m.seq_p, m.seq_n, few, reinterpret_cast<const uint4*>(meta_src),
                      reinterpret_cast<uint4*>(meta_dst), units, md.Hkv, md.cap, max_nodes);
 }
 

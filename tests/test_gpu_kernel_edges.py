@@ -582,3 +582,31 @@ def test_calls_in_a_row_keep_their_own_descriptions(dtype, max_nodes):
     ver.close()
     for i, (a, b) in enumerate(zip(*runs)):
         assert torch.isfinite(a).all() and torch.equal(a, b), i
+
+
+@pytest.mark.parametrize("batch", [8, 9])
+def test_attention_of_up_to_eight_sequences_and_more(batch):
+    """Up to eight sequences' places travel with the scatter's launch, more are read from the step's description: every tree's keys and
+    values land in its own slots.  Bound: bf16 outputs of O(1), 2^-9, and f16 weights, together under 2e-2."""
+    import torch
+    H, Hkv, most = 2, 1, 20
+    cfg = di.ModelConfig(f"scatter{batch}", 1, 128, H, Hkv, 128, 128, 64, dtype="bf16")
+    ver = _verifier(cfg, di.make_weights(cfg, seed=3), max_batch=batch, kv_capacity=192, max_nodes=most)
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    draw = lambda *shape: torch.randn(*shape, device="cuda", generator=g).bfloat16()
+    prefix, nodes = [7 * b for b in range(batch)], [1 + (5 * b) % most for b in range(batch)]
+    parents = [di.random_tree(n, None, seed=b) for b, n in enumerate(nodes)]
+    kp, vp = draw(batch, Hkv, 64, 128), draw(batch, Hkv, 64, 128)
+    q, kt, vt = draw(batch, most, H, 128), draw(batch, Hkv, most, 128), draw(batch, Hkv, most, 128)
+    for b, p in enumerate(prefix):
+        if p:
+            ver.kv_store(0, b, 0, kp[b, :, :p].contiguous(), vp[b, :, :p].contiguous())
+    out = ver.tree_attention(0, prefix, parents, q, kt, vt)
+    for b, (p, n) in enumerate(zip(prefix, nodes)):
+        k, v = ver.kv_load(0, b, 0, p + n)
+        assert torch.equal(k[:, p:], kt[b, :, :n]) and torch.equal(v[:, p:], vt[b, :, :n]), b
+        kk, vv = (torch.cat([a[b, :, :p], t[b, :, :n]], 1).transpose(0, 1).double().cpu().numpy() for a, t in ((kp, kt), (vp, vt)))
+        vis = np.concatenate([np.ones((n, p), bool), oracle.ancestor_mask(parents[b])], axis=1)
+        ref = oracle.masked_attention(q[b, :n].double().cpu().numpy(), kk, vv, vis)
+        assert np.abs(out[b, :n].double().cpu().numpy() - ref).max() <= 2e-2, b
+    ver.close()
