@@ -579,10 +579,11 @@ int clear_step_slots(ded_ctx* c) {
 // the sums of a tree do not depend on how much its neighbours in the batch fall short of it.  (They do depend on the room
 // that the context, sized by its max_batch and max_nodes, has for split sums.)
 int sum_rows(const ded_ctx* c) { return round_up(c->batch * c->n_step, 64); }
-GemmPlan plan_gemm(const ded_ctx* c, int rows_pad, int N, int K, int planes) {
+GemmPlan plan_gemm(const ded_ctx* c, int rows_pad, int N, int K, int planes, bool residual = false) {
   const int rows = sum_rows(c);
   const int cap = (int)std::min<int64_t>(8, c->part_elems / ((int64_t)rows * round_up(N, 64)));
-  GemmPlan plan = bf16_gemm_plan(rows, rows_pad, N, K, planes, std::max(cap, 1), c->part_elems);
+  GemmPlan plan = residual ? bf16_gemm_plan_residual(rows, rows_pad, N, K, std::max(cap, 1), c->part_elems)
+                           : bf16_gemm_plan(rows, rows_pad, N, K, planes, std::max(cap, 1), c->part_elems);
   if (!plan.tile && bf16_gemm_tiles(rows, N, plan) > kGemmCounters) plan.splits = 1;
   return plan;
 }
@@ -593,8 +594,9 @@ bool slim_step(const ded_ctx* c) {
   if (c->rows > BF16_SLIM_ROWS) return false;
   const int qd = md.H * md.hd, qkv_n = qd + 2 * md.Hkv * md.hd;
   auto fits = [&](int N, int K, int planes) { return bf16_gemm_slim_ok(plan_gemm(c, 64, N, K, planes), K, planes); };
-  return fits(md.V, md.d, 2) && (md.n_layers == 0 || (fits(qkv_n, md.d, 2) && fits(md.d, qd, 1) && fits(2 * md.F, md.d, 2) &&
-                                                      fits(md.d, md.F, 1)));
+  auto fits_residual = [&](int N, int K) { return bf16_gemm_slim_ok(plan_gemm(c, 64, N, K, 1, true), K, 1); };
+  return fits(md.V, md.d, 2) && (md.n_layers == 0 || (fits(qkv_n, md.d, 2) && fits_residual(md.d, qd) && fits(2 * md.F, md.d, 2) &&
+                                                      fits_residual(md.d, md.F)));
 }
 
 // LM head of the 16-bit path on the final residual stream (c->y_p / c->ssq as the last layer left them): the per-group top-2
@@ -651,7 +653,7 @@ int forward_bf16(ded_ctx* c, bool want_logits, float* logits_out) {
   // planes: 2 = the input is consumed as hi + lo, 1 = hi only (enough for the O and down projections)
   const bool slim = slim_step(c);
   auto gemm = [&](int cls, const bf16_t* xp, const void* w, int N, int K, int planes, const GemmEpilogue& epi) {
-    const GemmPlan plan = plan_gemm(c, rows_pad, N, K, planes);
+    const GemmPlan plan = plan_gemm(c, rows_pad, N, K, planes, epi.kind == EPI_RESIDUAL);
     ProfScope p(c, cls);
     if (slim)
       ok = bf16_gemm_slim(xp, (const bf16_t*)w, m.rows, rows_pad, N, K, planes, plan, epi, s) && ok;

@@ -180,16 +180,20 @@ struct GemmEpilogue {
 enum {
   TILE_256x256 = 1, TILE_256x192, TILE_256x128, TILE_128x256, TILE_128x192, TILE_128x128
 };
+constexpr int SUMMED_APART = -1;
 struct GemmPlan {
   int nwn;       // 0: stream kernel (one feature group per workgroup); 2..4: wide kernel, groups per workgroup
   int nw;        // stream kernel: wavefronts splitting the k range
   int splits;    // split-K slices
   int tile = 0;  // != 0: the tile kernel, with this workgroup tile
-  int whole = 0; // tile kernel: that many tiles whole, the others with k split `splits` ways
+  int whole = 0; // tile kernel: that many tiles whole, the others with k split `splits` ways; SUMMED_APART: all split, the
+                 // slices added by a launch of their own
   int ssq_waves = 1;  // tile kernel: shares in which a row's sums of squares are added
 };
 // sum_rows (a multiple of 64, >= rows_pad) decides into which k ranges the sums are split, rows_pad how they are run.
 GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, int max_splits, int64_t part_elems);
+// of a residual projection (one plane, EPI_RESIDUAL), whose sums may be added by a launch of their own
+GemmPlan bf16_gemm_plan_residual(int sum_rows, int rows_pad, int N, int K, int max_splits, int64_t part_elems);
 int bf16_gemm_tiles(int rows_pad, int N, const GemmPlan& plan);
 // GEMM on the matrix cores with a fused epilogue (skinny and tile kernels).  planes = 2 uses X = hi + lo, planes = 1 only
 // the hi plane.  rows_pad % 64 == 0, N % 16 == 0 (N % 64 for the paired epilogues), K % 128 == 0.  `part` (part_elems floats)

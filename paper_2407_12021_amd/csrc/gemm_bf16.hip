@@ -1210,6 +1210,7 @@ __device__ __forceinline__ f32x4_t slice_load16(const SliceRef& s, int byte) {
 }
 
 constexpr int TILE_WAVES = 8;
+constexpr int SUM_PARTS = 8;  // most k ranges of a product that gemm_sum_slices_kernel adds
 constexpr int TILE_LDS = 158 * 1024;  // of the CU's 160 KB, for the ring
 template <int PLANES, int GPW, int RBW>
 struct TileShape {
@@ -1467,6 +1468,13 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
       auto slice = [&](int pt) {
         return slice_ref(part + ((int64_t)pt * rest + rel) * S::TILE_ELEMS + (int64_t)wt * WT_ELEMS, WT_ELEMS * 4);
       };
+      if (EPI == EPI_RESIDUAL && !counters) {  // gemm_sum_slices_kernel does the rest
+        float* own = part + ((int64_t)cur_part * rest + rel) * S::TILE_ELEMS + (int64_t)wt * WT_ELEMS + llane * 4;
+#pragma unroll
+        for (int i = 0; i < NF; ++i) *reinterpret_cast<f32x4_t*>(own + i * 256) = acc[i / (TN * RBW)][i / RBW % TN][i % RBW];
+        if (!more) break;
+        continue;
+      }
       {
         const SliceRef own = slice(cur_part);
 #pragma unroll
@@ -1537,6 +1545,36 @@ __global__ __launch_bounds__(512, 2) void gemm_tile_kernel(float* __restrict__ p
   }
 }
 
+// The sums and the epilogue of tiles (128 features x RBW * 64 rows) whose slices the tile kernel has only stored: a wavefront per
+// 64 features and 16 rows, so that all CUs share what the last workgroup of a tile would do alone.  Bound by reading the slices
+// from the last-level cache and by its start: 144 rows x 4096 features in 8 ranges, 19 MB, 7.7 us; 256 rows, 34 MB, 10.2 us.
+template <int RBW>
+__global__ __launch_bounds__(256) void gemm_sum_slices_kernel(const float* __restrict__ part, int N, int row_tiles, int tiles, int parts,
+                                                              GemmEpilogue epi) {
+  using S = TileShape<1, 1, RBW>;
+  const int lane = threadIdx.x & 63, w = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int NG = N / (16 * TN), ng = w % NG, rb = w / NG;
+  if (rb * 16 >= epi.rows) return;
+  const int rt = rb / S::RBT, rg = rb % S::RBT / RBW, tile = ng / S::FG * row_tiles + rt;
+  const float* src = part + (int64_t)tile * S::TILE_ELEMS + (rg * S::FGS + ng % S::FGS) * (TN * RBW * 256) + rb % RBW * 256 + lane * 4;
+  f32x4_t v[SUM_PARTS][TN], sum[TN][1];
+#pragma unroll
+  for (int p = 0; p < SUM_PARTS; ++p)
+    if (p < parts) {
+#pragma unroll
+      for (int t = 0; t < TN; ++t) v[p][t] = *reinterpret_cast<const f32x4_t*>(src + (int64_t)p * tiles * S::TILE_ELEMS + t * (RBW * 256));
+    }
+#pragma unroll
+  for (int t = 0; t < TN; ++t) sum[t][0] = v[0][t];
+#pragma unroll
+  for (int p = 1; p < SUM_PARTS; ++p)
+    if (p < parts) {
+#pragma unroll
+      for (int t = 0; t < TN; ++t) sum[t][0] += v[p][t];
+    }
+  run_epilogue<EPI_RESIDUAL, 1>(epi, ng, N, rb, rb, 1.f, lane, sum);
+}
+
 // Sweep knob, compiled in only with -DDED_GEMM_TUNE_ENV (never in the library build): the environment variable
 // DED_GEMM_TUNE="nwn,splits" forces the kernel shape (nwn 0 = stream kernel).
 struct Tune {
@@ -1583,6 +1621,9 @@ bool tile_plan_ok(const GemmPlan& p, int rows_pad, int N, int K, int64_t part_el
   if (p.tile < TILE_256x256 || p.tile > TILE_128x128 || p.splits < 1) return false;
   const TileDims t = tile_dims(p.tile);
   const int64_t tiles = tile_count(p.tile, rows_pad, N), rest = tiles - p.whole;
+  if (p.whole == SUMMED_APART)
+    return p.tile >= TILE_128x256 && p.splits >= 2 && p.splits <= std::min(SUM_PARTS, K / (32 * PD)) && N % 64 == 0 &&
+           tiles * p.splits * t.groups * 64 * t.row_blocks * 16 <= part_elems;
   if (tiles * p.splits > (1 << 20) || p.whole < 0 || rest < 0) return false;
   if (p.splits == 1) return rest == 0;
   return rest > 0 && p.splits <= K / (32 * PD) && rest * TILE_WAVES <= kTickets &&
@@ -1685,12 +1726,14 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
     const TileDims t = tile_dims(plan.tile);
     const int row_tiles = (RB + t.row_blocks - 1) / t.row_blocks;
     const int tiles = ((N + 16 * TN - 1) / (16 * TN) + t.groups - 1) / t.groups * row_tiles;
-    const int items = plan.whole + (tiles - plan.whole) * splits;
+    const bool apart = plan.whole == SUMMED_APART;
+    const int whole = apart ? 0 : plan.whole, items = whole + (tiles - whole) * splits;
+    int* const tickets = apart ? nullptr : counters;
 #define DED_TILE(ID, GPW, RBW)                                                                                       \
   case ID:                                                                                                           \
     hipLaunchKernelGGL((gemm_tile_kernel<PLANES, EPI, GPW, RBW>), dim3(std::min(kCUs, items)), dim3(512), 0, s, part, xp, \
-                       wp, RB, N, KT, tiles, row_tiles, plan.whole, splits, plan.ssq_waves, counters, epi);                          \
-    return true;
+                       wp, RB, N, KT, tiles, row_tiles, whole, splits, plan.ssq_waves, tickets, epi);                        \
+    break;
     switch (plan.tile) {
       DED_TILE(TILE_256x256, 2, 4)
       DED_TILE(TILE_256x192, 2, 3)
@@ -1700,7 +1743,17 @@ bool launch_shape(const GemmPlan& plan, dim3 grid_stream, dim3 grid_wide, float*
       DED_TILE(TILE_128x128, 1, 2)
     }
 #undef DED_TILE
-    return false;
+    if constexpr (PLANES == 1 && EPI == EPI_RESIDUAL) {
+      if (apart) {
+        const dim3 grid((N / 64 * (epi.rows / 16) + 3) / 4);
+#define DED_SUM(RBW) hipLaunchKernelGGL((gemm_sum_slices_kernel<RBW>), grid, dim3(256), 0, s, part, N, row_tiles, tiles, splits, epi)
+        if (plan.tile == TILE_128x256) DED_SUM(4);
+        else if (plan.tile == TILE_128x192) DED_SUM(3);
+        else DED_SUM(2);
+#undef DED_SUM
+      }
+    }
+    return true;
   }
   // the logits epilogues read a single plane only where the projection is matrix-bound (the tile kernel above)
   if constexpr (PLANES == 1 && (EPI == EPI_LOGITS || EPI == EPI_TOP2)) {
@@ -1812,6 +1865,51 @@ GemmPlan bf16_gemm_plan(int sum_rows, int rows_pad, int N, int K, int planes, in
     if (p.tile && tile_us + 5.0 + 4.5 * tile_dims(p.tile).groups < wide_us(best.nwn, wgs, K)) return p;
   }
   return best;
+}
+
+// A narrow projection (O, down) has few tiles, so k is cut into many ranges, and the workgroup that finishes a tile last reads all of
+// its slices, up to 800 KB at the ~60 GB/s that a CU draws, while the others have left.  Where there are three ranges or more the
+// slices are added by a launch of their own that all CUs share.  (Two ranges: 8B shape, 600 rows, down 102 -> 108 us, 1024 rows
+// 129 -> 126; the existing hand-over stays.)  Below 256 rows the skinny kernels are the faster where the weights are few: O of the 7B
+// shape, 80 / 144 / 192 rows, us, stream / tile and sums 18.1 / 20.5, 24.9 / 26.4, 27.6 / 26.7, down of d = 2048, F = 8192 19.1 / 22.7,
+// 22.8 / 25.7, 26.0 / 27.1; hence 64 MB of weights.  us, before / now:
+//   down  7B   80 - 128 - 192 rows  34.0 - 37.5 - 56.6 / 32.9 - 35.2 - 41.4   320 - 512  61 - 75 / 50 - 62
+//         8B                        41.1 - 45.9 - 68.8 / 35.6 - 40.2 - 47.4              68 - 85 / 58 - 72
+//         13B                       48.1 - 58.4 - 70.2 / 42.7 - 46.7 - 54.9              80 - 97 / 68 - 86
+//   O     7B                                                                             40 - 46 / 32 - 39
+//         13B                                                                            47 - 60 / 39 - 49
+// 256 rows in full rounds of the existing ranges (N = 4096: 64 tiles in four) stay with them: down takes 46 us there and 42 apart, O
+// 28 and 29, and twice the slice bytes cost a 32-layer step at the chip's power limit more than that (prompt chunk of 256 rows, 8600 /
+// 8950).  Where the ranges do not fill the chip (13B: O 59 / 35, down 80 / 58) the sums go apart.
+// (A small tree beside one of 33 - 48 nodes, 64 packed rows that are summed like 128: 13B, down 34.1 / 36.6; 7B 35.0 / 27.9.)
+GemmPlan bf16_gemm_plan_residual(int sum_rows, int rows_pad, int N, int K, int max_splits, int64_t part_elems) {
+  auto apart = [&](int rows, int parts) {
+    constexpr double slot_us[3] = {0.50, 0.40, 0.31};  // see plan_tiles
+    GemmPlan best{0, 1, 1, 0, 0};
+    double cost = 1e300;
+    for (int tile = TILE_128x256; tile <= TILE_128x128; ++tile) {
+      const GemmPlan p{0, 1, parts, tile, SUMMED_APART};
+      const double c = row_tile_count(tile, rows) * slot_us[tile - TILE_128x256];
+      if (c < cost && tile_plan_ok(p, rows, N, K, part_elems)) cost = c, best = p;
+    }
+    return best;
+  };
+  bool worth = sum_rows >= 256 || (sum_rows > 64 && (int64_t)N * K * 2 >= (64 << 20));
+  if (sum_rows == 256) {
+    const GemmPlan p = bf16_gemm_plan(sum_rows, sum_rows, N, K, 1, max_splits, part_elems);
+    const int64_t items = p.whole + (tile_count(p.tile ? p.tile : TILE_128x128, sum_rows, N) - p.whole) * p.splits;
+    worth = items * 10 < (items + kCUs - 1) / kCUs * kCUs * 9;  // a round less than nine tenths full
+  }
+  if (worth) {
+    const int tiles = (N / 64 + 1) / 2 * ((sum_rows + 255) / 256);
+    const int parts = std::min({kCUs / tiles, SUM_PARTS, max_splits, K / 512});  // (16 ring slots each, at least)
+    // (room asked for sum_rows too, so that a ragged batch is summed like a full one)
+    if (parts >= 3 && apart(sum_rows, parts).tile) {
+      const GemmPlan p = apart(rows_pad, parts);
+      if (p.tile) return p;
+    }
+  }
+  return bf16_gemm_plan(sum_rows, rows_pad, N, K, 1, max_splits, part_elems);
 }
 
 int bf16_gemm_tiles(int rows_pad, int N, const GemmPlan& plan) {

@@ -189,6 +189,42 @@ def test_projections_at_tile_edges(case):
     assert err <= 2e-2
 
 
+# (d, H, Hkv, F, V) of one layer, prefix lengths, tree sizes, (tile, k ranges) of the down projection: residual projections whose slices
+# are added by a launch of their own.  All three tiles, surplus row blocks, two row tiles, 64 packed rows that are summed like
+# 128, 3 to 8 ranges that are and are not multiples of the ring
+APART_EDGES = [
+    ((1024, 8, 8, 2816, 1040), [5], [250], (4, 5)),
+    ((2048, 16, 4, 8192, 1040), [3, 0], [70, 130], (4, 8)),
+    ((1024, 8, 8, 1664, 1040), [0, 9], [256, 30], (5, 3)),
+    ((4096, 32, 8, 14336, 1040), [7], [150], (5, 8)),
+    ((4096, 32, 8, 14336, 1040), [7, 0], [48, 16], (6, 8)),
+]
+
+
+@pytest.mark.parametrize("case", range(len(APART_EDGES)))
+def test_residual_projections_summed_apart(case):
+    """Bound: the 16-bit path's 2e-2 logit tolerance, as above."""
+    import ctypes as C
+
+    from paper_2407_12021_amd import binding
+
+    class Plan(C.Structure):
+        _fields_ = [(n, C.c_int) for n in ("nwn", "nw", "splits", "tile", "whole", "ssq_waves")]
+
+    (d, H, Hkv, F, V), prefix_len, nodes, (tile, ranges) = APART_EDGES[case]
+    up = lambda x, to: -(-x // to) * to
+    sum_rows, rows = up(len(nodes) * up(max(nodes), 16), 64), up(sum(up(n, 16) for n in nodes), 64)
+    f = binding.lib()["_ZN3ded23bf16_gemm_plan_residualEiiiiil"]
+    f.restype, f.argtypes = Plan, [C.c_int] * 5 + [C.c_int64]
+    plan = f(sum_rows, rows, d, F, 8, 2 * F * max(512, sum_rows))
+    assert (plan.tile, plan.splits, plan.whole) == (tile, ranges, -1)
+    cfg = di.ModelConfig(f"apart-edge{case}", 1, d, H, Hkv, 128, F, V, dtype="bf16")
+    w = di.make_weights(cfg, seed=200 + case, gain_jitter=0.1, threads=16)
+    err = _step_error(cfg, w, prefix_len, nodes, seed=210 + case)
+    print(f"max |logit error| {err:.2e}")
+    assert err <= 2e-2
+
+
 # (d, H, Hkv, F, V) of one layer, prefix lengths, tree sizes, (N, K) of the projections that the tile kernel runs: steps of 97,
 # 144, 70 and 176 rows whose unsplit products run as two k ranges of the tile kernel, rows that fill no whole tile (wavefronts
 # without rows, and with a surplus block), a vocabulary that ends inside a feature group
